@@ -140,6 +140,19 @@ def test_small_f32_model_with_gqa_and_page_32():
     print("worst", r["worst"])
 
 
+@pytest.mark.parametrize("ms,gamma,ctx", [
+    # three rows; K = 132, 64 and 99 (the last one neither a whole number of 4-element loads nor of 16-wide steps)
+    (synth.ModelShape(1, 132, 1, 1, 64, 99, 501, 10000.0, dtype="f32"), [0, 1], [3, 17]),
+    # 17 and 33 rows (one past a row tile); K slices of unequal length (K = 1000 over 8 slices), more than 256 keys
+    (synth.ModelShape(1, 128, 2, 1, 128, 1000, 77, 10000.0, dtype="f32"), [7, 8], [300, 0]),
+    (synth.ModelShape(1, 64, 2, 2, 64, 16, 4099, 10000.0, dtype="f32"), [10, 10, 10], [255, 256, 1]),
+    # 70 rows: two row chunks; wide enough that K is not sliced (N = 4099 / 16 tiles over 8 waves)
+    (synth.ModelShape(1, 64, 1, 1, 64, 2100, 33000, 10000.0, dtype="f32"), [34, 34], [0, 40]),
+])
+def test_f32_projection_and_attention_edges(ms, gamma, ctx):
+    _run_case(ms, 87, np.array(gamma, np.int32), np.array(ctx, np.int32), 16, std=0.08)
+
+
 @pytest.mark.parametrize("gamma", [[3, 1, 5], [16, 12, 9, 15, 11, 14]])
 def test_bf16_wide_vocabulary_statistics_from_the_lm_head_epilogue(gamma):
     # V / 128 >= 192: the LM head takes the 8-wave kernel (12 rows) or the tall one (83 rows) as one launch, whose
