@@ -5,15 +5,16 @@
 //   K pages [page][H_kv][slot][hd]   (key-major: a key's head vector is contiguous)
 //   V pages [page][H_kv][hd][slot]   (transposed: the slots of one channel are contiguous)
 //
-// bf16 path (MFMA): one workgroup per (server, KV head, KV split), one wave per 32 of the
+// bf16 path (MFMA): one workgroup per (server, group of query rows, KV head, KV split), one wave per 32 of the
 // T_i * G query rows that share the KV head (token-major, head-minor), so each K/V byte leaves
 // HBM once per workgroup; K/V stream through a two-stage LDS buffer filled by direct global->LDS
 // loads.  The first product is computed transposed (S^T = K Q^T), which leaves a query's scores in
 // the registers of two lanes, in exactly the order the second product (O^T += V^T P) wants its P
-// operand, so P never leaves registers and neither product needs an LDS transpose.  The number of
-// KV splits of a server follows its own context length (a fixed number of 32-key steps per
+// operand, so P never leaves registers and neither product needs an LDS transpose.  Blocks of a few rows are one
+// group; prompt blocks are cut into groups of 4 waves, each with the keys up to its own last row.  The number of
+// KV splits of a group follows its own key count (a fixed number of 32-key steps per
 // workgroup), so ragged batches stay balanced.  Partial results of the splits are merged by
-// attn_combine_kernel.
+// attn_combine_kernel; where no group is split the kernel stores the final result itself.
 //
 // fp32 path: one workgroup per (row, head), lanes over keys, online softmax per lane.
 #include "common.h"
@@ -120,7 +121,7 @@ __global__ __launch_bounds__(kRowThreads) void attn_rowwise_kernel(const float* 
 // ------------------------------------------------------------------------------------------
 // bf16 MFMA path.  1-D grid over the (work list entry, KV head) items (item_of_workgroup), NW waves per workgroup.
 //
-// A workgroup owns one split of one (server, KV head): a server's steps are dealt evenly to its
+// A workgroup owns one split of one (server, query group, KV head): a group's steps are dealt evenly to its
 // ceil(steps / steps_per_split) splits; a step is 32
 // keys = two 16-key tiles = 16 KB of K and V at hd 128.  K/V go from global memory straight into
 // a two-stage LDS buffer with direct global->LDS loads (no register staging).  A stage has four
@@ -130,7 +131,7 @@ __global__ __launch_bounds__(kRowThreads) void attn_rowwise_kernel(const float* 
 // were measured, with and without the arithmetic: no gain.)  K is placed in LDS so that lane (g, c) of fragment (tile, ks) holds
 // key c, channels 32 ks + 8 g .. at fragment * 1 KB + lane * 16; V pages are copied verbatim
 // ([channel][16 slots] per tile).
-// Wave w computes query rows 32 w .. 32 w + 31 of the T_i * G rows that share the KV head (token-major,
+// Wave w computes query rows 32 w .. 32 w + 31 of the group's rows that share the KV head (token-major,
 // head-minor); both products use the 32x32x16 MFMA (twice the issue rate of the 16x16x32 one on this
 // chip):
 //   S^T (32 keys x 32 queries) = K Q^T : A = K, lane l holds key l%32 (tile l%32/16 of the step),
@@ -141,122 +142,94 @@ __global__ __launch_bounds__(kRowThreads) void attn_rowwise_kernel(const float* 
 //       A = V^T in the same key order: channel 32 dt + l%32, two 8-byte runs of the transposed page.
 // A query row lives in lanes l and l + 32: one lane swap finishes its max and its sum, and the
 // accumulator rescale is a per-lane multiply.  P enters the second product as a two-term bf16 sum.
-// partial_o [R][H][max_splits][HD] fp32, partial_ml [R][H][max_splits][2]; splits beyond a server's own
+// partial_o [R][H][max_splits][HD] fp32, partial_ml [R][H][max_splits][2]; splits beyond a group's own
 // count are never written and never read.
 // ------------------------------------------------------------------------------------------
-// Work list of a step: one entry per (server, split) that has keys, so that the grid holds no workgroup
+// Work list of a step: one entry per (server, query group, split) that has keys, so that the grid holds no workgroup
 // that starts only to find its split empty (ragged contexts), and an entry carries all a workgroup needs
 // before its first load, the pages of its first step included: start-up costs one dependent read instead
 // of three.  list = int header[8] (header[0] = number of entries), then the entries.
+// A query group is `group_tokens` consecutive tokens of a block (its last group may be shorter); n_tokens is the
+// number of block tokens up to the end of the group, so ctx + n_tokens is the number of keys the group sees.
 struct AttnWork {
-  int srv, split, row0, n_tokens, ctx, page0, page1, pad;
+  int srv, split, row0, n_tokens, ctx, page0, page1, tok0;
 };
 static_assert(sizeof(AttnWork) == 32, "entries are read as one 32-byte load");
 
 // One workgroup.  The entries are written in the order of decreasing split length (counting sort over the
-// lengths, which the splits of a server take only two of), because the hardware deals the workgroups of a
+// lengths, which the splits of a group take only two of), because the hardware deals the workgroups of a
 // launch to the compute units round robin by their linear index and a compute unit's finishing time follows
 // the sum of the steps it was dealt: attn_kernel walks the sorted list in a serpentine (item_of_workgroup),
 // so every compute unit gets one long, one medium, ... split instead of whatever the server order brings.
-// Splits longer than kSortBins - 1 steps are not sorted (server order).  Entries beyond the capacity are
+// Splits of kSortBins - 1 steps and more share a bin (any order).  A server's (group, split) pairs are dealt to
+// 1024 / n_servers lanes (a power of two, at least one): one prompt block of 64 groups fills the workgroup, with many
+// servers a lane takes one each.  Entries beyond the capacity are
 // dropped (cannot happen when the host's copy of the batch geometry matches the device's).
 constexpr int kSortBins = 1024;
+constexpr int kWorkThreads = 1024;
 
-__global__ __launch_bounds__(256) void attn_work_kernel(const int* __restrict__ cu_rows,
-                                                        const int* __restrict__ ctx_len, int n_servers,
-                                                        const int* __restrict__ block_table, int max_blocks,
-                                                        int page_size, int steps_per_split, int capacity,
-                                                        int* __restrict__ list) {
-  __shared__ int bin[kSortBins];      // entries per split length, then the first position of a length
-  __shared__ int scan[256];
-  __shared__ int total_sh;
+__global__ __launch_bounds__(kWorkThreads) void attn_work_kernel(const int* __restrict__ cu_rows,
+                                                                 const int* __restrict__ ctx_len, int n_servers,
+                                                                 const int* __restrict__ block_table, int max_blocks,
+                                                                 int page_size, int steps_per_split, int group_tokens,
+                                                                 int capacity, int* __restrict__ list) {
+  __shared__ int bin[kSortBins];      // entries per split length, then the next position of a length
+  __shared__ int scan[kWorkThreads];
   const int tid = threadIdx.x;
-  const bool sorted = steps_per_split < kSortBins;
-  for (int b = tid; b < kSortBins; b += 256) bin[b] = 0;
-  if (tid == 0) total_sh = 0;
+  int lanes = 1;                      // per server
+  while (lanes * 2 * n_servers <= kWorkThreads) lanes *= 2;
+  const int per_pass = kWorkThreads / lanes, sub = tid & (lanes - 1);
+  bin[tid] = 0;
   __syncthreads();
-  // a server's splits: count of them, `rem` of base + 1 steps followed by count - rem of base steps
-  auto shape = [&](int srv, int& row0, int& T, int& L, int& count, int& base, int& rem) {
-    row0 = cu_rows[srv];
-    T = cu_rows[srv + 1] - row0;
-    L = ctx_len[srv];
-    const int steps = (L + T + 31) >> 5;
-    count = (steps + steps_per_split - 1) / steps_per_split;
-    base = count > 0 ? steps / count : 0;
-    rem = steps - base * count;
+  // f(row0, L, first token, block tokens up to the group's end, split, splits of the group, steps of the group)
+  auto for_each_split = [&](int srv, auto f) {
+    const int row0 = cu_rows[srv], T = cu_rows[srv + 1] - row0, L = ctx_len[srv];
+    const int n_groups = (T + group_tokens - 1) / group_tokens;
+    const int most = (((L + T + 31) >> 5) + steps_per_split - 1) / steps_per_split;      // splits of the last group
+    for (int e = sub; e < n_groups * most; e += lanes) {
+      const int g = e / most, sp = e - g * most;
+      const int t_end = min(T, (g + 1) * group_tokens);
+      const int steps = (L + t_end + 31) >> 5, count = (steps + steps_per_split - 1) / steps_per_split;
+      if (sp < count) f(row0, L, g * group_tokens, t_end, sp, count, steps);
+    }
   };
-  if (sorted) {
-    for (int srv = tid; srv < n_servers; srv += 256) {
-      int row0, T, L, count, base, rem;
-      shape(srv, row0, T, L, count, base, rem);
-      if (rem > 0) atomicAdd(&bin[base + 1], rem);
-      if (count - rem > 0) atomicAdd(&bin[base], count - rem);
-    }
+  // the steps of a group are dealt evenly to its splits: `rem` of base + 1 followed by count - rem of base steps
+  auto bin_of = [&](int sp, int count, int steps) {
+    const int base = steps / count, rem = steps - base * count;
+    return kSortBins - 1 - min(kSortBins - 1, base + (sp < rem ? 1 : 0));      // longest first
+  };
+  for (int srv = tid / lanes; srv < n_servers; srv += per_pass)
+    for_each_split(srv, [&](int, int, int, int, int sp, int count, int steps) { atomicAdd(&bin[bin_of(sp, count, steps)], 1); });
+  __syncthreads();
+  const int mine = bin[tid];
+  scan[tid] = mine;
+  __syncthreads();
+  for (int off = 1; off < kSortBins; off <<= 1) {
+    const int v = tid >= off ? scan[tid - off] : 0;
     __syncthreads();
-    // first position of each length, longest first: lane t owns bins kSortBins - 1 - 4 t down to ... - 3
-    int mine[4], sum = 0;
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      mine[k] = bin[kSortBins - 1 - (4 * tid + k)];
-      sum += mine[k];
-    }
-    scan[tid] = sum;
-    __syncthreads();
-    for (int off = 1; off < 256; off <<= 1) {
-      const int v = tid >= off ? scan[tid - off] : 0;
-      __syncthreads();
-      scan[tid] += v;
-      __syncthreads();
-    }
-    int at = scan[tid] - sum;
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      bin[kSortBins - 1 - (4 * tid + k)] = at;
-      at += mine[k];
-    }
-    if (tid == 255) total_sh = scan[255];
+    scan[tid] += v;
     __syncthreads();
   }
+  bin[tid] = scan[tid] - mine;
+  const int total = scan[kSortBins - 1];
+  __syncthreads();
   AttnWork* entries = reinterpret_cast<AttnWork*>(list + 8);
-  for (int c0 = 0; c0 < n_servers; c0 += 256) {
-    const int srv = c0 + tid;
-    int row0 = 0, T = 0, L = 0, count = 0, base = 0, rem = 0;
-    if (srv < n_servers) shape(srv, row0, T, L, count, base, rem);
-    int first_long = 0, first_short = 0;      // positions of the server's base + 1 and base step splits
-    if (sorted) {
-      if (rem > 0) first_long = atomicAdd(&bin[base + 1], rem);
-      if (count - rem > 0) first_short = atomicAdd(&bin[base], count - rem);
-    } else {
-      scan[tid] = count;
-      __syncthreads();
-      for (int off = 1; off < 256; off <<= 1) {
-        const int v = tid >= off ? scan[tid - off] : 0;
-        __syncthreads();
-        scan[tid] += v;
-        __syncthreads();
-      }
-      first_long = total_sh + scan[tid] - count;
-      first_short = first_long + rem;
-      __syncthreads();
-      if (tid == 255) total_sh += scan[255];
-      __syncthreads();
-    }
-    const int last_tile_key = ((L + T - 1) >> 4) << 4;
-    for (int sp = 0; sp < count; ++sp) {
-      const int pos = sp < rem ? first_long + sp : first_short + (sp - rem);
-      if (pos >= capacity) continue;
-      AttnWork w;
-      w.srv = srv; w.split = sp; w.row0 = row0; w.n_tokens = T; w.ctx = L; w.pad = 0;
-      // (the server's steps are dealt evenly to its splits, as in attn_kernel)
+  for (int srv = tid / lanes; srv < n_servers; srv += per_pass)
+    for_each_split(srv, [&](int row0, int L, int tok0, int t_end, int sp, int count, int steps) {
+      const int pos = atomicAdd(&bin[bin_of(sp, count, steps)], 1);
+      if (pos >= capacity) return;
+      const int base = steps / count, rem = steps - base * count;
+      const int last_tile_key = ((L + t_end - 1) >> 4) << 4;
       const int key0 = min((sp * base + min(sp, rem)) * 32, last_tile_key), key1 = min(key0 + 16, last_tile_key);
+      AttnWork w;
+      w.srv = srv; w.split = sp; w.row0 = row0; w.n_tokens = t_end; w.ctx = L; w.tok0 = tok0;
       w.page0 = block_table[(size_t)srv * max_blocks + key0 / page_size];
       w.page1 = block_table[(size_t)srv * max_blocks + key1 / page_size];
       entries[pos] = w;
-    }
-  }
-  __syncthreads();
-  if (tid == 0) list[0] = min(total_sh, capacity);
+    });
+  if (tid == 0) list[0] = min(total, capacity);
 }
+static_assert(kSortBins == kWorkThreads, "one lane per bin");
 
 // Which (work list entry, KV head) a workgroup of the 1-D attention grid takes: the items, entry-major (the KV
 // heads of an entry are neighbours, so they go to the 8 XCDs), in rounds of one item per compute unit, the
@@ -308,9 +281,9 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NW == 1
                                                          const int* __restrict__ block_table, int max_blocks,
                                                          const int* __restrict__ work, int n_work, int page_size,
                                                          int n_heads, int n_kv, int steps_per_split,
-                                                         int max_splits, int q_row_offset,
-                                                         float* __restrict__ partial_o,
-                                                         float* __restrict__ partial_ml) {
+                                                         int max_splits, float* __restrict__ partial_o,
+                                                         float* __restrict__ partial_ml,
+                                                         bf16_t* __restrict__ attn_out) {
   constexpr int KS = HD / 32;            // 1 KB loads per part
   constexpr int KK = HD / 16;            // k steps of the first product
   constexpr int DT = HD / 32;            // 32-channel tiles of the second product
@@ -331,7 +304,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NW == 1
   const int g = lane >> 4, c = lane & 15;            // loader roles
   const int n_keys = L + T;
   const int n_steps_all = (n_keys + 31) >> 5;
-  // the server's steps are dealt evenly to its ceil(steps / steps_per_split) splits (sizes differ by at most
+  // the group's steps are dealt evenly to its ceil(steps / steps_per_split) splits (sizes differ by at most
   // one): a short remainder split would leave its slot idle while the full-length ones decide the duration
   const int n_splits = (n_steps_all + steps_per_split - 1) / steps_per_split;
   if (split >= n_splits) return;
@@ -344,7 +317,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NW == 1
   const int last_tile_key = ((n_keys - 1) >> 4) << 4;
 
   // ---- this wave's 32 query rows
-  const int tile_row0 = q_row_offset + wave * 32;
+  const int tile_row0 = wk.tok0 * G + wave * 32;
   const int rows = T * G - tile_row0;
   const bool has_rows = rows > 0;
   const int my_lr = tile_row0 + c32;
@@ -560,8 +533,19 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NW == 1
     }
   }
 
-  // ---- this split's partial result: lane l holds query row l%32, channels 32 dt + 8 b + 4 h + (0..3)
+  // ---- lane l holds query row l%32, channels 32 dt + 8 b + 4 h + (0..3)
   if (!my_ok) return;
+  if (attn_out) {      // no group of the launch is split: the result is final
+    bf16_t* dst = attn_out + ((size_t)(row0 + my_j) * n_heads + kh * G + my_hg) * HD + 4 * h;
+#pragma unroll
+    for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+      for (int b = 0; b < 4; ++b)
+        *reinterpret_cast<uint2*>(dst + dt * 32 + b * 8) =
+            make_uint2(pack_bf16x2(oacc[dt][4 * b] / l_run, oacc[dt][4 * b + 1] / l_run),
+                       pack_bf16x2(oacc[dt][4 * b + 2] / l_run, oacc[dt][4 * b + 3] / l_run));
+    return;
+  }
   const size_t out_idx = ((size_t)(row0 + my_j) * n_heads + kh * G + my_hg) * max_splits + split;
   if (h == 0) {
     partial_ml[out_idx * 2 + 0] = m_run;
@@ -576,15 +560,15 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NW == 1
           make_float4(oacc[dt][4 * b], oacc[dt][4 * b + 1], oacc[dt][4 * b + 2], oacc[dt][4 * b + 3]);
 }
 
-// attn_out[r][h*HD + d] = sum_s o_s * 2^(m_s - M) / sum_s l_s * 2^(m_s - M) over the row's server's own
-// splits.  grid (R*H), block HD.
+// attn_out[r][h*HD + d] = sum_s o_s * 2^(m_s - M) / sum_s l_s * 2^(m_s - M) over the splits of the row's query
+// group.  grid (R*H), block HD.
 template <int HD>
 __global__ void attn_combine_kernel(const float* __restrict__ partial_o, const float* __restrict__ partial_ml,
                                     int max_splits, int steps_per_split, const int4* __restrict__ row_info,
                                     int n_heads, bf16_t* __restrict__ attn_out) {
   const size_t rh = blockIdx.x;
   const int d = threadIdx.x;
-  const int n_keys = row_info[rh / n_heads].z;      // keys of the row's server (per-row table of the step)
+  const int n_keys = row_info[rh / n_heads].z;      // keys of the row's query group (per-row table of the step)
   const int n_splits = (((n_keys + 31) >> 5) + steps_per_split - 1) / steps_per_split;
   // one pass with a running maximum, so that no load waits for the maximum over all splits
   const float2* ml = reinterpret_cast<const float2*>(partial_ml) + rh * max_splits;
@@ -605,23 +589,59 @@ __global__ void attn_combine_kernel(const float* __restrict__ partial_o, const f
 
 }  // namespace
 
-// The most 32-key steps any compute unit is dealt when every server's steps are cut into splits of at most t
-// steps: item_of_workgroup's serpentine over the (server, split, KV head) items in the order of decreasing
+// Query groups: waves per workgroup and tokens per group.  Up to 8 tiles of 32 query rows (T * G rows share a KV
+// head) a block is one group of as many waves.  Longer blocks (prompts) are cut into groups of 4 waves: the groups are
+// workgroups of one launch, each with the keys up to its own last token, which halves the work of a causal prompt
+// and needs no KV splits to fill the chip.  (One launch per 8 tiles, every one of them over all keys in up to 11
+// splits, took 720 us per layer for a 2047-token prompt at 32 heads and 107 us to merge the partials; now 116 us.
+// 8 prompts of 128 tokens: 30 us and 14 us, now 14 us.)
+constexpr int kMaxWaves = 8;
+constexpr int kGroupWaves = 4;
+void attention_groups(int group, int max_block_tokens, int* waves, int* group_tokens) {
+  const int tiles = ceil_div(max_block_tokens * group, 32);
+  *waves = tiles > kMaxWaves ? kGroupWaves : tiles > 0 ? tiles : 1;
+  *group_tokens = *waves * 32 / group;      // (32 is a multiple of the group size)
+}
+
+// Calls f(steps) for every (server, query group): its number of 32-key steps.
+template <typename F>
+static void for_each_group(int n_servers, const int* gamma_host, const int* ctx_len_host, int group_tokens, F f) {
+  for (int i = 0; i < n_servers; ++i) {
+    const int T = gamma_host[i] + 1;
+    for (int t0 = 0; t0 < T; t0 += group_tokens)
+      f(((long)ctx_len_host[i] + std::min(T, t0 + group_tokens) + 31) / 32);
+  }
+}
+
+// Entries of the work list: (server, query group, split) triples.
+long attention_items(int n_servers, const int* gamma_host, const int* ctx_len_host, int group_tokens, int steps_per_split) {
+  long n = 0;
+  for_each_group(n_servers, gamma_host, ctx_len_host, group_tokens,
+                 [&](long st) { n += (st + steps_per_split - 1) / steps_per_split; });
+  return n;
+}
+
+// Most (server, query group) pairs of a batch of that size (a group has at least kGroupWaves * 32 / 8 tokens
+// or is its server's last one).
+long attention_max_groups(int max_rows, int max_servers) { return (long)max_servers + max_rows / (kGroupWaves * 4); }
+
+// The most 32-key steps any compute unit is dealt when every group's steps are cut into splits of at most t
+// steps: item_of_workgroup's serpentine over the (server, group, split, KV head) items in the order of decreasing
 // length, which is the order of the work list.  items: their number.  Splits of 2047 steps and more are not
 // modelled (the histogram lives on the stack): the largest long.
-long attention_busiest_cu(int n_kv, int n_servers, const int* gamma_host, const int* ctx_len_host, long t,
-                          long* items_out) {
+long attention_busiest_cu(int n_kv, int n_servers, const int* gamma_host, const int* ctx_len_host, int group_tokens,
+                          long t, long* items_out) {
   constexpr long kCus = kComputeUnits, kMaxLen = 2048;
   long n_of_len[kMaxLen] = {0};
   long items = 0;
-  for (int i = 0; i < n_servers; ++i) {
-    const long st = ((long)ctx_len_host[i] + gamma_host[i] + 1 + 31) / 32, n = (st + t - 1) / t;
+  for_each_group(n_servers, gamma_host, ctx_len_host, group_tokens, [&](long st) {
+    const long n = (st + t - 1) / t;
     const long base = st / n, rem = st - base * n;
     items += n * n_kv;
-    if (t + 2 > kMaxLen) continue;
+    if (t + 2 > kMaxLen) return;
     n_of_len[base + 1] += rem * n_kv;
     n_of_len[base] += (n - rem) * n_kv;
-  }
+  });
   if (items_out) *items_out = items;
   if (t + 2 > kMaxLen) return std::numeric_limits<long>::max();
   const long rounds = (items + kCus - 1) / kCus;
@@ -636,36 +656,38 @@ long attention_busiest_cu(int n_kv, int n_servers, const int* gamma_host, const 
 }
 
 // KV steps (32 keys) per split, and the resulting largest split count, for a batch of n_servers servers with
-// the given draft lengths and contexts and query tiles of at most max_block_tokens rows.  A server's steps
+// the given draft lengths and contexts and blocks of at most max_block_tokens rows.  A group's steps
 // are cut into ceil(steps / steps_per_split) splits of equal length up to one step.  All workgroups of the
 // launch should be resident at once (they share the memory bandwidth; a second round starts with the chip
 // half empty: measured on the 70B shape, 5.9 instead of 6.7 ms per step), which also keeps the partial
 // results few; a floor on the steps per split bounds what the partial results cost on small batches.
+// Prompt blocks whose unsplit groups already give every compute unit a workgroup are not split at all: they are
+// bound by arithmetic, the serpentine deals long and short groups evenly, and splits would only add partial results.
 void attention_plan(int n_kv, int group, int max_block_tokens, int n_servers, const int* gamma_host,
                     const int* ctx_len_host, int* steps_per_split, int* max_splits) {
-  const int tiles = ceil_div(max_block_tokens * group, 32);
-  const int waves = tiles < 8 ? (tiles > 0 ? tiles : 1) : 8;
+  int waves, group_tokens;
+  attention_groups(group, max_block_tokens, &waves, &group_tokens);
   constexpr int kWavesPerCu = 12;    // by registers (three waves per SIMD)
   const int wgs_per_cu = kWavesPerCu / waves < 5 ? (kWavesPerCu / waves > 0 ? kWavesPerCu / waves : 1) : 5;   // 5 workgroups by LDS
   const long slots = (long)kComputeUnits * wgs_per_cu;
-  auto steps_of = [&](int i) { return ((long)ctx_len_host[i] + gamma_host[i] + 1 + 31) / 32; };
-  long total_steps = 0, max_steps = 1;
-  for (int i = 0; i < n_servers; ++i) {
-    total_steps += steps_of(i);
-    if (steps_of(i) > max_steps) max_steps = steps_of(i);
-  }
+  long total_steps = 0, max_steps = 1, n_groups = 0;
+  for_each_group(n_servers, gamma_host, ctx_len_host, group_tokens, [&](long st) {
+    total_steps += st;
+    max_steps = std::max(max_steps, st);
+    n_groups += 1;
+  });
   // workgroups of a launch with splits of at most t steps
   auto workgroups = [&](long t) {
-    long c = 0;
-    for (int i = 0; i < n_servers; ++i) c += (steps_of(i) + t - 1) / t;
-    return c * n_kv;
+    return attention_items(n_servers, gamma_host, ctx_len_host, group_tokens, (int)t) * n_kv;
   };
-  long lo = (max_steps + 31) / 32;                        // at most 32 splits per server
+  long lo = (max_steps + 31) / 32;                        // at most 32 splits per group
   if (lo < 6) lo = 6;                                     // at least 6 steps per split (partial-result traffic)
   if (lo > max_steps) lo = max_steps;
   const long fit = slots - slots / 16;                    // all resident at once, with some slack for placement
   long sps;
-  if (workgroups(max_steps) <= fit) {
+  if (n_groups > n_servers && n_groups * n_kv >= kComputeUnits) {
+    sps = max_steps;
+  } else if (workgroups(max_steps) <= fit) {
     // the shortest splits whose workgroups are all resident at once ...
     long a = lo, b = max_steps;
     while (a < b) {
@@ -678,16 +700,16 @@ void attention_plan(int n_kv, int group, int max_block_tokens, int n_servers, co
     // servers (5.3 against 5.6 ms of attention per step).  Small differences do not pay for the workgroups that
     // are then missing per compute unit (8 servers at 2048 tokens: 2 x 9 steps on 512 workgroups took 17.1 us
     // per layer, 3 x 6 on 704 take 15.1), hence the margin of 8 %.
-    long best = attention_busiest_cu(n_kv, n_servers, gamma_host, ctx_len_host, sps, nullptr);
+    long best = attention_busiest_cu(n_kv, n_servers, gamma_host, ctx_len_host, group_tokens, sps, nullptr);
     for (long t = sps + 1; t <= sps + sps / 2 && t <= max_steps; ++t) {
-      const long l = attention_busiest_cu(n_kv, n_servers, gamma_host, ctx_len_host, t, nullptr);
+      const long l = attention_busiest_cu(n_kv, n_servers, gamma_host, ctx_len_host, group_tokens, t, nullptr);
       if (l * 100 < best * 92) {
         best = l;
         sps = t;
       }
     }
   } else {
-    // more (server, KV head) pairs than slots: several rounds of workgroups anyway
+    // more (group, KV head) pairs than slots: several rounds of workgroups anyway
     sps = (total_steps * n_kv + slots / 2 - 1) / (slots / 2);
     if (sps < lo) sps = lo;
     if (sps > max_steps) sps = max_steps;
@@ -706,29 +728,25 @@ size_t attention_workspace_floats(int n_rows, int n_heads, int hd, int max_split
 template <int HD, int G>
 static gs_status launch_mfma_g(const bf16_t* q, const bf16_t* k_pages, const bf16_t* v_pages, const int* block_table,
                                int max_blocks, const int* work, int n_work, int page_size,
-                               int n_heads, int n_kv, int max_block_tokens, int steps_per_split, int max_splits,
-                               float* po, float* pml, hipStream_t stream) {
-  const int tiles = ceil_div(max_block_tokens * G, 32);
+                               int n_heads, int n_kv, int waves, int steps_per_split, int max_splits,
+                               float* po, float* pml, bf16_t* attn_out, hipStream_t stream) {
   dim3 grid((unsigned)n_work * (unsigned)n_kv);      // one workgroup per (entry, KV head) item, see item_of_workgroup
-  for (int t0 = 0; t0 < tiles; t0 += 8) {      // at most 8 query tiles (waves) per workgroup
-    const int waves = tiles - t0 < 8 ? tiles - t0 : 8;
 #define GS_RING(NW_)                                                                                              \
   attn_kernel<HD, G, NW_><<<grid, 64 * NW_, 0, stream>>>(q, k_pages, v_pages, block_table, max_blocks, work,      \
                                                          n_work, page_size, n_heads, n_kv, steps_per_split, max_splits,   \
-                                                         t0 * 32, po, pml)
-    switch (waves) {
-      case 1: GS_RING(1); break;
-      case 2: GS_RING(2); break;
-      case 3: GS_RING(3); break;
-      case 4: GS_RING(4); break;
-      case 5: GS_RING(5); break;
-      case 6: GS_RING(6); break;
-      case 7: GS_RING(7); break;
-      default: GS_RING(8); break;
-    }
-#undef GS_RING
-    GS_LAUNCH_CHECK("attn");
+                                                         po, pml, attn_out)
+  switch (waves) {
+    case 1: GS_RING(1); break;
+    case 2: GS_RING(2); break;
+    case 3: GS_RING(3); break;
+    case 4: GS_RING(4); break;
+    case 5: GS_RING(5); break;
+    case 6: GS_RING(6); break;
+    case 7: GS_RING(7); break;
+    default: GS_RING(8); break;
   }
+#undef GS_RING
+  GS_LAUNCH_CHECK("attn");
   return GS_OK;
 }
 
@@ -737,20 +755,21 @@ size_t attention_work_ints(int capacity) { return 8 + 8 * (size_t)capacity; }
 
 // Builds the step's work list (bf16 path): once per step, the block tables being the same for every layer.
 gs_status launch_attention_work(const int* cu_rows, const int* ctx_len, int n_servers, const int* block_table,
-                                int max_blocks, int page_size, int steps_per_split, int capacity, int* work,
-                                hipStream_t stream) {
-  attn_work_kernel<<<1, 256, 0, stream>>>(cu_rows, ctx_len, n_servers, block_table, max_blocks, page_size,
-                                          steps_per_split, capacity, work);
+                                int max_blocks, int page_size, int steps_per_split, int group_tokens, int capacity,
+                                int* work, hipStream_t stream) {
+  attn_work_kernel<<<1, kWorkThreads, 0, stream>>>(cu_rows, ctx_len, n_servers, block_table, max_blocks, page_size,
+                                                   steps_per_split, group_tokens, capacity, work);
   GS_LAUNCH_CHECK("attn_work");
   return GS_OK;
 }
 
 // attn_out [R][H*hd] (storage type).  scratch: attention_workspace_floats floats; work, n_work: the step's work
-// list and its length as the host computes it from its copy of the batch geometry (bf16 path only).
+// list and its length as the host computes it from its copy of the batch geometry (bf16 path only).  waves: per
+// workgroup (attention_groups).  split: whether any group has more than one split.
 gs_status launch_attention(int dtype, const void* q, const void* k_pages, const void* v_pages,
                            const int* block_table, int max_blocks, const int* cu_rows, const int* ctx_len,
                            int n_servers, int n_rows, int page_size, int n_heads, int n_kv, int hd,
-                           int max_block_tokens, int steps_per_split, int max_splits, const void* row_info,
+                           int waves, int steps_per_split, int max_splits, bool split, const void* row_info,
                            const int* work, int n_work, float* scratch, void* attn_out, hipStream_t stream) {
   if (dtype == GS_F32) {
     dim3 grid(n_rows, n_heads);
@@ -777,11 +796,12 @@ gs_status launch_attention(int dtype, const void* q, const void* k_pages, const 
 #define GS_ATTN_CASE(HD_, G_)                                                                                     \
   if (hd == HD_ && G == G_)                                                                                       \
     st = launch_mfma_g<HD_, G_>(qb, kb, vb, block_table, max_blocks, work, n_work, page_size, n_heads, n_kv,     \
-                                max_block_tokens, steps_per_split, max_splits, po, pml, stream);
+                                waves, steps_per_split, max_splits, po, pml,                                       \
+                                split ? nullptr : static_cast<bf16_t*>(attn_out), stream);
   GS_ATTN_CASE(128, 1) GS_ATTN_CASE(128, 2) GS_ATTN_CASE(128, 4) GS_ATTN_CASE(128, 8)
   GS_ATTN_CASE(64, 1) GS_ATTN_CASE(64, 2) GS_ATTN_CASE(64, 4) GS_ATTN_CASE(64, 8)
 #undef GS_ATTN_CASE
-  if (st != GS_OK) return st;
+  if (st != GS_OK || !split) return st;
   if (hd == 128)
     attn_combine_kernel<128><<<n_rows * n_heads, 128, 0, stream>>>(po, pml, max_splits, steps_per_split,
                                                                    static_cast<const int4*>(row_info), n_heads,

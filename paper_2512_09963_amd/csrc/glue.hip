@@ -109,18 +109,20 @@ __global__ __launch_bounds__(1024) void add_rmsnorm_kernel(float* __restrict__ x
 }
 
 // Per-row facts that every layer of a step shares: where the row's K/V go (page, slot), how many keys
-// its server has after the append, and the rotary sine/cosine of its position.  rope [R][hd/2] (cos, sin).  The angle pos * theta^(-2i/hd)
+// its attention query group (group_tokens consecutive tokens of the block) sees, and the rotary sine/cosine of its position.  rope [R][hd/2] (cos, sin).  The angle pos * theta^(-2i/hd)
 // reaches thousands of radians: it is formed in double, so that the rotated values agree with a
 // float64 evaluation to fp32 rounding.  grid R, block hd/2.
 __global__ void row_meta_kernel(const int* __restrict__ cu_rows, const int* __restrict__ ctx_len, int n_servers,
                                 const int* __restrict__ block_table, int max_blocks, int page_size, int hd,
-                                double log2_theta, int4* __restrict__ row_slot, float2* __restrict__ rope) {
+                                double log2_theta, int group_tokens, int4* __restrict__ row_slot,
+                                float2* __restrict__ rope) {
   const int r = blockIdx.x, i = threadIdx.x;
   const int srv = server_of_row(cu_rows, n_servers, r);
-  const int pos = ctx_len[srv] + (r - cu_rows[srv]);
-  if (i == 0)      // (page, slot) of the row's own K/V, keys of its server after the append, server
+  const int j = r - cu_rows[srv], pos = ctx_len[srv] + j;
+  if (i == 0)      // (page, slot) of the row's own K/V, keys its attention query group sees, server
     row_slot[r] = make_int4(block_table[(size_t)srv * max_blocks + pos / page_size], pos % page_size,
-                            ctx_len[srv] + (cu_rows[srv + 1] - cu_rows[srv]), srv);
+                            ctx_len[srv] + min(cu_rows[srv + 1] - cu_rows[srv], (j / group_tokens + 1) * group_tokens),
+                            srv);
   const double inv_freq = exp2(-2.0 * (double)i / (double)hd * log2_theta);
   double sn, cs;
   sincos((double)pos * inv_freq, &sn, &cs);
@@ -221,10 +223,10 @@ gs_status launch_add_rmsnorm(int dtype, float* x, const float* partial, int n_sp
 }
 
 gs_status launch_row_meta(const int* cu_rows, const int* ctx_len, int n_servers, int n_rows, const int* block_table,
-                          int max_blocks, int page_size, int hd, float rope_theta, void* row_slot, void* rope,
-                          hipStream_t stream) {
+                          int max_blocks, int page_size, int hd, float rope_theta, int group_tokens, void* row_slot,
+                          void* rope, hipStream_t stream) {
   row_meta_kernel<<<n_rows, hd / 2, 0, stream>>>(cu_rows, ctx_len, n_servers, block_table, max_blocks, page_size, hd,
-                                                 log2((double)rope_theta), static_cast<int4*>(row_slot),
+                                                 log2((double)rope_theta), group_tokens, static_cast<int4*>(row_slot),
                                                  static_cast<float2*>(rope));
   GS_LAUNCH_CHECK("row_meta");
   return GS_OK;

@@ -23,26 +23,29 @@ gs_status launch_embed(int dtype, const void* embed, const int* tokens, float* x
 gs_status launch_add_rmsnorm(int dtype, float* x, const float* partial, int n_splits, int n_rows, const float* w,
                              float eps, void* h, int d, hipStream_t stream);
 gs_status launch_row_meta(const int* cu_rows, const int* ctx_len, int n_servers, int n_rows, const int* block_table,
-                          int max_blocks, int page_size, int hd, float rope_theta, void* row_slot, void* rope,
-                          hipStream_t stream);
+                          int max_blocks, int page_size, int hd, float rope_theta, int group_tokens, void* row_slot,
+                          void* rope, hipStream_t stream);
 gs_status launch_rope_append(int dtype, const float* qkv, int n_splits, int n_rows, const void* row_slot,
                              const void* rope, int page_size, int n_heads, int n_kv, int hd, void* q_out,
                              void* k_pages, void* v_pages, hipStream_t stream);
 gs_status launch_swiglu(int dtype, const float* gu, int n_splits, int n_rows, int F, void* act, hipStream_t stream);
 void attention_plan(int n_kv, int group, int max_block_tokens, int n_servers, const int* gamma_host,
                     const int* ctx_len_host, int* steps_per_split, int* max_splits);
-long attention_busiest_cu(int n_kv, int n_servers, const int* gamma_host, const int* ctx_len_host, long t,
-                          long* items_out);
+void attention_groups(int group, int max_block_tokens, int* waves, int* group_tokens);
+long attention_items(int n_servers, const int* gamma_host, const int* ctx_len_host, int group_tokens, int steps_per_split);
+long attention_max_groups(int max_rows, int max_servers);
+long attention_busiest_cu(int n_kv, int n_servers, const int* gamma_host, const int* ctx_len_host, int group_tokens,
+                          long t, long* items_out);
 size_t attention_workspace_floats(int n_rows, int n_heads, int hd, int max_splits);
 gs_status launch_attention(int dtype, const void* q, const void* k_pages, const void* v_pages,
                            const int* block_table, int max_blocks, const int* cu_rows, const int* ctx_len,
                            int n_servers, int n_rows, int page_size, int n_heads, int n_kv, int hd,
-                           int max_block_tokens, int steps_per_split, int max_splits, const void* row_info,
+                           int waves, int steps_per_split, int max_splits, bool split, const void* row_info,
                            const int* work, int n_work, float* scratch, void* attn_out, hipStream_t stream);
 size_t attention_work_ints(int capacity);
 gs_status launch_attention_work(const int* cu_rows, const int* ctx_len, int n_servers, const int* block_table,
-                                int max_blocks, int page_size, int steps_per_split, int capacity, int* work,
-                                hipStream_t stream);
+                                int max_blocks, int page_size, int steps_per_split, int group_tokens, int capacity,
+                                int* work, hipStream_t stream);
 gs_status launch_accept(int n_servers, int n_rows, const int* cu_rows, int vocab, int elem, const void* target_logits,
                         const void* q_probs, const int* draft_tokens, const float* u_accept,
                         const float* u_resample, const gs_accept_out* out, void* workspace, hipStream_t stream,
@@ -131,7 +134,8 @@ Plan make_plan(const gs_ctx* ctx, int max_rows, int max_servers, int max_ctx, vo
   const int max_steps = (max_ctx + 31) / 32;
   const int max_splits = std::max(1, std::min(32, (max_steps + 5) / 6)) | 1;   // odd, like the planner's
   p.attn_scratch = c.take<float>(gs::attention_workspace_floats(max_rows, m.n_heads, m.head_dim, max_splits));
-  p.attn_work_capacity = max_servers * max_splits;
+  // (a work list of 2^31 ints is refused below: at most 2^20 rows and far fewer groups)
+  p.attn_work_capacity = (int)std::min<long>(gs::attention_max_groups(max_rows, max_servers) * max_splits, 1L << 27);
   p.attn_work = c.take<int>(gs::attention_work_ints(p.attn_work_capacity));
   p.logits = c.take<float>(R * m.vocab);
   p.draft_tokens = c.take<int>(R);
@@ -414,9 +418,11 @@ extern "C" gs_status gs_verify_batch(gs_ctx* ctx, const gs_kv_cache* kv, const g
   const int rows = (int)R, d = m.d_model, hq = m.n_heads * m.head_dim, qkv = (m.n_heads + 2 * m.n_kv_heads) * m.head_dim;
   const int F = m.d_ffn;
   const size_t layer_stride = (size_t)kv->n_pages * m.n_kv_heads * kv->page_size * m.head_dim * ctx->elem;
-  int attn_sps = 1, attn_splits = 1;
+  int attn_sps = 1, attn_splits = 1, attn_waves = 1, group_tokens = 1;
+  gs::attention_groups(m.n_heads / m.n_kv_heads, max_t, &attn_waves, &group_tokens);
   gs::attention_plan(m.n_kv_heads, m.n_heads / m.n_kv_heads, max_t, n, b->gamma_host, b->ctx_len_host, &attn_sps,
                      &attn_splits);
+  bool attn_split = max_ctx > 32L * attn_sps;      // any group with more than one split
   gs_status st;
 #define GS_TRY(call)          \
   do {                        \
@@ -424,9 +430,8 @@ extern "C" gs_status gs_verify_batch(gs_ctx* ctx, const gs_kv_cache* kv, const g
     if (st != GS_OK) return st; \
   } while (0)
 
-  int attn_items = 0;      // (server, split) pairs with keys: the length of the attention work list
-  for (int i = 0; i < n; ++i)
-    attn_items += ((b->ctx_len_host[i] + b->gamma_host[i] + 1 + 31) / 32 + attn_sps - 1) / attn_sps;
+  // (server, query group, split) triples: the length of the attention work list
+  const long attn_items = gs::attention_items(n, b->gamma_host, b->ctx_len_host, group_tokens, attn_sps);
   if (attn_items > p.attn_work_capacity) return gs::fail(GS_ECAPACITY, "attention work list overflow");
 
   StageTimer timer(ctx, stream);
@@ -438,10 +443,11 @@ extern "C" gs_status gs_verify_batch(gs_ctx* ctx, const gs_kv_cache* kv, const g
   } while (0)
   GS_STAGE(GS_STAGE_GLUE, gs::launch_embed(act, ctx->embed, b->tokens, p.x, rows, d, m.vocab, stream));
   GS_STAGE(GS_STAGE_GLUE, gs::launch_row_meta(b->cu_rows, b->ctx_len, n, rows, b->block_table, b->max_blocks, kv->page_size,
-                                              m.head_dim, m.rope_theta, p.row_slot, p.rope, stream));
+                                              m.head_dim, m.rope_theta, group_tokens, p.row_slot, p.rope, stream));
   if (act == GS_BF16)
     GS_STAGE(GS_STAGE_GLUE, gs::launch_attention_work(b->cu_rows, b->ctx_len, n, b->block_table, b->max_blocks,
-                                                      kv->page_size, attn_sps, p.attn_work_capacity, p.attn_work, stream));
+                                                      kv->page_size, attn_sps, group_tokens, p.attn_work_capacity, p.attn_work,
+                                                      stream));
   const float* pending = nullptr;   // split-K partials of the projection whose result is still to be added to x
   int pending_splits = 0;
   for (int l = 0; l < m.n_layers; ++l) {
@@ -455,8 +461,8 @@ extern "C" gs_status gs_verify_batch(gs_ctx* ctx, const gs_kv_cache* kv, const g
     GS_STAGE(GS_STAGE_GLUE, gs::launch_rope_append(act, p.partial, gs::gemm_splits(m.dtype, rows, qkv, d), rows, p.row_slot,
                                   p.rope, kv->page_size, m.n_heads, m.n_kv_heads, m.head_dim, p.q, kl, vl, stream));
     GS_STAGE(GS_STAGE_ATTENTION, gs::launch_attention(act, p.q, kl, vl, b->block_table, b->max_blocks, b->cu_rows, b->ctx_len, n, rows,
-                                kv->page_size, m.n_heads, m.n_kv_heads, m.head_dim, max_t, attn_sps, attn_splits,
-                                p.row_slot, p.attn_work, attn_items, p.attn_scratch, p.attn, stream));
+                                kv->page_size, m.n_heads, m.n_kv_heads, m.head_dim, attn_waves, attn_sps, attn_splits,
+                                attn_split, p.row_slot, p.attn_work, (int)attn_items, p.attn_scratch, p.attn, stream));
     GS_STAGE(GS_STAGE_GEMM, gs::launch_gemm(m.dtype, p.attn, ctx->wo[l], p.partial, rows, d, hq, stream));
     GS_STAGE(GS_STAGE_GLUE, gs::launch_add_rmsnorm(act, p.x, p.partial, gs::gemm_splits(m.dtype, rows, d, hq), rows,
                                                    ctx->norm2[l], m.rms_eps, p.h, d, stream));
@@ -551,10 +557,11 @@ extern "C" gs_status gs_plan_attention(int n_kv_heads, int group, int n_servers,
       return gs::fail(GS_EINVAL, "server %d: gamma = %d, ctx_len = %d", i, gamma_host[i], ctx_len_host[i]);
     max_t = std::max(max_t, gamma_host[i] + 1);
   }
-  int sps = 1, splits = 1;
+  int sps = 1, splits = 1, waves = 1, group_tokens = 1;
+  gs::attention_groups(group, max_t, &waves, &group_tokens);
   gs::attention_plan(n_kv_heads, group, max_t, n_servers, gamma_host, ctx_len_host, &sps, &splits);
   long items = 0;
-  const long busiest = gs::attention_busiest_cu(n_kv_heads, n_servers, gamma_host, ctx_len_host, sps, &items);
+  const long busiest = gs::attention_busiest_cu(n_kv_heads, n_servers, gamma_host, ctx_len_host, group_tokens, sps, &items);
   *steps_per_split = sps;
   if (n_workgroups) *n_workgroups = items;
   if (busiest_cu_steps) *busiest_cu_steps = busiest;

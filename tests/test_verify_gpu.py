@@ -153,6 +153,20 @@ def test_f32_projection_and_attention_edges(ms, gamma, ctx):
     _run_case(ms, 87, np.array(gamma, np.int32), np.array(ctx, np.int32), 16, std=0.08)
 
 
+@pytest.mark.parametrize("heads,n_kv,hd,gamma,ctx,page", [
+    # blocks of more than 256 query rows per KV head are cut into query groups of 128 rows: group ends on and one past a
+    # tile, one-row remainders, decode-sized servers beside them, contexts that are cut into KV splits
+    (4, 1, 128, [64, 2, 127, 0], [0, 500, 77, 33], 16),
+    (8, 1, 64, [47, 48, 31, 15], [700, 0, 16, 1500], 32),
+    (2, 2, 64, [256, 258, 5], [31, 0, 1025], 16),
+    # enough groups for every compute unit: nothing is split, the kernel stores the result itself
+    (64, 8, 64, [511, 3], [0, 900], 64),
+])
+def test_bf16_prompt_blocks_in_query_groups(heads, n_kv, hd, gamma, ctx, page):
+    ms = synth.ModelShape(1, 128, heads, n_kv, hd, 256, 1024, 10000.0, dtype="bf16")
+    _run_case(ms, 88, np.array(gamma, np.int32), np.array(ctx, np.int32), page, std=0.08)
+
+
 @pytest.mark.parametrize("gamma", [[3, 1, 5], [16, 12, 9, 15, 11, 14]])
 def test_bf16_wide_vocabulary_statistics_from_the_lm_head_epilogue(gamma):
     # V / 128 >= 192: the LM head takes the 8-wave kernel (12 rows) or the tall one (83 rows) as one launch, whose
