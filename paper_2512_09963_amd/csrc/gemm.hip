@@ -26,6 +26,7 @@
 // fp32 path: plain LDS-tiled FMA kernel for the small fp32 configuration.
 #include "common.h"
 #include "device_types.h"
+#include "gemm_common.h"
 
 namespace gs {
 namespace {
@@ -42,33 +43,6 @@ constexpr int kSkinnyDepth = 4;     // k steps of weights and activations in fli
 constexpr int kTargetWorkgroups = 512;   // about two per CU
 constexpr int kBK = 64;           // k elements per step
 constexpr int kLdsRow = kBK + 8;  // padded LDS row (bf16 elements): 144 bytes
-
-// Merge of two online-softmax pairs (max, sum exp(x - max)).
-__device__ __forceinline__ void merge_stat(float& m, float& s, float m2, float s2) {
-  const float M = fmaxf(m, m2);
-  s = s * __expf(m - M) + s2 * __expf(m2 - M);
-  m = M;
-}
-
-// Reductions over the 16 lanes of a DPP row (lanes 16 g .. 16 g + 15) with data-parallel-primitive moves, which
-// are modifiers of ordinary vector instructions (a shuffle through the LDS crossbar costs an LDS instruction
-// each): neighbours in a quad, the other pair of the quad, the mirrored quad of the half row, the mirrored half.
-template <int CTRL>
-__device__ __forceinline__ float dpp_move(float v) {
-  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, false));
-}
-__device__ __forceinline__ float row16_max(float v) {
-  v = fmaxf(v, dpp_move<0xB1>(v));      // quad_perm(1, 0, 3, 2)
-  v = fmaxf(v, dpp_move<0x4E>(v));      // quad_perm(2, 3, 0, 1)
-  v = fmaxf(v, dpp_move<0x141>(v));     // row_half_mirror
-  return fmaxf(v, dpp_move<0x140>(v));  // row_mirror
-}
-__device__ __forceinline__ float row16_sum(float v) {
-  v += dpp_move<0xB1>(v);
-  v += dpp_move<0x4E>(v);
-  v += dpp_move<0x141>(v);
-  return v + dpp_move<0x140>(v);
-}
 
 // STATS (LM head, one K split): the epilogue also reduces every output row over the workgroup's columns to the
 // pair (max, sum exp(y - max)) and stores it at stats[row][column block], so that the vocabulary softmax
@@ -308,19 +282,16 @@ __global__ __launch_bounds__(64 * NW) void gemm_bf16_gate_up_kernel(const bf16_t
   }
 }
 
-// More than 64 rows (a few hundred per step with tens of draft servers): the same streaming design
-// with a taller and wider wave tile.  A wave owns NT column tiles and all MT * 16 rows of its row
-// chunk, so every activation fragment read from LDS feeds NT MFMAs and every weight fragment MT of
-// them; a workgroup covers NT * 64 columns.  Two shapes are used: (MT <= 10, NT = 2, two steps of
-// prefetch) while the weight stream still matters (up to a few hundred rows), and (MT = 8, NT = 4, no
-// register prefetch: the second wave on each SIMD hides the latency) for row counts where the MFMA
-// pipes are the bound.  Both fit two waves per SIMD.
+// 640 rows and more: the same streaming design with a taller and wider wave tile.  A wave owns NT column tiles and
+// all MT * 16 rows of its row chunk, so every activation fragment read from LDS feeds NT MFMAs and every weight
+// fragment MT of them; a workgroup covers NT * 64 columns.  (MT = 8, NT = 4, no register prefetch: the second
+// wave on each SIMD hides the latency.)
 // Row chunks of one column block are separate workgroups that read the same weights: workgroups are
 // handed to the 8 XCDs round robin by their linear index, so the chunks of a column block get indices
 // that are 8 apart and land on the same XCD one after the other, and all but the first find the weights
 // in that XCD's L2.  grid (ceil(N / (64 NT) / 8) * 8 * m_chunks, S).
-// GATE_UP (NT = 2, one K split): the wave's two column tiles are feature tile t of the gate half and of the
-// up half of a [2F][K] matrix, and the epilogue stores act[r][f] = silu(gate) * up as bf16 ([M][N/2], at P)
+// GATE_UP (one K split): half of the wave's column tiles are feature tiles of the gate half and half the same ones of
+// the up half of a [2F][K] matrix, and the epilogue stores act[r][f] = silu(gate) * up as bf16 ([M][N/2], at P)
 // instead of the fp32 sums.
 // STATS: as in the skinny kernel, (max, sum exp) of every row over the workgroup's 64 NT columns.
 template <int MT, int NT, int DEPTH, bool GATE_UP = false, bool STATS = false>
@@ -597,44 +568,51 @@ gs_status launch_pack_weight(const void* src, void* dst, int N, int K, hipStream
 
 // Which bf16 kernel serves a shape, and how the launch is cut.
 struct GemmPlan {
-  bool tall;      // gemm_bf16_tall_kernel (more than 64 rows, N a multiple of 128)
+  enum Kind {
+    kSkinny,      // up to 32 rows, where the weight stream is all there is (5 rows, 28672 x 4096: 38.9 us, 40 with the wide
+                  // kernel), up to 64 rows where K is split (inside a step: QKV of the 8B shape 13.7 us, 15.2 there, O and
+                  // down 17.8, 18.1), and column counts that are no multiple of 128
+    kWide,        // gemm_wide.hip: from there to 639 rows
+    kTall         // 640 rows and more, N a multiple of 256 (1024 rows, 28672 x 4096: 275 us, 286 with 2 x 2 waves there)
+  } kind;
   int waves;      // skinny: waves per workgroup (4 or 8)
   int mt;         // row tiles per workgroup
-  int nt;         // tall: column tiles per wave (2 or 4)
   int m_chunks;   // row chunks (separate workgroups)
   int splits;     // K splits
   int k_per;      // k elements per split (multiple of 64)
+  WidePlan wide;
 };
+constexpr int kTallNt = 4;      // column tiles per wave of the tall kernel
 
 static GemmPlan gemm_plan(int M, int N, int K) {
   GemmPlan p;
   const int tiles = ceil_div(M, 16);
-  p.tall = tiles > 4 && N % 128 == 0;
-  p.nt = 1;
   int n_blocks;
-  if (p.tall && tiles >= 40 && N % 256 == 0) {        // 640 rows and more: MFMA-bound shape
+  const bool can_wide = tiles > 2 && N % 128 == 0;
+  if (can_wide) p.wide = wide_plan(M, N, K, false);
+  if (tiles >= 40 && N % 256 == 0) {
+    p.kind = GemmPlan::kTall;
     p.waves = 4;
-    p.nt = 4;
     p.mt = 8;
-    p.m_chunks = ceil_div(tiles, 8);
-    n_blocks = N / 256;
-  } else if (p.tall) {
-    p.waves = 4;
-    p.nt = 2;
-    p.m_chunks = ceil_div(tiles, 10);
-    const int per = ceil_div(tiles, p.m_chunks);      // 3 .. 10 row tiles per chunk
-    p.mt = per <= 6 ? 6 : per <= 8 ? 8 : 10;
-    p.m_chunks = ceil_div(tiles, p.mt);
-    n_blocks = N / 128;
+    n_blocks = N / (64 * kTallNt);
+  } else if (can_wide && (tiles > 4 || p.wide.splits == 1)) {
+    p.kind = GemmPlan::kWide;
+    p.waves = p.wide.wm * p.wide.wn;
+    p.mt = p.wide.mt;
+    p.m_chunks = p.wide.m_chunks;
+    p.splits = p.wide.splits;
+    p.k_per = p.wide.k_per;
+    return p;
   } else {
     // wide matrices get 8 waves (128 columns per workgroup), which halves the number of times the
     // activation rows are re-read from L2; narrower ones keep 4 so that the launch still has
     // enough workgroups
+    p.kind = GemmPlan::kSkinny;
     p.waves = (N % 128 == 0 && N / 128 >= 192) ? 8 : 4;
     p.mt = tiles <= 1 ? 1 : tiles <= 2 ? 2 : tiles <= 4 ? 4 : 8;
-    p.m_chunks = ceil_div(tiles, p.mt);
     n_blocks = N / (16 * p.waves);
   }
+  p.m_chunks = ceil_div(tiles, p.mt);
   const int wgs = n_blocks * p.m_chunks;
   int want = (kTargetWorkgroups + wgs / 2) / wgs;                // about two workgroups per CU
   const int max_s = K / 512 > 0 ? K / 512 : 1;             // at least 8 steps per split
@@ -662,43 +640,37 @@ static void launch_skinny(const GemmPlan& p, const bf16_t* x, const bf16_t* w, f
   const int n_blocks = N / (16 * NW);
   const int gx = p.m_chunks > 1 ? ceil_div(n_blocks, 8) * 8 * p.m_chunks : n_blocks;
   const dim3 grid(gx, p.splits, 1);
-  switch (p.mt) {
-    case 1: gemm_bf16_skinny_kernel<1, kSkinnyDepth, NW><<<grid, 64 * NW, 0, stream>>>(x, w, P, M, N, K, p.k_per, 1); break;
-    case 2: gemm_bf16_skinny_kernel<2, kSkinnyDepth, NW><<<grid, 64 * NW, 0, stream>>>(x, w, P, M, N, K, p.k_per, 1); break;
-    case 4: gemm_bf16_skinny_kernel<4, kSkinnyDepth, NW><<<grid, 64 * NW, 0, stream>>>(x, w, P, M, N, K, p.k_per, 1); break;
-    default:
-      gemm_bf16_skinny_kernel<8, kSkinnyDepth, NW><<<grid, 64 * NW, 0, stream>>>(x, w, P, M, N, K, p.k_per, p.m_chunks);
-  }
+#define GS_SKINNY(MT_, CHUNKS_) \
+  gemm_bf16_skinny_kernel<MT_, kSkinnyDepth, NW><<<grid, 64 * NW, 0, stream>>>(x, w, P, M, N, K, p.k_per, CHUNKS_)
+  if (p.mt == 1) GS_SKINNY(1, 1);
+  else if (p.mt == 2) GS_SKINNY(2, 1);
+  else if (p.mt == 4) GS_SKINNY(4, 1);
+  else if constexpr (NW == 4) GS_SKINNY(8, p.m_chunks);      // (8 waves: N is a multiple of 128, so the wide kernel)
+#undef GS_SKINNY
 }
 
+template <bool GATE_UP, bool STATS>
 static void launch_tall(const GemmPlan& p, const bf16_t* x, const bf16_t* w, float* P, int M, int N, int K,
-                        hipStream_t stream) {
-  const dim3 grid(ceil_div(N / (64 * p.nt), 8) * 8 * p.m_chunks, p.splits, 1);
-  if (p.nt == 4) {
-    gemm_bf16_tall_kernel<8, 4, 1><<<grid, 256, 0, stream>>>(x, w, P, M, N, K, p.k_per, p.m_chunks);
-    return;
-  }
-  switch (p.mt) {
-    case 6: gemm_bf16_tall_kernel<6, 2, 2><<<grid, 256, 0, stream>>>(x, w, P, M, N, K, p.k_per, p.m_chunks); break;
-    case 8: gemm_bf16_tall_kernel<8, 2, 2><<<grid, 256, 0, stream>>>(x, w, P, M, N, K, p.k_per, p.m_chunks); break;
-    default: gemm_bf16_tall_kernel<10, 2, 2><<<grid, 256, 0, stream>>>(x, w, P, M, N, K, p.k_per, p.m_chunks);
-  }
+                        float2* stats, int n_stat_blocks, hipStream_t stream) {
+  const dim3 grid(ceil_div(N / (64 * kTallNt), 8) * 8 * p.m_chunks, p.splits, 1);
+  gemm_bf16_tall_kernel<8, kTallNt, 1, GATE_UP, STATS><<<grid, 256, 0, stream>>>(x, w, P, M, N, K, p.k_per, p.m_chunks,
+                                                                                stats, n_stat_blocks);
 }
 
-// Gate/up with the SwiGLU fused: 4 waves (64 features per workgroup; 224 workgroups for F = 14336, each wave
-// streaming 256 KB without a K split), weights fetched 6 steps ahead (with 4 the unsplit kernel is 4.5 us
+// Gate/up with the SwiGLU fused, up to 32 rows: 4 waves (64 features per workgroup; 224 workgroups for F = 14336, each
+// wave streaming 256 KB without a K split), weights fetched 6 steps ahead (with 4 the unsplit kernel is 4.5 us
 // slower than the split one on the 8B shape, with 6 it is 1.3 us slower and the 6 us of the separate SwiGLU
 // kernel and its launch boundary are gone; 2 waves double the activation re-reads, 8 leave half the CUs idle).
 constexpr int kGateUpWaves = 4;
 constexpr int kGateUpDepth = 6;
 
 // Whether the gate/up projection of this shape runs with the SwiGLU fused: bf16, and either up to 64 rows or
-// a shape that the tall kernel serves without a K split anyway.
+// a shape whose kernel needs no K split anyway.
 bool gate_up_fused(int dtype, int M, int F, int K) {
   if (dtype != GS_BF16 || M <= 0 || F % (16 * kGateUpWaves) != 0 || K % kBK != 0) return false;
   if (M <= 64) return true;
   const GemmPlan p = gemm_plan(M, 2 * F, K);
-  return p.tall && p.splits == 1;
+  return p.kind != GemmPlan::kSkinny && p.splits == 1;
 }
 
 // act [M][F] (bf16) = silu(X Wg^T) * (X Wu^T), W = [Wg; Wu] packed; only for shapes gate_up_fused accepts.
@@ -708,27 +680,17 @@ gs_status launch_gemm_gate_up(const void* X, const void* W, void* act, int M, in
   const bf16_t* w = static_cast<const bf16_t*>(W);
   bf16_t* a = static_cast<bf16_t*>(act);
   const int tiles = ceil_div(M, 16);
-  if (tiles > 4) {      // tall kernel, one K split, gate and up tile per wave
+  if (tiles > 2) {
     const GemmPlan p = gemm_plan(M, 2 * F, K);
-    const dim3 grid(ceil_div(2 * F / (64 * p.nt), 8) * 8 * p.m_chunks, 1, 1);
-    float* out = static_cast<float*>(act);
-    if (p.nt == 4) {
-      gemm_bf16_tall_kernel<8, 4, 1, true><<<grid, 256, 0, stream>>>(x, w, out, M, 2 * F, K, K, p.m_chunks);
-      GS_LAUNCH_CHECK("gemm_gate_up_tall");
-      return GS_OK;
-    }
-    switch (p.mt) {
-      case 6: gemm_bf16_tall_kernel<6, 2, 2, true><<<grid, 256, 0, stream>>>(x, w, out, M, 2 * F, K, K, p.m_chunks); break;
-      case 8: gemm_bf16_tall_kernel<8, 2, 2, true><<<grid, 256, 0, stream>>>(x, w, out, M, 2 * F, K, K, p.m_chunks); break;
-      default: gemm_bf16_tall_kernel<10, 2, 2, true><<<grid, 256, 0, stream>>>(x, w, out, M, 2 * F, K, K, p.m_chunks);
-    }
+    if (p.kind != GemmPlan::kTall)      // (2 F is a multiple of 128)
+      return launch_wide_gate_up(wide_plan(M, 2 * F, K, true), x, w, a, M, 2 * F, K, stream);
+    launch_tall<true, false>(p, x, w, static_cast<float*>(act), M, 2 * F, K, nullptr, 0, stream);
     GS_LAUNCH_CHECK("gemm_gate_up_tall");
     return GS_OK;
   }
   const int grid = F / (16 * NW);
   if (tiles <= 1) gemm_bf16_gate_up_kernel<1, D, NW><<<grid, 64 * NW, 0, stream>>>(x, w, a, M, F, K);
-  else if (tiles <= 2) gemm_bf16_gate_up_kernel<2, D, NW><<<grid, 64 * NW, 0, stream>>>(x, w, a, M, F, K);
-  else gemm_bf16_gate_up_kernel<4, D, NW><<<grid, 64 * NW, 0, stream>>>(x, w, a, M, F, K);
+  else gemm_bf16_gate_up_kernel<2, D, NW><<<grid, 64 * NW, 0, stream>>>(x, w, a, M, F, K);
   GS_LAUNCH_CHECK("gemm_gate_up");
   return GS_OK;
 }
@@ -739,7 +701,7 @@ int gemm_stat_blocks(int dtype, int M, int N, int K) {
   if (dtype != GS_BF16 || M <= 0) return 0;
   const GemmPlan p = gemm_plan(M, N, K);
   if (p.splits != 1) return 0;
-  return p.tall ? N / (64 * p.nt) : N / (16 * p.waves);
+  return p.kind == GemmPlan::kWide ? p.wide.n_blocks : p.kind == GemmPlan::kTall ? N / (64 * kTallNt) : N / (16 * p.waves);
 }
 
 // Y [M][N] = X W^T (one K split) and stats [M][gemm_stat_blocks] = per row and column block (max, sum exp(y - max)).
@@ -751,12 +713,9 @@ gs_status launch_gemm_stats(const void* X, const void* W, float* Y, void* stats,
   float2* st = static_cast<float2*>(stats);
   const int nb = gemm_stat_blocks(GS_BF16, M, N, K);
   if (nb == 0) return fail(GS_EUNSUPPORTED, "this projection shape does not emit softmax statistics");
-  if (p.tall) {
-    const dim3 grid(ceil_div(N / (64 * p.nt), 8) * 8 * p.m_chunks, 1, 1);
-    if (p.nt == 4) gemm_bf16_tall_kernel<8, 4, 1, false, true><<<grid, 256, 0, stream>>>(x, w, Y, M, N, K, p.k_per, p.m_chunks, st, nb);
-    else if (p.mt == 6) gemm_bf16_tall_kernel<6, 2, 2, false, true><<<grid, 256, 0, stream>>>(x, w, Y, M, N, K, p.k_per, p.m_chunks, st, nb);
-    else if (p.mt == 8) gemm_bf16_tall_kernel<8, 2, 2, false, true><<<grid, 256, 0, stream>>>(x, w, Y, M, N, K, p.k_per, p.m_chunks, st, nb);
-    else gemm_bf16_tall_kernel<10, 2, 2, false, true><<<grid, 256, 0, stream>>>(x, w, Y, M, N, K, p.k_per, p.m_chunks, st, nb);
+  if (p.kind == GemmPlan::kWide) return launch_wide_stats(p.wide, x, w, Y, st, M, N, K, stream);
+  if (p.kind == GemmPlan::kTall) {
+    launch_tall<false, true>(p, x, w, Y, M, N, K, st, nb, stream);
   } else {
     const int n_blocks = N / (16 * p.waves);
     const int gx = p.m_chunks > 1 ? ceil_div(n_blocks, 8) * 8 * p.m_chunks : n_blocks;
@@ -764,13 +723,9 @@ gs_status launch_gemm_stats(const void* X, const void* W, float* Y, void* stats,
     const int mc = p.mt == 8 ? p.m_chunks : 1;
 #define GS_SKINNY_STATS(MT_, NW_) \
   gemm_bf16_skinny_kernel<MT_, kSkinnyDepth, NW_, true><<<grid, 64 * NW_, 0, stream>>>(x, w, Y, M, N, K, p.k_per, mc, st, nb)
-    if (p.waves == 8) {
-      switch (p.mt) {
-        case 1: GS_SKINNY_STATS(1, 8); break;
-        case 2: GS_SKINNY_STATS(2, 8); break;
-        case 4: GS_SKINNY_STATS(4, 8); break;
-        default: GS_SKINNY_STATS(8, 8);
-      }
+    if (p.waves == 8) {      // (up to 32 rows: more take the wide kernel where N is a multiple of 128 and K is not split)
+      if (p.mt == 1) GS_SKINNY_STATS(1, 8);
+      else GS_SKINNY_STATS(2, 8);
     } else {
       switch (p.mt) {
         case 1: GS_SKINNY_STATS(1, 4); break;
@@ -816,7 +771,8 @@ gs_status launch_gemm(int dtype, const void* X, const void* W, float* P, int M, 
     const GemmPlan p = gemm_plan(M, N, K);
     const bf16_t* x = static_cast<const bf16_t*>(X);
     const bf16_t* w = static_cast<const bf16_t*>(W);
-    if (p.tall) launch_tall(p, x, w, P, M, N, K, stream);
+    if (p.kind == GemmPlan::kWide) return launch_wide(p.wide, x, w, P, M, N, K, stream);
+    if (p.kind == GemmPlan::kTall) launch_tall<false, false>(p, x, w, P, M, N, K, nullptr, 0, stream);
     else if (p.waves == 8) launch_skinny<8>(p, x, w, P, M, N, K, stream);
     else launch_skinny<4>(p, x, w, P, M, N, K, stream);
     GS_LAUNCH_CHECK("gemm_bf16");

@@ -1,0 +1,362 @@
+// bf16 projections for 33 to a few hundred rows (MFMA): the packed weight stream of gemm.hip with a software pipeline
+// that leaves neither the matrix pipe nor the stream waiting.
+//
+// What bounds it: up to about 130 rows the weight stream (HBM), above the matrix pipe together with the LDS
+// reads of the activations: a 1 KB activation fragment feeds NT MFMAs of 16 cycles, so at NT = 2 the LDS delivers its
+// limit of 128 bytes per cycle and compute unit; tiles of more than 8 row tiles therefore take NT = 4.
+// The predecessor of this kernel (two LDS buffers, fragments read where they are used, all loads of a step in one
+// burst behind the barrier) was held up by neither: the loads' addresses, the LDS stores and the first fragment reads
+// of a step ran while the matrix pipe was idle, and the compiler sank the loads to the end of the step, where the
+// next one waited for them.  Here
+//   * a step (64 of k) is a sequence of MT blocks, one per row tile, each of which issues its share of the next weight
+//     loads, one piece of the next activation tile (LDS store of the piece that has landed, load of the one after)
+//     and the fragment reads of the row tile two blocks ahead, and then its 2 NT MFMAs; a scheduling barrier after
+//     every block keeps the compiler from undoing that order
+//   * the activation tile lives in three LDS buffers, so that the fragments of the next step's first two blocks can be
+//     read before the barrier that ends the step (the buffer they come from was published one barrier earlier)
+//   * activation rows are 128 bytes in LDS, their 16-byte pieces XOR-swizzled by the row pair: conflict-free reads
+//   * loads are buffer loads: the descriptor moves with k on the scalar unit and the lane offsets are constant, so a
+//     load costs no vector instruction for its address; rows past the end read as zero by the descriptor's range
+// Three shapes: WM x WN waves, each with MT x NT tiles of 16 x 16, KG groups of them that share K:
+//   1 x 8 (256 columns, wide matrices), up to 128 rows: no weight byte is loaded twice
+//   1 x 4 (128 columns) with KG = 2: the two halves of K in one workgroup, their sums meet in LDS: as many waves as 1 x 8
+//     without halving the workgroups of a narrower matrix, and half the partial results of a further K split (which the
+//     gate/up projection, whose epilogue applies the SwiGLU, must not have)
+//   2 x 2 (128 columns, up to 352 rows in one workgroup): both row halves load the weights, the second time from L1
+// Measured inside a verification step (us per launch; predecessor in brackets), N x K:
+//   53 rows   gate/up 28672 x 4096 39.7 (46.0) = 5.9 TB/s, LM head 128256 x 4096 181 (188)
+//   92 rows   gate/up 57344 x 8192 142 (181) = 6.6 TB/s, 8192 x 28672 and 8192 x 8192 55 (60) on average, 10240 x 8192
+//             35.7 (37.9), LM head 128256 x 8192 347 (455) = 6.1 TB/s
+//   324 rows  gate/up 28672 x 4096 82.7 (124) = 0.92 PFLOP/s, 4096 x 14336 and 4096 x 4096 33.6 (38) on average, 6144 x 4096
+//             25.0 (39), LM head 128256 x 4096 348 (440)
+#include "common.h"
+#include "device_types.h"
+#include "gemm_common.h"
+#include <algorithm>
+
+namespace gs {
+namespace {
+
+typedef unsigned int uintx4_t __attribute__((ext_vector_type(4)));
+
+enum { kPlain = 0, kGateUp = 1, kStats = 2 };
+
+// MODE: kPlain stores the fp32 sums [split][M][N] at P; kGateUp (one split): the wave's tiles are NT / 2 feature tiles of
+// the gate half and the same ones of the up half of a [2F][K] matrix (N = 2F), and act[M][F] = silu(gate) * up is
+// stored as bf16 at P; kStats (one split): also (max, sum exp) of every row over the workgroup's columns.
+// DB, DA: steps of weights and of activations held in registers.  POL: cache policy of the weight loads (2: do not
+// displace other lines; for weights that one workgroup reads once).
+// grid (column blocks, rounded up to a multiple of 8, times row chunks; K splits), see gemm.hip for the chunk order.
+template <int WM, int WN, int KG, int MT, int NT, int DB, int DA, int POL, int WPE, int MODE>
+__global__ __launch_bounds__(64 * WM * WN * KG) __attribute__((amdgpu_waves_per_eu(WPE, WPE))) void gemm_bf16_wide_kernel(
+    const bf16_t* __restrict__ X, const bf16_t* __restrict__ Wp, float* __restrict__ P, int M, int N, int K,
+    int k_per_split, int m_chunks, float2* __restrict__ stats, int n_stat_blocks) {
+  static_assert(MT >= 2, "fragments are read two row tiles ahead");
+  static_assert(DB % DA == 0, "the unrolled ring addresses the activation slots statically");
+  static_assert(KG == 1 || (KG == 2 && MODE != kStats), "sums of two K groups");
+  constexpr int ROWS = WM * MT * 16, THREADS = 64 * WM * WN;       // of one K group
+  constexpr int PASSES = (ROWS * 8 + THREADS - 1) / THREADS;
+  constexpr int TILE = ROWS * 128;                                 // bytes of one activation buffer
+  __shared__ __attribute__((aligned(16))) unsigned char xs_all[KG * 3 * TILE];
+  const int lane = threadIdx.x & 63;
+  const int wave_all = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int kg = wave_all / (WM * WN), wave = wave_all % (WM * WN);
+  const int tid = threadIdx.x - kg * THREADS;
+  unsigned char* xs = xs_all + kg * 3 * TILE;
+  const int g = lane >> 4, c = lane & 15;
+  const int xcd = blockIdx.x & 7, t = blockIdx.x >> 3;
+  const int m_chunk = t % m_chunks;
+  const int n_block = (t / m_chunks) * 8 + xcd;
+  if (n_block * (16 * NT * WN) >= N) return;      // padding of the grid to a multiple of 8 column blocks
+  const int wm = wave / WN, wn = wave % WN;
+  const int n_tile0 = (n_block * WN + wn) * (MODE == kGateUp ? NT / 2 : NT);
+  const int split = blockIdx.y;
+  const int m0 = m_chunk * ROWS;
+  const int split_begin = split * k_per_split, split_end = min(K, split_begin + k_per_split);
+  // the K groups take the halves of the split, rounded to steps; both run the same number of steps (barriers), a
+  // step past the end multiplies zeros
+  const int split_steps = (split_end - split_begin) / 64;
+  const int n_steps = (split_steps + KG - 1) / KG;
+  const int own_steps = min(n_steps, split_steps - kg * n_steps);
+  const int k_begin = split_begin + (own_steps > 0 ? kg * n_steps * 64 : 0);
+  const int last = max(own_steps - 1, 0);
+  const char* xbase = reinterpret_cast<const char*>(X + (size_t)m0 * K + k_begin);
+  const unsigned x_bytes = ((unsigned)min(ROWS, M - m0) * (unsigned)K - (unsigned)k_begin) * 2u;
+  const size_t w_stride = (size_t)(N / 16) * 2048;
+  const char* wbase = reinterpret_cast<const char*>(Wp) + (size_t)(k_begin / 64) * w_stride + (size_t)n_tile0 * 2048;
+  const unsigned w_bytes = (unsigned)w_stride - (unsigned)n_tile0 * 2048u;
+  unsigned xoff[PASSES], loff[PASSES];
+#pragma unroll
+  for (int p = 0; p < PASSES; ++p) {
+    // (a last pass with fewer pieces than lanes moves the last piece several times)
+    const int ch = min(tid + p * THREADS, ROWS * 8 - 1), row = ch >> 3, piece = ch & 7;
+    xoff[p] = (unsigned)row * (unsigned)K * 2u + piece * 16u;
+    loff[p] = row * 128 + ((piece ^ ((row >> 1) & 7)) << 4);
+  }
+  // a step past the K group's own end has an empty descriptor: it reads zeros
+  auto x_rsrc = [&](int step) {
+    const int s = min(step, last);      // (KG = 1: re-read, never used)
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(xbase + (size_t)s * 128), 0,
+                                             (KG == 1 || step < own_steps) ? x_bytes - (unsigned)s * 128u : 0u, 0x00020000);
+  };
+  auto w_rsrc = [&](int step) {
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(wbase + (size_t)min(step, last) * w_stride), 0, w_bytes,
+                                             0x00020000);
+  };
+  uintx4_t xreg[DA][PASSES];
+  uintx4_t wreg[DB][NT][2];
+  const unsigned woff = lane * 16;
+  const unsigned up_off = MODE == kGateUp ? (unsigned)(N / 32) * 2048u - (unsigned)(NT / 2) * 2048u : 0u;
+#define GS_LOAD_X(slot, p, r) xreg[slot][p] = __builtin_amdgcn_raw_buffer_load_b128(r, xoff[p], 0, 0)
+  // piece i of the wave's weights of a step: tile i / 2, half i % 2
+#define GS_LOAD_W(slot, i, r)                                                                                       \
+  wreg[slot][(i) >> 1][(i) & 1] = __builtin_amdgcn_raw_buffer_load_b128(                                            \
+      r, woff + (i) * 1024, (MODE == kGateUp && (i) >= NT) ? up_off : 0u, POL)
+  floatx4_t acc[MT][NT];
+#pragma unroll
+  for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) acc[mt][nt] = floatx4_t{0.f, 0.f, 0.f, 0.f};
+  // fragment of row tile mt: lane (g, c) holds row c, pieces 2 g (first MFMA) and 2 g + 1 (second)
+  const int a0 = (wm * MT * 16 + c) * 128 + (((2 * g) ^ ((c >> 1) & 7)) << 4);
+  const int a1 = (wm * MT * 16 + c) * 128 + (((2 * g + 1) ^ ((c >> 1) & 7)) << 4);
+  {
+    uintx4_t r0[PASSES], r1[PASSES];
+    auto rx0 = x_rsrc(0), rx1 = x_rsrc(1);
+#pragma unroll
+    for (int p = 0; p < PASSES; ++p) r0[p] = __builtin_amdgcn_raw_buffer_load_b128(rx0, xoff[p], 0, 0);
+#pragma unroll
+    for (int d = 0; d < DB - 1; ++d) {
+      auto rw = w_rsrc(d);
+#pragma unroll
+      for (int i = 0; i < 2 * NT; ++i) GS_LOAD_W(d, i, rw);
+    }
+#pragma unroll
+    for (int p = 0; p < PASSES; ++p) r1[p] = __builtin_amdgcn_raw_buffer_load_b128(rx1, xoff[p], 0, 0);
+#pragma unroll
+    for (int d = 0; d < DA; ++d) {
+      auto rx = x_rsrc(d + 2);
+#pragma unroll
+      for (int p = 0; p < PASSES; ++p) GS_LOAD_X(d, p, rx);
+    }
+#pragma unroll
+    for (int p = 0; p < PASSES; ++p) *reinterpret_cast<uintx4_t*>(&xs[loff[p]]) = r0[p];
+#pragma unroll
+    for (int p = 0; p < PASSES; ++p) *reinterpret_cast<uintx4_t*>(&xs[TILE + loff[p]]) = r1[p];
+  }
+  __syncthreads();
+  bf16x8_t an[2][2];      // fragments of the next two row tiles
+  auto frag = [&](int buf, int mt, bf16x8_t (&a)[2]) {
+    a[0] = *reinterpret_cast<const bf16x8_t*>(&xs[buf + a0 + mt * 2048]);
+    a[1] = *reinterpret_cast<const bf16x8_t*>(&xs[buf + a1 + mt * 2048]);
+  };
+  frag(0, 0, an[0]);
+  frag(0, 1, an[1]);
+  int b0 = 0;             // byte offset of the current step's buffer
+  constexpr int WB = (2 * NT + MT - 1) / MT > 2 ? (2 * NT + MT - 1) / MT : 2;      // weight loads per block (early blocks)
+  constexpr int XB = (PASSES + MT - 1) / MT;                                       // activation pieces per block
+  for (int base = 0;; base += DB) {
+    bool done = false;
+#pragma unroll
+    for (int d = 0; d < DB; ++d) {
+      const int step = base + d;
+      if (!done) {
+        const int b1 = b0 == 2 * TILE ? 0 : b0 + TILE, b2 = b1 == 2 * TILE ? 0 : b1 + TILE;
+        auto rx = x_rsrc(step + 2 + DA);
+        auto rw = w_rsrc(step + DB - 1);
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt) {
+          const bf16x8_t ac[2] = {an[0][0], an[0][1]};
+          an[0][0] = an[1][0];
+          an[0][1] = an[1][1];
+          if (mt + 2 < MT) frag(b0, mt + 2, an[1]); else frag(b1, mt + 2 - MT, an[1]);
+#pragma unroll
+          for (int i = mt * WB; i < (mt + 1) * WB; ++i)
+            if (i < 2 * NT) GS_LOAD_W((d + DB - 1) % DB, i, rw);
+#pragma unroll
+          for (int p = mt * XB; p < (mt + 1) * XB; ++p)
+            if (p < PASSES) {
+              *reinterpret_cast<uintx4_t*>(&xs[b2 + loff[p]]) = xreg[d % DA][p];
+              GS_LOAD_X(d % DA, p, rx);
+            }
+#pragma unroll
+          for (int h = 0; h < 2; ++h)
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt)
+              acc[mt][nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                  ac[h], *reinterpret_cast<const bf16x8_t*>(&wreg[d % DB][nt][h]), acc[mt][nt], 0, 0, 0);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+        __syncthreads();
+        b0 = b1;
+        done = step + 1 >= n_steps;
+      }
+    }
+    if (done) break;
+  }
+#undef GS_LOAD_X
+#undef GS_LOAD_W
+
+  if constexpr (KG == 2) {
+    // (the last step's barrier: all reads of the activation buffers are done but for fragments nobody uses)
+    static_assert(KG * 3 * TILE >= MT * NT * 16 * THREADS, "the sums of one K group fit the activation buffers");
+    __syncthreads();
+    floatx4_t* sums = reinterpret_cast<floatx4_t*>(xs_all);
+    if (kg == 1) {
+#pragma unroll
+      for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) sums[(mt * NT + nt) * THREADS + tid] = acc[mt][nt];
+    }
+    __syncthreads();
+    if (kg == 1) return;
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt) acc[mt][nt] += sums[(mt * NT + nt) * THREADS + tid];
+  }
+  const int row0 = m0 + wm * MT * 16;
+  if constexpr (MODE == kGateUp) {
+    bf16_t* act = reinterpret_cast<bf16_t*>(P);
+    const int F = N / 2;
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int row = row0 + mt * 16 + g * 4 + i;
+        if (row < M) {
+#pragma unroll
+          for (int ft = 0; ft < NT / 2; ++ft) {
+            const float gt = acc[mt][ft][i];
+            act[(size_t)row * F + (n_tile0 + ft) * 16 + c] =
+                float_to_bf16(gt / (1.0f + expf(-gt)) * acc[mt][NT / 2 + ft][i]);
+          }
+        }
+      }
+    return;
+  }
+  float* out = P + (size_t)split * M * N;
+#pragma unroll
+  for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int row = row0 + mt * 16 + g * 4 + i;
+      if (row < M) {
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) out[(size_t)row * N + (n_tile0 + nt) * 16 + c] = acc[mt][nt][i];
+      }
+    }
+  if constexpr (MODE == kStats) {
+    static_assert(3 * TILE >= WN * ROWS * (int)sizeof(float2), "the statistics fit the activation buffers");
+    float2* st = reinterpret_cast<float2*>(xs_all);      // [WN][ROWS]
+    __syncthreads();
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        float mx = acc[mt][0][i];
+#pragma unroll
+        for (int nt = 1; nt < NT; ++nt) mx = fmaxf(mx, acc[mt][nt][i]);
+        mx = row16_max(mx);
+        float e = 0.f;
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) e += __expf(acc[mt][nt][i] - mx);
+        e = row16_sum(e);
+        if (c == 0) st[wn * ROWS + wm * MT * 16 + mt * 16 + g * 4 + i] = make_float2(mx, e);
+      }
+    __syncthreads();
+    for (int r = tid; r < ROWS; r += THREADS)
+      if (m0 + r < M) {
+        float m = st[r].x, sum = st[r].y;
+#pragma unroll
+        for (int w = 1; w < WN; ++w) merge_stat(m, sum, st[w * ROWS + r].x, st[w * ROWS + r].y);
+        stats[(size_t)(m0 + r) * n_stat_blocks + n_block] = make_float2(m, sum);
+      }
+  }
+}
+
+}  // namespace
+
+WidePlan wide_plan(int M, int N, int K, bool one_split) {
+  WidePlan p;
+  const int tiles = ceil_div(M, 16);
+  p.nt = 2;
+  if (tiles <= 8) {
+    p.wm = 1;
+    p.mt = tiles <= 4 ? 4 : tiles <= 6 ? 6 : 8;
+    p.m_chunks = 1;
+    // 256 columns per workgroup where that still leaves a workgroup for three compute units in four (28672 columns
+    // of the 8B gate/up projection would leave 112); narrower matrices take 128
+    p.wn = (N % 256 == 0 && N / 256 >= 192) ? 8 : 4;
+  } else {
+    // 2 x 2 waves, up to 22 row tiles per workgroup; more rows in equal chunks
+    p.wm = 2;
+    p.wn = 2;
+    p.nt = 4;
+    const int chunks = ceil_div(tiles, 22), half = ceil_div(ceil_div(tiles, chunks), 2);
+    p.mt = half <= 5 ? 5 : half <= 6 ? 6 : half <= 8 ? 8 : half <= 10 ? 10 : 11;
+    p.m_chunks = ceil_div(tiles, 2 * p.mt);
+  }
+  p.n_blocks = N / (16 * p.nt * p.wn);
+  const int wgs = p.n_blocks * p.m_chunks;
+  // one workgroup per compute unit (registers and LDS of every shape fit that many); at least 8 steps per split
+  const int want = (256 + wgs / 2) / wgs, max_s = std::max(1, K / 512);
+  const int s = one_split ? 1 : std::max(1, std::min(want, max_s));
+  p.k_per = ceil_div(ceil_div(K, s), 64) * 64;
+  p.splits = ceil_div(K, p.k_per);
+  return p;
+}
+
+template <int MODE>
+static gs_status launch_mode(const WidePlan& p, const bf16_t* x, const bf16_t* w, float* out, int M, int N, int K,
+                             float2* stats, hipStream_t stream) {
+  const dim3 grid(ceil_div(p.n_blocks, 8) * 8 * p.m_chunks, p.splits, 1);
+#define GS_WIDE(WM, WN, KG, MT, NT, DB, DA, POL, WPE)                                                              \
+  gemm_bf16_wide_kernel<WM, WN, KG, MT, NT, DB, DA, POL, WPE, MODE>                                                 \
+      <<<grid, 64 * WM * WN * KG, 0, stream>>>(x, w, out, M, N, K, p.k_per, p.m_chunks, stats, p.n_blocks)
+  if (p.wm == 2) {
+    switch (p.mt) {
+      case 5: GS_WIDE(2, 2, 1, 5, 4, 2, 1, 0, 1); break;
+      case 6: GS_WIDE(2, 2, 1, 6, 4, 2, 1, 0, 1); break;
+      case 8: GS_WIDE(2, 2, 1, 8, 4, 2, 1, 0, 1); break;
+      case 10: GS_WIDE(2, 2, 1, 10, 4, 2, 1, 0, 1); break;
+      default: GS_WIDE(2, 2, 1, 11, 4, 2, 1, 0, 1);
+    }
+  } else if (p.wn == 8) {
+    switch (p.mt) {
+      case 4: GS_WIDE(1, 8, 1, 4, 2, 4, 2, 2, 2); break;
+      case 6: GS_WIDE(1, 8, 1, 6, 2, 4, 2, 2, 2); break;
+      default: GS_WIDE(1, 8, 1, 8, 2, 4, 2, 2, 2);
+    }
+  } else if constexpr (MODE == kStats) {
+    switch (p.mt) {
+      case 4: GS_WIDE(1, 4, 1, 4, 2, 4, 2, 2, 1); break;
+      case 6: GS_WIDE(1, 4, 1, 6, 2, 4, 2, 2, 1); break;
+      default: GS_WIDE(1, 4, 1, 8, 2, 4, 2, 2, 1);
+    }
+  } else {
+    switch (p.mt) {
+      case 4: GS_WIDE(1, 4, 2, 4, 2, 4, 2, 2, 2); break;
+      case 6: GS_WIDE(1, 4, 2, 6, 2, 4, 2, 2, 2); break;
+      default: GS_WIDE(1, 4, 2, 8, 2, 4, 2, 2, 2);
+    }
+  }
+#undef GS_WIDE
+  GS_LAUNCH_CHECK("gemm_bf16_wide");
+  return GS_OK;
+}
+
+gs_status launch_wide(const WidePlan& p, const bf16_t* x, const bf16_t* w, float* out, int M, int N, int K,
+                      hipStream_t stream) {
+  return launch_mode<kPlain>(p, x, w, out, M, N, K, nullptr, stream);
+}
+gs_status launch_wide_gate_up(const WidePlan& p, const bf16_t* x, const bf16_t* w, bf16_t* act, int M, int N, int K,
+                              hipStream_t stream) {
+  return launch_mode<kGateUp>(p, x, w, reinterpret_cast<float*>(act), M, N, K, nullptr, stream);
+}
+gs_status launch_wide_stats(const WidePlan& p, const bf16_t* x, const bf16_t* w, float* y, float2* stats, int M, int N,
+                            int K, hipStream_t stream) {
+  return launch_mode<kStats>(p, x, w, y, M, N, K, stats, stream);
+}
+
+}  // namespace gs
