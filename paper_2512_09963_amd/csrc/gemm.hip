@@ -625,6 +625,8 @@ static GemmPlan gemm_plan(int M, int N, int K) {
 
 int gemm_w4_splits(int M, int N, int K);
 gs_status launch_gemm_w4(const void* X, const void* Wpacked, float* P, int M, int N, int K, hipStream_t stream);
+bool w4_gate_up_fused(int M, int F);
+gs_status launch_gemm_w4_gate_up(const void* X, const void* Wpacked, void* act, int M, int F, int K, hipStream_t stream);
 
 // Number of K splits the projection kernel will use for this shape (1 for fp32).
 int gemm_splits(int dtype, int M, int N, int K) {
@@ -664,9 +666,10 @@ static void launch_tall(const GemmPlan& p, const bf16_t* x, const bf16_t* w, flo
 constexpr int kGateUpWaves = 4;
 constexpr int kGateUpDepth = 6;
 
-// Whether the gate/up projection of this shape runs with the SwiGLU fused: bf16, and either up to 64 rows or
+// Whether the gate/up projection of this shape runs with the SwiGLU fused: 4-bit where its kernel does, bf16, and either up to 64 rows or
 // a shape whose kernel needs no K split anyway.
 bool gate_up_fused(int dtype, int M, int F, int K) {
+  if (dtype == GS_W4) return M > 0 && w4_gate_up_fused(M, F);
   if (dtype != GS_BF16 || M <= 0 || F % (16 * kGateUpWaves) != 0 || K % kBK != 0) return false;
   if (M <= 64) return true;
   const GemmPlan p = gemm_plan(M, 2 * F, K);
@@ -674,7 +677,9 @@ bool gate_up_fused(int dtype, int M, int F, int K) {
 }
 
 // act [M][F] (bf16) = silu(X Wg^T) * (X Wu^T), W = [Wg; Wu] packed; only for shapes gate_up_fused accepts.
-gs_status launch_gemm_gate_up(const void* X, const void* W, void* act, int M, int F, int K, hipStream_t stream) {
+gs_status launch_gemm_gate_up(int dtype, const void* X, const void* W, void* act, int M, int F, int K,
+                              hipStream_t stream) {
+  if (dtype == GS_W4) return launch_gemm_w4_gate_up(X, W, act, M, F, K, stream);
   constexpr int NW = kGateUpWaves, D = kGateUpDepth;
   const bf16_t* x = static_cast<const bf16_t*>(X);
   const bf16_t* w = static_cast<const bf16_t*>(W);

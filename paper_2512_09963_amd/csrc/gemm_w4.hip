@@ -2,16 +2,12 @@
 // the AWQ checkpoints the paper's 70B verifier uses, Section IV-A): Y = X * W^T with
 // W[n][k] = (code[n][k] - zero[n][k/128]) * scale[n][k/128], codes and zeros in 0..15, scales bf16.
 //
-// Same streaming design as the bf16 kernel, with a quarter of the weight bytes, which moves the bound from
-// HBM to the dequantisation arithmetic and the MFMA pipe; so the kernel uses the 32x32x16 MFMA (twice the
-// issue rate of the 16x16x32 one on this chip): a wave owns 32 output columns and up to 128 rows and reads,
-// per 64-wide k step, 16 bytes per lane (32 codes of one column) plus one 32-bit word with the column's
-// scale and zero point; the codes are turned into bf16 in registers and fed to the MFMA as the B operand.
-// Beyond 64 rows a wave owns two such column tiles, so that an activation fragment read from LDS feeds two MFMAs.
-// Dequantisation: four codes are spread to the bytes of a word (two mask operations per eight codes), each
-// byte is converted to fp32 by the byte-conversion instruction, fma(c, scale, -zero * scale) = (c - zero) *
-// scale is exact in fp32 (5 x 8 significant bits), and the packed conversion rounds it to bf16 (nearest
-// even): every dequantised weight is a function of (c, zero, scale) alone, the same on every path.
+// Same streaming design as the bf16 kernels, with a quarter of the weight bytes, which moves the bound from
+// HBM to the dequantisation arithmetic and the MFMA pipe: a wave owns NT tiles of 32 output columns and up to 128 rows and
+// reads, per 64-wide k step and tile, 16 bytes per lane (32 codes of one column) plus, every two steps, one 32-bit word with
+// the column's scale and zero point; the codes are turned into bf16 in registers and fed to the 32x32x16 MFMA as the B
+// operand.  Every dequantised weight is (c - zero) * scale, exact in fp32 (4 x 8 significant bits), rounded to bf16 (nearest
+// even): a function of (c, zero, scale) alone, the same on every path.
 //
 // Packed layout (gs_pack_weight_w4):
 //   codes [K/64][N/32][64 lanes][4 words]: lane l holds column l%32, and word kg holds inputs
@@ -19,193 +15,306 @@
 //         nibbles of bytes 0..3 and codes 4..7 in the high nibbles, so that (word & 0x0F0F0F0F) and
 //         ((word >> 4) & 0x0F0F0F0F) each hold four codes, one per byte
 //   meta  [K/128][N] words: bf16 scale in the high half, zero point in the low byte
-// Activations go through LDS exactly as in the bf16 kernels.  Rows beyond 128 are served in chunks of 128 by
-// separate workgroups (XCD-aware order, see the bf16 kernel); a taller tile is not built for this format.
+// Rows beyond 128 are served in chunks of 128 by separate workgroups (XCD-aware order, see the bf16 kernel).
 #include "common.h"
 #include "device_types.h"
+#include <algorithm>
 
 namespace gs {
 namespace {
 
 constexpr int kBK = 64;
-constexpr int kLdsRow = kBK + 8;
 constexpr int kGroup = 128;
 
 typedef __attribute__((__vector_size__(16 * sizeof(float)))) float floatx16_t;
 
-struct W4Step {
-  uint4 codes;       // word kg = the 8 codes of k group kg
-  uint32_t meta;
+// word: codes 0..3 in the even nibbles of bytes 0..3, codes 4..7 in the odd nibbles.  A nibble OR-ed into the mantissa of
+// 1024 is the half-precision number 1024 + c (even nibble) or 1024 + 16 c (odd nibble), two to a word, and the
+// mixed-precision fma reads either half: (1024 + c) * scale - (1024 + z) * scale = (c - z) * scale, exact in fp32
+// (11 x 8 significant bits, one rounding at the end, which has nothing to round).  17 instructions per 8 codes
+// (23 with byte conversions).  Scales of 2^117 and more overflow the constant term.
+typedef _Float16 half2_vec __attribute__((ext_vector_type(2)));
+struct DequantScale {
+  float s, b, s16, b16;
 };
-
-// float(byte B of x): the byte-select forms of the conversion, written out because the compiler otherwise
-// extracts each nibble with a bit-field instruction first (two instructions per code instead of one)
-template <int B>
-__device__ __forceinline__ float byte_to_float(uint32_t x) {
-  float f;
-  if constexpr (B == 0) asm("v_cvt_f32_ubyte0_e32 %0, %1" : "=v"(f) : "v"(x));
-  else if constexpr (B == 1) asm("v_cvt_f32_ubyte1_e32 %0, %1" : "=v"(f) : "v"(x));
-  else if constexpr (B == 2) asm("v_cvt_f32_ubyte2_e32 %0, %1" : "=v"(f) : "v"(x));
-  else asm("v_cvt_f32_ubyte3_e32 %0, %1" : "=v"(f) : "v"(x));
-  return f;
+__device__ __forceinline__ DequantScale dequant_scale(uint32_t meta) {
+  DequantScale d;
+  const float z = (float)(meta & 0xffu);
+  d.s = __uint_as_float(meta & 0xffff0000u);
+  d.b = -(1024.0f + z) * d.s;
+  d.s16 = d.s * 0.0625f;
+  d.b16 = -(64.0f + z) * d.s;
+  return d;
 }
-
-// word: codes 0..3 in the even nibbles of bytes 0..3, codes 4..7 in the odd nibbles
-__device__ __forceinline__ bf16x8_t dequant8(uint32_t word, float scale, float neg_zs) {
-  const uint32_t lo4 = word & 0x0F0F0F0Fu, hi4 = (word >> 4) & 0x0F0F0F0Fu;
+__device__ __forceinline__ bf16x8_t dequant8(uint32_t word, const DequantScale& d) {
+  uint32_t magic = 0x64006400u;
+  asm("" : "+v"(magic));      // (in a register: and-or takes one constant)
+  auto halves = [&](uint32_t w, uint32_t mask) {
+    const uint32_t h = (w & mask) | magic;
+    return *reinterpret_cast<const half2_vec*>(&h);
+  };
+  const half2_vec e = halves(word, 0x000F000Fu), o = halves(word, 0x00F000F0u);                  // codes 0, 2 and 4, 6
+  const half2_vec e8 = halves(word >> 8, 0x000F000Fu), o8 = halves(word >> 8, 0x00F000F0u);      // codes 1, 3 and 5, 7
   uint4 out;
-  out.x = pack_bf16x2(fmaf(byte_to_float<0>(lo4), scale, neg_zs), fmaf(byte_to_float<1>(lo4), scale, neg_zs));
-  out.y = pack_bf16x2(fmaf(byte_to_float<2>(lo4), scale, neg_zs), fmaf(byte_to_float<3>(lo4), scale, neg_zs));
-  out.z = pack_bf16x2(fmaf(byte_to_float<0>(hi4), scale, neg_zs), fmaf(byte_to_float<1>(hi4), scale, neg_zs));
-  out.w = pack_bf16x2(fmaf(byte_to_float<2>(hi4), scale, neg_zs), fmaf(byte_to_float<3>(hi4), scale, neg_zs));
+  out.x = pack_bf16x2(fmaf((float)e[0], d.s, d.b), fmaf((float)e8[0], d.s, d.b));
+  out.y = pack_bf16x2(fmaf((float)e[1], d.s, d.b), fmaf((float)e8[1], d.s, d.b));
+  out.z = pack_bf16x2(fmaf((float)o[0], d.s16, d.b16), fmaf((float)o8[0], d.s16, d.b16));
+  out.w = pack_bf16x2(fmaf((float)o[1], d.s16, d.b16), fmaf((float)o8[1], d.s16, d.b16));
   return *reinterpret_cast<const bf16x8_t*>(&out);
 }
 
-// MT32 row tiles of 32 rows per workgroup (1, 2 or 4), NW waves of NT 32-column tiles each.  With one
-// column tile per wave every MFMA needs an activation fragment of its own from LDS (1 KB per 32 MFMA
-// cycles and wave: the LDS limit at four row tiles); with two, a fragment serves two MFMAs.  DX: steps the
-// activation tile is fetched ahead (registers, then LDS); the weights are fetched DW steps ahead.
-template <int MT32, int NW, int NT, int DW, int DX>
-__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(MT32 == 4 && NW >= 4 ? 2 : 1))) void gemm_w4_kernel(const bf16_t* __restrict__ X,
-                                                          const uint4* __restrict__ codes,
-                                                          const uint32_t* __restrict__ meta,
-                                                          float* __restrict__ P, int M, int N, int K,
-                                                          int k_per_split, int m_chunks) {
-  static_assert(DW % DX == 0, "the unrolled ring addresses the activation slots statically");
-  constexpr int ROWS = MT32 * 32;
-  __shared__ __attribute__((aligned(16))) bf16_t xs[2][ROWS * kLdsRow];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+typedef unsigned int uintx4_t __attribute__((ext_vector_type(4)));
+
+enum { kPlain = 0, kGateUp = 1 };
+
+// WN waves side by side, each with NT 32-column tiles and all MT 32-row tiles; KG groups of them take K slices of the
+// workgroup's range, and their sums meet in LDS.  DB, DA: steps (64 of k) of weights and of activations in
+// registers.
+// MODE kGateUp (one K split): the wave's tiles are NT / 2 feature tiles of the gate half and the same ones of the up half of a
+// [2F][K] matrix (N = 2F), and act[M][F] = silu(gate) * up is stored as bf16 at P.
+// Pipeline, as in gemm_wide.hip: a step is four blocks, one per k group of 16, each of which reads the activation
+// fragments of two blocks ahead from LDS (three buffers), dequantises the weights of the next block, moves its share of
+// the next activation tile and weights, and issues its MT * NT MFMAs.
+// grid (column blocks, rounded up to a multiple of 8, times row chunks; K splits).
+template <int WN, int KG, int MT, int NT, int DB, int DA, int WPE, int MODE>
+__global__ __launch_bounds__(64 * WN * KG) __attribute__((amdgpu_waves_per_eu(WPE, WPE))) void gemm_w4_kernel(
+    const bf16_t* __restrict__ X, const uint4* __restrict__ codes, const uint32_t* __restrict__ meta,
+    float* __restrict__ P, int M, int N, int K, int k_per_split, int m_chunks) {
+  static_assert(MODE != kGateUp || NT % 2 == 0, "gate and up tile of every feature tile");
+  static_assert(DB % 2 == 0 && DB % DA == 0, "a scale group is two steps; rings are addressed statically");
+  constexpr int ROWS = MT * 32, THREADS = 64 * WN;      // THREADS: of one K group
+  constexpr int PASSES = (ROWS * 8 + THREADS - 1) / THREADS;
+  constexpr int TILE = ROWS * 128;
+  // three activation buffers per K group; after the loop the sums that one K group hands over
+  constexpr int RING = KG * 3 * TILE, SUMS = KG > 1 ? MT * NT * 64 * THREADS : 0;
+  __shared__ __attribute__((aligned(16))) unsigned char xs_all[RING > SUMS ? RING : SUMS];
+  const int lane = threadIdx.x & 63;
+  const int wave_all = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int kg = wave_all / WN, wn = wave_all % WN;
+  const int tid = threadIdx.x - kg * THREADS;
+  unsigned char* xs = xs_all + kg * 3 * TILE;
   const int h = lane >> 5, c32 = lane & 31;
-  int n_block = blockIdx.x, m_chunk = 0;
-  if (m_chunks > 1) {
-    const int xcd = blockIdx.x & 7, t = blockIdx.x >> 3;
-    m_chunk = t % m_chunks;
-    n_block = (t / m_chunks) * 8 + xcd;
-    if (n_block * (32 * NW * NT) >= N) return;
-  }
-  const int n_tile = (n_block * NW + wave) * NT;        // first 32-column tile of this wave
-  const int n0 = n_tile * 32;
+  const int xcd = blockIdx.x & 7, t = blockIdx.x >> 3;
+  const int m_chunk = t % m_chunks;
+  const int n_block = (t / m_chunks) * 8 + xcd;
+  if (n_block * (32 * NT * WN) >= N) return;      // padding of the grid to a multiple of 8 column blocks
+  const int n_tile0 = (n_block * WN + wn) * (MODE == kGateUp ? NT / 2 : NT);
   const int split = blockIdx.y;
   const int m0 = m_chunk * ROWS;
-  const int k_begin = split * k_per_split;
-  const int k_end = min(K, k_begin + k_per_split);
-  const int n_steps = (k_end - k_begin) / kBK;
-  const int step0 = k_begin / kBK;
-
-  constexpr int kThreads = 64 * NW;
-  constexpr int kChunks = ROWS * 8;
-  constexpr int kPasses = (kChunks + kThreads - 1) / kThreads;
-  uint4 xreg[DX][kPasses];
-  auto load_x = [&](int slot, int step) {
+  const int split_begin = split * k_per_split, split_end = min(K, split_begin + k_per_split);
+  // the K groups take whole scale groups (two steps) and run the same number of steps (barriers); a step past a group's
+  // own end multiplies zeros
+  const int split_steps = (split_end - split_begin) / 64;
+  const int n_steps = (split_steps / 2 + KG - 1) / KG * 2;
+  const int own_steps = min(n_steps, split_steps - kg * n_steps);
+  const int k_begin = split_begin + (own_steps > 0 ? kg * n_steps * 64 : 0);
+  const int last = max(own_steps - 1, 0);
+  const char* xbase = reinterpret_cast<const char*>(X + (size_t)m0 * K + k_begin);
+  const unsigned x_bytes = ((unsigned)min(ROWS, M - m0) * (unsigned)K - (unsigned)k_begin) * 2u;
+  const size_t c_stride = (size_t)(N / 32) * 1024;      // code bytes of one step
+  const char* cbase = reinterpret_cast<const char*>(codes) + (size_t)(k_begin / 64) * c_stride + (size_t)n_tile0 * 1024;
+  const unsigned c_bytes = (unsigned)c_stride - (unsigned)n_tile0 * 1024u;
+  const char* mbase = reinterpret_cast<const char*>(meta + (size_t)(k_begin / kGroup) * N + n_tile0 * 32);
+  const unsigned m_bytes = (unsigned)(N - n_tile0 * 32) * 4u;
+  unsigned xoff[PASSES], loff[PASSES];
 #pragma unroll
-    for (int p = 0; p < kPasses; ++p) {
-      const int ch = tid + p * kThreads;
-      const int row = ch >> 3, col = (ch & 7) * 8;
-      uint4 v = make_uint4(0, 0, 0, 0);
-      if (ch < kChunks && m0 + row < M)
-        v = *reinterpret_cast<const uint4*>(X + (size_t)(m0 + row) * K + k_begin + step * kBK + col);
-      xreg[slot][p] = v;
-    }
+  for (int p = 0; p < PASSES; ++p) {
+    // (a last pass with fewer pieces than lanes moves the last piece several times)
+    const int ch = min(tid + p * THREADS, ROWS * 8 - 1), row = ch >> 3, piece = ch & 7;
+    xoff[p] = (unsigned)row * (unsigned)K * 2u + piece * 16u;
+    loff[p] = row * 128 + ((piece ^ ((row >> 1) & 7)) << 4);
+  }
+  auto x_rsrc = [&](int step) {      // rows past the end and steps past the K group's end read as zero
+    const int s = min(step, last);
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(xbase + (size_t)s * 128), 0,
+                                             (KG == 1 || step < own_steps) ? x_bytes - (unsigned)s * 128u : 0u, 0x00020000);
   };
-  auto store_x = [&](int buf, int slot) {
-#pragma unroll
-    for (int p = 0; p < kPasses; ++p) {
-      const int ch = tid + p * kThreads;
-      const int row = ch >> 3, col = (ch & 7) * 8;
-      if (ch < kChunks) *reinterpret_cast<uint4*>(&xs[buf][row * kLdsRow + col]) = xreg[slot][p];
-    }
+  auto c_rsrc = [&](int step) {
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(cbase + (size_t)min(step, last) * c_stride), 0, c_bytes, 0x00020000);
   };
-  const size_t code_stride = (size_t)(N / 32) * 64;       // uint4 per k step
-  const uint4* cbase = codes + (size_t)step0 * code_stride + (size_t)n_tile * 64 + lane;
-  const uint32_t* mbase = meta + n0 + c32;
-  W4Step wreg[DW][NT];
-  auto load_w = [&](int slot, int step) {
-#pragma unroll
-    for (int nt = 0; nt < NT; ++nt) {
-      wreg[slot][nt].codes = cbase[(size_t)step * code_stride + nt * 64];
-      wreg[slot][nt].meta = mbase[(size_t)((step0 + step) >> 1) * N + nt * 32];
-    }
+  auto m_rsrc = [&](int step) {
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(mbase + (size_t)(min(step, last) >> 1) * N * 4), 0, m_bytes, 0x00020000);
   };
-
-  floatx16_t acc[MT32][NT];
+  uintx4_t xreg[DA][PASSES];
+  uintx4_t creg[DB][NT];
+  unsigned mreg[DB / 2][NT];
+  constexpr int UP = MODE == kGateUp ? NT / 2 : NT;      // first tile of the up half
+  const unsigned up_tiles = MODE == kGateUp ? (unsigned)(N / 64 - NT / 2) : 0u;
+  const unsigned coff = lane * 16, moff = c32 * 4;
+#define GS_LOAD_X(slot, p, r) xreg[slot][p] = __builtin_amdgcn_raw_buffer_load_b128(r, xoff[p], 0, 0)
+#define GS_LOAD_C(slot, nt, r) \
+  creg[slot][nt] = __builtin_amdgcn_raw_buffer_load_b128(r, coff + (nt) * 1024, (nt) >= UP ? up_tiles * 1024u : 0u, 0)
+#define GS_LOAD_M(slot, nt, r) \
+  mreg[slot][nt] = __builtin_amdgcn_raw_buffer_load_b32(r, moff + (nt) * 128, (nt) >= UP ? up_tiles * 128u : 0u, 0)
+  floatx16_t acc[MT][NT];
 #pragma unroll
-  for (int mt = 0; mt < MT32; ++mt)
+  for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
       for (int e = 0; e < 16; ++e) acc[mt][nt][e] = 0.f;
+  // fragment of row tile mt, k group q: lane holds row lane % 32, piece 2 q + lane / 32
+  int a_off[4];
 #pragma unroll
-  for (int d = 0; d < DW; ++d)
-    if (d < n_steps) {
-      load_w(d, d);
-      if (d < DX) load_x(d, d);
-    }
-  // A fragment of row tile mt, k group kg: row mt*32 + lane%32, 16-byte piece 2 kg + lane/32
-  const int a_lane = c32 * kLdsRow + h * 8;
-  auto dequant_group = [&](const W4Step (&w)[NT], int kg, bf16x8_t (&b)[NT]) {
+  for (int q = 0; q < 4; ++q) a_off[q] = c32 * 128 + (((2 * q + h) ^ ((c32 >> 1) & 7)) << 4);
+  {
+    uintx4_t r0[PASSES], r1[PASSES];
+    auto rx0 = x_rsrc(0), rx1 = x_rsrc(1);
 #pragma unroll
-    for (int nt = 0; nt < NT; ++nt) {
-      const float scale = __uint_as_float(w[nt].meta & 0xffff0000u);
-      const float neg_zs = -(float)(w[nt].meta & 0xffu) * scale;
-      const uint32_t cw = kg == 0 ? w[nt].codes.x : kg == 1 ? w[nt].codes.y : kg == 2 ? w[nt].codes.z : w[nt].codes.w;
-      b[nt] = dequant8(cw, scale, neg_zs);
-    }
-  };
-  // Software pipeline: the activation fragments (LDS) and the dequantised weights (vector ALU) of k group
-  // kg + 1 are produced while the MFMAs of group kg run; the weights of a step's first group are dequantised
-  // during the last group of the step before, since they do not wait for the barrier.
-  bf16x8_t b_cur[NT];
-  if (n_steps > 0) dequant_group(wreg[0], 0, b_cur);
-  for (int base = 0; base < n_steps; base += DW) {
+    for (int p = 0; p < PASSES; ++p) r0[p] = __builtin_amdgcn_raw_buffer_load_b128(rx0, xoff[p], 0, 0);
 #pragma unroll
-    for (int d = 0; d < DW; ++d) {
-      const int step = base + d;
-      if (step < n_steps) {
-        const int buf = step & 1;
-        store_x(buf, d % DX);
-        __syncthreads();
-        W4Step w[NT];
+    for (int d = 0; d < DB - 1; ++d) {
+      auto rc = c_rsrc(d), rm = m_rsrc(d);
 #pragma unroll
-        for (int nt = 0; nt < NT; ++nt) w[nt] = wreg[d][nt];
-        if (step + DW < n_steps) load_w(d, step + DW);
-        if (step + DX < n_steps) load_x(d % DX, step + DX);
-        bf16x8_t a_cur[MT32];
-#pragma unroll
-        for (int mt = 0; mt < MT32; ++mt)
-          a_cur[mt] = *reinterpret_cast<const bf16x8_t*>(&xs[buf][mt * 32 * kLdsRow + a_lane]);
-#pragma unroll
-        for (int kg = 0; kg < 4; ++kg) {
-          bf16x8_t a_nxt[MT32], b_nxt[NT];
-          if (kg < 3) {
-#pragma unroll
-            for (int mt = 0; mt < MT32; ++mt)
-              a_nxt[mt] = *reinterpret_cast<const bf16x8_t*>(&xs[buf][mt * 32 * kLdsRow + a_lane + (kg + 1) * 16]);
-            dequant_group(w, kg + 1, b_nxt);
-          } else if (step + 1 < n_steps) {
-            dequant_group(wreg[(d + 1) % DW], 0, b_nxt);
-          }
-#pragma unroll
-          for (int mt = 0; mt < MT32; ++mt)
-#pragma unroll
-            for (int nt = 0; nt < NT; ++nt)
-              acc[mt][nt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a_cur[mt], b_cur[nt], acc[mt][nt], 0, 0, 0);
-#pragma unroll
-          for (int mt = 0; mt < MT32; ++mt) a_cur[mt] = a_nxt[mt];
-#pragma unroll
-          for (int nt = 0; nt < NT; ++nt) b_cur[nt] = b_nxt[nt];
-        }
+      for (int nt = 0; nt < NT; ++nt) {
+        GS_LOAD_C(d, nt, rc);
+        if (d % 2 == 0) GS_LOAD_M(d / 2, nt, rm);
       }
     }
+#pragma unroll
+    for (int p = 0; p < PASSES; ++p) r1[p] = __builtin_amdgcn_raw_buffer_load_b128(rx1, xoff[p], 0, 0);
+#pragma unroll
+    for (int d = 0; d < DA; ++d) {
+      auto rx = x_rsrc(d + 2);
+#pragma unroll
+      for (int p = 0; p < PASSES; ++p) GS_LOAD_X(d, p, rx);
+    }
+#pragma unroll
+    for (int p = 0; p < PASSES; ++p) *reinterpret_cast<uintx4_t*>(&xs[loff[p]]) = r0[p];
+#pragma unroll
+    for (int p = 0; p < PASSES; ++p) *reinterpret_cast<uintx4_t*>(&xs[TILE + loff[p]]) = r1[p];
+  }
+  __syncthreads();
+  bf16x8_t an[4][MT];      // fragments of this block and the next two
+  auto frag = [&](int buf, int q, bf16x8_t (&a)[MT]) {
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt) a[mt] = *reinterpret_cast<const bf16x8_t*>(&xs[buf + a_off[q] + mt * 4096]);
+  };
+  frag(0, 0, an[0]);
+  frag(0, 1, an[1]);
+  DequantScale ds[NT];
+  bf16x8_t bn[2][NT];      // dequantised weights of this block and the next
+#pragma unroll
+  for (int nt = 0; nt < NT; ++nt) {
+    ds[nt] = dequant_scale(mreg[0][nt]);
+    bn[0][nt] = dequant8(creg[0][nt][0], ds[nt]);
+  }
+  int b0 = 0;
+  for (int base = 0;; base += DB) {
+    bool done = false;
+#pragma unroll
+    for (int d = 0; d < DB; ++d) {
+      const int step = base + d;
+      if (!done) {
+        const int b1 = b0 == 2 * TILE ? 0 : b0 + TILE, b2 = b1 == 2 * TILE ? 0 : b1 + TILE;
+        auto rx = x_rsrc(step + 2 + DA);
+        auto rc = c_rsrc(step + DB - 1), rm = m_rsrc(step + DB - 1);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          if (q < 2) frag(b0, q + 2, an[q + 2]); else frag(b1, q - 2, an[q - 2]);
+          if (q == 0) {
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt) GS_LOAD_C((d + DB - 1) % DB, nt, rc);
+          }
+          if ((d + DB - 1) % 2 == 0 && q == 1) {
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt) GS_LOAD_M((d + DB - 1) % DB / 2, nt, rm);
+          }
+#pragma unroll
+          for (int p = q * PASSES / 4; p < (q + 1) * PASSES / 4; ++p) {
+            *reinterpret_cast<uintx4_t*>(&xs[b2 + loff[p]]) = xreg[d % DA][p];
+            GS_LOAD_X(d % DA, p, rx);
+          }
+          // the next block's weights: k group q + 1 of this step, or group 0 of the next (another scale group after
+          // an odd step)
+          if (q < 3) {
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt) bn[(q + 1) % 2][nt] = dequant8(creg[d % DB][nt][q + 1], ds[nt]);
+          } else {
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt) {
+              if (d % 2 == 1) ds[nt] = dequant_scale(mreg[(d + 1) % DB / 2][nt]);
+              bn[(q + 1) % 2][nt] = dequant8(creg[(d + 1) % DB][nt][0], ds[nt]);
+            }
+          }
+#pragma unroll
+          for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt)
+              acc[mt][nt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(an[q][mt], bn[q % 2][nt], acc[mt][nt], 0, 0, 0);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+        __syncthreads();
+        b0 = b1;
+        done = step + 1 >= n_steps;
+      }
+    }
+    if (done) break;
+  }
+#undef GS_LOAD_X
+#undef GS_LOAD_C
+#undef GS_LOAD_M
+
+  if constexpr (KG > 1) {
+    // the K groups' sums in a fixed order: group g hands its sums to group 0, one at a time
+    floatx4_t* sums = reinterpret_cast<floatx4_t*>(xs_all);
+#pragma unroll
+    for (int src = 1; src < KG; ++src) {
+      __syncthreads();
+      if (kg == src) {
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+          for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+              sums[((mt * NT + nt) * 4 + e) * THREADS + tid] =
+                  floatx4_t{acc[mt][nt][4 * e], acc[mt][nt][4 * e + 1], acc[mt][nt][4 * e + 2], acc[mt][nt][4 * e + 3]};
+      }
+      __syncthreads();
+      if (kg == 0) {
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+          for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+              const floatx4_t v = sums[((mt * NT + nt) * 4 + e) * THREADS + tid];
+#pragma unroll
+              for (int j = 0; j < 4; ++j) acc[mt][nt][4 * e + j] += v[j];
+            }
+      }
+    }
+    if (kg != 0) return;
+  }
+  if constexpr (MODE == kGateUp) {
+    bf16_t* act = reinterpret_cast<bf16_t*>(P);
+    const int F = N / 2;
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) {
+        const int row = m0 + mt * 32 + (v >> 2) * 8 + h * 4 + (v & 3);
+        if (row < M) {
+#pragma unroll
+          for (int ft = 0; ft < NT / 2; ++ft) {
+            const float gt = acc[mt][ft][v];
+            act[(size_t)row * F + (n_tile0 + ft) * 32 + c32] =
+                float_to_bf16(gt / (1.0f + expf(-gt)) * acc[mt][NT / 2 + ft][v]);
+          }
+        }
+      }
+    return;
   }
   float* out = P + (size_t)split * M * N;
 #pragma unroll
-  for (int mt = 0; mt < MT32; ++mt)
+  for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
     for (int v = 0; v < 16; ++v) {
       const int row = m0 + mt * 32 + (v >> 2) * 8 + h * 4 + (v & 3);
       if (row < M) {
 #pragma unroll
-        for (int nt = 0; nt < NT; ++nt) out[(size_t)row * N + n0 + nt * 32 + c32] = acc[mt][nt][v];
+        for (int nt = 0; nt < NT; ++nt) out[(size_t)row * N + (n_tile0 + nt) * 32 + c32] = acc[mt][nt][v];
       }
     }
 }
@@ -256,54 +365,79 @@ gs_status launch_pack_weight_w4(const void* q, const void* scales, const void* z
   return GS_OK;
 }
 
-// Launch shape of the 4-bit kernel: 32-row tiles per workgroup (1, 2 or 4), row chunks of 128, waves, column
-// tiles per wave, K splits.
+// Launch shape of the 4-bit kernel: waves x kg waves per workgroup, nt column tiles per wave, mt row tiles of 32.
+//   up to 32 rows: the weight stream is all there is; 8 waves side by side, two workgroups per compute unit
+//   33 to 96 rows: 4 waves x 2 K groups; two column tiles per wave (a fragment read from LDS feeds two MFMAs) for matrices of
+//     192 blocks of 256 columns and more, and where every wave still gets 16 steps; otherwise one
+//     (92 rows, isolated: 8192 x 28672 49 us with two, 54 with one; 8192 x 8192 22.0 and 20.8; 10240 x 8192 26.5 and 25.8)
+//   more rows: chunks of 128; 8 waves side by side with one tile (two do not fit the registers)
+// Inside a verification step, us per launch (predecessor, with two LDS buffers and one burst of loads per step, in
+// brackets): 92 rows, 70B shape: gate/up 102 (123, and 8.5 for the separate SwiGLU), 8192 x 28672 51, 8192 x 8192 22.5 (67
+// on average), QKV 26.8 (33.5), LM head 202 (250); 53 rows, 8B shape: gate/up 28.6 (32, and 6), 4096 x 14336 15.6 (18.5),
+// QKV 12.2 (15.1), 4096 x 4096 10.8 (11.3), LM head 85.5 (89.6).
 struct W4Plan {
-  int mt32, m_chunks, waves, nt, splits, k_per;
+  int mt, m_chunks, waves, kg, nt, n_blocks, splits, k_per;
 };
 
 static W4Plan w4_plan(int M, int N, int K) {
   W4Plan p;
-  p.mt32 = M <= 32 ? 1 : M <= 64 ? 2 : 4;
-  p.m_chunks = ceil_div(M, 32 * p.mt32);
+  p.mt = M <= 32 ? 1 : M <= 64 ? 2 : M <= 96 ? 3 : 4;
+  p.m_chunks = ceil_div(M, 32 * p.mt);
+  int target = 256;      // workgroups: one per compute unit
   p.nt = 1;
-  if (p.mt32 == 4 && N % 512 == 0 && N / 512 >= 96) {
-    p.waves = 8; p.nt = 2;
-  } else if (p.mt32 == 4 && N % 256 == 0) {
-    p.waves = 4; p.nt = 2;
+  if (p.mt == 1 || p.mt == 4) {
+    p.waves = N % 256 == 0 ? 8 : 4;
+    p.kg = p.waves == 8 ? 1 : 2;
+    if (p.mt == 1) target = 512;
   } else {
-    p.waves = (N % 256 == 0 && N / 256 >= 96) ? 8 : (N % 128 == 0 ? 4 : 2);
+    p.waves = 4;
+    p.kg = 2;
+    if (N % 256 == 0) {
+      const int blocks = N / 256, s = blocks >= 192 ? 1 : std::max(1, target / blocks);
+      if (blocks >= 192 || K / 64 >= 16 * p.kg * s) p.nt = 2;
+    }
   }
-  const int wgs = N / (32 * p.waves * p.nt) * p.m_chunks;
-  // K splits: enough workgroups to stream from every CU while the weights are the bound (512); one workgroup
-  // per CU at four row tiles, where the MFMA work is the bound and every further split only adds an
-  // M x N fp32 partial result to write and re-read (measured on the 70B shape: 68 instead of 77 us per launch)
-  const int target = p.mt32 == 4 ? 256 : 512;
-  int want = (target + wgs / 2) / wgs;
-  const int max_s = K / 512 > 0 ? K / 512 : 1;
-  int s = want < max_s ? want : max_s;
-  if (s < 1) s = 1;
-  p.k_per = ceil_div(ceil_div(K, s), kGroup) * kGroup;      // whole groups per split
+  if (N % (32 * p.waves * p.nt) != 0) {      // N is a multiple of 64
+    p.waves = 2;
+    p.kg = p.mt == 4 ? 2 : 4;      // (LDS: kg x 3 activation buffers)
+  }
+  p.n_blocks = N / (32 * p.waves * p.nt);
+  // K splits: every one adds an M x N fp32 partial result to write and re-read, so as many as fill the chip once, with
+  // at least 8 steps per K group
+  const int wgs = p.n_blocks * p.m_chunks;
+  const int s = std::max(1, std::min(target / wgs, K / (512 * p.kg)));
+  p.k_per = ceil_div(ceil_div(K, s), kGroup) * kGroup;      // whole scale groups per split
   p.splits = ceil_div(K, p.k_per);
   return p;
 }
 
 int gemm_w4_splits(int M, int N, int K) { return M <= 0 ? 1 : w4_plan(M, N, K).splits; }
 
-template <int NW>
-static void launch_w4(const W4Plan& p, const bf16_t* x, const uint4* codes, const uint32_t* meta, float* P, int M,
-                      int N, int K, hipStream_t stream) {
-  const int n_blocks = N / (32 * NW * p.nt);
-  const int gx = p.m_chunks > 1 ? ceil_div(n_blocks, 8) * 8 * p.m_chunks : n_blocks;
-  const dim3 grid(gx, p.splits, 1);
-  if (p.mt32 == 1)
-    gemm_w4_kernel<1, NW, 1, 4, 4><<<grid, 64 * NW, 0, stream>>>(x, codes, meta, P, M, N, K, p.k_per, p.m_chunks);
-  else if (p.mt32 == 2)
-    gemm_w4_kernel<2, NW, 1, 4, 4><<<grid, 64 * NW, 0, stream>>>(x, codes, meta, P, M, N, K, p.k_per, p.m_chunks);
-  else if (p.nt == 1)
-    gemm_w4_kernel<4, NW, 1, 4, 4><<<grid, 64 * NW, 0, stream>>>(x, codes, meta, P, M, N, K, p.k_per, p.m_chunks);
-  else
-    gemm_w4_kernel<4, NW, 2, 2, (NW >= 8 ? 2 : 1)><<<grid, 64 * NW, 0, stream>>>(x, codes, meta, P, M, N, K, p.k_per, p.m_chunks);
+// Whether the gate/up projection runs unsplit with the SwiGLU in its epilogue: up to 64 rows with 2 waves x 4 K groups
+// (128 columns per workgroup; 53 rows of the 8B shape 28 us, against 25 and a separate SwiGLU of 6), up to 96 with 4 x 2
+// (256 columns), where that fills more than half of the compute units.
+static int w4_gate_up_blocks(int M, int F) {
+  if (M <= 64) return F % 64 == 0 ? F / 64 : 0;
+  return M <= 96 && F % 128 == 0 ? F / 128 : 0;
+}
+bool w4_gate_up_fused(int M, int F) { return w4_gate_up_blocks(M, F) > 128; }
+
+#define GS_W4(WN, KG, MT, NT, WPE, MODE)                                                                            \
+  gemm_w4_kernel<WN, KG, MT, NT, 4, 2, WPE, MODE><<<grid, 64 * WN * KG, 0, stream>>>(x, codes, meta, P, M, N, K, k_per, chunks)
+
+// act [M][F] (bf16) = silu(X Wg^T) * (X Wu^T); only where w4_gate_up_fused.
+gs_status launch_gemm_w4_gate_up(const void* X, const void* Wpacked, void* act, int M, int F, int K, hipStream_t stream) {
+  const bf16_t* x = static_cast<const bf16_t*>(X);
+  const int N = 2 * F, k_per = K, chunks = 1;
+  const uint4* codes = static_cast<const uint4*>(Wpacked);
+  const uint32_t* meta = reinterpret_cast<const uint32_t*>(static_cast<const char*>(Wpacked) + w4_code_bytes(N, K));
+  float* P = static_cast<float*>(act);
+  const dim3 grid(ceil_div(w4_gate_up_blocks(M, F), 8) * 8, 1, 1);
+  if (M <= 32) GS_W4(2, 4, 1, 2, 2, kGateUp);
+  else if (M <= 64) GS_W4(2, 4, 2, 2, 2, kGateUp);
+  else GS_W4(4, 2, 3, 2, 2, kGateUp);
+  GS_LAUNCH_CHECK("gemm_w4_gate_up");
+  return GS_OK;
 }
 
 // P [splits][M][N] fp32 partial sums of X [M][K] (bf16) * W^T with W given in the packed 4-bit layout.
@@ -313,11 +447,32 @@ gs_status launch_gemm_w4(const void* X, const void* Wpacked, float* P, int M, in
   const bf16_t* x = static_cast<const bf16_t*>(X);
   const uint4* codes = static_cast<const uint4*>(Wpacked);
   const uint32_t* meta = reinterpret_cast<const uint32_t*>(static_cast<const char*>(Wpacked) + w4_code_bytes(N, K));
-  if (p.waves == 8) launch_w4<8>(p, x, codes, meta, P, M, N, K, stream);
-  else if (p.waves == 4) launch_w4<4>(p, x, codes, meta, P, M, N, K, stream);
-  else launch_w4<2>(p, x, codes, meta, P, M, N, K, stream);
+  const int k_per = p.k_per, chunks = p.m_chunks;
+  const dim3 grid(ceil_div(p.n_blocks, 8) * 8 * p.m_chunks, p.splits, 1);
+  switch (p.mt) {
+    case 1:
+      if (p.waves == 8) GS_W4(8, 1, 1, 1, 4, kPlain);
+      else if (p.waves == 4) GS_W4(4, 2, 1, 1, 4, kPlain);
+      else GS_W4(2, 4, 1, 1, 4, kPlain);
+      break;
+    case 2:
+      if (p.nt == 2) GS_W4(4, 2, 2, 2, 2, kPlain);
+      else if (p.waves == 4) GS_W4(4, 2, 2, 1, 2, kPlain);
+      else GS_W4(2, 4, 2, 1, 2, kPlain);
+      break;
+    case 3:
+      if (p.nt == 2) GS_W4(4, 2, 3, 2, 2, kPlain);
+      else if (p.waves == 4) GS_W4(4, 2, 3, 1, 2, kPlain);
+      else GS_W4(2, 4, 3, 1, 2, kPlain);
+      break;
+    default:
+      if (p.waves == 8) GS_W4(8, 1, 4, 1, 2, kPlain);
+      else if (p.waves == 4) GS_W4(4, 2, 4, 1, 2, kPlain);
+      else GS_W4(2, 2, 4, 1, 1, kPlain);
+  }
   GS_LAUNCH_CHECK("gemm_w4");
   return GS_OK;
 }
+#undef GS_W4
 
 }  // namespace gs

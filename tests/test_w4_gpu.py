@@ -74,6 +74,22 @@ def test_w4_model_matches_oracle(gamma, ctx):
     _run(ms, 95, np.array(gamma, np.int32), np.array(ctx, np.int32))
 
 
+@pytest.mark.parametrize("rows", [16, 32, 33, 64, 65, 96, 97, 128, 129, 257])
+def test_w4_projections_at_the_edges_of_the_row_tiles(rows):
+    # widths that are multiples of 64 only (QKV 192, vocabulary 1088); K of one scale group (fewer than the K groups of a
+    # workgroup) and of nine
+    ms = synth.ModelShape(1, 128, 1, 1, 64, 1152, 1088, 10000.0, dtype="bf16")
+    hd2 = dataclasses.replace(ms, n_heads=2)      # n_heads * head_dim is a multiple of 128
+    _run(hd2, 94, np.array([rows // 2 - 1, rows - rows // 2 - 1], np.int32), np.array([9, 0], np.int32))
+
+
+@pytest.mark.parametrize("rows", [20, 50, 90, 110])
+def test_w4_gate_up_with_the_swiglu_in_its_epilogue(rows):
+    # F / 128 = 130 column blocks: unsplit and fused up to 96 rows, split beyond
+    ms = synth.ModelShape(1, 384, 2, 1, 64, 16640, 1024, 10000.0, dtype="bf16")
+    _run(ms, 93, np.array([rows - 3, 1], np.int32), np.array([9, 0], np.int32), std=0.05)
+
+
 def test_w4_wide_matrices_use_eight_waves():
     # N / 128 >= 192 for gate/up (2F = 24576) and the LM head: the 8-wave launch shape
     ms = synth.ModelShape(1, 128, 2, 1, 64, 12288, 24576, 10000.0, dtype="bf16")
