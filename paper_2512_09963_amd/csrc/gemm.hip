@@ -17,13 +17,13 @@
 //   * K is split across workgroups when N alone gives too few of them to fill 256 CUs; the
 //     fp32 partial sums [S][M][N] are summed by the consumer kernel, in a fixed order
 //   * the gate/up projection, where it runs without a K split, applies the SwiGLU in its epilogue and
-//     stores the bf16 activation instead of fp32 sums (gemm_bf16_gate_up_kernel, GATE_UP of the tall kernel).
+//     stores the bf16 activation instead of fp32 sums (gemm_wide.hip, GATE_UP of the tall kernel).
 // k order inside a step is permuted identically for both operands (lane group g takes
 // k = 16g .. 16g+15, first half to the first MFMA, second half to the second), which leaves
 // the dot products unchanged.  Measured without the activation side, on the gate/up shape: 6.2 TB/s
 // in this order, 5.4 TB/s with each tile's k steps contiguous, 4.4 TB/s for row-major weight rows.
 //
-// fp32 path: plain LDS-tiled FMA kernel for the small fp32 configuration.
+// fp32 path: gemm_f32_kernel, on the fp32 matrix instruction, for the small fp32 configuration.
 #include "common.h"
 #include "device_types.h"
 #include "gemm_common.h"
@@ -39,6 +39,7 @@ __device__ __forceinline__ uint4 stream_load(const uint4* p) {
   return make_uint4(v.x, v.y, v.z, v.w);
 }
 
+constexpr int kSkinnyWaves = 4;     // per workgroup (64 columns)
 constexpr int kSkinnyDepth = 4;     // k steps of weights and activations in flight per wave
 constexpr int kTargetWorkgroups = 512;   // about two per CU
 constexpr int kBK = 64;           // k elements per step
@@ -182,102 +183,6 @@ __global__ __launch_bounds__(64 * NW) void gemm_bf16_skinny_kernel(const bf16_t*
 #pragma unroll
       for (int w = 1; w < NW; ++w) merge_stat(m, sum, st[w][tid].x, st[w][tid].y);
       stats[(size_t)(m0 + tid) * n_stat_blocks + n_block] = make_float2(m, sum);
-    }
-  }
-}
-
-// Gate/up projection with the SwiGLU in its epilogue (up to 64 rows): act[r][f] = silu(X W_gate^T) * (X W_up^T)
-// with W = [gate rows; up rows] ([2F][K], packed).  A wave owns feature tile t of both halves (column tiles
-// t and F/16 + t of the packed matrix), so the gate and the up value of an output sit in the same register
-// of the same lane; K is not split, so the sums are complete when the loop ends and the fp32 partial result
-// ([splits][R][2F], written and read back by a separate kernel otherwise) never exists.  grid F / (16 NW).
-template <int MT, int DEPTH, int NW>
-__global__ __launch_bounds__(64 * NW) void gemm_bf16_gate_up_kernel(const bf16_t* __restrict__ X,
-                                                                    const bf16_t* __restrict__ Wp,
-                                                                    bf16_t* __restrict__ act, int M, int F, int K) {
-  __shared__ __attribute__((aligned(16))) bf16_t xs[2][MT * 16 * kLdsRow];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int g = lane >> 4, c = lane & 15;
-  const int f_tile = blockIdx.x * NW + wave;
-  const int n_steps = K / kBK;
-
-  constexpr int kChunks = MT * 128;
-  constexpr int kGemmThreads = 64 * NW;
-  constexpr int kPasses = (kChunks + kGemmThreads - 1) / kGemmThreads;
-  uint4 xreg[DEPTH][kPasses];
-  auto load_x = [&](int slot, int step) {
-#pragma unroll
-    for (int p = 0; p < kPasses; ++p) {
-      const int ch = tid + p * kGemmThreads;
-      const int row = ch >> 3, col = (ch & 7) * 8;
-      uint4 v = make_uint4(0, 0, 0, 0);
-      if (ch < kChunks && row < M) v = *reinterpret_cast<const uint4*>(X + (size_t)row * K + step * kBK + col);
-      xreg[slot][p] = v;
-    }
-  };
-  auto store_x = [&](int buf, int slot) {
-#pragma unroll
-    for (int p = 0; p < kPasses; ++p) {
-      const int ch = tid + p * kGemmThreads;
-      const int row = ch >> 3, col = (ch & 7) * 8;
-      if (ch < kChunks) *reinterpret_cast<uint4*>(&xs[buf][row * kLdsRow + col]) = xreg[slot][p];
-    }
-  };
-  const size_t w_step_stride = (size_t)(2 * F / 16) * 128;
-  const uint4* wgate = reinterpret_cast<const uint4*>(Wp) + (size_t)f_tile * 128 + lane;
-  const uint4* wup = wgate + (size_t)(F / 16) * 128;
-  uint4 wreg[DEPTH][2][2];
-  auto load_w = [&](int slot, int step) {
-    const size_t o = (size_t)step * w_step_stride;
-    wreg[slot][0][0] = stream_load(wgate + o);
-    wreg[slot][0][1] = stream_load(wgate + o + 64);
-    wreg[slot][1][0] = stream_load(wup + o);
-    wreg[slot][1][1] = stream_load(wup + o + 64);
-  };
-  floatx4_t acc_g[MT], acc_u[MT];
-#pragma unroll
-  for (int mt = 0; mt < MT; ++mt) acc_g[mt] = acc_u[mt] = floatx4_t{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-  for (int d = 0; d < DEPTH; ++d)
-    if (d < n_steps) {
-      load_w(d, d);
-      load_x(d, d);
-    }
-  for (int base = 0; base < n_steps; base += DEPTH) {
-#pragma unroll
-    for (int d = 0; d < DEPTH; ++d) {
-      const int step = base + d;
-      if (step < n_steps) {
-        const int buf = step & 1;
-        store_x(buf, d);
-        __syncthreads();
-        const uint4 g0 = wreg[d][0][0], g1 = wreg[d][0][1], u0 = wreg[d][1][0], u1 = wreg[d][1][1];
-        if (step + DEPTH < n_steps) {
-          load_w(d, step + DEPTH);
-          load_x(d, step + DEPTH);
-        }
-        const bf16x8_t bg0 = *reinterpret_cast<const bf16x8_t*>(&g0), bg1 = *reinterpret_cast<const bf16x8_t*>(&g1);
-        const bf16x8_t bu0 = *reinterpret_cast<const bf16x8_t*>(&u0), bu1 = *reinterpret_cast<const bf16x8_t*>(&u1);
-#pragma unroll
-        for (int mt = 0; mt < MT; ++mt) {
-          const bf16_t* ap = &xs[buf][(mt * 16 + c) * kLdsRow + g * 16];
-          const bf16x8_t a0 = *reinterpret_cast<const bf16x8_t*>(ap);
-          const bf16x8_t a1 = *reinterpret_cast<const bf16x8_t*>(ap + 8);
-          acc_g[mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a0, bg0, acc_g[mt], 0, 0, 0);
-          acc_u[mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a0, bu0, acc_u[mt], 0, 0, 0);
-          acc_g[mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a1, bg1, acc_g[mt], 0, 0, 0);
-          acc_u[mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a1, bu1, acc_u[mt], 0, 0, 0);
-        }
-      }
-    }
-  }
-#pragma unroll
-  for (int mt = 0; mt < MT; ++mt) {
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int row = mt * 16 + g * 4 + i;
-      const float gt = acc_g[mt][i];
-      if (row < M) act[(size_t)row * F + f_tile * 16 + c] = float_to_bf16(gt / (1.0f + expf(-gt)) * acc_u[mt][i]);
     }
   }
 }
@@ -569,13 +474,12 @@ gs_status launch_pack_weight(const void* src, void* dst, int N, int K, hipStream
 // Which bf16 kernel serves a shape, and how the launch is cut.
 struct GemmPlan {
   enum Kind {
-    kSkinny,      // up to 32 rows, where the weight stream is all there is (5 rows, 28672 x 4096: 38.9 us, 40 with the wide
-                  // kernel), up to 64 rows where K is split (inside a step: QKV of the 8B shape 13.7 us, 15.2 there, O and
-                  // down 17.8, 18.1), and column counts that are no multiple of 128
-    kWide,        // gemm_wide.hip: from there to 639 rows
+    kSkinny,      // up to 64 rows where K is split over workgroups (inside a step at 53 rows: QKV of the 8B shape 13.7 us,
+                  // 15.2 with the wide kernel, O and down 17.8 on average, 18.1), and column counts that are no
+                  // multiple of 128
+    kWide,        // gemm_wide.hip: everything else up to 639 rows
     kTall         // 640 rows and more, N a multiple of 256 (1024 rows, 28672 x 4096: 275 us, 286 with 2 x 2 waves there)
   } kind;
-  int waves;      // skinny: waves per workgroup (4 or 8)
   int mt;         // row tiles per workgroup
   int m_chunks;   // row chunks (separate workgroups)
   int splits;     // K splits
@@ -588,29 +492,22 @@ static GemmPlan gemm_plan(int M, int N, int K) {
   GemmPlan p;
   const int tiles = ceil_div(M, 16);
   int n_blocks;
-  const bool can_wide = tiles > 2 && N % 128 == 0;
-  if (can_wide) p.wide = wide_plan(M, N, K, false);
+  if (N % 128 == 0) p.wide = wide_plan(M, N, K, false);
   if (tiles >= 40 && N % 256 == 0) {
     p.kind = GemmPlan::kTall;
-    p.waves = 4;
     p.mt = 8;
     n_blocks = N / (64 * kTallNt);
-  } else if (can_wide && (tiles > 4 || p.wide.splits == 1)) {
+  } else if (N % 128 == 0 && (tiles > 4 || p.wide.splits == 1)) {
     p.kind = GemmPlan::kWide;
-    p.waves = p.wide.wm * p.wide.wn;
     p.mt = p.wide.mt;
     p.m_chunks = p.wide.m_chunks;
     p.splits = p.wide.splits;
     p.k_per = p.wide.k_per;
     return p;
   } else {
-    // wide matrices get 8 waves (128 columns per workgroup), which halves the number of times the
-    // activation rows are re-read from L2; narrower ones keep 4 so that the launch still has
-    // enough workgroups
     p.kind = GemmPlan::kSkinny;
-    p.waves = (N % 128 == 0 && N / 128 >= 192) ? 8 : 4;
     p.mt = tiles <= 1 ? 1 : tiles <= 2 ? 2 : tiles <= 4 ? 4 : 8;
-    n_blocks = N / (16 * p.waves);
+    n_blocks = N / (16 * kSkinnyWaves);
   }
   p.m_chunks = ceil_div(tiles, p.mt);
   const int wgs = n_blocks * p.m_chunks;
@@ -636,18 +533,22 @@ int gemm_splits(int dtype, int M, int N, int K) {
   return gemm_plan(M, N, K).splits;
 }
 
-template <int NW>
+template <bool STATS>
 static void launch_skinny(const GemmPlan& p, const bf16_t* x, const bf16_t* w, float* P, int M, int N, int K,
-                          hipStream_t stream) {
+                          float2* stats, int n_stat_blocks, hipStream_t stream) {
+  constexpr int NW = kSkinnyWaves;
   const int n_blocks = N / (16 * NW);
   const int gx = p.m_chunks > 1 ? ceil_div(n_blocks, 8) * 8 * p.m_chunks : n_blocks;
   const dim3 grid(gx, p.splits, 1);
-#define GS_SKINNY(MT_, CHUNKS_) \
-  gemm_bf16_skinny_kernel<MT_, kSkinnyDepth, NW><<<grid, 64 * NW, 0, stream>>>(x, w, P, M, N, K, p.k_per, CHUNKS_)
-  if (p.mt == 1) GS_SKINNY(1, 1);
-  else if (p.mt == 2) GS_SKINNY(2, 1);
-  else if (p.mt == 4) GS_SKINNY(4, 1);
-  else if constexpr (NW == 4) GS_SKINNY(8, p.m_chunks);      // (8 waves: N is a multiple of 128, so the wide kernel)
+#define GS_SKINNY(MT_, CHUNKS_)                                                                                     \
+  gemm_bf16_skinny_kernel<MT_, kSkinnyDepth, NW, STATS><<<grid, 64 * NW, 0, stream>>>(x, w, P, M, N, K, p.k_per,     \
+                                                                                    CHUNKS_, stats, n_stat_blocks)
+  switch (p.mt) {
+    case 1: GS_SKINNY(1, 1); break;
+    case 2: GS_SKINNY(2, 1); break;
+    case 4: GS_SKINNY(4, 1); break;
+    default: GS_SKINNY(8, p.m_chunks);
+  }
 #undef GS_SKINNY
 }
 
@@ -659,18 +560,11 @@ static void launch_tall(const GemmPlan& p, const bf16_t* x, const bf16_t* w, flo
                                                                                 stats, n_stat_blocks);
 }
 
-// Gate/up with the SwiGLU fused, up to 32 rows: 4 waves (64 features per workgroup; 224 workgroups for F = 14336, each
-// wave streaming 256 KB without a K split), weights fetched 6 steps ahead (with 4 the unsplit kernel is 4.5 us
-// slower than the split one on the 8B shape, with 6 it is 1.3 us slower and the 6 us of the separate SwiGLU
-// kernel and its launch boundary are gone; 2 waves double the activation re-reads, 8 leave half the CUs idle).
-constexpr int kGateUpWaves = 4;
-constexpr int kGateUpDepth = 6;
-
 // Whether the gate/up projection of this shape runs with the SwiGLU fused: 4-bit where its kernel does, bf16, and either up to 64 rows or
 // a shape whose kernel needs no K split anyway.
 bool gate_up_fused(int dtype, int M, int F, int K) {
   if (dtype == GS_W4) return M > 0 && w4_gate_up_fused(M, F);
-  if (dtype != GS_BF16 || M <= 0 || F % (16 * kGateUpWaves) != 0 || K % kBK != 0) return false;
+  if (dtype != GS_BF16 || M <= 0 || F % 64 != 0 || K % kBK != 0) return false;
   if (M <= 64) return true;
   const GemmPlan p = gemm_plan(M, 2 * F, K);
   return p.kind != GemmPlan::kSkinny && p.splits == 1;
@@ -680,23 +574,13 @@ bool gate_up_fused(int dtype, int M, int F, int K) {
 gs_status launch_gemm_gate_up(int dtype, const void* X, const void* W, void* act, int M, int F, int K,
                               hipStream_t stream) {
   if (dtype == GS_W4) return launch_gemm_w4_gate_up(X, W, act, M, F, K, stream);
-  constexpr int NW = kGateUpWaves, D = kGateUpDepth;
   const bf16_t* x = static_cast<const bf16_t*>(X);
   const bf16_t* w = static_cast<const bf16_t*>(W);
-  bf16_t* a = static_cast<bf16_t*>(act);
-  const int tiles = ceil_div(M, 16);
-  if (tiles > 2) {
-    const GemmPlan p = gemm_plan(M, 2 * F, K);
-    if (p.kind != GemmPlan::kTall)      // (2 F is a multiple of 128)
-      return launch_wide_gate_up(wide_plan(M, 2 * F, K, true), x, w, a, M, 2 * F, K, stream);
-    launch_tall<true, false>(p, x, w, static_cast<float*>(act), M, 2 * F, K, nullptr, 0, stream);
-    GS_LAUNCH_CHECK("gemm_gate_up_tall");
-    return GS_OK;
-  }
-  const int grid = F / (16 * NW);
-  if (tiles <= 1) gemm_bf16_gate_up_kernel<1, D, NW><<<grid, 64 * NW, 0, stream>>>(x, w, a, M, F, K);
-  else gemm_bf16_gate_up_kernel<2, D, NW><<<grid, 64 * NW, 0, stream>>>(x, w, a, M, F, K);
-  GS_LAUNCH_CHECK("gemm_gate_up");
+  const GemmPlan p = gemm_plan(M, 2 * F, K);
+  if (p.kind != GemmPlan::kTall)      // (2 F is a multiple of 128)
+    return launch_wide_gate_up(wide_plan(M, 2 * F, K, true), x, w, static_cast<bf16_t*>(act), M, 2 * F, K, stream);
+  launch_tall<true, false>(p, x, w, static_cast<float*>(act), M, 2 * F, K, nullptr, 0, stream);
+  GS_LAUNCH_CHECK("gemm_gate_up_tall");
   return GS_OK;
 }
 
@@ -706,7 +590,7 @@ int gemm_stat_blocks(int dtype, int M, int N, int K) {
   if (dtype != GS_BF16 || M <= 0) return 0;
   const GemmPlan p = gemm_plan(M, N, K);
   if (p.splits != 1) return 0;
-  return p.kind == GemmPlan::kWide ? p.wide.n_blocks : p.kind == GemmPlan::kTall ? N / (64 * kTallNt) : N / (16 * p.waves);
+  return p.kind == GemmPlan::kWide ? p.wide.n_blocks : p.kind == GemmPlan::kTall ? N / (64 * kTallNt) : N / (16 * kSkinnyWaves);
 }
 
 // Y [M][N] = X W^T (one K split) and stats [M][gemm_stat_blocks] = per row and column block (max, sum exp(y - max)).
@@ -719,28 +603,8 @@ gs_status launch_gemm_stats(const void* X, const void* W, float* Y, void* stats,
   const int nb = gemm_stat_blocks(GS_BF16, M, N, K);
   if (nb == 0) return fail(GS_EUNSUPPORTED, "this projection shape does not emit softmax statistics");
   if (p.kind == GemmPlan::kWide) return launch_wide_stats(p.wide, x, w, Y, st, M, N, K, stream);
-  if (p.kind == GemmPlan::kTall) {
-    launch_tall<false, true>(p, x, w, Y, M, N, K, st, nb, stream);
-  } else {
-    const int n_blocks = N / (16 * p.waves);
-    const int gx = p.m_chunks > 1 ? ceil_div(n_blocks, 8) * 8 * p.m_chunks : n_blocks;
-    const dim3 grid(gx, 1, 1);
-    const int mc = p.mt == 8 ? p.m_chunks : 1;
-#define GS_SKINNY_STATS(MT_, NW_) \
-  gemm_bf16_skinny_kernel<MT_, kSkinnyDepth, NW_, true><<<grid, 64 * NW_, 0, stream>>>(x, w, Y, M, N, K, p.k_per, mc, st, nb)
-    if (p.waves == 8) {      // (up to 32 rows: more take the wide kernel where N is a multiple of 128 and K is not split)
-      if (p.mt == 1) GS_SKINNY_STATS(1, 8);
-      else GS_SKINNY_STATS(2, 8);
-    } else {
-      switch (p.mt) {
-        case 1: GS_SKINNY_STATS(1, 4); break;
-        case 2: GS_SKINNY_STATS(2, 4); break;
-        case 4: GS_SKINNY_STATS(4, 4); break;
-        default: GS_SKINNY_STATS(8, 4);
-      }
-    }
-#undef GS_SKINNY_STATS
-  }
+  if (p.kind == GemmPlan::kTall) launch_tall<false, true>(p, x, w, Y, M, N, K, st, nb, stream);
+  else launch_skinny<true>(p, x, w, Y, M, N, K, st, nb, stream);
   GS_LAUNCH_CHECK("gemm_bf16_stats");
   return GS_OK;
 }
@@ -778,8 +642,7 @@ gs_status launch_gemm(int dtype, const void* X, const void* W, float* P, int M, 
     const bf16_t* w = static_cast<const bf16_t*>(W);
     if (p.kind == GemmPlan::kWide) return launch_wide(p.wide, x, w, P, M, N, K, stream);
     if (p.kind == GemmPlan::kTall) launch_tall<false, false>(p, x, w, P, M, N, K, nullptr, 0, stream);
-    else if (p.waves == 8) launch_skinny<8>(p, x, w, P, M, N, K, stream);
-    else launch_skinny<4>(p, x, w, P, M, N, K, stream);
+    else launch_skinny<false>(p, x, w, P, M, N, K, nullptr, 0, stream);
     GS_LAUNCH_CHECK("gemm_bf16");
   } else {
     launch_f32(static_cast<const float*>(X), static_cast<const float*>(W), P, M, N, K, stream);

@@ -1,4 +1,4 @@
-// bf16 projections for 33 to a few hundred rows (MFMA): the packed weight stream of gemm.hip with a software pipeline
+// bf16 projections for up to a few hundred rows (MFMA): the packed weight stream of gemm.hip with a software pipeline
 // that leaves neither the matrix pipe nor the stream waiting.
 //
 // What bounds it: up to about 130 rows the weight stream (HBM), above the matrix pipe together with the LDS
@@ -283,7 +283,7 @@ WidePlan wide_plan(int M, int N, int K, bool one_split) {
   p.nt = 2;
   if (tiles <= 8) {
     p.wm = 1;
-    p.mt = tiles <= 4 ? 4 : tiles <= 6 ? 6 : 8;
+    p.mt = tiles <= 2 ? 2 : tiles <= 4 ? 4 : tiles <= 6 ? 6 : 8;
     p.m_chunks = 1;
     // 256 columns per workgroup where that still leaves a workgroup for three compute units in four (28672 columns
     // of the 8B gate/up projection would leave 112); narrower matrices take 128
@@ -300,7 +300,7 @@ WidePlan wide_plan(int M, int N, int K, bool one_split) {
   p.n_blocks = N / (16 * p.nt * p.wn);
   const int wgs = p.n_blocks * p.m_chunks;
   // one workgroup per compute unit (registers and LDS of every shape fit that many); at least 8 steps per split
-  const int want = (256 + wgs / 2) / wgs, max_s = std::max(1, K / 512);
+  const int want = 256 / wgs, max_s = std::max(1, K / 512);
   const int s = one_split ? 1 : std::max(1, std::min(want, max_s));
   p.k_per = ceil_div(ceil_div(K, s), 64) * 64;
   p.splits = ceil_div(K, p.k_per);
@@ -324,18 +324,21 @@ static gs_status launch_mode(const WidePlan& p, const bf16_t* x, const bf16_t* w
     }
   } else if (p.wn == 8) {
     switch (p.mt) {
+      case 2: GS_WIDE(1, 8, 1, 2, 2, 4, 2, 2, 2); break;
       case 4: GS_WIDE(1, 8, 1, 4, 2, 4, 2, 2, 2); break;
       case 6: GS_WIDE(1, 8, 1, 6, 2, 4, 2, 2, 2); break;
       default: GS_WIDE(1, 8, 1, 8, 2, 4, 2, 2, 2);
     }
   } else if constexpr (MODE == kStats) {
     switch (p.mt) {
+      case 2: GS_WIDE(1, 4, 1, 2, 2, 4, 2, 2, 1); break;
       case 4: GS_WIDE(1, 4, 1, 4, 2, 4, 2, 2, 1); break;
       case 6: GS_WIDE(1, 4, 1, 6, 2, 4, 2, 2, 1); break;
       default: GS_WIDE(1, 4, 1, 8, 2, 4, 2, 2, 1);
     }
   } else {
     switch (p.mt) {
+      case 2: GS_WIDE(1, 4, 2, 2, 2, 4, 2, 2, 2); break;
       case 4: GS_WIDE(1, 4, 2, 4, 2, 4, 2, 2, 2); break;
       case 6: GS_WIDE(1, 4, 2, 6, 2, 4, 2, 2, 2); break;
       default: GS_WIDE(1, 4, 2, 8, 2, 4, 2, 2, 2);

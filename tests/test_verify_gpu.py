@@ -153,7 +153,7 @@ def test_f32_projection_and_attention_edges(ms, gamma, ctx):
     _run_case(ms, 87, np.array(gamma, np.int32), np.array(ctx, np.int32), 16, std=0.08)
 
 
-@pytest.mark.parametrize("rows", [33, 64, 65, 96, 97, 128, 129, 160, 161, 193, 257, 321, 352, 353, 385, 639, 640])
+@pytest.mark.parametrize("rows", [3, 16, 17, 32, 33, 64, 65, 96, 97, 128, 129, 160, 161, 193, 257, 321, 352, 353, 385, 639, 640])
 def test_bf16_projections_at_the_edges_of_the_row_tiles(rows):
     # every row-tile count of the wide kernel and one row on either side; K of 3 steps (an odd count for the two K groups
     # of the gate/up projection) and of 17 steps in two unequal splits; a vocabulary of 171 column blocks: statistics
@@ -162,7 +162,7 @@ def test_bf16_projections_at_the_edges_of_the_row_tiles(rows):
     _run_case(ms, 89, np.array(gamma, np.int32), np.array([9, 0], np.int32), 16, std=0.08)
 
 
-@pytest.mark.parametrize("rows", [40, 90, 120])
+@pytest.mark.parametrize("rows", [5, 40, 90, 120])
 def test_bf16_projections_with_256_columns_per_workgroup(rows):
     # N / 256 >= 192 for the gate/up projection and the LM head; K of one step
     ms = synth.ModelShape(1, 64, 1, 1, 64, 24576, 49152, 10000.0, dtype="bf16")
