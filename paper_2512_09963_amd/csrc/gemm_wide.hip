@@ -3,7 +3,7 @@
 //
 // What bounds it: up to about 130 rows the weight stream (HBM), above the matrix pipe together with the LDS
 // reads of the activations: a 1 KB activation fragment feeds NT MFMAs of 16 cycles, so at NT = 2 the LDS delivers its
-// limit of 128 bytes per cycle and compute unit; tiles of more than 8 row tiles therefore take NT = 4.
+// limit of 128 bytes per cycle and compute unit; where the matrix pipe is the bound (more than 12 row tiles) NT is 4.
 // The predecessor of this kernel (two LDS buffers, fragments read where they are used, all loads of a step in one
 // burst behind the barrier) was held up by neither: the loads' addresses, the LDS stores and the first fragment reads
 // of a step ran while the matrix pipe was idle, and the compiler sank the loads to the end of the step, where the
@@ -18,7 +18,7 @@
 //   * loads are buffer loads: the descriptor moves with k on the scalar unit and the lane offsets are constant, so a
 //     load costs no vector instruction for its address; rows past the end read as zero by the descriptor's range
 // Three shapes: WM x WN waves, each with MT x NT tiles of 16 x 16, KG groups of them that share K:
-//   1 x 8 (256 columns, wide matrices), up to 128 rows: no weight byte is loaded twice
+//   1 x 8 (256 columns, wide matrices), up to 192 rows: no weight byte is loaded twice
 //   1 x 4 (128 columns) with KG = 2: the two halves of K in one workgroup, their sums meet in LDS: as many waves as 1 x 8
 //     without halving the workgroups of a narrower matrix, and half the partial results of a further K split (which the
 //     gate/up projection, whose epilogue applies the SwiGLU, must not have)
@@ -281,9 +281,9 @@ WidePlan wide_plan(int M, int N, int K, bool one_split) {
   WidePlan p;
   const int tiles = ceil_div(M, 16);
   p.nt = 2;
-  if (tiles <= 8) {
+  if (tiles <= 12) {
     p.wm = 1;
-    p.mt = tiles <= 2 ? 2 : tiles <= 4 ? 4 : tiles <= 6 ? 6 : 8;
+    p.mt = std::max(2, (tiles + 1) / 2 * 2);
     p.m_chunks = 1;
     // 256 columns per workgroup where that still leaves a workgroup for three compute units in four (28672 columns
     // of the 8B gate/up projection would leave 112); narrower matrices take 128
@@ -294,7 +294,7 @@ WidePlan wide_plan(int M, int N, int K, bool one_split) {
     p.wn = 2;
     p.nt = 4;
     const int chunks = ceil_div(tiles, 22), half = ceil_div(ceil_div(tiles, chunks), 2);
-    p.mt = half <= 5 ? 5 : half <= 6 ? 6 : half <= 8 ? 8 : half <= 10 ? 10 : 11;
+    p.mt = half <= 8 ? 8 : half <= 10 ? 10 : 11;
     p.m_chunks = ceil_div(tiles, 2 * p.mt);
   }
   p.n_blocks = N / (16 * p.nt * p.wn);
@@ -316,8 +316,6 @@ static gs_status launch_mode(const WidePlan& p, const bf16_t* x, const bf16_t* w
       <<<grid, 64 * WM * WN * KG, 0, stream>>>(x, w, out, M, N, K, p.k_per, p.m_chunks, stats, p.n_blocks)
   if (p.wm == 2) {
     switch (p.mt) {
-      case 5: GS_WIDE(2, 2, 1, 5, 4, 2, 1, 0, 1); break;
-      case 6: GS_WIDE(2, 2, 1, 6, 4, 2, 1, 0, 1); break;
       case 8: GS_WIDE(2, 2, 1, 8, 4, 2, 1, 0, 1); break;
       case 10: GS_WIDE(2, 2, 1, 10, 4, 2, 1, 0, 1); break;
       default: GS_WIDE(2, 2, 1, 11, 4, 2, 1, 0, 1);
@@ -327,21 +325,27 @@ static gs_status launch_mode(const WidePlan& p, const bf16_t* x, const bf16_t* w
       case 2: GS_WIDE(1, 8, 1, 2, 2, 4, 2, 2, 2); break;
       case 4: GS_WIDE(1, 8, 1, 4, 2, 4, 2, 2, 2); break;
       case 6: GS_WIDE(1, 8, 1, 6, 2, 4, 2, 2, 2); break;
-      default: GS_WIDE(1, 8, 1, 8, 2, 4, 2, 2, 2);
+      case 8: GS_WIDE(1, 8, 1, 8, 2, 4, 2, 2, 2); break;
+      case 10: GS_WIDE(1, 8, 1, 10, 2, 4, 2, 2, 2); break;
+      default: GS_WIDE(1, 8, 1, 12, 2, 4, 2, 2, 2);
     }
   } else if constexpr (MODE == kStats) {
     switch (p.mt) {
       case 2: GS_WIDE(1, 4, 1, 2, 2, 4, 2, 2, 1); break;
       case 4: GS_WIDE(1, 4, 1, 4, 2, 4, 2, 2, 1); break;
       case 6: GS_WIDE(1, 4, 1, 6, 2, 4, 2, 2, 1); break;
-      default: GS_WIDE(1, 4, 1, 8, 2, 4, 2, 2, 1);
+      case 8: GS_WIDE(1, 4, 1, 8, 2, 4, 2, 2, 1); break;
+      case 10: GS_WIDE(1, 4, 1, 10, 2, 4, 2, 2, 1); break;
+      default: GS_WIDE(1, 4, 1, 12, 2, 4, 2, 2, 1);
     }
   } else {
     switch (p.mt) {
       case 2: GS_WIDE(1, 4, 2, 2, 2, 4, 2, 2, 2); break;
       case 4: GS_WIDE(1, 4, 2, 4, 2, 4, 2, 2, 2); break;
       case 6: GS_WIDE(1, 4, 2, 6, 2, 4, 2, 2, 2); break;
-      default: GS_WIDE(1, 4, 2, 8, 2, 4, 2, 2, 2);
+      case 8: GS_WIDE(1, 4, 2, 8, 2, 4, 2, 2, 2); break;
+      case 10: GS_WIDE(1, 4, 2, 10, 2, 4, 2, 2, 2); break;
+      default: GS_WIDE(1, 4, 2, 12, 2, 4, 2, 2, 2);
     }
   }
 #undef GS_WIDE
