@@ -3,6 +3,7 @@
 // rotary embedding + KV-page append, SwiGLU.  All arithmetic is fp32; T is the storage
 // type of the tensors fed to the next projection and of the KV pages (float or bf16).
 #include "common.h"
+#include "attn_work.h"
 #include "device_types.h"
 
 namespace gs {
@@ -28,15 +29,6 @@ __device__ __forceinline__ int server_of_row(const int* __restrict__ cu_rows, in
     if (cu_rows[mid] <= r) lo = mid; else hi = mid;
   }
   return lo;
-}
-
-template <typename T>
-__global__ __launch_bounds__(256) void embed_kernel(const T* __restrict__ embed, const int* __restrict__ tokens,
-                                                    float* __restrict__ x, int d, int vocab) {
-  const int r = blockIdx.x;
-  const int tok = min(max(tokens[r], 0), vocab - 1);      // an id outside the vocabulary is never used as an index
-  const T* src = embed + (size_t)tok * d;
-  for (int i = threadIdx.x; i < d; i += 256) x[(size_t)r * d + i] = Storage<T>::load(src + i);
 }
 
 // x[r] += sum_s partial[s][r] (if partial), then h[r] = x[r] * w / sqrt(mean(x[r]^2) + eps).
@@ -108,25 +100,88 @@ __global__ __launch_bounds__(1024) void add_rmsnorm_kernel(float* __restrict__ x
   for (int i = i1 + bd; i < d4; i += bd) emit(i, xr[i], wr[i], inv);
 }
 
-// Per-row facts that every layer of a step shares: where the row's K/V go (page, slot), how many keys
-// its attention query group (group_tokens consecutive tokens of the block) sees, and the rotary sine/cosine of its position.  rope [R][hd/2] (cos, sin).  The angle pos * theta^(-2i/hd)
-// reaches thousands of radians: it is formed in double, so that the rotated values agree with a
-// float64 evaluation to fp32 rounding.  grid R, block hd/2.
-__global__ void row_meta_kernel(const int* __restrict__ cu_rows, const int* __restrict__ ctx_len, int n_servers,
-                                const int* __restrict__ block_table, int max_blocks, int page_size, int hd,
-                                double log2_theta, int group_tokens, int4* __restrict__ row_slot,
-                                float2* __restrict__ rope) {
-  const int r = blockIdx.x, i = threadIdx.x;
-  const int srv = server_of_row(cu_rows, n_servers, r);
-  const int j = r - cu_rows[srv], pos = ctx_len[srv] + j;
-  if (i == 0)      // (page, slot) of the row's own K/V, keys its attention query group sees, server
-    row_slot[r] = make_int4(block_table[(size_t)srv * max_blocks + pos / page_size], pos % page_size,
-                            ctx_len[srv] + min(cu_rows[srv + 1] - cu_rows[srv], (j / group_tokens + 1) * group_tokens),
-                            srv);
-  const double inv_freq = exp2(-2.0 * (double)i / (double)hd * log2_theta);
-  double sn, cs;
-  sincos((double)pos * inv_freq, &sn, &cs);
-  rope[(size_t)r * (hd >> 1) + i] = make_float2((float)cs, (float)sn);
+// Everything of a step that precedes the first projection, in one launch (five dependent-looking launches of 3 to 17 us
+// otherwise: 27 us of a 53-row step, 6 now; the roles are independent of each other).  Workgroups by index:
+//   [0, R)       embedding row r into the residual stream (storage type -> fp32, 4 elements per lane and pass) and its
+//                first RMSNorm h[r] = x[r] * w / sqrt(mean(x[r]^2) + eps)
+//   [R, 2 R)     per-row facts that every layer shares: where the row's K/V go (page, slot), how many keys its attention
+//                query group (group_tokens consecutive tokens of the block) sees, and the rotary sine/cosine of its
+//                position, rope [R][hd/2] (cos, sin).  The angle pos * theta^(-2i/hd) reaches thousands of radians: it
+//                is formed in double, so that the rotated values agree with a float64 evaluation to fp32 rounding.
+//                Also draft_tokens[cu_rows[i] - i + j] = tokens[cu_rows[i] + 1 + j]: the drafts without the pending tokens.
+//   2 R          the attention work list (bf16 models: the grid has this workgroup only then)
+struct StepBegin {
+  const void* embed;
+  const int* tokens;
+  float* x;
+  const float* norm;
+  void* h;
+  const int* cu_rows;
+  const int* ctx_len;
+  const int* block_table;
+  int4* row_slot;
+  float2* rope;
+  int* draft_tokens;
+  int* attn_work;
+  double log2_theta;
+  float eps;
+  int n_rows, d, vocab, n_servers, max_blocks, page_size, hd, group_tokens, steps_per_split, work_capacity;
+};
+
+template <typename T>
+__global__ __launch_bounds__(kWorkThreads) void step_begin_kernel(StepBegin a) {
+  __shared__ int shared[2 * kSortBins];
+  const int tid = threadIdx.x;
+  if ((int)blockIdx.x < a.n_rows) {
+    const int r = blockIdx.x;
+    const int tok = min(max(a.tokens[r], 0), a.vocab - 1);      // an id outside the vocabulary is never used as an index
+    const T* src = static_cast<const T*>(a.embed) + (size_t)tok * a.d;
+    float4* xr = reinterpret_cast<float4*>(a.x + (size_t)r * a.d);
+    const float4* wr = reinterpret_cast<const float4*>(a.norm);
+    T* hr = static_cast<T*>(a.h) + (size_t)r * a.d;
+    const int d4 = a.d >> 2;
+    float ss = 0.f;
+    float4 v0 = make_float4(0.f, 0.f, 0.f, 0.f), w0 = v0;      // the first pass stays in registers (all of a row to d = 4096)
+    for (int i = tid; i < d4; i += kWorkThreads) {
+      const float4 v = make_float4(Storage<T>::load(src + 4 * i), Storage<T>::load(src + 4 * i + 1),
+                                   Storage<T>::load(src + 4 * i + 2), Storage<T>::load(src + 4 * i + 3));
+      if (i == tid) {
+        w0 = wr[i];
+        v0 = v;
+      }
+      xr[i] = v;
+      ss += (v.x * v.x + v.y * v.y) + (v.z * v.z + v.w * v.w);
+    }
+    const float tot = block_sum(ss, reinterpret_cast<float*>(shared));
+    const float inv = 1.0f / sqrtf(tot / (float)a.d + a.eps);
+    for (int i = tid; i < d4; i += kWorkThreads) {
+      const float4 v = i == tid ? v0 : xr[i], w = i == tid ? w0 : wr[i];
+      Storage<T>::store(hr + 4 * i + 0, v.x * inv * w.x);
+      Storage<T>::store(hr + 4 * i + 1, v.y * inv * w.y);
+      Storage<T>::store(hr + 4 * i + 2, v.z * inv * w.z);
+      Storage<T>::store(hr + 4 * i + 3, v.w * inv * w.w);
+    }
+  } else if ((int)blockIdx.x < 2 * a.n_rows) {
+    if (tid >= 64) return;
+    const int r = blockIdx.x - a.n_rows;
+    const int srv = server_of_row(a.cu_rows, a.n_servers, r);
+    const int row0 = a.cu_rows[srv], j = r - row0, pos = a.ctx_len[srv] + j;
+    if (tid == 0) {
+      a.row_slot[r] = make_int4(a.block_table[(size_t)srv * a.max_blocks + pos / a.page_size], pos % a.page_size,
+                                a.ctx_len[srv] + min(a.cu_rows[srv + 1] - row0, (j / a.group_tokens + 1) * a.group_tokens),
+                                srv);
+      if (j > 0) a.draft_tokens[r - srv - 1] = a.tokens[r];
+    }
+    for (int i = tid; i < (a.hd >> 1); i += 64) {
+      const double inv_freq = exp2(-2.0 * (double)i / (double)a.hd * a.log2_theta);
+      double sn, cs;
+      sincos((double)pos * inv_freq, &sn, &cs);
+      a.rope[(size_t)r * (a.hd >> 1) + i] = make_float2((float)cs, (float)sn);
+    }
+  } else {
+    build_attention_work(a.cu_rows, a.ctx_len, a.n_servers, a.block_table, a.max_blocks, a.page_size, a.steps_per_split,
+                         a.group_tokens, a.work_capacity, a.attn_work, shared);
+  }
 }
 
 // Sums the QKV partials, rotates Q and K at the row's position, stores Q [R][H][hd] and
@@ -205,10 +260,18 @@ __global__ __launch_bounds__(256) void swiglu_kernel(const float* __restrict__ g
     __VA_ARGS__                                   \
   }
 
-gs_status launch_embed(int dtype, const void* embed, const int* tokens, float* x, int n_rows, int d, int vocab,
-                       hipStream_t stream) {
-  GS_DISPATCH_T(dtype, embed_kernel<T><<<n_rows, 256, 0, stream>>>(static_cast<const T*>(embed), tokens, x, d, vocab);)
-  GS_LAUNCH_CHECK("embed");
+// work_list: whether the step's attention needs its work list (bf16 models).
+gs_status launch_step_begin(int dtype, const void* embed, const int* tokens, float* x, const float* norm, float eps, void* h,
+                            int n_rows, int d, int vocab, const int* cu_rows, const int* ctx_len, int n_servers,
+                            const int* block_table, int max_blocks, int page_size, int hd, float rope_theta,
+                            int group_tokens, int steps_per_split, int work_capacity, bool work_list, void* row_slot,
+                            void* rope, int* draft_tokens, int* attn_work, hipStream_t stream) {
+  const StepBegin a{embed, tokens, x, norm, h, cu_rows, ctx_len, block_table, static_cast<int4*>(row_slot),
+                    static_cast<float2*>(rope), draft_tokens, attn_work, log2((double)rope_theta), eps, n_rows, d, vocab,
+                    n_servers, max_blocks, page_size, hd, group_tokens, steps_per_split, work_capacity};
+  const unsigned grid = 2u * (unsigned)n_rows + (work_list ? 1u : 0u);
+  GS_DISPATCH_T(dtype, step_begin_kernel<T><<<grid, kWorkThreads, 0, stream>>>(a);)
+  GS_LAUNCH_CHECK("step_begin");
   return GS_OK;
 }
 
@@ -219,16 +282,6 @@ gs_status launch_add_rmsnorm(int dtype, float* x, const float* partial, int n_sp
   GS_DISPATCH_T(dtype, add_rmsnorm_kernel<T><<<n_rows, threads, 0, stream>>>(x, partial, n_splits, n_rows, w, eps,
                                                                             static_cast<T*>(h), d);)
   GS_LAUNCH_CHECK("add_rmsnorm");
-  return GS_OK;
-}
-
-gs_status launch_row_meta(const int* cu_rows, const int* ctx_len, int n_servers, int n_rows, const int* block_table,
-                          int max_blocks, int page_size, int hd, float rope_theta, int group_tokens, void* row_slot,
-                          void* rope, hipStream_t stream) {
-  row_meta_kernel<<<n_rows, hd / 2, 0, stream>>>(cu_rows, ctx_len, n_servers, block_table, max_blocks, page_size, hd,
-                                                 log2((double)rope_theta), group_tokens, static_cast<int4*>(row_slot),
-                                                 static_cast<float2*>(rope));
-  GS_LAUNCH_CHECK("row_meta");
   return GS_OK;
 }
 

@@ -1,6 +1,7 @@
 // gs_verify_batch: the decoder forward over the ragged speculative blocks followed by
 // rejection-verification, enqueued on one stream without host synchronisation.
-// Per layer: add+RMSNorm -> QKV projection -> rotary + KV append -> attention -> O projection
+// First one launch for the embedding, the first norm, the per-row tables and the attention work list; then
+// per layer: add+RMSNorm -> QKV projection -> rotary + KV append -> attention -> O projection
 //            -> add+RMSNorm -> gate/up projection -> SwiGLU -> down projection.
 // The residual stream and the logits are fp32; tensors fed to a projection and the KV
 // pages are in the model's storage type.
@@ -18,13 +19,13 @@ gs_status launch_pack_weight_w4(const void* q, const void* scales, const void* z
 gs_status launch_gemm(int dtype, const void* X, const void* W, float* P, int M, int N, int K, hipStream_t stream);
 bool gate_up_fused(int dtype, int M, int F, int K);
 gs_status launch_gemm_gate_up(int dtype, const void* X, const void* W, void* act, int M, int F, int K, hipStream_t stream);
-gs_status launch_embed(int dtype, const void* embed, const int* tokens, float* x, int n_rows, int d, int vocab,
-                       hipStream_t);
+gs_status launch_step_begin(int dtype, const void* embed, const int* tokens, float* x, const float* norm, float eps, void* h,
+                            int n_rows, int d, int vocab, const int* cu_rows, const int* ctx_len, int n_servers,
+                            const int* block_table, int max_blocks, int page_size, int hd, float rope_theta,
+                            int group_tokens, int steps_per_split, int work_capacity, bool work_list, void* row_slot,
+                            void* rope, int* draft_tokens, int* attn_work, hipStream_t stream);
 gs_status launch_add_rmsnorm(int dtype, float* x, const float* partial, int n_splits, int n_rows, const float* w,
                              float eps, void* h, int d, hipStream_t stream);
-gs_status launch_row_meta(const int* cu_rows, const int* ctx_len, int n_servers, int n_rows, const int* block_table,
-                          int max_blocks, int page_size, int hd, float rope_theta, int group_tokens, void* row_slot,
-                          void* rope, hipStream_t stream);
 gs_status launch_rope_append(int dtype, const float* qkv, int n_splits, int n_rows, const void* row_slot,
                              const void* rope, int page_size, int n_heads, int n_kv, int hd, void* q_out,
                              void* k_pages, void* v_pages, hipStream_t stream);
@@ -43,9 +44,6 @@ gs_status launch_attention(int dtype, const void* q, const void* k_pages, const 
                            int waves, int steps_per_split, int max_splits, bool split, const void* row_info,
                            const int* work, int n_work, float* scratch, void* attn_out, hipStream_t stream);
 size_t attention_work_ints(int capacity);
-gs_status launch_attention_work(const int* cu_rows, const int* ctx_len, int n_servers, const int* block_table,
-                                int max_blocks, int page_size, int steps_per_split, int group_tokens, int capacity,
-                                int* work, hipStream_t stream);
 gs_status launch_accept(int n_servers, int n_rows, const int* cu_rows, int vocab, int elem, const void* target_logits,
                         const void* q_probs, const int* draft_tokens, const float* u_accept,
                         const float* u_resample, const gs_accept_out* out, void* workspace, hipStream_t stream,
@@ -156,14 +154,6 @@ __global__ void sum_partials_kernel(const float* __restrict__ partial, int n_spl
   float acc = 0.f;
   for (int s = 0; s < n_splits; ++s) acc += partial[(size_t)s * n + i];
   y[i] = acc;
-}
-
-// draft_tokens[cu_rows[i] - i + j] = tokens[cu_rows[i] + 1 + j]: the drafts without the pending tokens
-__global__ void gather_draft_tokens_kernel(const int* __restrict__ tokens, const int* __restrict__ cu_rows,
-                                           int n_servers, int* __restrict__ draft_tokens) {
-  const int srv = blockIdx.x;
-  const int r0 = cu_rows[srv], gamma = cu_rows[srv + 1] - r0 - 1;
-  for (int j = threadIdx.x; j < gamma; j += blockDim.x) draft_tokens[r0 - srv + j] = tokens[r0 + 1 + j];
 }
 
 // Measurement aid (gs_probe_stream_read): the plainest possible streaming read, 16-byte non-temporal loads,
@@ -441,17 +431,15 @@ extern "C" gs_status gs_verify_batch(gs_ctx* ctx, const gs_kv_cache* kv, const g
     GS_TRY(call);               \
     GS_TRY(timer.end());        \
   } while (0)
-  GS_STAGE(GS_STAGE_GLUE, gs::launch_embed(act, ctx->embed, b->tokens, p.x, rows, d, m.vocab, stream));
-  GS_STAGE(GS_STAGE_GLUE, gs::launch_row_meta(b->cu_rows, b->ctx_len, n, rows, b->block_table, b->max_blocks, kv->page_size,
-                                              m.head_dim, m.rope_theta, group_tokens, p.row_slot, p.rope, stream));
-  if (act == GS_BF16)
-    GS_STAGE(GS_STAGE_GLUE, gs::launch_attention_work(b->cu_rows, b->ctx_len, n, b->block_table, b->max_blocks,
-                                                      kv->page_size, attn_sps, group_tokens, p.attn_work_capacity, p.attn_work,
-                                                      stream));
+  GS_STAGE(GS_STAGE_GLUE, gs::launch_step_begin(act, ctx->embed, b->tokens, p.x, ctx->norm1[0], m.rms_eps, p.h, rows, d, m.vocab,
+                                                b->cu_rows, b->ctx_len, n, b->block_table, b->max_blocks, kv->page_size,
+                                                m.head_dim, m.rope_theta, group_tokens, attn_sps, p.attn_work_capacity,
+                                                act == GS_BF16, p.row_slot, p.rope, p.draft_tokens, p.attn_work, stream));
   const float* pending = nullptr;   // split-K partials of the projection whose result is still to be added to x
   int pending_splits = 0;
   for (int l = 0; l < m.n_layers; ++l) {
-    GS_STAGE(GS_STAGE_GLUE, gs::launch_add_rmsnorm(act, p.x, pending, pending_splits, rows, ctx->norm1[l], m.rms_eps, p.h, d, stream));
+    if (l > 0)      // (the first norm comes with the embedding)
+      GS_STAGE(GS_STAGE_GLUE, gs::launch_add_rmsnorm(act, p.x, pending, pending_splits, rows, ctx->norm1[l], m.rms_eps, p.h, d, stream));
     if (ctx->residual_trace)   // residual stream entering layer l (complete once the pending partials are added)
       GS_HIP_CHECK(hipMemcpyAsync(ctx->residual_trace + (size_t)l * rows * d, p.x, sizeof(float) * rows * d,
                                   hipMemcpyDeviceToDevice, stream));
@@ -496,10 +484,6 @@ extern "C" gs_status gs_verify_batch(gs_ctx* ctx, const gs_kv_cache* kv, const g
     GS_LAUNCH_CHECK("sum_partials");
   }
   if (do_accept) {
-    if (G > 0) {
-      gather_draft_tokens_kernel<<<n, 64, 0, stream>>>(b->tokens, b->cu_rows, n, p.draft_tokens);
-      GS_LAUNCH_CHECK("gather_draft_tokens");
-    }
     GS_STAGE(GS_STAGE_ACCEPT, gs::launch_accept(n, rows, b->cu_rows, m.vocab, GS_F32, logits, b->q_probs, p.draft_tokens,
                                                 b->u_accept, b->u_resample, out, p.accept_ws, stream,
                                                 stat_blocks > 0 ? p.lm_stats : nullptr, stat_blocks));
