@@ -47,34 +47,31 @@ __device__ __forceinline__ void merge_pair(float& m, float& s, float m2, float s
   s = a + b;
 }
 
-__device__ __forceinline__ float max4(const float4& v) { return fmaxf(fmaxf(v.x, v.y), fmaxf(v.z, v.w)); }
-
-// Sixteen bytes of a row: 4 floats or 8 bfloat16, widened to float.  STREAM: the load does not displace
-// cache lines (the logits are read once by the statistics pass).
-typedef float __attribute__((ext_vector_type(4))) float4_vec;
+// Sixteen bytes of a row: 4 floats or 8 bfloat16, widened to float.
 typedef unsigned int __attribute__((ext_vector_type(4))) uint4_vec;
 template <typename T> struct Pack;
 template <> struct Pack<float> {
   static constexpr int W = 4;
-  template <bool STREAM>
-  static __device__ __forceinline__ void load(const float* p, float (&v)[4]) {
-    const float4_vec x = STREAM ? __builtin_nontemporal_load(reinterpret_cast<const float4_vec*>(p))
-                                : *reinterpret_cast<const float4_vec*>(p);
-    v[0] = x.x; v[1] = x.y; v[2] = x.z; v[3] = x.w;
+  static constexpr unsigned kNegInf = 0xff800000u;      // a 32-bit word of -infinity
+  static __device__ __forceinline__ void widen(const uint4_vec& x, float (&v)[4]) {
+    v[0] = __uint_as_float(x.x); v[1] = __uint_as_float(x.y); v[2] = __uint_as_float(x.z); v[3] = __uint_as_float(x.w);
   }
 };
 template <> struct Pack<bf16_t> {
   static constexpr int W = 8;
-  template <bool STREAM>
-  static __device__ __forceinline__ void load(const bf16_t* p, float (&v)[8]) {
-    const uint4_vec x = STREAM ? __builtin_nontemporal_load(reinterpret_cast<const uint4_vec*>(p))
-                               : *reinterpret_cast<const uint4_vec*>(p);
+  static constexpr unsigned kNegInf = 0xff80ff80u;
+  static __device__ __forceinline__ void widen(const uint4_vec& x, float (&v)[8]) {
     v[0] = __uint_as_float(x.x << 16); v[1] = __uint_as_float(x.x & 0xffff0000u);
     v[2] = __uint_as_float(x.y << 16); v[3] = __uint_as_float(x.y & 0xffff0000u);
     v[4] = __uint_as_float(x.z << 16); v[5] = __uint_as_float(x.z & 0xffff0000u);
     v[6] = __uint_as_float(x.w << 16); v[7] = __uint_as_float(x.w & 0xffff0000u);
   }
 };
+// sixteen bytes at p, widened
+template <typename T>
+__device__ __forceinline__ void load_pack(const T* p, float (&v)[Pack<T>::W]) {
+  Pack<T>::widen(*reinterpret_cast<const uint4_vec*>(p), v);
+}
 template <int W>
 __device__ __forceinline__ float max_of(const float (&v)[W]) {
   float m = fmaxf(fmaxf(v[0], v[1]), fmaxf(v[2], v[3]));
@@ -90,6 +87,9 @@ __device__ __forceinline__ float sum_exp_of(const float (&v)[W], float mm) {
 
 // ---------------------------------------------------------------------------------------
 // row_stats: grid chunks * rows (chunk fastest).  VEC: rows are 16-byte aligned and V % 4 == 0.
+// Bound by the read stream; bfloat16 rows nearly as much by the exponentials (8 per 16 bytes), so the loads of the next
+// four packs are issued before the current four are reduced (576 x 151936 bfloat16: 37.4 us without, see the launch
+// comment in launch_accept_t for what it takes now).
 // ---------------------------------------------------------------------------------------
 template <typename T, bool VEC>
 __global__ __launch_bounds__(kStatsThreads) void row_stats_kernel(const T* __restrict__ logits, int vocab,
@@ -105,23 +105,34 @@ __global__ __launch_bounds__(kStatsThreads) void row_stats_kernel(const T* __res
   if (VEC) {
     const T* p = base + begin;
     const int n_pk = (end - begin) / W;
-    for (int i = threadIdx.x; i < n_pk; i += 4 * kStatsThreads) {
-      float v0[W], v1[W], v2[W], v3[W];
+    constexpr int kStep = 4 * kStatsThreads;
+    auto load4 = [&](int i, uint4_vec (&raw)[4]) {
 #pragma unroll
-      for (int k = 0; k < W; ++k) v1[k] = v2[k] = v3[k] = -INFINITY;
-      Pack<T>::template load<true>(p + (size_t)i * W, v0);
-      if (i + kStatsThreads < n_pk) Pack<T>::template load<true>(p + (size_t)(i + kStatsThreads) * W, v1);
-      if (i + 2 * kStatsThreads < n_pk) Pack<T>::template load<true>(p + (size_t)(i + 2 * kStatsThreads) * W, v2);
-      if (i + 3 * kStatsThreads < n_pk) Pack<T>::template load<true>(p + (size_t)(i + 3 * kStatsThreads) * W, v3);
-      const float bm = fmaxf(fmaxf(max_of<W>(v0), max_of<W>(v1)), fmaxf(max_of<W>(v2), max_of<W>(v3)));
+      for (int k = 0; k < 4; ++k) {
+        raw[k] = uint4_vec{Pack<T>::kNegInf, Pack<T>::kNegInf, Pack<T>::kNegInf, Pack<T>::kNegInf};
+        const int j = i + k * kStatsThreads;
+        if (j < n_pk) raw[k] = __builtin_nontemporal_load(reinterpret_cast<const uint4_vec*>(p + (size_t)j * W));
+      }
+    };
+    uint4_vec cur[4];
+    load4(threadIdx.x, cur);
+    for (int i0 = 0; i0 < n_pk; i0 += kStep) {
+      uint4_vec nxt[4];
+      if (i0 + kStep < n_pk) load4(i0 + kStep + threadIdx.x, nxt);
+      float v[4][W];
+#pragma unroll
+      for (int k = 0; k < 4; ++k) Pack<T>::widen(cur[k], v[k]);
+      const float bm = fmaxf(fmaxf(max_of<W>(v[0]), max_of<W>(v[1])), fmaxf(max_of<W>(v[2]), max_of<W>(v[3])));
       if (bm > m) {
         s *= __expf(m - bm);     // m = -inf gives exp(-inf) = 0 and s is 0 anyway
         m = bm;
       }
       const float mm = (m == -INFINITY) ? 0.f : m;   // a lane that has seen only -inf adds exp(-inf) = 0
-      const float a0 = sum_exp_of<W>(v0, mm), a1 = sum_exp_of<W>(v1, mm);
-      const float a2 = sum_exp_of<W>(v2, mm), a3 = sum_exp_of<W>(v3, mm);
+      const float a0 = sum_exp_of<W>(v[0], mm), a1 = sum_exp_of<W>(v[1], mm);
+      const float a2 = sum_exp_of<W>(v[2], mm), a3 = sum_exp_of<W>(v[3], mm);
       s += (a0 + a1) + (a2 + a3);
+#pragma unroll
+      for (int k = 0; k < 4; ++k) cur[k] = nxt[k];
     }
   } else {
     for (int i = begin + threadIdx.x; i < end; i += kStatsThreads) {
@@ -202,7 +213,7 @@ __device__ __forceinline__ void load_weights8(const T* __restrict__ lrow, const 
 #pragma unroll
     for (int h = 0; h < 8 / W; ++h) {
       float part[W];
-      Pack<T>::template load<false>(lrow + t0 + h * W, part);
+      load_pack<T>(lrow + t0 + h * W, part);
 #pragma unroll
       for (int k = 0; k < W; ++k) l[h * W + k] = part[k];
     }
@@ -210,7 +221,7 @@ __device__ __forceinline__ void load_weights8(const T* __restrict__ lrow, const 
 #pragma unroll
       for (int h = 0; h < 8 / W; ++h) {
         float part[W];
-        Pack<T>::template load<false>(qrow + t0 + h * W, part);
+        load_pack<T>(qrow + t0 + h * W, part);
 #pragma unroll
         for (int k = 0; k < W; ++k) q[h * W + k] = part[k];
       }
@@ -285,8 +296,18 @@ __device__ __forceinline__ Decision decide_server(int srv, const int* __restrict
   int first_reject = gamma;    // smallest rejected draft index seen by this lane
   float stat = 0.f;
   bool bad_id = false;         // a draft token id outside the vocabulary: never used as an index
-  for (int j = lane; j < gamma; j += 64) {
+  // lane j takes row j of the block, the bonus row among them, so that the statistics of the row the token is drawn from are
+  // already in a register of some lane (blocks of up to 64 rows: its first pass)
+  float own_m = 0.f, own_s = 1.f;
+  for (int j = lane; j <= gamma; j += 64) {
     const int row = row0 + j;
+    float m, s;
+    row_max_sum(partial, row, n_chunks, m, s);
+    if (j == lane) {
+      own_m = m;
+      own_s = s;
+    }
+    if (j == gamma) break;
     int tok = draft_tokens[d0 + j];
     if (tok < 0 || tok >= vocab) {
       bad_id = true;
@@ -295,8 +316,6 @@ __device__ __forceinline__ Decision decide_server(int srv, const int* __restrict
     const float u = u_accept[d0 + j];
     const float lg = Storage<T>::load(logits + (size_t)row * vocab + tok);
     const float q = Storage<T>::load(q_probs + (size_t)(d0 + j) * vocab + tok);
-    float m, s;
-    row_max_sum(partial, row, n_chunks, m, s);
     const float p = expf(lg - m) / s;
     const float ratio = (q == 0.f) ? INFINITY : p / q;
     if (write_out && ratio_out) ratio_out[d0 + j] = ratio;
@@ -316,8 +335,8 @@ __device__ __forceinline__ Decision decide_server(int srv, const int* __restrict
   Decision d;
   d.row = row0 + m_acc;
   d.q_row = (m_acc < gamma) ? d0 + m_acc : -1;
-  float m, s;
-  row_max_sum(partial, d.row, n_chunks, m, s);
+  float m = __shfl(own_m, m_acc & 63), s = __shfl(own_s, m_acc & 63);
+  if (m_acc >= 64) row_max_sum(partial, d.row, n_chunks, m, s);      // (uniform over the wave)
   d.row_max = m;
   d.inv_z = 1.f / s;
   return d;
@@ -403,10 +422,33 @@ __global__ __launch_bounds__(kTileThreads) void pick_token_kernel(const Decision
   __shared__ int sh_tile, sh_found, sh_last_pos;
   float w[8];
 
-  // total mass: workgroup scan over the tile sums (fixed order: deterministic)
   const double* sums = tile_sums + (size_t)srv * n_tiles;
+  const double u = (double)u_resample[srv];
   double total = 0.0;
-  for (int base = 0; base < n_tiles; base += kTileThreads) {
+  // Up to 256 tiles (a vocabulary of 524288 tokens): every wave scans all tile sums by itself, four per lane, so that the
+  // tile is found without a barrier; the sums and the uniform are loaded beside the decision.
+  constexpr int kPerLane = 4;
+  const bool small = n_tiles <= 64 * kPerLane;
+  const int lane = threadIdx.x & 63;
+  double own[kPerLane], before = 0.0, incl = 0.0;      // this lane's tiles; sums of all tiles before and up to them
+  if (small) {
+    double sum = 0.0;
+#pragma unroll
+    for (int k = 0; k < kPerLane; ++k) {
+      own[k] = lane * kPerLane + k < n_tiles ? sums[lane * kPerLane + k] : 0.0;
+      sum += own[k];
+    }
+    incl = sum;
+    for (int off = 1; off < 64; off <<= 1) {
+      const double o = __shfl_up(incl, off);
+      if (lane >= off) incl += o;
+    }
+    before = __shfl_up(incl, 1);
+    if (lane == 0) before = 0.0;
+    total = __shfl(incl, 63);
+  }
+  // more tiles: workgroup scan over the tile sums (fixed order: deterministic)
+  for (int base = 0; !small && base < n_tiles; base += kTileThreads) {
     const int t = base + threadIdx.x;
     double ex;
     const double incl = block_scan(t < n_tiles ? sums[t] : 0.0, wave_tot, ex);
@@ -433,7 +475,7 @@ __global__ __launch_bounds__(kTileThreads) void pick_token_kernel(const Decision
     total = tot;
   }
 
-  const double target = (double)u_resample[srv] * total;
+  const double target = u * total;
   if (threadIdx.x == 0) {
     sh_found = -1;
     sh_last_pos = -1;
@@ -442,7 +484,36 @@ __global__ __launch_bounds__(kTileThreads) void pick_token_kernel(const Decision
   }
   __syncthreads();
 
-  if (!fallback) {
+  int small_tile = 0;
+  double small_prefix = 0.0;
+  if (!fallback && small) {
+    // The lane in whose tiles the running sum crosses the target: at most one, because a lane's `before` is the previous
+    // lane's `incl` to the last bit.  Inside it the first tile that crosses, or, where the order of the additions leaves
+    // none, its last tile with mass; the nearest lane with mass below if it has none; the last mass of all if no lane
+    // crosses.  A tile without mass is never chosen.
+    int cross = -1, last = -1;
+    double run = before, cross_prefix = 0.0, last_prefix = 0.0;
+#pragma unroll
+    for (int k = 0; k < kPerLane; ++k) {
+      const double next = run + own[k];
+      if (own[k] > 0.0) {
+        last = lane * kPerLane + k;
+        last_prefix = run;
+        if (cross < 0 && next > target) {
+          cross = last;
+          cross_prefix = run;
+        }
+      }
+      run = next;
+    }
+    const unsigned long long crossing = __ballot(incl > target && !(before > target)), massed = __ballot(last >= 0);
+    const int at = crossing ? __ffsll(crossing) - 1 : 63;
+    const unsigned long long up_to = massed & (~0ull >> (63 - at));
+    const int from = up_to ? 63 - __clzll(up_to) : massed ? __ffsll(massed) - 1 : 0;
+    const bool use_cross = crossing && from == at && __shfl(cross, from) >= 0;
+    small_tile = max(__shfl(use_cross ? cross : last, from), 0);      // (0: no mass anywhere)
+    small_prefix = __shfl(use_cross ? cross_prefix : last_prefix, from);
+  } else if (!fallback) {
     // the tile in which the running sum crosses the target: exactly one lane sees the crossing
     __shared__ int sh_last_tile;
     __shared__ double sh_carry;
@@ -487,8 +558,8 @@ __global__ __launch_bounds__(kTileThreads) void pick_token_kernel(const Decision
   }
 
   // Walk tiles: a single tile in the normal path, all tiles until found in the fallback path.
-  int tile = fallback ? 0 : sh_tile;
-  double prefix = fallback ? 0.0 : sh_prefix;
+  int tile = fallback ? 0 : small ? small_tile : sh_tile;
+  double prefix = fallback ? 0.0 : small ? small_prefix : sh_prefix;
   int last_pos_any = -1;
   for (;;) {
     const int t0 = tile * kTileElems + threadIdx.x * 8;
