@@ -343,12 +343,12 @@ __device__ __forceinline__ Decision decide_server(int srv, const int* __restrict
 }
 
 // ---------------------------------------------------------------------------------------
-// draw_tiles: grid tile groups * servers (group fastest), 256 lanes.  A workgroup owns kTilesPerGroup
-// consecutive 2048-token tiles; group 0 also stores the server's outputs and its decision.
+// draw_tiles: grid tile groups * servers (group fastest), 256 lanes.  A workgroup owns TILES
+// consecutive 2048-token tiles; group 0 also stores the server's outputs and its decision.  Every workgroup repeats the
+// decision (5 us of dependent loads), so it takes four tiles, unless even single tiles leave compute units without a
+// workgroup: then the time of one workgroup is the time of the launch.
 // ---------------------------------------------------------------------------------------
-constexpr int kTilesPerGroup = 4;
-
-template <typename T, bool VEC>
+template <typename T, bool VEC, int TILES>
 __global__ __launch_bounds__(kTileThreads) void draw_tiles_kernel(const int* __restrict__ cu_rows, int vocab,
                                                                   int n_chunks, int n_tiles, int n_groups,
                                                                   const float2* __restrict__ partial,
@@ -363,7 +363,7 @@ __global__ __launch_bounds__(kTileThreads) void draw_tiles_kernel(const int* __r
                                                                   double* __restrict__ tile_sums) {
   const int srv = blockIdx.x / n_groups, group = blockIdx.x - srv * n_groups;
   __shared__ Decision sh_d;
-  __shared__ double part[kTileThreads / 64];
+  __shared__ double part[TILES][kTileThreads / 64];
   if (threadIdx.x < 64) {
     const Decision dd = decide_server<T>(srv, cu_rows, vocab, n_chunks, partial, logits, q_probs, draft_tokens, u_accept,
                                       group == 0, accepted_len, accept_stat, ratio_out);
@@ -378,27 +378,30 @@ __global__ __launch_bounds__(kTileThreads) void draw_tiles_kernel(const int* __r
   const T* lrow = logits + (size_t)d.row * vocab;
   const T* qrow = residual ? q_probs + (size_t)d.q_row * vocab : nullptr;
   // all loads of the group's tiles are issued before the first is consumed
-  float w[kTilesPerGroup][8];
+  float w[TILES][8];
 #pragma unroll
-  for (int k = 0; k < kTilesPerGroup; ++k) {
-    const int tile = group * kTilesPerGroup + k;
+  for (int k = 0; k < TILES; ++k) {
+    const int tile = group * TILES + k;
     if (tile < n_tiles)
       load_weights8<T, VEC>(lrow, qrow, tile * kTileElems + threadIdx.x * 8, vocab, d.row_max, d.inv_z, residual, w[k]);
+    else
+      for (int e = 0; e < 8; ++e) w[k][e] = 0.f;
   }
+  double acc[TILES];
 #pragma unroll
-  for (int k = 0; k < kTilesPerGroup; ++k) {
-    const int tile = group * kTilesPerGroup + k;
-    if (tile >= n_tiles) break;
-    double acc = (double)sum8(w[k]);
-    for (int off = 32; off > 0; off >>= 1) acc += __shfl_down(acc, off);
-    if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = acc;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-      double t = part[0];
-      for (int wv = 1; wv < kTileThreads / 64; ++wv) t += part[wv];
-      tile_sums[(size_t)srv * n_tiles + tile] = t;
-    }
-    __syncthreads();
+  for (int k = 0; k < TILES; ++k) acc[k] = (double)sum8(w[k]);
+  for (int off = 32; off > 0; off >>= 1)
+#pragma unroll
+    for (int k = 0; k < TILES; ++k) acc[k] += __shfl_down(acc[k], off);
+  if ((threadIdx.x & 63) == 0)
+#pragma unroll
+    for (int k = 0; k < TILES; ++k) part[k][threadIdx.x >> 6] = acc[k];
+  __syncthreads();
+  const int k = threadIdx.x, tile = group * TILES + k;
+  if (k < TILES && tile < n_tiles) {
+    double t = part[k][0];
+    for (int wv = 1; wv < kTileThreads / 64; ++wv) t += part[k][wv];
+    tile_sums[(size_t)srv * n_tiles + tile] = t;
   }
 }
 
@@ -662,12 +665,16 @@ gs_status launch_accept_t(const AcceptPlan& p, int n_servers, int n_rows, const 
     row_stats_kernel<T, VEC><<<g1, kStatsThreads, 0, stream>>>(target_logits, vocab, p.chunk_len, p.n_chunks, p.partial);
     GS_LAUNCH_CHECK("row_stats");
   }
-  const int n_groups = ceil_div(p.n_tiles, kTilesPerGroup);
+  const int tiles = (long)n_servers * p.n_tiles <= 512 ? 1 : 4;      // (two workgroups per compute unit)
+  const int n_groups = ceil_div(p.n_tiles, tiles);
   const unsigned g2 = (unsigned)n_groups * (unsigned)n_servers;
-  draw_tiles_kernel<T, VEC><<<g2, kTileThreads, 0, stream>>>(cu_rows, vocab, n_chunks, p.n_tiles, n_groups, p.partial,
-                                                             target_logits, q_probs, draft_tokens, u_accept,
-                                                             out->accepted_len, out->accept_stat, out->ratio,
-                                                             p.decision, p.tile_sums);
+#define GS_DRAW(TILES)                                                                                              \
+  draw_tiles_kernel<T, VEC, TILES><<<g2, kTileThreads, 0, stream>>>(                                                \
+      cu_rows, vocab, n_chunks, p.n_tiles, n_groups, p.partial, target_logits, q_probs, draft_tokens, u_accept,     \
+      out->accepted_len, out->accept_stat, out->ratio, p.decision, p.tile_sums)
+  if (tiles == 1) GS_DRAW(1);
+  else GS_DRAW(4);
+#undef GS_DRAW
   GS_LAUNCH_CHECK("draw_tiles");
   pick_token_kernel<T, VEC><<<n_servers, kTileThreads, 0, stream>>>(p.decision, vocab, p.n_tiles, target_logits, q_probs,
                                                                     p.tile_sums, u_resample, out->next_token);
