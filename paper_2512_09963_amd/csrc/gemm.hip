@@ -17,7 +17,7 @@
 //   * K is split across workgroups when N alone gives too few of them to fill 256 CUs; the
 //     fp32 partial sums [S][M][N] are summed by the consumer kernel, in a fixed order
 //   * the gate/up projection, where it runs without a K split, applies the SwiGLU in its epilogue and
-//     stores the bf16 activation instead of fp32 sums (gemm_wide.hip, GATE_UP of the tall kernel).
+//     stores the bf16 activation instead of fp32 sums (gemm_wide.hip).
 // k order inside a step is permuted identically for both operands (lane group g takes
 // k = 16g .. 16g+15, first half to the first MFMA, second half to the second), which leaves
 // the dot products unchanged.  Measured without the activation side, on the gate/up shape: 6.2 TB/s
@@ -187,175 +187,6 @@ __global__ __launch_bounds__(64 * NW) void gemm_bf16_skinny_kernel(const bf16_t*
   }
 }
 
-// 640 rows and more: the same streaming design with a taller and wider wave tile.  A wave owns NT column tiles and
-// all MT * 16 rows of its row chunk, so every activation fragment read from LDS feeds NT MFMAs and every weight
-// fragment MT of them; a workgroup covers NT * 64 columns.  (MT = 8, NT = 4, no register prefetch: the second
-// wave on each SIMD hides the latency.)
-// Row chunks of one column block are separate workgroups that read the same weights: workgroups are
-// handed to the 8 XCDs round robin by their linear index, so the chunks of a column block get indices
-// that are 8 apart and land on the same XCD one after the other, and all but the first find the weights
-// in that XCD's L2.  grid (ceil(N / (64 NT) / 8) * 8 * m_chunks, S).
-// GATE_UP (one K split): half of the wave's column tiles are feature tiles of the gate half and half the same ones of
-// the up half of a [2F][K] matrix, and the epilogue stores act[r][f] = silu(gate) * up as bf16 ([M][N/2], at P)
-// instead of the fp32 sums.
-// STATS: as in the skinny kernel, (max, sum exp) of every row over the workgroup's 64 NT columns.
-template <int MT, int NT, int DEPTH, bool GATE_UP = false, bool STATS = false>
-__global__ __launch_bounds__(256, 2) void gemm_bf16_tall_kernel(const bf16_t* __restrict__ X,
-                                                                const bf16_t* __restrict__ Wp,
-                                                                float* __restrict__ P, int M, int N, int K,
-                                                                int k_per_split, int m_chunks,
-                                                                float2* __restrict__ stats = nullptr,
-                                                                int n_stat_blocks = 0) {
-  static_assert(!GATE_UP || NT % 2 == 0, "gate and up tile of every feature tile");
-  __shared__ __attribute__((aligned(16))) bf16_t xs[2][MT * 16 * kLdsRow];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int g = lane >> 4, c = lane & 15;
-  const int xcd = blockIdx.x & 7, t = blockIdx.x >> 3;
-  const int m_chunk = t % m_chunks;
-  const int n_block = (t / m_chunks) * 8 + xcd;
-  if (n_block * (64 * NT) >= N) return;        // padding of the grid to a multiple of 8 column blocks
-  // first column tile of the wave; with GATE_UP its tiles are NT/2 neighbouring feature tiles of the gate
-  // half followed by the same ones of the up half (N/32 tiles further)
-  const int n_tile0 = GATE_UP ? (n_block * 4 + wave) * (NT / 2) : (n_block * 4 + wave) * NT;
-  auto tile_offset = [&](int nt) { return GATE_UP ? (nt % (NT / 2)) + (nt / (NT / 2)) * (N / 32) : nt; };
-  const int split = blockIdx.y;
-  const int m0 = m_chunk * (MT * 16);
-  const int k_begin = split * k_per_split;
-  const int k_end = min(K, k_begin + k_per_split);
-  const int n_steps = (k_end - k_begin) / kBK;
-
-  constexpr int kChunks = MT * 128;
-  constexpr int kPasses = (kChunks + 255) / 256;
-  uint4 xreg[DEPTH][kPasses];
-  auto load_x = [&](int slot, int step) {
-#pragma unroll
-    for (int p = 0; p < kPasses; ++p) {
-      const int ch = tid + p * 256;
-      const int row = ch >> 3, col = (ch & 7) * 8;
-      uint4 v = make_uint4(0, 0, 0, 0);
-      if (ch < kChunks && m0 + row < M)
-        v = *reinterpret_cast<const uint4*>(X + (size_t)(m0 + row) * K + k_begin + step * kBK + col);
-      xreg[slot][p] = v;
-    }
-  };
-  auto store_x = [&](int buf, int slot) {
-#pragma unroll
-    for (int p = 0; p < kPasses; ++p) {
-      const int ch = tid + p * 256;
-      const int row = ch >> 3, col = (ch & 7) * 8;
-      if (ch < kChunks) *reinterpret_cast<uint4*>(&xs[buf][row * kLdsRow + col]) = xreg[slot][p];
-    }
-  };
-  const size_t w_step_stride = (size_t)(N / 16) * 128;
-  const uint4* wbase = reinterpret_cast<const uint4*>(Wp) + (size_t)(k_begin / kBK) * w_step_stride + (size_t)n_tile0 * 128 + lane;
-  uint4 wreg[DEPTH][NT][2];
-  auto load_w = [&](int slot, int step) {
-    const uint4* p = wbase + (size_t)step * w_step_stride;
-#pragma unroll
-    for (int nt = 0; nt < NT; ++nt) {
-      wreg[slot][nt][0] = p[(size_t)tile_offset(nt) * 128];
-      wreg[slot][nt][1] = p[(size_t)tile_offset(nt) * 128 + 64];
-    }
-  };
-
-  floatx4_t acc[MT][NT];
-#pragma unroll
-  for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-    for (int nt = 0; nt < NT; ++nt) acc[mt][nt] = floatx4_t{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-  for (int d = 0; d < DEPTH; ++d)
-    if (d < n_steps) {
-      load_w(d, d);
-      load_x(d, d);
-    }
-  for (int base = 0; base < n_steps; base += DEPTH) {
-#pragma unroll
-    for (int d = 0; d < DEPTH; ++d) {
-      const int step = base + d;
-      if (step < n_steps) {
-        const int buf = step & 1;
-        store_x(buf, d);
-        __syncthreads();
-        if (step + DEPTH < n_steps) load_x(d, step + DEPTH);
-        bf16x8_t b[NT][2];
-#pragma unroll
-        for (int nt = 0; nt < NT; ++nt) {
-          b[nt][0] = *reinterpret_cast<const bf16x8_t*>(&wreg[d][nt][0]);
-          b[nt][1] = *reinterpret_cast<const bf16x8_t*>(&wreg[d][nt][1]);
-        }
-        if (step + DEPTH < n_steps) load_w(d, step + DEPTH);
-#pragma unroll
-        for (int mt = 0; mt < MT; ++mt) {
-          const bf16_t* ap = &xs[buf][(mt * 16 + c) * kLdsRow + g * 16];
-          const bf16x8_t a0 = *reinterpret_cast<const bf16x8_t*>(ap);
-          const bf16x8_t a1 = *reinterpret_cast<const bf16x8_t*>(ap + 8);
-#pragma unroll
-          for (int nt = 0; nt < NT; ++nt) {
-            acc[mt][nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a0, b[nt][0], acc[mt][nt], 0, 0, 0);
-            acc[mt][nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a1, b[nt][1], acc[mt][nt], 0, 0, 0);
-          }
-        }
-      }
-    }
-  }
-
-  if constexpr (GATE_UP) {
-    bf16_t* act = reinterpret_cast<bf16_t*>(P);
-    const int F = N / 2;
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int row = m0 + mt * 16 + g * 4 + i;
-        if (row < M) {
-#pragma unroll
-          for (int ft = 0; ft < NT / 2; ++ft) {
-            const float gt = acc[mt][ft][i];
-            act[(size_t)row * F + (n_tile0 + ft) * 16 + c] = float_to_bf16(gt / (1.0f + expf(-gt)) * acc[mt][NT / 2 + ft][i]);
-          }
-        }
-      }
-    return;
-  }
-  float* out = P + (size_t)split * M * N;
-#pragma unroll
-  for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int row = m0 + mt * 16 + g * 4 + i;
-      if (row < M) {
-#pragma unroll
-        for (int nt = 0; nt < NT; ++nt) out[(size_t)row * N + (n_tile0 + nt) * 16 + c] = acc[mt][nt][i];
-      }
-    }
-  if constexpr (STATS) {
-    __shared__ float2 st[4][MT * 16];
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        float mx = acc[mt][0][i];
-#pragma unroll
-        for (int nt = 1; nt < NT; ++nt) mx = fmaxf(mx, acc[mt][nt][i]);
-        mx = row16_max(mx);
-        float e = 0.f;
-#pragma unroll
-        for (int nt = 0; nt < NT; ++nt) e += __expf(acc[mt][nt][i] - mx);
-        e = row16_sum(e);
-        if (c == 0) st[wave][mt * 16 + g * 4 + i] = make_float2(mx, e);
-      }
-    __syncthreads();
-    for (int r = tid; r < MT * 16; r += 256)
-      if (m0 + r < M) {
-        float m = st[0][r].x, sum = st[0][r].y;
-#pragma unroll
-        for (int w = 1; w < 4; ++w) merge_stat(m, sum, st[w][r].x, st[w][r].y);
-        stats[(size_t)(m0 + r) * n_stat_blocks + n_block] = make_float2(m, sum);
-      }
-  }
-}
-
 // fp32 (v_mfma_f32_16x16x4_f32: fp32 products, fp32 sums).  The fp32 models are small (K of a few hundred, a few dozen
 // rows), so a launch is bound by the latency of its loads, not by a rate: what counts is that no wave walks
 // a long serial k chain and that enough waves run.  A workgroup's 8 waves are ks slices of K times 8 / ks column
@@ -477,8 +308,7 @@ struct GemmPlan {
     kSkinny,      // up to 64 rows where K is split over workgroups (inside a step at 53 rows: QKV of the 8B shape 13.7 us,
                   // 15.2 with the wide kernel, O and down 17.8 on average, 18.1), and column counts that are no
                   // multiple of 128
-    kWide,        // gemm_wide.hip: everything else up to 639 rows
-    kTall         // 640 rows and more, N a multiple of 256 (1024 rows, 28672 x 4096: 275 us, 286 with 2 x 2 waves there)
+    kWide         // gemm_wide.hip: everything else
   } kind;
   int mt;         // row tiles per workgroup
   int m_chunks;   // row chunks (separate workgroups)
@@ -486,18 +316,13 @@ struct GemmPlan {
   int k_per;      // k elements per split (multiple of 64)
   WidePlan wide;
 };
-constexpr int kTallNt = 4;      // column tiles per wave of the tall kernel
 
 static GemmPlan gemm_plan(int M, int N, int K) {
   GemmPlan p;
   const int tiles = ceil_div(M, 16);
   int n_blocks;
   if (N % 128 == 0) p.wide = wide_plan(M, N, K, false);
-  if (tiles >= 40 && N % 256 == 0) {
-    p.kind = GemmPlan::kTall;
-    p.mt = 8;
-    n_blocks = N / (64 * kTallNt);
-  } else if (N % 128 == 0 && (tiles > 4 || p.wide.splits == 1)) {
+  if (N % 128 == 0 && (tiles > 4 || p.wide.splits == 1)) {
     p.kind = GemmPlan::kWide;
     p.mt = p.wide.mt;
     p.m_chunks = p.wide.m_chunks;
@@ -552,14 +377,6 @@ static void launch_skinny(const GemmPlan& p, const bf16_t* x, const bf16_t* w, f
 #undef GS_SKINNY
 }
 
-template <bool GATE_UP, bool STATS>
-static void launch_tall(const GemmPlan& p, const bf16_t* x, const bf16_t* w, float* P, int M, int N, int K,
-                        float2* stats, int n_stat_blocks, hipStream_t stream) {
-  const dim3 grid(ceil_div(N / (64 * kTallNt), 8) * 8 * p.m_chunks, p.splits, 1);
-  gemm_bf16_tall_kernel<8, kTallNt, 1, GATE_UP, STATS><<<grid, 256, 0, stream>>>(x, w, P, M, N, K, p.k_per, p.m_chunks,
-                                                                                stats, n_stat_blocks);
-}
-
 // Whether the gate/up projection of this shape runs with the SwiGLU fused: 4-bit where its kernel does, bf16, and either up to 64 rows or
 // a shape whose kernel needs no K split anyway.
 bool gate_up_fused(int dtype, int M, int F, int K) {
@@ -576,12 +393,8 @@ gs_status launch_gemm_gate_up(int dtype, const void* X, const void* W, void* act
   if (dtype == GS_W4) return launch_gemm_w4_gate_up(X, W, act, M, F, K, stream);
   const bf16_t* x = static_cast<const bf16_t*>(X);
   const bf16_t* w = static_cast<const bf16_t*>(W);
-  const GemmPlan p = gemm_plan(M, 2 * F, K);
-  if (p.kind != GemmPlan::kTall)      // (2 F is a multiple of 128)
-    return launch_wide_gate_up(wide_plan(M, 2 * F, K, true), x, w, static_cast<bf16_t*>(act), M, 2 * F, K, stream);
-  launch_tall<true, false>(p, x, w, static_cast<float*>(act), M, 2 * F, K, nullptr, 0, stream);
-  GS_LAUNCH_CHECK("gemm_gate_up_tall");
-  return GS_OK;
+  // (2 F is a multiple of 128)
+  return launch_wide_gate_up(wide_plan(M, 2 * F, K, true), x, w, static_cast<bf16_t*>(act), M, 2 * F, K, stream);
 }
 
 // Number of column blocks per row of the statistics that launch_gemm_stats writes for this shape, or 0 where
@@ -590,7 +403,7 @@ int gemm_stat_blocks(int dtype, int M, int N, int K) {
   if (dtype != GS_BF16 || M <= 0) return 0;
   const GemmPlan p = gemm_plan(M, N, K);
   if (p.splits != 1) return 0;
-  return p.kind == GemmPlan::kWide ? p.wide.n_blocks : p.kind == GemmPlan::kTall ? N / (64 * kTallNt) : N / (16 * kSkinnyWaves);
+  return p.kind == GemmPlan::kWide ? p.wide.n_blocks : N / (16 * kSkinnyWaves);
 }
 
 // Y [M][N] = X W^T (one K split) and stats [M][gemm_stat_blocks] = per row and column block (max, sum exp(y - max)).
@@ -603,8 +416,7 @@ gs_status launch_gemm_stats(const void* X, const void* W, float* Y, void* stats,
   const int nb = gemm_stat_blocks(GS_BF16, M, N, K);
   if (nb == 0) return fail(GS_EUNSUPPORTED, "this projection shape does not emit softmax statistics");
   if (p.kind == GemmPlan::kWide) return launch_wide_stats(p.wide, x, w, Y, st, M, N, K, stream);
-  if (p.kind == GemmPlan::kTall) launch_tall<false, true>(p, x, w, Y, M, N, K, st, nb, stream);
-  else launch_skinny<true>(p, x, w, Y, M, N, K, st, nb, stream);
+  launch_skinny<true>(p, x, w, Y, M, N, K, st, nb, stream);
   GS_LAUNCH_CHECK("gemm_bf16_stats");
   return GS_OK;
 }
@@ -641,8 +453,7 @@ gs_status launch_gemm(int dtype, const void* X, const void* W, float* P, int M, 
     const bf16_t* x = static_cast<const bf16_t*>(X);
     const bf16_t* w = static_cast<const bf16_t*>(W);
     if (p.kind == GemmPlan::kWide) return launch_wide(p.wide, x, w, P, M, N, K, stream);
-    if (p.kind == GemmPlan::kTall) launch_tall<false, false>(p, x, w, P, M, N, K, nullptr, 0, stream);
-    else launch_skinny<false>(p, x, w, P, M, N, K, nullptr, 0, stream);
+    launch_skinny<false>(p, x, w, P, M, N, K, nullptr, 0, stream);
     GS_LAUNCH_CHECK("gemm_bf16");
   } else {
     launch_f32(static_cast<const float*>(X), static_cast<const float*>(W), P, M, N, K, stream);

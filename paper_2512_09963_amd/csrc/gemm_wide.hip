@@ -1,4 +1,4 @@
-// bf16 projections for up to a few hundred rows (MFMA): the packed weight stream of gemm.hip with a software pipeline
+// bf16 projections (MFMA): the packed weight stream of gemm.hip with a software pipeline
 // that leaves neither the matrix pipe nor the stream waiting.
 //
 // What bounds it: up to about 130 rows the weight stream (HBM), above the matrix pipe together with the LDS
@@ -17,12 +17,15 @@
 //   * activation rows are 128 bytes in LDS, their 16-byte pieces XOR-swizzled by the row pair: conflict-free reads
 //   * loads are buffer loads: the descriptor moves with k on the scalar unit and the lane offsets are constant, so a
 //     load costs no vector instruction for its address; rows past the end read as zero by the descriptor's range
-// Three shapes: WM x WN waves, each with MT x NT tiles of 16 x 16, KG groups of them that share K:
+// The shapes: WM x WN waves, each with MT x NT tiles of 16 x 16, KG groups of them that share K:
 //   1 x 8 (256 columns, wide matrices), up to 192 rows: no weight byte is loaded twice
 //   1 x 4 (128 columns) with KG = 2: the two halves of K in one workgroup, their sums meet in LDS: as many waves as 1 x 8
 //     without halving the workgroups of a narrower matrix, and half the partial results of a further K split (which the
 //     gate/up projection, whose epilogue applies the SwiGLU, must not have)
 //   2 x 2 (128 columns, up to 352 rows in one workgroup): both row halves load the weights, the second time from L1
+//   1 x 4 of 128 x 64 (256 columns, chunks of 128 rows) from 640 rows on, where the matrix pipe and the power it draws are
+//     the bound: 1.0 to 1.1 PFLOP/s, 1.25 to 1.3 on matrices of zeros, 1.86 with the global loads of the loop taken out
+//     (rates of a work copy at 2048 x 28672 x 4096; more weights or activations in flight change nothing)
 // Measured inside a verification step (us per launch; predecessor in brackets), N x K:
 //   53 rows   gate/up 28672 x 4096 39.7 (46.0) = 5.9 TB/s, LM head 128256 x 4096 181 (188)
 //   92 rows   gate/up 57344 x 8192 142 (181) = 6.6 TB/s, 8192 x 28672 and 8192 x 8192 55 (60) on average, 10240 x 8192
@@ -46,7 +49,10 @@ enum { kPlain = 0, kGateUp = 1, kStats = 2 };
 // stored as bf16 at P; kStats (one split): also (max, sum exp) of every row over the workgroup's columns.
 // DB, DA: steps of weights and of activations held in registers.  POL: cache policy of the weight loads (2: do not
 // displace other lines; for weights that one workgroup reads once).
-// grid (column blocks, rounded up to a multiple of 8, times row chunks; K splits), see gemm.hip for the chunk order.
+// grid (column blocks, rounded up to a multiple of 8, times row chunks; K splits).  Row chunks of one column block are separate
+// workgroups that read the same weights: workgroups are handed to the 8 XCDs round robin by their linear index, so the
+// chunks of a column block get indices that are 8 apart and land on the same XCD one after the other, and all but the first
+// find the weights in that XCD's L2.
 template <int WM, int WN, int KG, int MT, int NT, int DB, int DA, int POL, int WPE, int MODE>
 __global__ __launch_bounds__(64 * WM * WN * KG) __attribute__((amdgpu_waves_per_eu(WPE, WPE))) void gemm_bf16_wide_kernel(
     const bf16_t* __restrict__ X, const bf16_t* __restrict__ Wp, float* __restrict__ P, int M, int N, int K,
@@ -281,7 +287,17 @@ WidePlan wide_plan(int M, int N, int K, bool one_split) {
   WidePlan p;
   const int tiles = ceil_div(M, 16);
   p.nt = 2;
-  if (tiles <= 12) {
+  int target = 256;      // workgroups: one per compute unit (registers and LDS of every shape fit that many) ...
+  if (tiles >= 40 && N % 256 == 0) {
+    // 640 rows and more: 1 x 4 waves of 128 x 64, two workgroups per compute unit, so that a unit that finishes one takes the
+    // next while the other runs on (256 x 256 tiles of 8 waves: 447 instead of 392 us for gate/up at 2047 rows, 3.5 rounds)
+    p.wm = 1;
+    p.wn = 4;
+    p.nt = 4;
+    p.mt = 8;
+    p.m_chunks = ceil_div(tiles, 8);
+    target = 512;
+  } else if (tiles <= 12) {
     p.wm = 1;
     p.mt = std::max(2, (tiles + 1) / 2 * 2);
     p.m_chunks = 1;
@@ -299,8 +315,8 @@ WidePlan wide_plan(int M, int N, int K, bool one_split) {
   }
   p.n_blocks = N / (16 * p.nt * p.wn);
   const int wgs = p.n_blocks * p.m_chunks;
-  // one workgroup per compute unit (registers and LDS of every shape fit that many); at least 8 steps per split
-  const int want = 256 / wgs, max_s = std::max(1, K / 512);
+  // ... and never a second round for a few more; at least 8 steps per split
+  const int want = target / wgs, max_s = std::max(1, K / 512);
   const int s = one_split ? 1 : std::max(1, std::min(want, max_s));
   p.k_per = ceil_div(ceil_div(K, s), 64) * 64;
   p.splits = ceil_div(K, p.k_per);
@@ -314,7 +330,9 @@ static gs_status launch_mode(const WidePlan& p, const bf16_t* x, const bf16_t* w
 #define GS_WIDE(WM, WN, KG, MT, NT, DB, DA, POL, WPE)                                                              \
   gemm_bf16_wide_kernel<WM, WN, KG, MT, NT, DB, DA, POL, WPE, MODE>                                                 \
       <<<grid, 64 * WM * WN * KG, 0, stream>>>(x, w, out, M, N, K, p.k_per, p.m_chunks, stats, p.n_blocks)
-  if (p.wm == 2) {
+  if (p.wm == 1 && p.nt == 4) {
+    GS_WIDE(1, 4, 1, 8, 4, 2, 1, 0, 2);
+  } else if (p.wm == 2) {
     switch (p.mt) {
       case 8: GS_WIDE(2, 2, 1, 8, 4, 2, 1, 0, 1); break;
       case 10: GS_WIDE(2, 2, 1, 10, 4, 2, 1, 0, 1); break;
