@@ -16,6 +16,7 @@
 // Bandwidth-bound: row_stats streams 4*V bytes per target row; the draw touches O(N*V) bytes.
 #include "common.h"
 #include "device_types.h"
+#include <algorithm>
 #include <cmath>
 #include <mutex>
 
@@ -643,10 +644,11 @@ AcceptPlan plan_chunks(int n_servers, int n_rows, int vocab, void* workspace, in
 }
 
 // pack: elements per 16-byte load of the element type (4 for fp32, 8 for bf16); a chunk is a whole number of them.
-// A batch that fits the static scratch only with the coarse chunks keeps them.
-AcceptPlan plan_accept(int n_servers, int n_rows, int vocab, void* workspace, int pack = 4) {
+// The coarse chunks where the workspace of `capacity` bytes does not hold the finer ones: a workspace may have been sized
+// for a larger batch, whose chunks per row are fewer.
+AcceptPlan plan_accept(int n_servers, int n_rows, int vocab, void* workspace, size_t capacity, int pack) {
   const AcceptPlan p = plan_chunks(n_servers, n_rows, vocab, workspace, pack, pick_chunks(n_rows, vocab, pack));
-  if (p.bytes <= GS_ACCEPT_STATIC_SCRATCH_BYTES) return p;
+  if (p.bytes <= capacity) return p;
   return plan_chunks(n_servers, n_rows, vocab, workspace, pack, coarse_chunks(n_rows, vocab));
 }
 
@@ -690,10 +692,10 @@ gs_status launch_accept_t(const AcceptPlan& p, int n_servers, int n_rows, const 
 // null: then the logits are read once more for them.
 gs_status launch_accept(int n_servers, int n_rows, const int* cu_rows, int vocab, int elem, const void* target_logits,
                         const void* q_probs, const int* draft_tokens, const float* u_accept,
-                        const float* u_resample, const gs_accept_out* out, void* workspace, hipStream_t stream,
-                        const void* row_stats, int n_stat_blocks) {
+                        const float* u_resample, const gs_accept_out* out, void* workspace, size_t workspace_bytes,
+                        hipStream_t stream, const void* row_stats, int n_stat_blocks) {
   const int pack = elem == GS_BF16 ? 8 : 4;
-  const AcceptPlan p = plan_accept(n_servers, n_rows, vocab, workspace, pack);
+  const AcceptPlan p = plan_accept(n_servers, n_rows, vocab, workspace, workspace_bytes, pack);
   const bool vec = (vocab % pack == 0) && (reinterpret_cast<uintptr_t>(target_logits) % 16 == 0) &&
                    (q_probs == nullptr || reinterpret_cast<uintptr_t>(q_probs) % 16 == 0);
 #define GS_ACCEPT(T_, VEC_)                                                                                        \
@@ -705,10 +707,18 @@ gs_status launch_accept(int n_servers, int n_rows, const int* cu_rows, int vocab
 #undef GS_ACCEPT
 }
 
+// What a call cannot do without (the coarse chunks), and what it is asked to bring: the finer chunks, unless only the
+// coarse ones fit the static scratch.
+size_t accept_min_bytes(int n_servers, int n_rows, int vocab) {
+  size_t need = 0;
+  for (int pack : {4, 8}) need = std::max(need, plan_accept(n_servers, n_rows, vocab, nullptr, 0, pack).bytes);
+  return need;
+}
 size_t accept_workspace_bytes(int n_servers, int n_rows, int vocab) {
-  const size_t a = plan_accept(n_servers, n_rows, vocab, nullptr, 4).bytes;
-  const size_t b = plan_accept(n_servers, n_rows, vocab, nullptr, 8).bytes;
-  return a > b ? a : b;
+  size_t want = 0;
+  for (int pack : {4, 8})
+    want = std::max(want, plan_accept(n_servers, n_rows, vocab, nullptr, GS_ACCEPT_STATIC_SCRATCH_BYTES, pack).bytes);
+  return std::max(want, accept_min_bytes(n_servers, n_rows, vocab));
 }
 
 }  // namespace gs
@@ -739,10 +749,10 @@ gs_status accept_entry(int elem, int n_servers, const int* gamma_host, const int
   if (n_rows > kMaxAcceptRows) return fail(GS_EINVAL, "too many rows (at most %ld)", kMaxAcceptRows);
   if (n_draft > 0 && (!q_probs || !draft_tokens || !u_accept))
     return fail(GS_EINVAL, "q_probs, draft_tokens and u_accept are required when any gamma > 0");
-  if (workspace_bytes < accept_workspace_bytes(n_servers, (int)n_rows, vocab))
+  if (workspace_bytes < accept_min_bytes(n_servers, (int)n_rows, vocab))
     return fail(GS_ECAPACITY, "workspace of %zu bytes is smaller than gs_accept_workspace_bytes", workspace_bytes);
   return launch_accept(n_servers, (int)n_rows, cu_rows, vocab, elem, target_logits, q_probs, draft_tokens, u_accept,
-                       u_resample, out, workspace, static_cast<hipStream_t>(hip_stream), nullptr, 0);
+                       u_resample, out, workspace, workspace_bytes, static_cast<hipStream_t>(hip_stream), nullptr, 0);
 }
 
 }  // namespace
@@ -808,7 +818,7 @@ extern "C" gs_status gs_accept_reject_static(int n_servers, const int* gamma_hos
     n_rows += gamma_host[i] + 1;
   }
   if (n_rows > gs::kMaxAcceptRows) return gs::fail(GS_EINVAL, "too many rows");
-  const size_t need = gs::accept_workspace_bytes(n_servers, (int)n_rows, vocab);
+  const size_t need = gs::accept_min_bytes(n_servers, (int)n_rows, vocab);
   if (need > GS_ACCEPT_STATIC_SCRATCH_BYTES)
     return gs::fail(GS_ECAPACITY, "this batch needs %zu bytes of scratch, the static array holds %zu", need,
                     (size_t)GS_ACCEPT_STATIC_SCRATCH_BYTES);

@@ -46,12 +46,12 @@ gs_status launch_attention(int dtype, const void* q, const void* k_pages, const 
 size_t attention_work_ints(int capacity);
 gs_status launch_accept(int n_servers, int n_rows, const int* cu_rows, int vocab, int elem, const void* target_logits,
                         const void* q_probs, const int* draft_tokens, const float* u_accept,
-                        const float* u_resample, const gs_accept_out* out, void* workspace, hipStream_t stream,
-                        const void* row_stats, int n_stat_blocks);
+                        const float* u_resample, const gs_accept_out* out, void* workspace, size_t workspace_bytes,
+                        hipStream_t stream, const void* row_stats, int n_stat_blocks);
 int gemm_stat_blocks(int dtype, int M, int N, int K);
 gs_status launch_gemm_stats(const void* X, const void* W, float* Y, void* stats, int M, int N, int K,
                             hipStream_t stream);
-size_t accept_workspace_bytes(int n_servers, int n_rows, int vocab);
+size_t accept_min_bytes(int n_servers, int n_rows, int vocab);
 
 }  // namespace gs
 
@@ -91,6 +91,7 @@ struct Plan {
   int* attn_work;   // the step's (server, split) work list of the attention kernel
   int attn_work_capacity;
   void* accept_ws;
+  size_t accept_bytes;
   void* lm_stats;   // [R][column blocks] (max, sum exp) pairs from the LM-head projection's epilogue
   size_t bytes;
 };
@@ -139,9 +140,9 @@ Plan make_plan(const gs_ctx* ctx, int max_rows, int max_servers, int max_ctx, vo
   p.draft_tokens = c.take<int>(R);
   p.row_slot = c.take<int>(4 * R);
   p.rope = c.take<float>(R * m.head_dim);
-  size_t acc = 0;
-  for (int n = 1; n <= max_servers; ++n) acc = std::max(acc, gs::accept_workspace_bytes(n, max_rows, m.vocab));
-  p.accept_ws = c.take<char>(acc);
+  p.accept_bytes = 0;
+  for (int n = 1; n <= max_servers; ++n) p.accept_bytes = std::max(p.accept_bytes, gs::accept_min_bytes(n, max_rows, m.vocab));
+  p.accept_ws = c.take<char>(p.accept_bytes);
   p.lm_stats = c.take<float>(2 * R * (size_t)(m.vocab / 64 + 1));     // at least 64 columns per block
   p.bytes = c.used();
   return p;
@@ -485,7 +486,7 @@ extern "C" gs_status gs_verify_batch(gs_ctx* ctx, const gs_kv_cache* kv, const g
   }
   if (do_accept) {
     GS_STAGE(GS_STAGE_ACCEPT, gs::launch_accept(n, rows, b->cu_rows, m.vocab, GS_F32, logits, b->q_probs, p.draft_tokens,
-                                                b->u_accept, b->u_resample, out, p.accept_ws, stream,
+                                                b->u_accept, b->u_resample, out, p.accept_ws, p.accept_bytes, stream,
                                                 stat_blocks > 0 ? p.lm_stats : nullptr, stat_blocks));
   }
 #undef GS_STAGE

@@ -17,7 +17,7 @@ def _as_bf16(inp: synth.AcceptInputs):
                                q_probs=synth.round_to_bf16(inp.q_probs))
 
 
-def _run_gpu(inp: synth.AcceptInputs, want_ratio=True, offset_elems=0, pinned_out=False, bf16=False):
+def _run_gpu(inp: synth.AcceptInputs, want_ratio=True, offset_elems=0, pinned_out=False, bf16=False, ws_bytes=None):
     import torch
     from paper_2512_09963_amd import binding as gsb
     dev = torch.device("cuda:0")
@@ -45,7 +45,7 @@ def _run_gpu(inp: synth.AcceptInputs, want_ratio=True, offset_elems=0, pinned_ou
                for k, v in out.items()}
     for k in ("accepted_len", "next_token"):
         out[k].fill_(-7)
-    ws = torch.empty(gsb.gs_accept_workspace_bytes(n, R, V), dtype=torch.uint8, device=dev)
+    ws = torch.empty(ws_bytes or gsb.gs_accept_workspace_bytes(n, R, V), dtype=torch.uint8, device=dev)
     (gsb.gs_accept_reject_bf16 if bf16 else gsb.gs_accept_reject)(inp.gamma, cu, V, tl, q, toks, ua, ur, out, ws)
     torch.cuda.synchronize()
     return {k: (v.cpu().numpy() if v is not None else None) for k, v in out.items()}
@@ -191,3 +191,56 @@ def test_bf16_inputs_config2_full_size(sigma):
     bands = _check(inp, got)
     print(f"bf16 inputs, sigma={sigma}: mean accepted/gamma = {got['accepted_len'].mean() / 8:.3f}, bands = {bands}")
     assert bands["n_band_m"] + bands["n_band_tok"] <= 2
+
+
+@pytest.mark.parametrize("bf16", [False, True])
+@pytest.mark.parametrize("packs,extra", [(1024, 0), (1024, 1), (1023, 0), (2048, 0), (2049, 0), (5 * 1024 - 1, 0), (37 * 1024 + 1, 0)])
+def test_chunks_of_whole_steps(packs, extra, bf16):
+    """Rows that end on, just before and just after a step of the statistics kernel (1024 packs of 16 bytes); extra: an
+    element more, which takes the scalar loads.  The first half of one row is -infinity: chunks without mass."""
+    vocab = packs * (8 if bf16 else 4) + extra
+    gamma = np.array([2, 0, 66, 1] if packs <= 2049 else [2, 0, 1], dtype=np.int32)      # a block of more than 64 rows
+    inp = synth.accept_inputs(700 + packs + extra, gamma, vocab, 0.7)
+    inp.target_logits[1, :vocab // 2] = -np.inf
+    if bf16:
+        inp = _as_bf16(inp)
+    bands = _check(inp, _run_gpu(inp, bf16=bf16))
+    assert bands["n_band_m"] + bands["n_band_tok"] <= 1
+
+
+@pytest.mark.parametrize("n,vocab", [(4, 262144), (5, 262144),         # 512 and 640 tiles: one and four tiles per workgroup
+                                     (1, 2048), (1, 2049), (2, 524288), (2, 524292)])    # 1, 2, 256 and 257 tiles per row
+@pytest.mark.parametrize("where", ["spread", "ends", "last"])
+def test_draw_over_tiles(n, vocab, where):
+    """The drawn token over the tile counts at which the draw and the pick take another path; mass everywhere, in the first
+    and last tokens only, or in the last token only."""
+    inp = synth.accept_inputs(800 + n, np.ones(n, dtype=np.int32), vocab, 0.5)
+    if where != "spread":
+        keep = np.zeros(vocab, bool)
+        keep[-1] = True
+        if where == "ends":
+            keep[:3] = keep[vocab // 2] = True
+        inp.target_logits[:, ~keep] = -np.inf
+    inp.u_accept[:] = np.where(np.arange(n) % 2 == 0, 1.5, inp.u_accept)      # every other server rejects: residual draws
+    inp.u_resample[:] = np.array([0.0, 0.5, 1.0 - 2.0 ** -24, 0.25, 0.75], np.float32)[:n]
+    got = _run_gpu(inp)
+    bands = _check(inp, got)
+    assert bands["n_band_m"] + bands["n_band_tok"] <= (2 if where == "spread" else 0)
+    if where == "last":
+        np.testing.assert_array_equal(got["next_token"], vocab - 1)
+
+
+def test_workspace_sized_for_the_coarse_chunks():
+    """A workspace that holds only one pair per 4096 tokens, as one sized for a larger batch does: taken, with the coarse
+    chunks; a byte less is refused before anything is launched."""
+    from paper_2512_09963_amd import binding as gsb
+    vocab, gamma = 40000, np.full(10, 3, dtype=np.int32)
+    inp = synth.accept_inputs(900, gamma, vocab, 1.0)
+    up = lambda b: -(-b // 256) * 256
+    coarse = up(40 * 9 * 8) + up(10 * 16) + up(10 * -(-vocab // 2048) * 8)
+    assert coarse < gsb.gs_accept_workspace_bytes(10, 40, vocab)
+    bands = _check(inp, _run_gpu(inp, ws_bytes=coarse))
+    assert bands["n_band_m"] + bands["n_band_tok"] <= 1
+    with pytest.raises(gsb.GsError) as e:
+        _run_gpu(inp, ws_bytes=coarse - 1)
+    assert e.value.code == -3
