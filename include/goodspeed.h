@@ -199,7 +199,8 @@ gs_status gs_pack_weight(const void* w_rowmajor /* dev */, void* w_packed /* dev
  * 4-bit projection weights for GS_W4 models (weight-only quantisation in groups of 128 inputs, the format
  * family of the AWQ checkpoints of the paper's 70B verifier, Section IV-A):
  *   W[n][k] = (code[n][k] - zero[n][k/128]) * scale[n][k/128],  codes and zeros in 0..15, scales bf16;
- * every dequantised weight is rounded to bf16 (nearest even) before it enters the product.
+ * every dequantised weight is rounded to bf16 (nearest even) before it enters the product.  Scales of a magnitude
+ * below 2^117 (the dequantisation carries 1024 of them).
  * gs_pack_weight_w4 turns the three arrays into the layout the projection kernel streams
  * (gs_w4_packed_bytes bytes: the codes tile-packed like the bf16 weights, then one word of scale and zero
  * per column and group).  k_in must be a multiple of 128, n_out of 64.
@@ -300,7 +301,8 @@ gs_status gs_check_batch(const gs_ctx* ctx, const gs_kv_cache* kv, const gs_batc
  * N contexts of different length) that gs_verify_batch would use for a batch of this geometry.  n_kv_heads,
  * group = query heads per KV head; gamma_host, ctx_len_host: host, [n_servers].  Out: steps_per_split = the
  * longest run of 32-key steps one workgroup takes (a server with s steps is cut into ceil(s / steps_per_split)
- * splits of equal length up to one step); n_workgroups = (server, split, KV head) items of the launch;
+ * splits of equal length up to one step); n_workgroups = (server, query group, split, KV head) items of the launch (a
+ * block of up to 8 waves of query rows is one group, longer ones are cut into groups);
  * busiest_cu_steps = the most steps any of the 256 compute units is dealt.  GS_EINVAL on negative entries. */
 gs_status gs_plan_attention(int n_kv_heads, int group, int n_servers, const int* gamma_host,
                             const int* ctx_len_host, int* steps_per_split, long* n_workgroups,

@@ -515,7 +515,7 @@ constexpr int kGroupWaves = 4;
 void attention_groups(int group, int max_block_tokens, int* waves, int* group_tokens) {
   const int tiles = ceil_div(max_block_tokens * group, 32);
   *waves = tiles > kMaxWaves ? kGroupWaves : tiles > 0 ? tiles : 1;
-  *group_tokens = *waves * 32 / group;      // (32 is a multiple of the group size)
+  *group_tokens = std::max(1, *waves * 32 / group);      // (a batch has groups of 1, 2, 4 or 8: 32 is a multiple of them)
 }
 
 // Calls f(steps) for every (server, query group): its number of 32-key steps.

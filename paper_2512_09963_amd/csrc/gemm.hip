@@ -1,8 +1,9 @@
 // Dense projections Y = X * W^T of the decoder (QKV, O, gate/up, down, LM head).
 //
 // bf16 path (MFMA): the verify step has few rows (tens to a few hundred) against
-// matrices of 10^7..10^9 weights, so every weight byte is used by only M rows: the kernel
-// is a weight-streaming kernel bound by HBM, and the layout serves the stream:
+// matrices of 10^7..10^9 weights, so every weight byte is used by only M rows: the kernels
+// are weight-streaming kernels bound by HBM, and the layout serves the stream.  Most shapes go to the pipelined
+// kernel of gemm_wide.hip (same packed weights); the one here serves what GemmPlan says:
 //   * the weights are stored tile-packed (gs_pack_weight): the 2 KB that one wavefront needs
 //     per 64-wide k step for its 16 output columns is contiguous, and the blocks are ordered
 //     [k_step][n_tile][half][lane][8 bf16]: at one k step the blocks of neighbouring column tiles
@@ -11,7 +12,7 @@
 //     copy, which keeps DRAM pages open) instead of thousands of unrelated 2 KB pieces.  Each
 //     wave issues two fully coalesced 1 KB loads per step, straight into the MFMA B operand (no
 //     LDS hop for weights); DEPTH steps are kept in flight
-//   * the activations (all M rows of the k step, at most 128) are staged once per workgroup
+//   * the activations (the rows of a chunk, at most 128) are staged once per workgroup
 //     in LDS (padded rows: conflict-free 16-byte reads) and shared by the four waves; their
 //     global loads run DEPTH steps ahead as well, so a step never waits on the L2 round trip
 //   * K is split across workgroups when N alone gives too few of them to fill 256 CUs; the
@@ -377,8 +378,8 @@ static void launch_skinny(const GemmPlan& p, const bf16_t* x, const bf16_t* w, f
 #undef GS_SKINNY
 }
 
-// Whether the gate/up projection of this shape runs with the SwiGLU fused: 4-bit where its kernel does, bf16, and either up to 64 rows or
-// a shape whose kernel needs no K split anyway.
+// Whether the gate/up projection of this shape runs with the SwiGLU fused: 4-bit where its kernel does; bf16 up to 64 rows
+// and where the kernel needs no K split anyway.
 bool gate_up_fused(int dtype, int M, int F, int K) {
   if (dtype == GS_W4) return M > 0 && w4_gate_up_fused(M, F);
   if (dtype != GS_BF16 || M <= 0 || F % 64 != 0 || K % kBK != 0) return false;

@@ -174,3 +174,12 @@ def test_attention_plan_of_the_measured_workloads():
     assert items == 8 * -(-4097 // sps) and items <= 32 * 8
     with pytest.raises(gsb.GsError):
         gsb.gs_plan_attention(8, 4, [-1], [10])
+
+
+@pytest.mark.parametrize("group", [1, 3, 8, 40, 200, 300, 5000])
+def test_attention_plan_of_any_group_size(group):
+    """The planner is asked for geometries that no batch has (groups that do not divide 32, or exceed all query rows of a
+    workgroup): it answers with a plan of at least one item per server and KV head."""
+    gamma, ctx = [0, 8, 300], [1000, 0, 50]
+    sps, items, busiest = gsb.gs_plan_attention(2, group, gamma, ctx)
+    assert 1 <= sps <= 32 and items >= 2 * len(gamma) and busiest >= sps
