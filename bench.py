@@ -24,20 +24,22 @@ HBM_PEAK_GBS = 8000.0
 MFMA_BF16_PEAK_TFLOPS = 2500.0   # dense bf16
 
 # HBM bytes per projection launch from the FETCH_SIZE / WRITE_SIZE counter runs summarised in
-# profiles/hbm_traffic_counters.md (121.79 MB fetched + 5.34 MB written, scaled by the copy-kernel factors
-# given there).  Valid only for the kernel source it was taken with: reported as null once gemm.hip changes.
-GEMM_TRAFFIC = {"gemm_hip_sha256": "def0d05baaf8661cf2cf8a42697f8573210332859236e6e404e9fda1c04617e1",
-                "bytes_per_launch": 127128302}
+# profiles/hbm_traffic_counters.md (123.31 MB fetched + 5.34 MB written, scaled by the copy-kernel factors
+# given there).  Valid only for the kernel sources it was taken with: reported as null once they change.
+GEMM_SOURCES = ("gemm_common.h", "gemm.hip", "gemm_wide.hip")
+GEMM_TRAFFIC = {"sources_sha256": "897c97c48342dfc9d4608b1a33e4c8a8bc45c3329b56cf8848180eda0cc15ce9",
+                "bytes_per_launch": 128650268}
 
 
 def measured_traffic():
     import hashlib
-    src = os.path.join(ROOT, "paper_2512_09963_amd", "csrc", "gemm.hip")
+    h = hashlib.sha256()
     try:
-        h = hashlib.sha256(open(src, "rb").read()).hexdigest()
+        for name in GEMM_SOURCES:
+            h.update(open(os.path.join(ROOT, "paper_2512_09963_amd", "csrc", name), "rb").read())
     except OSError:
         return None
-    return GEMM_TRAFFIC["bytes_per_launch"] if h == GEMM_TRAFFIC["gemm_hip_sha256"] else None
+    return GEMM_TRAFFIC["bytes_per_launch"] if h.hexdigest() == GEMM_TRAFFIC["sources_sha256"] else None
 
 
 def parse():
