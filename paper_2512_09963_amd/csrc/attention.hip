@@ -22,7 +22,6 @@
 #include "device_types.h"
 #include <algorithm>
 #include <cmath>
-#include <limits>
 
 namespace gs {
 namespace {
@@ -542,32 +541,33 @@ long attention_max_groups(int max_rows, int max_servers) { return (long)max_serv
 
 // The most 32-key steps any compute unit is dealt when every group's steps are cut into splits of at most t
 // steps: item_of_workgroup's serpentine over the (server, group, split, KV head) items in the order of decreasing
-// length, which is the order of the work list.  items: their number.  Splits of 2047 steps and more are not
-// modelled (the histogram lives on the stack): the largest long.
+// length, which is the order of the work list.  items: their number.  The histogram of lengths lives on the stack: splits
+// of 2047 steps and more are counted in units of 2, 4, ... steps, rounded up.
 long attention_busiest_cu(int n_kv, int n_servers, const int* gamma_host, const int* ctx_len_host, int group_tokens,
                           long t, long* items_out) {
   constexpr long kCus = kComputeUnits, kMaxLen = 2048;
   long n_of_len[kMaxLen] = {0};
   long items = 0;
+  int shift = 0;
+  while ((t >> shift) + 2 > kMaxLen) ++shift;
+  auto units = [&](long len) { return (len + (1L << shift) - 1) >> shift; };
   for_each_group(n_servers, gamma_host, ctx_len_host, group_tokens, [&](long st) {
     const long n = (st + t - 1) / t;
     const long base = st / n, rem = st - base * n;
     items += n * n_kv;
-    if (t + 2 > kMaxLen) return;
-    n_of_len[base + 1] += rem * n_kv;
-    n_of_len[base] += (n - rem) * n_kv;
+    if (rem > 0) n_of_len[units(base + 1)] += rem * n_kv;
+    n_of_len[units(base)] += (n - rem) * n_kv;
   });
   if (items_out) *items_out = items;
-  if (t + 2 > kMaxLen) return std::numeric_limits<long>::max();
   const long rounds = (items + kCus - 1) / kCus;
   long load[kCus] = {0};
   long pos = 0;
-  for (long len = t + 1; len >= 1; --len)
+  for (long len = units(t); len >= 1; --len)
     for (long k = 0; k < n_of_len[len]; ++k, ++pos) {
       const long round = pos / kCus, c = pos - round * kCus;
       load[((rounds - 1 - round) & 1) ? kCus - 1 - c : c] += len;
     }
-  return *std::max_element(load, load + kCus);
+  return *std::max_element(load, load + kCus) << shift;
 }
 
 // KV steps (32 keys) per split, and the resulting largest split count, for a batch of n_servers servers with
@@ -610,13 +610,14 @@ void attention_plan(int n_kv, int group, int max_block_tokens, int n_servers, co
       if (workgroups(mid) <= fit) b = mid; else a = mid + 1;
     }
     sps = a;
-    // ... unless splits up to half longer load the busiest compute unit clearly less (a compute unit's
+    // ... unless splits up to half longer than the best so far load the busiest compute unit clearly less (a compute unit's
     // finishing time follows the steps it is dealt): 3 x 22 instead of 4 x 19 steps at the 70B shape with 16
     // servers (5.3 against 5.6 ms of attention per step).  Small differences do not pay for the workgroups that
     // are then missing per compute unit (8 servers at 2048 tokens: 2 x 9 steps on 512 workgroups took 17.1 us
     // per layer, 3 x 6 on 704 take 15.1), hence the margin of 8 %.
+    const long stride = std::max(1L, sps / 1024);      // (at most a thousand candidates or so, however long the contexts)
     long best = attention_busiest_cu(n_kv, n_servers, gamma_host, ctx_len_host, group_tokens, sps, nullptr);
-    for (long t = sps + 1; t <= sps + sps / 2 && t <= max_steps; ++t) {
+    for (long t = sps + 1; t <= sps + sps / 2 && t <= max_steps; t += stride) {
       const long l = attention_busiest_cu(n_kv, n_servers, gamma_host, ctx_len_host, group_tokens, t, nullptr);
       if (l * 100 < best * 92) {
         best = l;

@@ -176,6 +176,21 @@ def test_attention_plan_of_the_measured_workloads():
         gsb.gs_plan_attention(8, 4, [-1], [10])
 
 
+@pytest.mark.parametrize("n,ctx", [(64, 131000), (48, 100000), (40, 200000)])
+def test_attention_plan_of_very_long_contexts(n, ctx):
+    """Splits of 2047 steps and more: their load is modelled too (in units of a few steps), so that as many splits are made
+    as fit the chip at once, here two or three per server on 720 or more slots."""
+    sps, items, busiest = gsb.gs_plan_attention(8, 4, [4] * n, [ctx] * n)
+    steps = -(-(ctx + 5) // 32)
+    want_items, want_busiest = _serpentine_busiest([steps] * n, sps, 8)
+    assert items == want_items == n * 8 * -(-steps // sps) and items >= 2 * n * 8
+    unit = 1
+    while sps // unit + 2 > 2048:
+        unit *= 2
+    rounds = -(-items // 256)
+    assert want_busiest <= busiest < want_busiest + rounds * unit
+
+
 @pytest.mark.parametrize("group", [1, 3, 8, 40, 200, 300, 5000])
 def test_attention_plan_of_any_group_size(group):
     """The planner is asked for geometries that no batch has (groups that do not divide 32, or exceed all query rows of a
