@@ -511,9 +511,9 @@ __global__ void attn_combine_kernel(const float* __restrict__ partial_o, const f
 // 8 prompts of 128 tokens: 30 us and 14 us, now 14 us.)
 constexpr int kMaxWaves = 8;
 constexpr int kGroupWaves = 4;
-void attention_groups(int group, int max_block_tokens, int* waves, int* group_tokens) {
-  const int tiles = ceil_div(max_block_tokens * group, 32);
-  *waves = tiles > kMaxWaves ? kGroupWaves : tiles > 0 ? tiles : 1;
+void attention_groups(int group, long max_block_tokens, int* waves, int* group_tokens) {
+  const long tiles = (max_block_tokens * group + 31) / 32;
+  *waves = tiles > kMaxWaves ? kGroupWaves : tiles > 0 ? (int)tiles : 1;
   *group_tokens = std::max(1, *waves * 32 / group);      // (a batch has groups of 1, 2, 4 or 8: 32 is a multiple of them)
 }
 
@@ -521,9 +521,8 @@ void attention_groups(int group, int max_block_tokens, int* waves, int* group_to
 template <typename F>
 static void for_each_group(int n_servers, const int* gamma_host, const int* ctx_len_host, int group_tokens, F f) {
   for (int i = 0; i < n_servers; ++i) {
-    const int T = gamma_host[i] + 1;
-    for (int t0 = 0; t0 < T; t0 += group_tokens)
-      f(((long)ctx_len_host[i] + std::min(T, t0 + group_tokens) + 31) / 32);
+    const long T = gamma_host[i] + 1L;
+    for (long t0 = 0; t0 < T; t0 += group_tokens) f((ctx_len_host[i] + std::min(T, t0 + group_tokens) + 31) / 32);
   }
 }
 
@@ -578,7 +577,7 @@ long attention_busiest_cu(int n_kv, int n_servers, const int* gamma_host, const 
 // results few; a floor on the steps per split bounds what the partial results cost on small batches.
 // Prompt blocks whose unsplit groups already give every compute unit a workgroup are not split at all: they are
 // bound by arithmetic, the serpentine deals long and short groups evenly, and splits would only add partial results.
-void attention_plan(int n_kv, int group, int max_block_tokens, int n_servers, const int* gamma_host,
+void attention_plan(int n_kv, int group, long max_block_tokens, int n_servers, const int* gamma_host,
                     const int* ctx_len_host, int* steps_per_split, int* max_splits) {
   int waves, group_tokens;
   attention_groups(group, max_block_tokens, &waves, &group_tokens);

@@ -30,9 +30,9 @@ gs_status launch_rope_append(int dtype, const float* qkv, int n_splits, int n_ro
                              const void* rope, int page_size, int n_heads, int n_kv, int hd, void* q_out,
                              void* k_pages, void* v_pages, hipStream_t stream);
 gs_status launch_swiglu(int dtype, const float* gu, int n_splits, int n_rows, int F, void* act, hipStream_t stream);
-void attention_plan(int n_kv, int group, int max_block_tokens, int n_servers, const int* gamma_host,
+void attention_plan(int n_kv, int group, long max_block_tokens, int n_servers, const int* gamma_host,
                     const int* ctx_len_host, int* steps_per_split, int* max_splits);
-void attention_groups(int group, int max_block_tokens, int* waves, int* group_tokens);
+void attention_groups(int group, long max_block_tokens, int* waves, int* group_tokens);
 long attention_items(int n_servers, const int* gamma_host, const int* ctx_len_host, int group_tokens, int steps_per_split);
 long attention_max_groups(int max_rows, int max_servers);
 long attention_busiest_cu(int n_kv, int n_servers, const int* gamma_host, const int* ctx_len_host, int group_tokens,
@@ -536,11 +536,11 @@ extern "C" gs_status gs_plan_attention(int n_kv_heads, int group, int n_servers,
                                        long* busiest_cu_steps) {
   if (n_kv_heads <= 0 || group <= 0 || n_servers <= 0 || !gamma_host || !ctx_len_host || !steps_per_split)
     return gs::fail(GS_EINVAL, "gs_plan_attention: bad argument");
-  int max_t = 0;
+  long max_t = 0;
   for (int i = 0; i < n_servers; ++i) {
     if (gamma_host[i] < 0 || ctx_len_host[i] < 0)
       return gs::fail(GS_EINVAL, "server %d: gamma = %d, ctx_len = %d", i, gamma_host[i], ctx_len_host[i]);
-    max_t = std::max(max_t, gamma_host[i] + 1);
+    max_t = std::max(max_t, gamma_host[i] + 1L);
   }
   int sps = 1, splits = 1, waves = 1, group_tokens = 1;
   gs::attention_groups(group, max_t, &waves, &group_tokens);

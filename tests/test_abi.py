@@ -191,6 +191,15 @@ def test_attention_plan_of_very_long_contexts(n, ctx):
     assert want_busiest <= busiest < want_busiest + rounds * unit
 
 
+@pytest.mark.parametrize("gamma,ctx,items", [(2 ** 31 - 1, 5, 2 ** 26), (2 ** 31 - 2, 5, 2 ** 26), (2 ** 31 - 1, 2 ** 31 - 1, 2 ** 26),
+                                             (2 ** 30, 0, 2 ** 25 + 1)])
+def test_attention_plan_of_the_largest_blocks(gamma, ctx, items):
+    """Blocks and contexts at the end of the integer range (no batch has them): the planner answers, with one item per query
+    group of 32 tokens and KV head."""
+    sps, got, busiest = gsb.gs_plan_attention(1, 4, [gamma], [ctx])
+    assert got == items and sps == -(-(ctx + gamma + 1) // 32) and busiest >= sps
+
+
 @pytest.mark.parametrize("group", [1, 3, 8, 40, 200, 300, 5000])
 def test_attention_plan_of_any_group_size(group):
     """The planner is asked for geometries that no batch has (groups that do not divide 32, or exceed all query rows of a
