@@ -14,7 +14,7 @@
 // group; prompt blocks are cut into groups of 4 waves, each with the keys up to its own last row.  The number of
 // KV splits of a group follows its own key count (a fixed number of 32-key steps per
 // workgroup), so ragged batches stay balanced.  Partial results of the splits are merged by
-// attn_combine_kernel; where no group is split the kernel stores the final result itself.
+// attn_combine_kernel; the result of a group that is not split is final and stored by the kernel itself.
 //
 // fp32 path: one workgroup per (row, head), lanes over keys, online softmax per lane.
 #include "common.h"
@@ -449,7 +449,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NW == 1
 
   // ---- lane l holds query row l%32, channels 32 dt + 8 b + 4 h + (0..3)
   if (!my_ok) return;
-  if (attn_out) {      // no group of the launch is split: the result is final
+  if (n_splits == 1) {      // the group is not split: the result is final
     bf16_t* dst = attn_out + ((size_t)(row0 + my_j) * n_heads + kh * G + my_hg) * HD + 4 * h;
 #pragma unroll
     for (int dt = 0; dt < DT; ++dt)
@@ -475,7 +475,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NW == 1
 }
 
 // attn_out[r][h*HD + d] = sum_s o_s * 2^(m_s - M) / sum_s l_s * 2^(m_s - M) over the splits of the row's query
-// group.  grid (R*H), block HD.
+// group; the rows of a group that is not split are final already.  grid (R*H), block HD.
 template <int HD>
 __global__ void attn_combine_kernel(const float* __restrict__ partial_o, const float* __restrict__ partial_ml,
                                     int max_splits, int steps_per_split, const int4* __restrict__ row_info,
@@ -484,6 +484,7 @@ __global__ void attn_combine_kernel(const float* __restrict__ partial_o, const f
   const int d = threadIdx.x;
   const int n_keys = row_info[rh / n_heads].z;      // keys of the row's query group (per-row table of the step)
   const int n_splits = (((n_keys + 31) >> 5) + steps_per_split - 1) / steps_per_split;
+  if (n_splits == 1) return;
   // one pass with a running maximum, so that no load waits for the maximum over all splits
   const float2* ml = reinterpret_cast<const float2*>(partial_ml) + rh * max_splits;
   const float* po = partial_o + rh * max_splits * HD + d;
@@ -517,12 +518,15 @@ void attention_groups(int group, long max_block_tokens, int* waves, int* group_t
   *group_tokens = std::max(1, *waves * 32 / group);      // (a batch has groups of 1, 2, 4 or 8: 32 is a multiple of them)
 }
 
-// Calls f(steps) for every (server, query group): its number of 32-key steps.
+// Calls f(steps, tokens) for every (server, query group): its number of 32-key steps and of tokens.
 template <typename F>
 static void for_each_group(int n_servers, const int* gamma_host, const int* ctx_len_host, int group_tokens, F f) {
   for (int i = 0; i < n_servers; ++i) {
     const long T = gamma_host[i] + 1L;
-    for (long t0 = 0; t0 < T; t0 += group_tokens) f((ctx_len_host[i] + std::min(T, t0 + group_tokens) + 31) / 32);
+    for (long t0 = 0; t0 < T; t0 += group_tokens) {
+      const long t1 = std::min(T, t0 + group_tokens);
+      f((ctx_len_host[i] + t1 + 31) / 32, t1 - t0);
+    }
   }
 }
 
@@ -530,7 +534,7 @@ static void for_each_group(int n_servers, const int* gamma_host, const int* ctx_
 long attention_items(int n_servers, const int* gamma_host, const int* ctx_len_host, int group_tokens, int steps_per_split) {
   long n = 0;
   for_each_group(n_servers, gamma_host, ctx_len_host, group_tokens,
-                 [&](long st) { n += (st + steps_per_split - 1) / steps_per_split; });
+                 [&](long st, long) { n += (st + steps_per_split - 1) / steps_per_split; });
   return n;
 }
 
@@ -550,7 +554,7 @@ long attention_busiest_cu(int n_kv, int n_servers, const int* gamma_host, const 
   int shift = 0;
   while ((t >> shift) + 2 > kMaxLen) ++shift;
   auto units = [&](long len) { return (len + (1L << shift) - 1) >> shift; };
-  for_each_group(n_servers, gamma_host, ctx_len_host, group_tokens, [&](long st) {
+  for_each_group(n_servers, gamma_host, ctx_len_host, group_tokens, [&](long st, long) {
     const long n = (st + t - 1) / t;
     const long base = st / n, rem = st - base * n;
     items += n * n_kv;
@@ -569,14 +573,46 @@ long attention_busiest_cu(int n_kv, int n_servers, const int* gamma_host, const 
   return *std::max_element(load, load + kCus) << shift;
 }
 
+// The split length for query groups that fill the chip.  On contexts of one length the serpentine deals the unsplit groups
+// evenly, and splits would only add partial results.  On unequal contexts the longest groups would run on when the rest of the
+// chip is done.  Fitted over batches of both kinds (261 to 2047 rows, contexts of 0 to 131000 tokens, the longest group in 1 to
+// 32 splits), a launch and its merge take 20 us + 0.91 us per step of the busiest compute unit + 6.3 us per split of 128 rows and
+// compute unit (its partial result).  So: the split count of the longest group, 2 .. 32, with the least steps + 7 x partial
+// results, unless that gains less than 8 % over none.  8 KV heads, group 4, us per layer unsplit and as chosen:
+// 8 x 128 tokens on 1 .. 1024 cached 57 and 35, 7 x 128 on none and 128 on 8192 cached 336 and 67, 1024 on none and 5 rows on
+// 16384 562 and 68, 256 on none and 24 x 5 rows on 8192 280 and 149.
+static long group_steps_per_split(int n_kv, int n_servers, const int* gamma_host, const int* ctx_len_host, int group_tokens,
+                                  long shortest, long max_steps) {
+  constexpr long kPartialSteps = 7;
+  // in units of 1 / (compute units x tokens of a group) steps
+  auto cost = [&](long t) {
+    long partial_tokens = 0;
+    for_each_group(n_servers, gamma_host, ctx_len_host, group_tokens, [&](long st, long tokens) {
+      const long n = (st + t - 1) / t;
+      if (n > 1) partial_tokens += n * tokens;
+    });
+    return attention_busiest_cu(n_kv, n_servers, gamma_host, ctx_len_host, group_tokens, t, nullptr) * kComputeUnits * group_tokens +
+           kPartialSteps * n_kv * partial_tokens;
+  };
+  const long unsplit = cost(max_steps);
+  long best = unsplit, sps = max_steps;
+  for (long k = 2; k <= 32 && (max_steps + k - 1) / k >= shortest; ++k) {
+    const long t = (max_steps + k - 1) / k, c = cost(t);
+    if (c < best && c < unsplit / 100 * 92) {
+      best = c;
+      sps = t;
+    }
+  }
+  return sps;
+}
+
 // KV steps (32 keys) per split, and the resulting largest split count, for a batch of n_servers servers with
 // the given draft lengths and contexts and blocks of at most max_block_tokens rows.  A group's steps
 // are cut into ceil(steps / steps_per_split) splits of equal length up to one step.  All workgroups of the
 // launch should be resident at once (they share the memory bandwidth; a second round starts with the chip
 // half empty: measured on the 70B shape, 5.9 instead of 6.7 ms per step), which also keeps the partial
 // results few; a floor on the steps per split bounds what the partial results cost on small batches.
-// Prompt blocks whose unsplit groups already give every compute unit a workgroup are not split at all: they are
-// bound by arithmetic, the serpentine deals long and short groups evenly, and splits would only add partial results.
+// Prompt blocks whose unsplit groups already give every compute unit a workgroup: see group_steps_per_split.
 void attention_plan(int n_kv, int group, long max_block_tokens, int n_servers, const int* gamma_host,
                     const int* ctx_len_host, int* steps_per_split, int* max_splits) {
   int waves, group_tokens;
@@ -585,7 +621,7 @@ void attention_plan(int n_kv, int group, long max_block_tokens, int n_servers, c
   const int wgs_per_cu = kWavesPerCu / waves < 5 ? (kWavesPerCu / waves > 0 ? kWavesPerCu / waves : 1) : 5;   // 5 workgroups by LDS
   const long slots = (long)kComputeUnits * wgs_per_cu;
   long total_steps = 0, max_steps = 1, n_groups = 0;
-  for_each_group(n_servers, gamma_host, ctx_len_host, group_tokens, [&](long st) {
+  for_each_group(n_servers, gamma_host, ctx_len_host, group_tokens, [&](long st, long) {
     total_steps += st;
     max_steps = std::max(max_steps, st);
     n_groups += 1;
@@ -600,7 +636,9 @@ void attention_plan(int n_kv, int group, long max_block_tokens, int n_servers, c
   const long fit = slots - slots / 16;                    // all resident at once, with some slack for placement
   long sps;
   if (n_groups > n_servers && n_groups * n_kv >= kComputeUnits) {
-    sps = max_steps;
+    // (beyond 2^17 groups, hundreds per compute unit, a search would take longer than it gains)
+    sps = n_groups > (1L << 17) ? max_steps
+                                : group_steps_per_split(n_kv, n_servers, gamma_host, ctx_len_host, group_tokens, lo, max_steps);
   } else if (workgroups(max_steps) <= fit) {
     // the shortest splits whose workgroups are all resident at once ...
     long a = lo, b = max_steps;
@@ -701,8 +739,8 @@ gs_status launch_attention(int dtype, const void* q, const void* k_pages, const 
 #define GS_ATTN_CASE(HD_, G_)                                                                                     \
   if (hd == HD_ && G == G_)                                                                                       \
     st = launch_mfma_g<HD_, G_>(qb, kb, vb, block_table, max_blocks, work, n_work, page_size, n_heads, n_kv,     \
-                                waves, steps_per_split, max_splits, po, pml,                                       \
-                                split ? nullptr : static_cast<bf16_t*>(attn_out), stream);
+                                waves, steps_per_split, max_splits, po, pml, static_cast<bf16_t*>(attn_out),       \
+                                stream);
   GS_ATTN_CASE(128, 1) GS_ATTN_CASE(128, 2) GS_ATTN_CASE(128, 4) GS_ATTN_CASE(128, 8)
   GS_ATTN_CASE(64, 1) GS_ATTN_CASE(64, 2) GS_ATTN_CASE(64, 4) GS_ATTN_CASE(64, 8)
 #undef GS_ATTN_CASE

@@ -176,6 +176,30 @@ def test_attention_plan_of_the_measured_workloads():
         gsb.gs_plan_attention(8, 4, [-1], [10])
 
 
+@pytest.mark.parametrize("gamma,ctx", [
+    ([127] * 8, [1, 2, 7, 19, 52, 141, 380, 1024]),
+    ([127] * 8, [0] * 7 + [4096]),
+    ([127] * 8, [0] * 7 + [8192]),
+    ([255] * 4, [0, 0, 0, 4096]),
+    ([1023, 4], [0, 16384]),
+    ([1023, 4], [0, 131000]),
+    ([255] + [4] * 24, [0] + [8192] * 24),
+])
+def test_attention_plan_of_prompts_on_unequal_contexts(gamma, ctx):
+    """Prompt blocks beside long contexts (8 KV heads, group 4: query groups of 32 tokens): the busiest compute unit stays
+    near the mean, and no group has more than 32 splits."""
+    sps, items, busiest = gsb.gs_plan_attention(8, 4, gamma, ctx)
+    steps = [-(-(c + min(g + 1, t + 32)) // 32) for g, c in zip(gamma, ctx) for t in range(0, g + 1, 32)]
+    assert (items, busiest) == _serpentine_busiest(steps, sps, 8)
+    assert 6 <= sps and -(-max(steps) // sps) <= 32
+    assert busiest <= 1.5 * sum(steps) * 8 / 256
+
+
+@pytest.mark.parametrize("gamma,ctx,sps", [([127] * 8, [0] * 8, 4), ([2046], [0], 64), ([127] * 8, [512] * 8, 20)])
+def test_attention_plan_of_prompts_on_equal_contexts_is_unsplit(gamma, ctx, sps):
+    assert gsb.gs_plan_attention(8, 4, gamma, ctx)[:2] == (sps, 8 * sum((g + 32) // 32 for g in gamma))
+
+
 @pytest.mark.parametrize("n,ctx", [(64, 131000), (48, 100000), (40, 200000)])
 def test_attention_plan_of_very_long_contexts(n, ctx):
     """Splits of 2047 steps and more: their load is modelled too (in units of a few steps), so that as many splits are made

@@ -175,8 +175,11 @@ def test_bf16_projections_with_256_columns_per_workgroup(rows):
     (4, 1, 128, [64, 2, 127, 0], [0, 500, 77, 33], 16),
     (8, 1, 64, [47, 48, 31, 15], [700, 0, 16, 1500], 32),
     (2, 2, 64, [256, 258, 5], [31, 0, 1025], 16),
-    # enough groups for every compute unit: nothing is split, the kernel stores the result itself
+    # enough groups for every compute unit beside a longer context: some groups are split, the kernel stores the others
     (64, 8, 64, [511, 3], [0, 900], 64),
+    (64, 8, 64, [255, 200, 2], [0, 31, 2500], 16),
+    # the same on equal contexts: nothing is split
+    (64, 8, 64, [255, 270], [100, 90], 32),
 ])
 def test_bf16_prompt_blocks_in_query_groups(heads, n_kv, hd, gamma, ctx, page):
     ms = synth.ModelShape(1, 128, heads, n_kv, hd, 256, 1024, 10000.0, dtype="bf16")
