@@ -199,8 +199,7 @@ gs_status gs_pack_weight(const void* w_rowmajor /* dev */, void* w_packed /* dev
  * 4-bit projection weights for GS_W4 models (weight-only quantisation in groups of 128 inputs, the format
  * family of the AWQ checkpoints of the paper's 70B verifier, Section IV-A):
  *   W[n][k] = (code[n][k] - zero[n][k/128]) * scale[n][k/128],  codes and zeros in 0..15, scales bf16;
- * every dequantised weight is rounded to bf16 (nearest even) before it enters the product.  Scales of a magnitude
- * below 2^117 (the dequantisation carries 1024 of them).
+ * every dequantised weight is rounded to bf16 (nearest even) before it enters the product.
  * gs_pack_weight_w4 turns the three arrays into the layout the projection kernel streams
  * (gs_w4_packed_bytes bytes: the codes tile-packed like the bf16 weights, then one word of scale and zero
  * per column and group).  k_in must be a multiple of 128, n_out of 64.

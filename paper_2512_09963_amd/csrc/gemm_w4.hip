@@ -19,6 +19,7 @@
 #include "common.h"
 #include "device_types.h"
 #include <algorithm>
+#include <type_traits>
 
 namespace gs {
 namespace {
@@ -32,16 +33,23 @@ typedef __attribute__((__vector_size__(16 * sizeof(float)))) float floatx16_t;
 // 1024 is the half-precision number 1024 + c (even nibble) or 1024 + 16 c (odd nibble), two to a word, and the
 // mixed-precision fma reads either half: (1024 + c) * scale - (1024 + z) * scale = (c - z) * scale, exact in fp32
 // (11 x 8 significant bits, one rounding at the end, which has nothing to round).  17 instructions per 8 codes
-// (23 with byte conversions).  Scales of 2^117 and more overflow the constant term.
+// (23 with byte conversions).  The constant term of a scale of kLargeScale and more may overflow: such groups are rare enough
+// that a wave which meets one goes on in a second loop that repairs their weights (dequant8_large), b holding the zero point
+// instead.  (8 layers of the 8B shape at 53 rows: this and its check of every scale group cost 0.1 to 0.4 % of the step, a branch
+// between any two blocks of the one loop 1.5 %; a choice between two bodies per step spills.)
+// (The 1024 trick is that of Kim et al., "Who Says Elephants Can't Run: Bringing Large Scale MoE Models into Cloud Scale
+// Production", 2022.)
 typedef _Float16 half2_vec __attribute__((ext_vector_type(2)));
+constexpr float kLargeScale = 0x1p117f;
 struct DequantScale {
   float s, b, s16, b16;
 };
+__device__ __forceinline__ bool large(const DequantScale& d) { return !(fabsf(d.s) < kLargeScale); }
 __device__ __forceinline__ DequantScale dequant_scale(uint32_t meta) {
   DequantScale d;
   const float z = (float)(meta & 0xffu);
   d.s = __uint_as_float(meta & 0xffff0000u);
-  d.b = -(1024.0f + z) * d.s;
+  d.b = large(d) ? z : -(1024.0f + z) * d.s;
   d.s16 = d.s * 0.0625f;
   d.b16 = -(64.0f + z) * d.s;
   return d;
@@ -60,6 +68,18 @@ __device__ __forceinline__ bf16x8_t dequant8(uint32_t word, const DequantScale& 
   out.y = pack_bf16x2(fmaf((float)e[1], d.s, d.b), fmaf((float)e8[1], d.s, d.b));
   out.z = pack_bf16x2(fmaf((float)o[0], d.s16, d.b16), fmaf((float)o8[0], d.s16, d.b16));
   out.w = pack_bf16x2(fmaf((float)o[1], d.s16, d.b16), fmaf((float)o8[1], d.s16, d.b16));
+  return *reinterpret_cast<const bf16x8_t*>(&out);
+}
+
+// The weights of a large scale, by the definition.
+__device__ __forceinline__ bf16x8_t dequant8_large(uint32_t word, const DequantScale& d) {
+  float v[8];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    v[i] = ((float)((word >> (8 * i)) & 15u) - d.b) * d.s;
+    v[4 + i] = ((float)((word >> (8 * i + 4)) & 15u) - d.b) * d.s;
+  }
+  const uint4 out = make_uint4(pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3]), pack_bf16x2(v[4], v[5]), pack_bf16x2(v[6], v[7]));
   return *reinterpret_cast<const bf16x8_t*>(&out);
 }
 
@@ -200,56 +220,97 @@ __global__ __launch_bounds__(64 * WN * KG) __attribute__((amdgpu_waves_per_eu(WP
     bn[0][nt] = dequant8(creg[0][nt][0], ds[nt]);
   }
   int b0 = 0;
-  for (int base = 0;; base += DB) {
-    bool done = false;
+  auto repair = [&](int nt, uint32_t word, bf16x8_t& w) {
+    if (large(ds[nt])) w = dequant8_large(word, ds[nt]);
+  };
+  // One step.  REPAIR: after every block the weights it has dequantised are repaired where their scale is large.
+  auto run_step = [&](auto REPAIR, int d, int step, int b1, int b2) __attribute__((always_inline)) {
+    auto rx = x_rsrc(step + 2 + DA);
+    auto rc = c_rsrc(step + DB - 1), rm = m_rsrc(step + DB - 1);
 #pragma unroll
-    for (int d = 0; d < DB; ++d) {
-      const int step = base + d;
-      if (!done) {
-        const int b1 = b0 == 2 * TILE ? 0 : b0 + TILE, b2 = b1 == 2 * TILE ? 0 : b1 + TILE;
-        auto rx = x_rsrc(step + 2 + DA);
-        auto rc = c_rsrc(step + DB - 1), rm = m_rsrc(step + DB - 1);
+    for (int q = 0; q < 4; ++q) {
+      if (q < 2) frag(b0, q + 2, an[q + 2]); else frag(b1, q - 2, an[q - 2]);
+      if (q == 0) {
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          if (q < 2) frag(b0, q + 2, an[q + 2]); else frag(b1, q - 2, an[q - 2]);
-          if (q == 0) {
+        for (int nt = 0; nt < NT; ++nt) GS_LOAD_C((d + DB - 1) % DB, nt, rc);
+      }
+      if ((d + DB - 1) % 2 == 0 && q == 1) {
 #pragma unroll
-            for (int nt = 0; nt < NT; ++nt) GS_LOAD_C((d + DB - 1) % DB, nt, rc);
-          }
-          if ((d + DB - 1) % 2 == 0 && q == 1) {
+        for (int nt = 0; nt < NT; ++nt) GS_LOAD_M((d + DB - 1) % DB / 2, nt, rm);
+      }
 #pragma unroll
-            for (int nt = 0; nt < NT; ++nt) GS_LOAD_M((d + DB - 1) % DB / 2, nt, rm);
-          }
+      for (int p = q * PASSES / 4; p < (q + 1) * PASSES / 4; ++p) {
+        *reinterpret_cast<uintx4_t*>(&xs[b2 + loff[p]]) = xreg[d % DA][p];
+        GS_LOAD_X(d % DA, p, rx);
+      }
+      // the next block's weights: k group q + 1 of this step, or group 0 of the next (another scale group after
+      // an odd step)
+      if (q < 3) {
 #pragma unroll
-          for (int p = q * PASSES / 4; p < (q + 1) * PASSES / 4; ++p) {
-            *reinterpret_cast<uintx4_t*>(&xs[b2 + loff[p]]) = xreg[d % DA][p];
-            GS_LOAD_X(d % DA, p, rx);
-          }
-          // the next block's weights: k group q + 1 of this step, or group 0 of the next (another scale group after
-          // an odd step)
-          if (q < 3) {
+        for (int nt = 0; nt < NT; ++nt) bn[(q + 1) % 2][nt] = dequant8(creg[d % DB][nt][q + 1], ds[nt]);
+      } else {
 #pragma unroll
-            for (int nt = 0; nt < NT; ++nt) bn[(q + 1) % 2][nt] = dequant8(creg[d % DB][nt][q + 1], ds[nt]);
-          } else {
-#pragma unroll
-            for (int nt = 0; nt < NT; ++nt) {
-              if (d % 2 == 1) ds[nt] = dequant_scale(mreg[(d + 1) % DB / 2][nt]);
-              bn[(q + 1) % 2][nt] = dequant8(creg[(d + 1) % DB][nt][0], ds[nt]);
-            }
-          }
-#pragma unroll
-          for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-            for (int nt = 0; nt < NT; ++nt)
-              acc[mt][nt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(an[q][mt], bn[q % 2][nt], acc[mt][nt], 0, 0, 0);
-          __builtin_amdgcn_sched_barrier(0);
+        for (int nt = 0; nt < NT; ++nt) {
+          if (d % 2 == 1) ds[nt] = dequant_scale(mreg[(d + 1) % DB / 2][nt]);
+          bn[(q + 1) % 2][nt] = dequant8(creg[(d + 1) % DB][nt][0], ds[nt]);
         }
-        __syncthreads();
-        b0 = b1;
-        done = step + 1 >= n_steps;
+      }
+#pragma unroll
+      for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt)
+          acc[mt][nt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(an[q][mt], bn[q % 2][nt], acc[mt][nt], 0, 0, 0);
+      __builtin_amdgcn_sched_barrier(0);
+      if constexpr (decltype(REPAIR)::value) {
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt)
+          repair(nt, q < 3 ? creg[d % DB][nt][(q + 1) % 4] : creg[(d + 1) % DB][nt][0], bn[(q + 1) % 2][nt]);
+        __builtin_amdgcn_sched_barrier(0);
       }
     }
-    if (done) break;
+  };
+  // whether some lane's current scale group has a large scale (uniform over the wave)
+  auto any_large = [&]() {
+    bool any = false;
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) any |= large(ds[nt]);
+    return __any(any);
+  };
+  auto next_buffers = [&](int& b1, int& b2) {
+    b1 = b0 == 2 * TILE ? 0 : b0 + TILE;
+    b2 = b1 == 2 * TILE ? 0 : b1 + TILE;
+  };
+  int step = 0, first_large = -1;
+  while (first_large < 0 && step < n_steps) {
+#pragma unroll
+    for (int d = 0; d < DB; ++d) {
+      if (d % 2 == 0 && __builtin_expect(any_large(), false)) {
+        first_large = step;
+        break;
+      }
+      int b1, b2;
+      next_buffers(b1, b2);
+      run_step(std::false_type(), d, step, b1, b2);
+      __syncthreads();
+      b0 = b1;
+      if (++step >= n_steps) break;
+    }
+  }
+  if (__builtin_expect(first_large >= 0, false)) {      // the rest of the steps, with every block's weights repaired
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) repair(nt, (first_large & 2) ? creg[2 % DB][nt][0] : creg[0][nt][0], bn[0][nt]);
+    for (int base = first_large & ~(DB - 1); step < n_steps; base += DB) {
+#pragma unroll
+      for (int d = 0; d < DB; ++d) {
+        if (base + d != step || step >= n_steps) continue;
+        int b1, b2;
+        next_buffers(b1, b2);
+        run_step(std::true_type(), d, step, b1, b2);
+        __syncthreads();
+        b0 = b1;
+        ++step;
+      }
+    }
   }
 #undef GS_LOAD_X
 #undef GS_LOAD_C

@@ -21,26 +21,27 @@ pytestmark = pytest.mark.gpu
 MATS = ("wqkv", "wo", "wgu", "wd")
 
 
-def _checkpoint(ms, seed, std):
-    """(GPU side: triples, oracle side: dequantised float64) for the top and every layer."""
+def _checkpoint(ms, seed, std, edit=lambda name, triple: triple):
+    """(GPU side: triples, oracle side: dequantised float64) for the top and every layer.  edit: changes a matrix' triple
+    for both sides."""
     top = synth.top_weights(ms, seed, std)
-    lm = synth.quantize_w4(top["lm_head"])
+    lm = edit("lm_head", synth.quantize_w4(top["lm_head"]))
     top_gpu = dict(top, lm_head=lm)
     top_ora = dict(top, lm_head=quant.dequant_w4(*lm))
     lay_gpu, lay_ora = [], []
     for l in range(ms.n_layers):
         W = synth.layer_weights(ms, seed, l, std)
-        trip = {k: synth.quantize_w4(W[k]) for k in MATS}
+        trip = {k: edit(k, synth.quantize_w4(W[k])) for k in MATS}
         lay_gpu.append(dict(W, **trip))
         lay_ora.append(dict(W, **{k: quant.dequant_w4(*trip[k]) for k in MATS}))
     return top_gpu, lay_gpu, top_ora, lay_ora
 
 
-def _run(ms, seed, gamma, ctx, std=0.08):
+def _run(ms, seed, gamma, ctx, std=0.08, edit=lambda name, triple: triple):
     import torch
     from paper_2512_09963_amd import workload as wl
     tol = TOL["bf16"]
-    top_gpu, lay_gpu, top_ora, lay_ora = _checkpoint(ms, seed, std)
+    top_gpu, lay_gpu, top_ora, lay_ora = _checkpoint(ms, seed, std, edit)
     batch = synth.make_batch(seed, gamma, ctx, 16, permute_pages=True)
     tokens, q, ua, ur = synth.verify_side_inputs(seed, ms.vocab, batch.gamma, sigma=0.5)
     cache = _oracle_cache(ms, seed, batch.n_pages, 16, True)
@@ -88,6 +89,31 @@ def test_w4_gate_up_with_the_swiglu_in_its_epilogue(rows):
     # F / 128 = 130 column blocks: unsplit and fused up to 96 rows, split beyond
     ms = synth.ModelShape(1, 384, 2, 1, 64, 16640, 1024, 10000.0, dtype="bf16")
     _run(ms, 93, np.array([rows - 3, 1], np.int32), np.array([9, 0], np.int32), std=0.05)
+
+
+@pytest.mark.parametrize("nonzero", [False, True])
+@pytest.mark.parametrize("rows", [20, 50, 90, 110])
+def test_w4_scales_near_the_largest_number(rows, nonzero):
+    """Groups with scales of 2^117 and more, at the start, inside and at the end of a row: weights of zero (code = zero point)
+    stay zeros in every matrix, others are the defined numbers (nonzero: tokens with one weight of +-2^118 each)."""
+    ms = synth.ModelShape(1, 384, 2, 1, 64, 8448, 1024, 10000.0, dtype="bf16")      # (F / 64 = 132: the fused gate/up kernel too)
+
+    def edit(name, triple):
+        codes, scale, zero = (a.copy() for a in triple)
+        n, groups = scale.shape
+        for i, exponent in enumerate((117, 118, 122, 127)):
+            for grp in {0, min(1, groups - 1), groups - 1}:
+                row = (37 + 13 * i + grp) % n
+                scale[row, grp] = np.float32(2.0 ** exponent)
+                zero[row, grp] = (5 * i + grp) % 16
+                codes[row, grp * 128:(grp + 1) * 128] = zero[row, grp]
+        if name == "lm_head" and nonzero:
+            for i, row in enumerate(range(300, 364)):
+                scale[row], zero[row], codes[row] = np.float32(2.0 ** 118), i % 16, i % 16
+                codes[row, 6 * i + 5] = i % 16 + (1 if i % 16 < 8 else -1)
+        return codes, scale, zero
+
+    _run(ms, 92, np.array([rows - 3, 1], np.int32), np.array([9, 0], np.int32), std=0.05, edit=edit)
 
 
 def test_w4_wide_matrices_use_eight_waves():
