@@ -123,7 +123,7 @@ __global__ __launch_bounds__(64 * WN * KG) __attribute__((amdgpu_waves_per_eu(WP
   const int m0 = m_chunk * ROWS;
   const int split_begin = split * k_per_split, split_end = min(K, split_begin + k_per_split);
   // the K groups take whole scale groups (two steps) and run the same number of steps (barriers); a step past a group's
-  // own end multiplies zeros
+  // own end multiplies zeros by weights of scale zero
   const int split_steps = (split_end - split_begin) / 64;
   const int n_steps = (split_steps / 2 + KG - 1) / KG * 2;
   const int own_steps = min(n_steps, split_steps - kg * n_steps);
@@ -150,10 +150,12 @@ __global__ __launch_bounds__(64 * WN * KG) __attribute__((amdgpu_waves_per_eu(WP
                                              (KG == 1 || step < own_steps) ? x_bytes - (unsigned)s * 128u : 0u, 0x00020000);
   };
   auto c_rsrc = [&](int step) {
-    return __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(cbase + (size_t)min(step, last) * c_stride), 0, c_bytes, 0x00020000);
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(cbase + (size_t)min(step, last) * c_stride), 0,
+                                             (KG == 1 || step < own_steps) ? c_bytes : 0u, 0x00020000);
   };
   auto m_rsrc = [&](int step) {
-    return __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(mbase + (size_t)(min(step, last) >> 1) * N * 4), 0, m_bytes, 0x00020000);
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(mbase + (size_t)(min(step, last) >> 1) * N * 4), 0,
+                                             (KG == 1 || step < own_steps) ? m_bytes : 0u, 0x00020000);
   };
   uintx4_t xreg[DA][PASSES];
   uintx4_t creg[DB][NT];

@@ -80,7 +80,7 @@ __global__ __launch_bounds__(64 * WM * WN * KG) __attribute__((amdgpu_waves_per_
   const int m0 = m_chunk * ROWS;
   const int split_begin = split * k_per_split, split_end = min(K, split_begin + k_per_split);
   // the K groups take the halves of the split, rounded to steps; both run the same number of steps (barriers), a
-  // step past the end multiplies zeros
+  // step past the end multiplies zeros by zeros
   const int split_steps = (split_end - split_begin) / 64;
   const int n_steps = (split_steps + KG - 1) / KG;
   const int own_steps = min(n_steps, split_steps - kg * n_steps);
@@ -106,8 +106,8 @@ __global__ __launch_bounds__(64 * WM * WN * KG) __attribute__((amdgpu_waves_per_
                                              (KG == 1 || step < own_steps) ? x_bytes - (unsigned)s * 128u : 0u, 0x00020000);
   };
   auto w_rsrc = [&](int step) {
-    return __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(wbase + (size_t)min(step, last) * w_stride), 0, w_bytes,
-                                             0x00020000);
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(wbase + (size_t)min(step, last) * w_stride), 0,
+                                             (KG == 1 || step < own_steps) ? w_bytes : 0u, 0x00020000);
   };
   uintx4_t xreg[DA][PASSES];
   uintx4_t wreg[DB][NT][2];

@@ -3,6 +3,8 @@
 Tolerances (relative to the row scale max|logit|, see tests/parity.py for the decisions):
 fp32 models 1e-4, bf16 models 2e-2.
 """
+import dataclasses
+
 import numpy as np
 import pytest
 
@@ -167,6 +169,44 @@ def test_bf16_projections_with_256_columns_per_workgroup(rows):
     # N / 256 >= 192 for the gate/up projection and the LM head; K of one step
     ms = synth.ModelShape(1, 64, 1, 1, 64, 24576, 49152, 10000.0, dtype="bf16")
     _run_case(ms, 90, np.array([rows - 3, 1], np.int32), np.array([9, 0], np.int32), 16, std=0.08)
+
+
+@pytest.mark.parametrize("dtype,d,k,rows", [
+    # the two K groups of a workgroup take steps 0, 1 and 2 of three; one and three scale groups on two K groups
+    ("bf16", 192, 150, 70), ("bf16", 192, 130, 150), ("w4", 128, 70, 50), ("w4", 384, 300, 90), ("w4", 384, 300, 50)])
+def test_an_infinite_weight_gives_an_infinite_output(dtype, d, k, rows):
+    """A K group with fewer steps than the others runs on over nothing: an infinite weight of its last step stays infinite in
+    the output (a value channel of the cache), and the other channels are finite."""
+    import torch
+    from paper_2512_09963_amd import workload as wl
+    ms = synth.ModelShape(1, d, 2, 1, 64, 256, 1024, 10000.0, dtype="bf16")
+    top, layers = _model(ms, 91, 0.08)
+    row = 3 * 64 + 5                       # channel 5 of the value head
+    if dtype == "w4":
+        ms = dataclasses.replace(ms, dtype="w4")
+        top["lm_head"] = synth.quantize_w4(top["lm_head"])
+        for name in ("wqkv", "wo", "wgu", "wd"):
+            layers[0][name] = synth.quantize_w4(layers[0][name])
+        codes, scale, zero = layers[0]["wqkv"]
+        grp = k // 128
+        scale[row, grp], zero[row, grp] = np.float32(2.0 ** 126), 3
+        codes[row, grp * 128:(grp + 1) * 128] = 3
+        codes[row, k] = 7                  # 4 * 2^126
+    else:
+        layers[0]["wqkv"][row, k] = np.inf
+    batch = synth.make_batch(91, np.array([rows - 3, 1], np.int32), np.array([9, 0], np.int32), 16, permute_pages=True)
+    tokens = synth.verify_side_inputs(91, ms.vocab, batch.gamma)[0]
+    kv = wl.KVCache(ms, batch.n_pages, 16)
+    wl.verify(wl.upload_model(ms, top, lambda l: layers[l]), kv, wl.DeviceBatch(batch, tokens))
+    torch.cuda.synchronize()
+    _, v = kv.get_layer(0)
+    cu = batch.cu_rows
+    for i in range(batch.n_servers):
+        for j in range(int(batch.gamma[i]) + 1):
+            pos = int(batch.ctx_len[i]) + j
+            got = v[int(batch.block_table[i, pos // 16]), 0, pos % 16]
+            assert got[5] == np.sign(top["embed"][tokens[cu[i] + j], k]) * np.inf, (i, j, got[5])
+            assert np.isfinite(np.delete(got, 5)).all()
 
 
 @pytest.mark.parametrize("heads,n_kv,hd,gamma,ctx,page", [
