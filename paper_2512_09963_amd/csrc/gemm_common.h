@@ -34,9 +34,9 @@ __device__ __forceinline__ float row16_sum(float v) {
   return v + dpp_move<0x140>(v);
 }
 
-// Launch of gemm_bf16_wide_kernel: wm x wn waves of mt x nt tiles, n_blocks column blocks.
+// Launch of gemm_bf16_wide_kernel: wm x wn waves of mt x nt tiles, kg groups of them, n_blocks column blocks.
 struct WidePlan {
-  int wm, wn, mt, nt, m_chunks, n_blocks, splits, k_per;
+  int wm, wn, kg, mt, nt, m_chunks, n_blocks, splits, k_per;
 };
 // one_split: the projection must not be split over workgroups (its epilogue needs the whole sums).
 WidePlan wide_plan(int M, int N, int K, bool one_split);

@@ -17,13 +17,15 @@
 //   * activation rows are 128 bytes in LDS, their 16-byte pieces XOR-swizzled by the row pair: conflict-free reads
 //   * loads are buffer loads: the descriptor moves with k on the scalar unit and the lane offsets are constant, so a
 //     load costs no vector instruction for its address; rows past the end read as zero by the descriptor's range
-// The shapes: WM x WN waves, each with MT x NT tiles of 16 x 16, KG groups of them that share K:
+// The shapes: WM x WN waves, each with MT x NT tiles of 16 x 16, KG groups of them that share K (which one a launch takes: kWideShapes):
 //   1 x 8 (256 columns, wide matrices), up to 192 rows: no weight byte is loaded twice
-//   1 x 4 (128 columns) with KG = 2: the two halves of K in one workgroup, their sums meet in LDS: as many waves as 1 x 8
-//     without halving the workgroups of a narrower matrix, and half the partial results of a further K split (which the
-//     gate/up projection, whose epilogue applies the SwiGLU, must not have)
+//   1 x 4 (128 columns) with KG = 2, all rows (up to 160) in one workgroup: the two halves of K in one workgroup, their sums meet
+//     in LDS: as many waves as 1 x 8 without halving the workgroups of a narrower matrix, and half the partial results of a
+//     further K split (which the gate/up projection, whose epilogue applies the SwiGLU, must not have)
+//   1 x 4 (128 columns) in row chunks of 64 to 192 rows, two workgroups per compute unit: narrow matrices and middling row counts,
+//     where the time of one workgroup is the time of the launch
 //   2 x 2 (128 columns, up to 352 rows in one workgroup): both row halves load the weights, the second time from L1
-//   1 x 4 of 128 x 64 (256 columns, chunks of 128 rows) from 640 rows on, where the matrix pipe and the power it draws are
+//   1 x 4 of 128 x 64 (256 columns, chunks of 128 rows) for many rows, where the matrix pipe and the power it draws are
 //     the bound: 1.0 to 1.1 PFLOP/s, 1.25 to 1.3 on matrices of zeros, 1.86 with the global loads of the loop taken out
 //     (rates of a work copy at 2048 x 28672 x 4096; more weights or activations in flight change nothing)
 // Measured inside a verification step (us per launch; predecessor in brackets), N x K:
@@ -283,44 +285,90 @@ __global__ __launch_bounds__(64 * WM * WN * KG) __attribute__((amdgpu_waves_per_
 
 }  // namespace
 
+// The shapes for more than 64 rows and what a launch takes with them (us), over 18 matrices of 1024 x 1024 to 28672 x 8192 and
+// 65 to 2047 rows in every shape and K split (rms 8 %):
+//   the larger of loop = steps x step time of the workgroups a compute unit has one after the other, and stream = weight bytes /
+//   5.5 TB/s; 0.2 of the smaller; 0.063 x tiles per SIMD and workgroup for the epilogue; 0.46 per MB of partial results (written
+//   here, read by the next kernel).
+// A step takes fixed_us + tile_us x tiles of 16 x 16 per SIMD, of two workgroups at once (shapes that fit a compute unit twice)
+// pair_fixed_us + pair_tile_us x tiles.  Row chunks read the weights again, from L2 for the most part: 0.19 of the stream each.
+// The fixed part is what a step's barrier and loads cost whatever the tile: few rows on a narrow matrix want small workgroups in
+// several row chunks, wide matrices and many rows large tiles.  Against one shape per range of rows (K groups up to 192 rows,
+// 2 x 2 waves up to 639, 128 x 64 per wave from there), isolated launches are faster by a factor of 1.19 on average and 0.96 at
+// worst: at 180 rows 2048 x 2048 14.8 -> 6.6 us and 6144 x 4096 21.4 -> 18.1, at 384 rows 10240 x 8192 115 -> 68.
+struct WideShape {
+  int wm, wn, kg, mt, nt;
+  float tile_us, fixed_us, pair_tile_us, pair_fixed_us;      // pair: 0 where a compute unit holds one workgroup
+};
+static const WideShape kWideShapes[] = {
+    {1, 4, 2, 6, 2, 0.0146f, 0.256f, 0.f, 0.f},         {1, 4, 2, 8, 2, 0.0146f, 0.256f, 0.f, 0.f},
+    {1, 4, 2, 10, 2, 0.0146f, 0.256f, 0.f, 0.f},        {1, 4, 1, 4, 2, 0.0152f, 0.271f, 0.0354f, 0.34f},
+    {1, 4, 1, 6, 2, 0.0152f, 0.271f, 0.0354f, 0.34f},   {1, 4, 1, 8, 2, 0.0152f, 0.271f, 0.0354f, 0.34f},
+    {1, 4, 1, 10, 2, 0.0152f, 0.271f, 0.0354f, 0.34f},  {1, 4, 1, 12, 2, 0.0152f, 0.271f, 0.0354f, 0.34f},
+    {1, 8, 1, 6, 2, 0.012f, 0.527f, 0.f, 0.f},          {1, 8, 1, 8, 2, 0.012f, 0.527f, 0.f, 0.f},
+    {1, 8, 1, 10, 2, 0.012f, 0.527f, 0.f, 0.f},         {1, 8, 1, 12, 2, 0.012f, 0.527f, 0.f, 0.f},
+    {2, 2, 1, 8, 4, 0.0153f, 0.311f, 0.f, 0.f},         {2, 2, 1, 10, 4, 0.0153f, 0.311f, 0.f, 0.f},
+    {2, 2, 1, 11, 4, 0.0153f, 0.311f, 0.f, 0.f},        {1, 4, 1, 8, 4, 0.f, 0.77f, 0.f, 1.22f}};
+
+static void cut_k(WidePlan& p, int K, int s) {
+  p.k_per = ceil_div(ceil_div(K, s), 64) * 64;
+  p.splits = ceil_div(K, p.k_per);
+}
+
+// The shape of kWideShapes and the K splits with the least time for more than 4 row tiles (N a multiple of 128).
+static WidePlan fastest_shape(int tiles, int N, int K, bool one_split) {
+  constexpr long kCus = 256;
+  float least = 0.f;
+  WidePlan best{};
+  for (const WideShape& w : kWideShapes) {
+    const int cols = 16 * w.nt * w.wn;
+    if (N % cols != 0) continue;
+    WidePlan p{w.wm, w.wn, w.kg, w.mt, w.nt, ceil_div(tiles, w.wm * w.mt), N / cols, 1, 0};
+    const bool halves = w.wm == 1 && w.nt == 4;      // 128 x 64 outputs per wave
+    // where one workgroup has all rows, K groups are better than the same tile without; they are not for weights that several
+    // workgroups read, nor 1 x 8 waves for more than two; 128 rows per wave pad few rows
+    if (p.m_chunks > 1 ? w.kg == 2 || (w.wn == 8 && p.m_chunks > 2) : w.wn == 4 && w.nt == 2 && w.kg == 1 && tiles <= 10) continue;
+    if (halves && tiles <= 12) continue;
+    const bool pairs = w.pair_fixed_us > 0.f && tiles > 12;
+    const float units = 0.25f * (float)(w.mt * w.nt * w.wm * w.wn);
+    const float single_us = w.fixed_us + w.tile_us * units, pair_us = w.pair_fixed_us + w.pair_tile_us * units;
+    const float stream = 2e-6f / 5.54f * (float)N * (float)K * (1.f + 0.195f * (float)(p.m_chunks - 1));
+    const long blocks = (long)p.n_blocks * p.m_chunks;
+    // K splits: as many as give every compute unit one workgroup (the largest tile also two), at least 8 steps each
+    for (long target = kCus; target <= (halves && !one_split && K >= 1024 ? 2 * kCus : kCus); target += kCus) {
+      cut_k(p, K, one_split ? 1 : std::max(1, std::min((int)(target / blocks), K / 512)));
+      const long wgs = blocks * p.splits, per_cu = (wgs + kCus - 1) / kCus, last = wgs % (2 * kCus);
+      const float steps_us = !pairs ? (float)per_cu * single_us
+                                    : (float)(wgs / (2 * kCus)) * pair_us + (last == 0 ? 0.f : last <= kCus ? single_us : pair_us);
+      const float loop = (float)(p.k_per / 64) * steps_us;
+      const float us = std::max(loop, stream) + 0.197f * std::min(loop, stream) + 0.0626f * units * (float)per_cu +
+                       0.46f * 64e-6f * (float)p.splits * (float)tiles * (float)N;
+      if (best.splits == 0 || us < least) {
+        least = us;
+        best = p;
+      }
+    }
+  }
+  return best;
+}
+
 WidePlan wide_plan(int M, int N, int K, bool one_split) {
-  WidePlan p;
   const int tiles = ceil_div(M, 16);
-  p.nt = 2;
-  int target = 256;      // workgroups: one per compute unit (registers and LDS of every shape fit that many) ...
-  if (tiles >= 40 && N % 256 == 0) {
-    // 640 rows and more: 1 x 4 waves of 128 x 64, two workgroups per compute unit, so that a unit that finishes one takes the
-    // next while the other runs on (256 x 256 tiles of 8 waves: 447 instead of 392 us for gate/up at 2047 rows, 3.5 rounds)
+  if (tiles <= 4) {
+    WidePlan p;
     p.wm = 1;
-    p.wn = 4;
-    p.nt = 4;
-    p.mt = 8;
-    p.m_chunks = ceil_div(tiles, 8);
-    target = 512;
-  } else if (tiles <= 12) {
-    p.wm = 1;
+    p.nt = 2;
     p.mt = std::max(2, (tiles + 1) / 2 * 2);
     p.m_chunks = 1;
     // 256 columns per workgroup where that still leaves a workgroup for three compute units in four (28672 columns
     // of the 8B gate/up projection would leave 112); narrower matrices take 128
     p.wn = (N % 256 == 0 && N / 256 >= 192) ? 8 : 4;
-  } else {
-    // 2 x 2 waves, up to 22 row tiles per workgroup; more rows in equal chunks
-    p.wm = 2;
-    p.wn = 2;
-    p.nt = 4;
-    const int chunks = ceil_div(tiles, 22), half = ceil_div(ceil_div(tiles, chunks), 2);
-    p.mt = half <= 8 ? 8 : half <= 10 ? 10 : 11;
-    p.m_chunks = ceil_div(tiles, 2 * p.mt);
+    p.kg = p.wn == 8 ? 1 : 2;
+    p.n_blocks = N / (32 * p.wn);
+    cut_k(p, K, one_split ? 1 : std::max(1, std::min(256 / p.n_blocks, K / 512)));
+    return p;
   }
-  p.n_blocks = N / (16 * p.nt * p.wn);
-  const int wgs = p.n_blocks * p.m_chunks;
-  // ... and never a second round for a few more; at least 8 steps per split
-  const int want = target / wgs, max_s = std::max(1, K / 512);
-  const int s = one_split ? 1 : std::max(1, std::min(want, max_s));
-  p.k_per = ceil_div(ceil_div(K, s), 64) * 64;
-  p.splits = ceil_div(K, p.k_per);
-  return p;
+  return fastest_shape(tiles, N, K, one_split);
 }
 
 template <int MODE>
@@ -347,23 +395,25 @@ static gs_status launch_mode(const WidePlan& p, const bf16_t* x, const bf16_t* w
       case 10: GS_WIDE(1, 8, 1, 10, 2, 4, 2, 2, 2); break;
       default: GS_WIDE(1, 8, 1, 12, 2, 4, 2, 2, 2);
     }
-  } else if constexpr (MODE == kStats) {
+  } else if (MODE == kStats && p.m_chunks == 1 && p.mt == 12) {
+    if constexpr (MODE == kStats) GS_WIDE(1, 4, 1, 12, 2, 4, 2, 2, 1);      // (spills where two workgroups share the registers)
+  } else if (p.m_chunks == 1 && (MODE == kStats || p.kg == 2)) {
+    // (the statistics take whole sums: one K group there, and two workgroups per compute unit)
+    constexpr int KG = MODE == kStats ? 1 : 2;
     switch (p.mt) {
-      case 2: GS_WIDE(1, 4, 1, 2, 2, 4, 2, 2, 1); break;
-      case 4: GS_WIDE(1, 4, 1, 4, 2, 4, 2, 2, 1); break;
-      case 6: GS_WIDE(1, 4, 1, 6, 2, 4, 2, 2, 1); break;
-      case 8: GS_WIDE(1, 4, 1, 8, 2, 4, 2, 2, 1); break;
-      case 10: GS_WIDE(1, 4, 1, 10, 2, 4, 2, 2, 1); break;
-      default: GS_WIDE(1, 4, 1, 12, 2, 4, 2, 2, 1);
+      case 2: GS_WIDE(1, 4, KG, 2, 2, 4, 2, 2, 2); break;
+      case 4: GS_WIDE(1, 4, KG, 4, 2, 4, 2, 2, 2); break;
+      case 6: GS_WIDE(1, 4, KG, 6, 2, 4, 2, 2, 2); break;
+      case 8: GS_WIDE(1, 4, KG, 8, 2, 4, 2, 2, 2); break;
+      default: GS_WIDE(1, 4, KG, 10, 2, 4, 2, 2, 2);
     }
   } else {
     switch (p.mt) {
-      case 2: GS_WIDE(1, 4, 2, 2, 2, 4, 2, 2, 2); break;
-      case 4: GS_WIDE(1, 4, 2, 4, 2, 4, 2, 2, 2); break;
-      case 6: GS_WIDE(1, 4, 2, 6, 2, 4, 2, 2, 2); break;
-      case 8: GS_WIDE(1, 4, 2, 8, 2, 4, 2, 2, 2); break;
-      case 10: GS_WIDE(1, 4, 2, 10, 2, 4, 2, 2, 2); break;
-      default: GS_WIDE(1, 4, 2, 12, 2, 4, 2, 2, 2);
+      case 4: GS_WIDE(1, 4, 1, 4, 2, 4, 2, 0, 2); break;
+      case 6: GS_WIDE(1, 4, 1, 6, 2, 4, 2, 0, 2); break;
+      case 8: GS_WIDE(1, 4, 1, 8, 2, 4, 2, 0, 2); break;
+      case 10: GS_WIDE(1, 4, 1, 10, 2, 4, 2, 0, 2); break;
+      default: GS_WIDE(1, 4, 1, 12, 2, 4, 2, 0, 2);
     }
   }
 #undef GS_WIDE

@@ -69,7 +69,7 @@ struct gs_ctx {
   std::vector<hipEvent_t> ev_start, ev_stop;
   std::vector<int> ev_stage;
   size_t ev_used = 0;
-  // workspace planning: prefix maxima of the split-K partial sizes over the row count (filled on demand;
+  // workspace planning: prefix maxima of the split-K partial sizes over the row tiles (filled on demand;
   // a context is used by one thread at a time)
   mutable std::vector<size_t> partial_prefix_max;
 };
@@ -96,25 +96,26 @@ struct Plan {
   size_t bytes;
 };
 
-// Largest split-K partial buffer any projection needs for up to max_rows rows.  The split counts are not
-// monotone in the row count, so the maximum runs over every row count; the prefix maxima are kept in the
-// context (one entry per row count seen so far), which makes the per-call cost a table lookup.
+// Largest split-K partial buffer any projection needs for up to max_rows rows.  The split counts depend on the rows'
+// number of 16-row tiles and are not monotone in it, so the maximum runs over every tile count; the prefix maxima are kept
+// in the context (one entry per tile count seen so far), which leaves one look at the splits per call.
 size_t max_partial_floats(const gs_ctx* ctx, int max_rows) {
   const gs_model_desc& m = ctx->desc;
   const int qkv = (m.n_heads + 2 * m.n_kv_heads) * m.head_dim;
   const int hq = m.n_heads * m.head_dim;
-  std::vector<size_t>& best = ctx->partial_prefix_max;
-  if (best.empty()) best.push_back(0);
-  for (int M = (int)best.size(); M <= max_rows; ++M) {
+  auto floats = [&](int M) {
     size_t a = (size_t)gs::gemm_splits(m.dtype, M, qkv, m.d_model) * M * qkv;
     size_t b = (size_t)gs::gemm_splits(m.dtype, M, m.d_model, hq) * M * m.d_model;
     size_t c = (size_t)gs::gemm_splits(m.dtype, M, 2 * m.d_ffn, m.d_model) * M * 2 * m.d_ffn;
     size_t d = (size_t)gs::gemm_splits(m.dtype, M, m.d_model, m.d_ffn) * M * m.d_model;
     const int sv = gs::gemm_splits(m.dtype, M, m.vocab, m.d_model);
     size_t e = sv > 1 ? (size_t)sv * M * m.vocab : 0;   // LM head partials only when it is split
-    best.push_back(std::max(std::max(best.back(), a), std::max(std::max(b, e), std::max(c, d))));
-  }
-  return best[max_rows];
+    return std::max(a, std::max(std::max(b, e), std::max(c, d)));
+  };
+  std::vector<size_t>& best = ctx->partial_prefix_max;
+  if (best.empty()) best.push_back(0);
+  for (int tiles = (int)best.size(); tiles <= max_rows / 16; ++tiles) best.push_back(std::max(best.back(), floats(16 * tiles)));
+  return max_rows % 16 ? std::max(best[max_rows / 16], floats(max_rows)) : best[max_rows / 16];
 }
 
 Plan make_plan(const gs_ctx* ctx, int max_rows, int max_servers, int max_ctx, void* ws) {

@@ -58,7 +58,7 @@ def _check_kv_rows(ms, kv_dev, cache, batch, tol):
                         f"{name} layer {l} server {i} pos {pos}"
 
 
-def _run_case(ms, seed, gamma, ctx_len, page, std, synthetic_kv=True, permute=True, sigma=0.5):
+def _run_case(ms, seed, gamma, ctx_len, page, std, synthetic_kv=True, permute=True, sigma=0.5, and_without_q=False):
     import torch
     from paper_2512_09963_amd import workload as wl
     tol = TOL[ms.dtype]
@@ -78,6 +78,10 @@ def _run_case(ms, seed, gamma, ctx_len, page, std, synthetic_kv=True, permute=Tr
                                     lambda l: layers[l], lambda l: cache[l])
     worst = assert_logits_close(got_logits, want_logits, tol)
     _check_kv_rows(ms, kv, cache, batch, tol)
+    if and_without_q:      # the LM head without the statistics in its epilogue
+        _, logits, _ = wl.verify(ver, kv, wl.DeviceBatch(batch, tokens))
+        torch.cuda.synchronize()
+        assert_logits_close(logits.cpu().numpy(), want_logits, tol, "logits without q")
     got = {k: v.cpu().numpy() for k, v in out.items()}
     cu = batch.cu_rows
     d_tok = np.concatenate([tokens[cu[i] + 1:cu[i + 1]] for i in range(batch.n_servers)]) if batch.n_draft else np.zeros(0, np.int32)
@@ -162,6 +166,19 @@ def test_bf16_projections_at_the_edges_of_the_row_tiles(rows):
     ms = synth.ModelShape(1, 192, 2, 1, 64, 1088, 21888, 10000.0, dtype="bf16")
     gamma = [rows // 2 - 1, rows - rows // 2 - 1]
     _run_case(ms, 89, np.array(gamma, np.int32), np.array([9, 0], np.int32), 16, std=0.08)
+
+
+@pytest.mark.parametrize("ffn,vocab,rows", [
+    # every shape of the pipelined kernel in each of its three epilogues, six steps of K: 1 x 8 waves of 6 to 12 row tiles, two row
+    # chunks of 1 x 4 and of 2 x 2, 128 x 64 per wave
+    *[(24576, 49152, r) for r in (70, 100, 130, 161, 200, 300, 321, 353, 400, 700)],
+    # column counts that are no multiple of 256: two K groups of 6 to 10 row tiles, one of 12, 2 x 2 of 8 to 11
+    *[(10944, 21888, r) for r in (65, 97, 129, 161, 193, 257, 321)],
+    # narrow: 1 x 4 in row chunks of 4 to 12 tiles
+    *[(4096, 8192, r) for r in (129, 200, 257, 321, 385, 520, 600, 700)]])
+def test_bf16_projection_shapes(ffn, vocab, rows):
+    ms = synth.ModelShape(1, 384, 2, 1, 64, ffn, vocab, 10000.0, dtype="bf16")
+    _run_case(ms, 85, np.array([rows - 3, 1], np.int32), np.array([9, 0], np.int32), 16, std=0.05, and_without_q=True)
 
 
 @pytest.mark.parametrize("rows", [5, 40, 90, 120])
