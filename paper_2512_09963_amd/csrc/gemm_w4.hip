@@ -429,7 +429,9 @@ gs_status launch_pack_weight_w4(const void* q, const void* scales, const void* z
 }
 
 // Launch shape of the 4-bit kernel: waves x kg waves per workgroup, nt column tiles per wave, mt row tiles of 32.
-//   up to 32 rows: the weight stream is all there is; 8 waves side by side, two workgroups per compute unit
+//   up to 32 rows: the weight stream is all there is; 8 waves side by side, K splits for two workgroups per compute unit up to
+//     16 rows, for one beyond, where the partial results weigh more (32 rows, 8192 x 8192: 14.5 us and 16.8 MB with two, 13.8 us
+//     and 8.4 MB with one)
 //   33 to 96 rows: 4 waves x 2 K groups; two column tiles per wave (a fragment read from LDS feeds two MFMAs) for matrices of
 //     192 blocks of 256 columns and more, and where every wave still gets 16 steps; otherwise one
 //     (92 rows, isolated: 8192 x 28672 49 us with two, 54 with one; 8192 x 8192 22.0 and 20.8; 10240 x 8192 26.5 and 25.8)
@@ -451,7 +453,7 @@ static W4Plan w4_plan(int M, int N, int K) {
   if (p.mt == 1 || p.mt == 4) {
     p.waves = N % 256 == 0 ? 8 : 4;
     p.kg = p.waves == 8 ? 1 : 2;
-    if (p.mt == 1) target = 512;
+    if (M <= 16) target = 512;
   } else {
     p.waves = 4;
     p.kg = 2;
