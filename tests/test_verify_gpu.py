@@ -183,7 +183,7 @@ def test_bf16_projection_shapes(ffn, vocab, rows):
 
 @pytest.mark.parametrize("rows", [5, 40, 90, 120])
 def test_bf16_projections_with_256_columns_per_workgroup(rows):
-    # N / 256 >= 192 for the gate/up projection and the LM head; K of one step
+    # 1 x 8 waves for the gate/up projection and the LM head; K of one step
     ms = synth.ModelShape(1, 64, 1, 1, 64, 24576, 49152, 10000.0, dtype="bf16")
     _run_case(ms, 90, np.array([rows - 3, 1], np.int32), np.array([9, 0], np.int32), 16, std=0.08)
 
@@ -245,7 +245,7 @@ def test_bf16_prompt_blocks_in_query_groups(heads, n_kv, hd, gamma, ctx, page):
 
 @pytest.mark.parametrize("gamma", [[3, 1, 5], [16, 12, 9, 15, 11, 14]])
 def test_bf16_wide_vocabulary_statistics_from_the_lm_head_epilogue(gamma):
-    # V / 128 >= 192: the LM head takes the 8-wave kernel (12 rows) or the tall one (83 rows) as one launch, whose
+    # V = 24576 at 12 and 83 rows: the LM head is one launch without a K split, whose
     # epilogue leaves the softmax statistics per column block; the accept stage merges them instead of
     # reading the logits again.  The decisions below are therefore checked against the oracle on that path.
     ms = synth.ModelShape(1, 128, 2, 1, 64, 256, 24576, 10000.0, dtype="bf16")
@@ -259,7 +259,7 @@ def test_bf16_page_size_64_and_single_server():
 
 @pytest.mark.parametrize("n_servers,gmax", [(10, 8), (24, 16)])
 def test_bf16_many_rows_use_the_tall_projection_kernel(n_servers, gmax):
-    # 60..250 target rows: more than one 64-row tile set, with and without row chunks
+    # 60..250 target rows (beyond 64 the pipelined kernel), with and without row chunks
     ms = synth.ModelShape(2, 256, 4, 2, 128, 512, 1024, 500000.0, dtype="bf16")
     rng = np.random.default_rng(81 + n_servers)
     gamma = rng.integers(gmax // 2, gmax + 1, n_servers).astype(np.int32)
@@ -435,3 +435,26 @@ def test_stream_read_probe_runs_and_validates_its_arguments():
     assert int(src[-1]) == (1 << 20) - 1
     with pytest.raises(gsb.GsError):
         gsb.gs_probe_stream_read(src[1:], sink)
+
+
+@pytest.mark.parametrize("dtype,rows", [("f32", 20), ("bf16", 12), ("bf16", 150), ("bf16", 420)])
+def test_results_do_not_depend_on_what_the_workspace_held(dtype, rows):
+    """The same call on a workspace of zeros and on one of NaN patterns gives the same bits (K splits, KV splits and accept
+    scratch are written before they are read, and every sum has a fixed order)."""
+    import torch
+    from paper_2512_09963_amd import workload as wl
+    ms = synth.ModelShape(2, 256, 4, 2, 64, 512, 2048, 10000.0, dtype=dtype)
+    top, layers = _model(ms, 84, 0.08)
+    batch = synth.make_batch(84, np.array([rows - 10, 3, 4], np.int32), np.array([700, 0, 90], np.int32), 16, permute_pages=True)
+    tokens, q, ua, ur = synth.verify_side_inputs(84, ms.vocab, batch.gamma, sigma=0.5)
+    ver = wl.upload_model(ms, top, lambda l: layers[l])
+    kv = wl.KVCache(ms, batch.n_pages, 16)
+    db = wl.DeviceBatch(batch, tokens, q, ua, ur)
+    results = []
+    for fill in (0, 255):
+        ws = torch.full((ver.gs_workspace_bytes(db.n_rows, db.n_servers, db.max_ctx),), fill, dtype=torch.uint8, device="cuda:0")
+        out, logits, _ = wl.verify(ver, kv, db, workspace=ws)
+        torch.cuda.synchronize()
+        results.append([logits.cpu(), kv.k.float().cpu(), kv.v.float().cpu()] + [out[k].cpu() for k in sorted(out)])
+    for a, b in zip(*results):
+        assert torch.equal(a, b)

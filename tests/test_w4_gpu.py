@@ -117,13 +117,13 @@ def test_w4_scales_near_the_largest_number(rows, nonzero):
 
 
 def test_w4_wide_matrices_use_eight_waves():
-    # N / 128 >= 192 for gate/up (2F = 24576) and the LM head: the 8-wave launch shape
+    # 8 rows, gate/up (2F = 24576) fused, the LM head with 8 waves side by side
     ms = synth.ModelShape(1, 128, 2, 1, 64, 12288, 24576, 10000.0, dtype="bf16")
     _run(ms, 96, np.array([4, 2], np.int32), np.array([10, 40], np.int32), std=0.05)
 
 
 def test_w4_wide_matrices_with_more_than_64_rows():
-    # 68 rows and N / 512 >= 96 for gate/up (2F = 49152) and the LM head: 8 waves with two column tiles each
+    # 68 rows and 192 blocks of 256 columns for gate/up (2F = 49152) and the LM head: two column tiles per wave
     ms = synth.ModelShape(1, 128, 2, 1, 64, 24576, 49152, 10000.0, dtype="bf16")
     _run(ms, 97, np.array([16, 16, 16, 16], np.int32), np.array([10, 40, 0, 77], np.int32), std=0.05)
 
@@ -137,11 +137,28 @@ def test_w4_real_8b_widths():
 
 
 def test_w4_real_70b_widths():
-    """d 8192, QKV 10240, FFN 28672 (K up to 28672), vocab 128256; one layer, 98 rows (the kernel shape with two
-    column tiles per wave), 4096-token contexts."""
+    """d 8192, QKV 10240, FFN 28672 (K up to 28672), vocab 128256; one layer, 98 rows (tiles of 128 rows: 8 waves
+    with one column tile each), 4096-token contexts."""
     ms = dataclasses.replace(synth.LLAMA3_70B, n_layers=1)
     gamma = synth.uniform_int(synth.MASTER_SEED, ("cfg5", "gamma"), 2, 8, 16)
     _run(ms, 99, gamma, np.full(16, 4096, np.int32), std=0.02)
+
+
+def test_w4_real_70b_widths_up_to_96_rows():
+    """The same widths at 92 rows: two column tiles per wave, fused gate/up, K splits of 32 steps and more per K group."""
+    ms = dataclasses.replace(synth.LLAMA3_70B, n_layers=1)
+    gamma = synth.uniform_int(synth.MASTER_SEED, ("cfg5", "gamma"), 2, 8, 16)
+    for i in np.argsort(-gamma, kind="stable")[:int(gamma.sum()) + 16 - 92]:
+        gamma[i] -= 1
+    assert int(gamma.sum()) + 16 == 92
+    _run(ms, 88, gamma, np.full(16, 300, np.int32), std=0.02)
+
+
+@pytest.mark.parametrize("rows", [50, 65, 92])
+def test_w4_two_column_tiles_over_many_steps(rows):
+    # the register rings of the two-tile kernels go round: 8 steps per K group in the LM head, 4 or 8 in the fused gate/up
+    ms = synth.ModelShape(1, 1024, 2, 1, 64, 16640, 49152, 10000.0, dtype="bf16")
+    _run(ms, 91, np.array([rows - 3, 1], np.int32), np.array([9, 0], np.int32), std=0.03)
 
 
 def test_w4_shapes_are_validated():
