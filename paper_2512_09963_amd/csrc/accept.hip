@@ -491,10 +491,11 @@ __global__ __launch_bounds__(kTileThreads) void pick_token_kernel(const Decision
   int small_tile = 0;
   double small_prefix = 0.0;
   if (!fallback && small) {
-    // The lane in whose tiles the running sum crosses the target: at most one, because a lane's `before` is the previous
-    // lane's `incl` to the last bit.  Inside it the first tile that crosses, or, where the order of the additions leaves
-    // none, its last tile with mass; the nearest lane with mass below if it has none; the last mass of all if no lane
-    // crosses.  A tile without mass is never chosen.
+    // The first lane in whose tiles the running sum crosses the target.  A lane's `before` is the previous lane's `incl`
+    // to the last bit; a second lane can cross only where the rounding of the scan lets a later `incl` fall below an
+    // earlier one, and the first is taken then too.  Inside it the first tile that crosses, or, where the order of the
+    // additions leaves none, its last tile with mass; the nearest lane with mass below if it has none; the last mass of
+    // all if no lane crosses.  A tile without mass is never chosen.
     int cross = -1, last = -1;
     double run = before, cross_prefix = 0.0, last_prefix = 0.0;
 #pragma unroll

@@ -162,9 +162,11 @@ __device__ __forceinline__ void item_of_workgroup(int wg, int n_items, int n_kv,
   kh = item - entry * n_kv;
 }
 
-// cache policy of the K/V loads (the builtin's last argument; bit 1 = non-temporal): a step reads its keys and
-// values once, so they should not displace the partial results and the block tables in L2 (measured: config 4
-// 3.4 instead of 3.6 ms of attention per step, config 3 unchanged)
+// cache policy of the K/V loads (the builtin's last argument; bit 1 = non-temporal).  A block of one row tile reads its
+// keys and values once; they should not displace the partial results and the block tables in L2 (32 ragged servers:
+// 3.4 instead of 3.6 ms of attention per step, 8 servers unchanged).  The query groups of a long prompt each read all
+// of its keys, and the policy costs them nothing: 112 to 114 us per layer with and without it for a prompt of 2047
+// tokens, 15.4 with and without for 8 of 128; 149 with, 176 without for one of 256 beside 24 blocks on 8192.
 constexpr int kKvLoadPolicy = 2;
 
 __device__ __forceinline__ void wait_all_vector_loads() {
