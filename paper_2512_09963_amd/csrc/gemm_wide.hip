@@ -29,11 +29,13 @@
 //     the bound: 1.0 to 1.1 PFLOP/s, 1.25 to 1.3 on matrices of zeros, 1.86 with the global loads of the loop taken out
 //     (rates of a work copy at 2048 x 28672 x 4096; more weights or activations in flight change nothing)
 // Measured inside a verification step (us per launch; predecessor in brackets), N x K:
-//   53 rows   gate/up 28672 x 4096 39.7 (46.0) = 5.9 TB/s, LM head 128256 x 4096 181 (188)
-//   92 rows   gate/up 57344 x 8192 142 (181) = 6.6 TB/s, 8192 x 28672 and 8192 x 8192 55 (60) on average, 10240 x 8192
-//             35.7 (37.9), LM head 128256 x 8192 347 (455) = 6.1 TB/s
-//   324 rows  gate/up 28672 x 4096 82.7 (124) = 0.92 PFLOP/s, 4096 x 14336 and 4096 x 4096 33.6 (38) on average, 6144 x 4096
-//             25.0 (39), LM head 128256 x 4096 348 (440)
+//   50 rows    gate/up 28672 x 4096 38.4 (46.0) = 6.1 TB/s, LM head 128256 x 4096 179 (188)
+//   98 rows    gate/up 57344 x 8192 142 (181) = 6.6 TB/s, 8192 x 28672 and 8192 x 8192 55 (60) on average, 10240 x 8192
+//              36.4 (37.9), LM head 128256 x 8192 331 (455) = 6.3 TB/s
+//   312 rows   gate/up 28672 x 4096 81 to 86 (124) = 0.85 to 0.9 PFLOP/s, 4096 x 14336 and 4096 x 4096 33.2 (38) on average,
+//              6144 x 4096 28.3 (39), LM head 128256 x 4096 341 to 362 (440)
+//   1024 rows  gate/up 213 to 220, 4096 x 14336 109, 6144 x 4096 64.8, 4096 x 4096 43.6
+// (two figures: the same kernel on two machines; the matrix-bound launches are the ones that differ)
 #include "common.h"
 #include "device_types.h"
 #include "gemm_common.h"
