@@ -20,6 +20,7 @@
 #include "common.h"
 #include "attn_work.h"
 #include "device_types.h"
+#include "gemm_common.h"
 #include <algorithm>
 #include <cmath>
 
@@ -28,93 +29,131 @@ namespace {
 
 constexpr float kNegBig = -1.0e30f;
 
-
-__device__ __forceinline__ int server_of_row(const int* __restrict__ cu_rows, int n_servers, int r) {
-  int lo = 0, hi = n_servers;
-  while (hi - lo > 1) {
-    int mid = (lo + hi) >> 1;
-    if (cu_rows[mid] <= r) lo = mid; else hi = mid;
-  }
-  return lo;
-}
-
 // ------------------------------------------------------------------------------------------
-// fp32 path.  grid (R, H), 4 waves: a lane takes keys tid, tid + 256, ... with an online softmax of its own, then
-// the lanes' states meet: the maximum by lane swaps, the rescaled sums 32 channels at a time through LDS.
-// Latency bound (a few dozen rows and keys): one wave per (row, head) with a per-channel merge that formed
-// 64 exponentials per channel took 22 us at 69 keys and head size 64, this takes 13.
-// Writes attn_out [R][H*hd].
+// fp32 path.  grid (R, H), 4 waves, kRowKeys keys at a time.  Scores: 16 lanes share a key (a lane has HD / 16 of its
+// channels, the sum is four row moves).  Output: a lane has the keys 4 i .. 4 i + 3 of HD / 64 channels, so that both
+// products read memory in whole lines; the four lanes of a channel are neighbours.  Latency bound (a few dozen rows and
+// keys): all loads of K and V of a chunk are issued before the first score, so a chunk costs two dependent trips to memory
+// (pages, then K and V), and the softmax state is formed by every wave for itself from the scores in LDS.  A lane per key
+// with the lanes' states merged at the end took 13.6 us at 16 rows of 4 heads, 69 keys and head size 64, this takes 6.9.
+// VEC: 16-byte loads (16-byte aligned pages, page size a multiple of 4).  Writes attn_out [R][H*hd].
 // ------------------------------------------------------------------------------------------
 constexpr int kRowThreads = 256;
-template <int HD>
+constexpr int kRowKeys = 128;
+__device__ __forceinline__ float wave_max(float v) {
+  v = row16_max(v);
+  v = fmaxf(v, __shfl_xor(v, 16));
+  return fmaxf(v, __shfl_xor(v, 32));
+}
+__device__ __forceinline__ float wave_sum(float v) {
+  v = row16_sum(v);
+  v += __shfl_xor(v, 16);
+  return v + __shfl_xor(v, 32);
+}
+template <int HD, bool VEC>
 __global__ __launch_bounds__(kRowThreads) void attn_rowwise_kernel(const float* __restrict__ q,
                                                                    const float* __restrict__ k_pages,
                                                                    const float* __restrict__ v_pages,
                                                                    const int* __restrict__ block_table, int max_blocks,
+                                                                   const int4* __restrict__ row_info,
                                                                    const int* __restrict__ cu_rows,
-                                                                   const int* __restrict__ ctx_len, int n_servers,
+                                                                   const int* __restrict__ ctx_len,
                                                                    int page_size, int n_heads, int n_kv,
                                                                    float* __restrict__ attn_out) {
-  const int r = blockIdx.x, h = blockIdx.y, tid = threadIdx.x;
-  const int srv = server_of_row(cu_rows, n_servers, r);
+  constexpr int C4 = HD / 64;                // groups of 4 channels of a lane (scores); channels of a lane (output)
+  constexpr int KP = kRowKeys / 16;          // passes over the keys of a chunk: 16 keys each
+  const int r = blockIdx.x, h = blockIdx.y, tid = threadIdx.x, lane = tid & 63;
+  const int srv = row_info[r].w;
   const int n_keys = ctx_len[srv] + (r - cu_rows[srv]) + 1;
   const int kh = h / (n_heads / n_kv);
-  __shared__ float qs[HD];
-  __shared__ float wave_m[kRowThreads / 64], wave_l[kRowThreads / 64];
-  __shared__ float part[kRowThreads][33];      // 32 channels of every lane (padded: conflict-free both ways)
-  __shared__ float sums[8][32];
-  for (int d = tid; d < HD; d += kRowThreads) qs[d] = q[((size_t)r * n_heads + h) * HD + d];
-  __syncthreads();
+  const int* bt = block_table + (size_t)srv * max_blocks;
+  __shared__ float score[kRowKeys], prob[kRowKeys];
+  const int kl = tid >> 4, cl = (tid & 15) * 4;      // scores: key of a pass, first channel
+  const int vq = (tid & 3) * 4, vd = tid >> 2;       // output: first key of a pass, channel
+  float4 qv[C4];
+#pragma unroll
+  for (int j = 0; j < C4; ++j) qv[j] = *reinterpret_cast<const float4*>(q + ((size_t)r * n_heads + h) * HD + j * 64 + cl);
   const float scale = 1.0f / sqrtf((float)HD);
   float m = kNegBig, l = 0.f;
-  float o[HD];
+  float o[C4];
 #pragma unroll
-  for (int d = 0; d < HD; ++d) o[d] = 0.f;
-  for (int key = tid; key < n_keys; key += kRowThreads) {
-    const int page = block_table[(size_t)srv * max_blocks + key / page_size];
-    const int slot = key % page_size;
-    const float* kp = k_pages + (((size_t)page * n_kv + kh) * page_size + slot) * HD;
-    float s = 0.f;
+  for (int j = 0; j < C4; ++j) o[j] = 0.f;
+  for (int base = 0; base < n_keys; base += kRowKeys) {
+    float4 kv[KP][C4], vv[KP][C4];
 #pragma unroll
-    for (int d = 0; d < HD; ++d) s = fmaf(qs[d], kp[d], s);
-    s *= scale;
-    const float m_new = fmaxf(m, s);
-    const float corr = expf(m - m_new), p = expf(s - m_new);
-    l = l * corr + p;
-    const float* vp = v_pages + ((size_t)page * n_kv + kh) * HD * page_size + slot;
+    for (int p = 0; p < KP; ++p) {
+      const int key = min(base + p * 16 + kl, n_keys - 1);      // (keys past the end re-read the last one)
+      const int blk = key / page_size;
+      const float* kp = k_pages + (((size_t)bt[blk] * n_kv + kh) * page_size + (key - blk * page_size)) * HD + cl;
 #pragma unroll
-    for (int d = 0; d < HD; ++d) o[d] = o[d] * corr + p * vp[(size_t)d * page_size];
-    m = m_new;
-  }
-  float M = m;
-  for (int off = 32; off > 0; off >>= 1) M = fmaxf(M, __shfl_xor(M, off));
-  if ((tid & 63) == 0) wave_m[tid >> 6] = M;
-  __syncthreads();
-  M = fmaxf(fmaxf(wave_m[0], wave_m[1]), fmaxf(wave_m[2], wave_m[3]));      // (key 0 exists: M is a score)
-  const float f = expf(m - M);       // 0 for a lane without keys
-  float L = l * f;
-  for (int off = 32; off > 0; off >>= 1) L += __shfl_xor(L, off);
-  if ((tid & 63) == 0) wave_l[tid >> 6] = L;
-  __syncthreads();
-  L = (wave_l[0] + wave_l[1]) + (wave_l[2] + wave_l[3]);
+      for (int j = 0; j < C4; ++j)
+        kv[p][j] = VEC ? *reinterpret_cast<const float4*>(kp + j * 64)
+                       : make_float4(kp[j * 64], kp[j * 64 + 1], kp[j * 64 + 2], kp[j * 64 + 3]);
+    }
 #pragma unroll
-  for (int d0 = 0; d0 < HD; d0 += 32) {
+    for (int p = 0; p < KP; ++p) {
+      const int key0 = base + p * 16 + vq;
 #pragma unroll
-    for (int d = 0; d < 32; ++d) part[tid][d] = o[d0 + d] * f;
-    __syncthreads();
-    const int d = tid & 31, grp = tid >> 5;
-    float acc = 0.f;
-#pragma unroll 8
-    for (int t = 0; t < 32; ++t) acc += part[grp * 32 + t][d];
-    sums[grp][d] = acc;
-    __syncthreads();
-    if (tid < 32) {
-      float s = sums[0][tid];
+      for (int j = 0; j < C4; ++j) vv[p][j] = make_float4(0.f, 0.f, 0.f, 0.f);
+      // four keys share a page where the page size is a multiple of 4; slots past the end hold stale data, never used
+      if constexpr (VEC) {
+        if (key0 < n_keys) {
+          const int blk = key0 / page_size;
+          const float* vp = v_pages + (((size_t)bt[blk] * n_kv + kh) * HD + vd) * page_size + (key0 - blk * page_size);
 #pragma unroll
-      for (int w = 1; w < 8; ++w) s += sums[w][tid];
-      attn_out[((size_t)r * n_heads + h) * HD + d0 + tid] = s / L;
+          for (int j = 0; j < C4; ++j) vv[p][j] = *reinterpret_cast<const float4*>(vp + (size_t)j * 64 * page_size);
+        }
+      } else {
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+          if (key0 + i < n_keys) {
+            const int blk = (key0 + i) / page_size;
+            const float* vp = v_pages + (((size_t)bt[blk] * n_kv + kh) * HD + vd) * page_size + (key0 + i - blk * page_size);
+#pragma unroll
+            for (int j = 0; j < C4; ++j) reinterpret_cast<float*>(&vv[p][j])[i] = vp[(size_t)j * 64 * page_size];
+          }
+      }
+    }
+#pragma unroll
+    for (int p = 0; p < KP; ++p) {
+      float s = 0.f;
+#pragma unroll
+      for (int j = 0; j < C4; ++j)
+        s += (qv[j].x * kv[p][j].x + qv[j].y * kv[p][j].y) + (qv[j].z * kv[p][j].z + qv[j].w * kv[p][j].w);
+      s = row16_sum(s);
+      if ((tid & 15) == 0) score[p * 16 + kl] = base + p * 16 + kl < n_keys ? s * scale : kNegBig;
     }
     __syncthreads();
+    // every wave forms the chunk's maximum and sum for itself; waves 0 and 1 store the weights
+    const float s0 = score[lane], s1 = score[64 + lane];
+    const float m_new = fmaxf(m, wave_max(fmaxf(s0, s1)));      // (a chunk has a key: m_new is a score)
+    const float corr = expf(m - m_new);
+    const float p0 = base + lane < n_keys ? expf(s0 - m_new) : 0.f, p1 = base + 64 + lane < n_keys ? expf(s1 - m_new) : 0.f;
+    l = l * corr + wave_sum(p0 + p1);
+    m = m_new;
+    if (tid < 64) prob[lane] = p0;
+    else if (tid < 128) prob[64 + lane] = p1;
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < C4; ++j) o[j] *= corr;
+#pragma unroll
+    for (int p = 0; p < KP; ++p)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const float w = prob[p * 16 + vq + i];
+        const bool has = base + p * 16 + vq + i < n_keys;      // (a weight of zero must not meet stale infinities)
+#pragma unroll
+        for (int j = 0; j < C4; ++j) o[j] = fmaf(w, has ? reinterpret_cast<const float*>(&vv[p][j])[i] : 0.f, o[j]);
+      }
+    // (the next chunk's scores are written after its loads; its barrier comes after all reads of prob here, and prob is
+    // written behind that barrier)
+  }
+#pragma unroll
+  for (int j = 0; j < C4; ++j) {
+    float v = o[j];
+    v += dpp_move<0xB1>(v);
+    v += dpp_move<0x4E>(v);
+    if ((tid & 3) == 0) attn_out[((size_t)r * n_heads + h) * HD + j * 64 + vd] = v / l;
   }
 }
 
@@ -722,12 +761,17 @@ gs_status launch_attention(int dtype, const void* q, const void* k_pages, const 
     const float* kf = static_cast<const float*>(k_pages);
     const float* vf = static_cast<const float*>(v_pages);
     float* of = static_cast<float*>(attn_out);
-    if (hd == 64)
-      attn_rowwise_kernel<64><<<grid, kRowThreads, 0, stream>>>(qf, kf, vf, block_table, max_blocks, cu_rows, ctx_len,
-                                                                n_servers, page_size, n_heads, n_kv, of);
-    else
-      attn_rowwise_kernel<128><<<grid, kRowThreads, 0, stream>>>(qf, kf, vf, block_table, max_blocks, cu_rows, ctx_len,
-                                                                 n_servers, page_size, n_heads, n_kv, of);
+    const bool vec = page_size % 4 == 0 && reinterpret_cast<uintptr_t>(k_pages) % 16 == 0 &&
+                     reinterpret_cast<uintptr_t>(v_pages) % 16 == 0;
+#define GS_ROWWISE(HD_, VEC_)                                                                                     \
+  attn_rowwise_kernel<HD_, VEC_><<<grid, kRowThreads, 0, stream>>>(qf, kf, vf, block_table, max_blocks,           \
+                                                                   static_cast<const int4*>(row_info), cu_rows, ctx_len, \
+                                                                   page_size, n_heads, n_kv, of)
+    if (hd == 64 && vec) GS_ROWWISE(64, true);
+    else if (hd == 64) GS_ROWWISE(64, false);
+    else if (vec) GS_ROWWISE(128, true);
+    else GS_ROWWISE(128, false);
+#undef GS_ROWWISE
     GS_LAUNCH_CHECK("attn_rowwise");
     return GS_OK;
   }
