@@ -45,11 +45,6 @@ __device__ __forceinline__ float wave_max(float v) {
   v = fmaxf(v, __shfl_xor(v, 16));
   return fmaxf(v, __shfl_xor(v, 32));
 }
-__device__ __forceinline__ float wave_sum(float v) {
-  v = row16_sum(v);
-  v += __shfl_xor(v, 16);
-  return v + __shfl_xor(v, 32);
-}
 template <int HD, bool VEC>
 __global__ __launch_bounds__(kRowThreads) void attn_rowwise_kernel(const float* __restrict__ q,
                                                                    const float* __restrict__ k_pages,

@@ -190,17 +190,22 @@ __global__ __launch_bounds__(64 * NW) void gemm_bf16_skinny_kernel(const bf16_t*
 
 // fp32 (v_mfma_f32_16x16x4_f32: fp32 products, fp32 sums).  The fp32 models are small (K of a few hundred, a few dozen
 // rows), so a launch is bound by the latency of its loads, not by a rate: what counts is that no wave walks
-// a long serial k chain and that enough waves run.  A workgroup's 8 waves are ks slices of K times 8 / ks column
-// tiles of 16; a wave takes 16 columns and MT * 16 rows straight from global memory (lane (g, c) reads 16 bytes
-// of row c at k + 4 g, the k order inside a 16-wide step being permuted alike in both operands), four steps in
-// flight, and the slices' sums meet in LDS in a fixed order.  2-layer model of width 256 / 1024 at 16 rows: the down
-// projection (K = 1024) 143 -> 6.3 us, the others 40 -> 4 us against one 64 x 64 tile per workgroup and no K split.
-// VEC: K % 4 == 0 and 16-byte aligned operands.  grid (column groups, row chunks of MT * 16).
+// a long serial k chain, that enough waves run, and how many launches a layer has.  A workgroup's 8 waves are ks slices of K
+// times 8 / ks column tiles of 16; a wave takes 16 columns and MT * 16 rows straight from global memory (lane (g, c) reads
+// 16 bytes of row c at k + 4 g, the k order inside a 16-wide step being permuted alike in both operands), two to eight steps
+// in flight, and the slices' sums meet in LDS in a fixed order.  2-layer model of width 256 / 1024 at 16 rows: a plain launch
+// 4 us, with the rotation or the SwiGLU and the rows' factors 5.7, the residual forms 4.6 (K = 256) and 6 (K = 1024); the whole
+// step 86 -> 76 us against separate kernels for norms, rotation and SwiGLU (25 launches, 16 now).
+// grid (column groups, row chunks of MT * 16).
 constexpr int kF32Waves = 8;
-template <bool VEC>
+// LOADS: kWholeSteps where K is a multiple of 16 and the operands are 16-byte aligned, kVec4 where K is a multiple of 4,
+// kElements otherwise.
+enum { kElements = 0, kVec4 = 1, kWholeSteps = 2 };
+template <int LOADS>
 __device__ __forceinline__ float4 load4_f32(const float* __restrict__ row, int k, int K) {
+  if constexpr (LOADS == kWholeSteps) return *reinterpret_cast<const float4*>(row + k);
   float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-  if constexpr (VEC) {
+  if constexpr (LOADS == kVec4) {
     if (k < K) v = *reinterpret_cast<const float4*>(row + k);
   } else {
     if (k + 0 < K) v.x = row[k + 0];
@@ -210,70 +215,157 @@ __device__ __forceinline__ float4 load4_f32(const float* __restrict__ row, int k
   }
   return v;
 }
-template <int MT, bool VEC>
+// MODE: kF32Plain stores Y [M][N].  The others (gemm_common.h; up to 64 rows, one row chunk) take pairs of column tiles, or
+// whole tiles, through LDS: kF32Qkv and kF32GateUp, whose input rows still need their factor, the two halves of a head's
+// rotation pairs and the gate and up tile of 16 features, kF32Residual the tiles of the residual stream.
+enum { kF32Plain = 0, kF32Qkv = 1, kF32GateUp = 2, kF32Residual = 3 };
+template <int MT, int LOADS, int MODE>
 __global__ __launch_bounds__(64 * kF32Waves) void gemm_f32_kernel(const float* __restrict__ X,
                                                                   const float* __restrict__ W, float* __restrict__ Y,
-                                                                  int M, int N, int K, int ks, int k_per) {
+                                                                  int M, int N, int K, int ks_log2, int k_per, RowNorm norm,
+                                                                  QkvOut qkv, ResidualOut res) {
+  constexpr bool PAIRS = MODE == kF32Qkv || MODE == kF32GateUp;
   __shared__ float red[kF32Waves][MT * 256];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  __shared__ float factor[MT * 16];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int g = lane >> 4, c = lane & 15;
-  const int tiles_per_wg = kF32Waves / ks;
-  const int n0 = (blockIdx.x * tiles_per_wg + wave / ks) * 16, slice = wave % ks;
+  const int ks = 1 << ks_log2, tiles_per_wg = kF32Waves >> ks_log2;
+  const int tile = blockIdx.x * tiles_per_wg + (wave >> ks_log2), slice = wave & (ks - 1);
+  const int half_log2 = MODE == kF32Qkv ? (qkv.hd == 128 ? 2 : 1) : 0;      // 16-column tiles of half a head
+  // first column of a tile; tiles 2 p and 2 p + 1 of a pair
+  auto first_column = [&](int t) {
+    if constexpr (MODE == kF32Qkv) {
+      const int pair = t >> 1, head = pair >> half_log2;
+      return head * qkv.hd + (pair - (head << half_log2)) * 16 + (t & 1) * (qkv.hd >> 1);
+    } else if constexpr (MODE == kF32GateUp) {
+      return (t >> 1) * 16 + (t & 1) * (N >> 1);
+    } else {
+      return t * 16;
+    }
+  };
+  const int n0 = first_column(tile);
   const int m0 = blockIdx.y * (MT * 16);
   const int k_begin = slice * k_per, k_end = min(K, k_begin + k_per);
+  RowFactors<MT * 16, kF32Waves> factors;
+  if constexpr (PAIRS) factors.load(norm, wave, lane, m0, M - m0);
+  // what the epilogue needs from memory for this lane's first element, fetched before the products
+  const int e_t = tid / (MT * 256), e_o = tid - e_t * (MT * 256), e_row = m0 + (e_o >> 4);
+  int4 e_slot = make_int4(0, 0, 0, 0);
+  float2 e_rope = make_float2(0.f, 0.f), e_res = e_rope;
+  if constexpr (MODE == kF32Qkv) {
+    const int pair = blockIdx.x * (tiles_per_wg / 2) + e_t;
+    if (e_t < tiles_per_wg / 2 && e_row < M && pair * 32 < N) {
+      e_slot = qkv.row_slot[e_row];
+      e_rope = qkv.rope[(size_t)e_row * (qkv.hd >> 1) + (pair & ((1 << half_log2) - 1)) * 16 + (e_o & 15)];
+    }
+  }
+  if constexpr (MODE == kF32Residual) {
+    const int col = (blockIdx.x * tiles_per_wg + e_t) * 16 + (e_o & 15);
+    if (e_t < tiles_per_wg && e_row < M && col < N) e_res = make_float2(res.x[(size_t)e_row * N + col], res.norm[col]);
+  }
   // rows and columns past the end re-read the last one; their sums are not stored
   const float* wrow = W + (size_t)min(n0 + c, N - 1) * K;
   const float* xrow[MT];
 #pragma unroll
   for (int mt = 0; mt < MT; ++mt) xrow[mt] = X + (size_t)min(m0 + mt * 16 + c, M - 1) * K;
-  floatx4_t acc[MT];
+  // MT = 1: four accumulators, so that a product does not wait for the one before it
+  constexpr int CHAINS = MT == 1 ? 4 : 1;
+  floatx4_t part[MT][CHAINS];
 #pragma unroll
-  for (int mt = 0; mt < MT; ++mt) acc[mt] = floatx4_t{0.f, 0.f, 0.f, 0.f};
-  constexpr int U = MT == 4 ? 2 : 4;      // steps in flight
-  for (int k0 = k_begin; k0 < k_end; k0 += 16 * U) {
-    float4 w[U], x[U][MT];
+  for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+    for (int j = 0; j < CHAINS; ++j) part[mt][j] = floatx4_t{0.f, 0.f, 0.f, 0.f};
+  constexpr int U = MT == 4 ? 2 : MT == 2 ? 4 : 8;      // steps in flight
+  float4 w[U], x[U][MT];
+  auto load_steps = [&](int k0) {
 #pragma unroll
     for (int u = 0; u < U; ++u) {
+      // (a step past the slice's end is neither read nor used, or reads zeros: its bound is the slice's end)
+      if (LOADS == kWholeSteps && k0 + 16 * u >= k_end) break;
       const int k = k0 + 16 * u + 4 * g;
-      // (a step past the slice's end reads nothing: its bound is then the slice's end)
-      w[u] = load4_f32<VEC>(wrow, k, k_end);
+      w[u] = load4_f32<LOADS>(wrow, k, k_end);
 #pragma unroll
-      for (int mt = 0; mt < MT; ++mt) x[u][mt] = load4_f32<VEC>(xrow[mt], k, k_end);
+      for (int mt = 0; mt < MT; ++mt) x[u][mt] = load4_f32<LOADS>(xrow[mt], k, k_end);
     }
+  };
+  if (k_begin < k_end) load_steps(k_begin);
+  if constexpr (PAIRS) factors.store(norm, wave, lane, factor);
+  for (int k0 = k_begin; k0 < k_end; k0 += 16 * U) {
 #pragma unroll
     for (int u = 0; u < U; ++u)
+      if (LOADS != kWholeSteps || k0 + 16 * u < k_end)
 #pragma unroll
-      for (int mt = 0; mt < MT; ++mt) {
-        acc[mt] = __builtin_amdgcn_mfma_f32_16x16x4f32(x[u][mt].x, w[u].x, acc[mt], 0, 0, 0);
-        acc[mt] = __builtin_amdgcn_mfma_f32_16x16x4f32(x[u][mt].y, w[u].y, acc[mt], 0, 0, 0);
-        acc[mt] = __builtin_amdgcn_mfma_f32_16x16x4f32(x[u][mt].z, w[u].z, acc[mt], 0, 0, 0);
-        acc[mt] = __builtin_amdgcn_mfma_f32_16x16x4f32(x[u][mt].w, w[u].w, acc[mt], 0, 0, 0);
-      }
+        for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+          for (int j = 0; j < 4; ++j)
+            part[mt][j % CHAINS] = __builtin_amdgcn_mfma_f32_16x16x4f32(reinterpret_cast<const float*>(&x[u][mt])[j],
+                                                                        reinterpret_cast<const float*>(&w[u])[j], part[mt][j % CHAINS], 0, 0, 0);
+    if (k0 + 16 * U < k_end) load_steps(k0 + 16 * U);
   }
+  floatx4_t acc[MT];
+#pragma unroll
+  for (int mt = 0; mt < MT; ++mt) acc[mt] = CHAINS == 4 ? (part[mt][0] + part[mt][1]) + (part[mt][CHAINS - 2] + part[mt][CHAINS - 1]) : part[mt][0];
   // register i of lane (g, c) is row 4 g + i, column c of the tile
-  if (ks == 1) {
-    if (n0 + c < N) {
+  if constexpr (MODE == kF32Plain) {
+    if (ks == 1) {
+      if (n0 + c < N) {
 #pragma unroll
-      for (int mt = 0; mt < MT; ++mt)
+        for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const int row = m0 + mt * 16 + g * 4 + i;
-          if (row < M) Y[(size_t)row * N + n0 + c] = acc[mt][i];
-        }
+          for (int i = 0; i < 4; ++i) {
+            const int row = m0 + mt * 16 + g * 4 + i;
+            if (row < M) Y[(size_t)row * N + n0 + c] = acc[mt][i];
+          }
+      }
+      return;
     }
-    return;
   }
 #pragma unroll
   for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
     for (int i = 0; i < 4; ++i) red[wave][(mt * 16 + g * 4 + i) * 16 + c] = acc[mt][i];
   __syncthreads();
+  // element o of tile t of the workgroup
+  auto sum_of = [&](int t, int o) {
+    float sum = red[t * ks][o];
+#pragma unroll
+    for (int s = 1; s < kF32Waves; ++s) sum += s < ks ? red[min(t * ks + s, kF32Waves - 1)][o] : 0.f;
+    return sum;
+  };
+  if constexpr (PAIRS) {
+    for (int e = tid; e < tiles_per_wg / 2 * MT * 256; e += 64 * kF32Waves) {
+      const int p = e / (MT * 256), o = e - p * (MT * 256);
+      const int row = m0 + (o >> 4), pair = blockIdx.x * (tiles_per_wg / 2) + p;
+      if (row >= M || pair * 32 >= N) continue;
+      const float f = factor[o >> 4], a = sum_of(2 * p, o) * f, b = sum_of(2 * p + 1, o) * f;
+      if constexpr (MODE == kF32GateUp) {
+        Y[(size_t)row * (N >> 1) + pair * 16 + (o & 15)] = a / (1.0f + expf(-a)) * b;
+      } else {
+        const int head = pair >> half_log2, i = (pair - (head << half_log2)) * 16 + (o & 15);
+        const bool first = e == tid;
+        store_qkv_pair<float>(qkv, row, head, i, a, b, first ? e_slot : qkv.row_slot[row],
+                              first ? e_rope : qkv.rope[(size_t)row * (qkv.hd >> 1) + i]);
+      }
+    }
+    return;
+  }
   for (int e = tid; e < tiles_per_wg * MT * 256; e += 64 * kF32Waves) {
     const int t = e / (MT * 256), o = e - t * (MT * 256);
     const int row = m0 + (o >> 4), col = (blockIdx.x * tiles_per_wg + t) * 16 + (o & 15);
-    float sum = red[t * ks][o];
-    for (int s = 1; s < ks; ++s) sum += red[t * ks + s][o];
-    if (row < M && col < N) Y[(size_t)row * N + col] = sum;
+    const float sum = sum_of(t, o);
+    if constexpr (MODE == kF32Residual) {
+      float v = 0.f;
+      if (row < M && col < N) {
+        const float2 xn = e == tid ? e_res : make_float2(res.x[(size_t)row * N + col], res.norm[col]);
+        v = xn.x + sum;
+        res.x[(size_t)row * N + col] = v;
+        static_cast<float*>(res.h)[(size_t)row * N + col] = v * xn.y;
+      }
+      const float sq = row16_sum(v * v);      // (16 lanes share a row and a tile)
+      if ((o & 15) == 0 && row < M && col < N) res.squares[(size_t)row * (N >> 4) + (col >> 4)] = sq;
+    } else {
+      if (row < M && col < N) Y[(size_t)row * N + col] = sum;
+    }
   }
 }
 
@@ -422,26 +514,64 @@ gs_status launch_gemm_stats(const void* X, const void* W, float* Y, void* stats,
   return GS_OK;
 }
 
-static void launch_f32(const float* x, const float* w, float* y, int M, int N, int K, hipStream_t stream) {
+template <int MODE>
+static void launch_f32(const float* x, const float* w, float* y, int M, int N, int K, const RowNorm& norm, const QkvOut& qkv,
+                       const ResidualOut& res, hipStream_t stream) {
   const int mt = M <= 16 ? 1 : M <= 32 ? 2 : 4;
   const int chunks = ceil_div(M, 16 * mt), tiles = ceil_div(N, 16);
-  // K slices: doubled until the launch has a workgroup per CU, as long as a slice keeps a 16-wide step of its own
-  int ks = 1;
-  while (ks < kF32Waves && ceil_div(tiles, kF32Waves / ks) * chunks < 256 && 32 * ks <= K) ks *= 2;
+  // K slices: doubled until the launch has a workgroup per CU, as long as a slice keeps a 16-wide step of its own (and a
+  // workgroup that takes pairs of tiles has two)
+  constexpr int kMost = MODE == kF32Qkv || MODE == kF32GateUp ? kF32Waves / 2 : kF32Waves;
+  int ks_log2 = 0;
+  while ((1 << ks_log2) < kMost && ceil_div(tiles, kF32Waves >> ks_log2) * chunks < 256 && (32 << ks_log2) <= K) ++ks_log2;
+  const int ks = 1 << ks_log2;
   const int k_per = ceil_div(ceil_div(K, ks), 16) * 16;
   const dim3 grid(ceil_div(tiles, kF32Waves / ks), chunks);
-  const bool vec = K % 4 == 0 && reinterpret_cast<uintptr_t>(x) % 16 == 0 && reinterpret_cast<uintptr_t>(w) % 16 == 0;
-#define GS_F32(MT_, VEC_) gemm_f32_kernel<MT_, VEC_><<<grid, 64 * kF32Waves, 0, stream>>>(x, w, y, M, N, K, ks, k_per)
-  if (vec) {
-    if (mt == 1) GS_F32(1, true);
-    else if (mt == 2) GS_F32(2, true);
-    else GS_F32(4, true);
+  const bool aligned = reinterpret_cast<uintptr_t>(x) % 16 == 0 && reinterpret_cast<uintptr_t>(w) % 16 == 0;
+#define GS_F32(MT_, LOADS_) \
+  gemm_f32_kernel<MT_, LOADS_, MODE><<<grid, 64 * kF32Waves, 0, stream>>>(x, w, y, M, N, K, ks_log2, k_per, norm, qkv, res)
+#define GS_F32_ROWS(LOADS_)           \
+  if (mt == 1) GS_F32(1, LOADS_);     \
+  else if (mt == 2) GS_F32(2, LOADS_); \
+  else GS_F32(4, LOADS_);
+  if (aligned && K % 16 == 0) {
+    GS_F32_ROWS(kWholeSteps)
+  } else if (aligned && K % 4 == 0) {
+    GS_F32_ROWS(kVec4)
   } else {
-    if (mt == 1) GS_F32(1, false);
-    else if (mt == 2) GS_F32(2, false);
-    else GS_F32(4, false);
+    GS_F32_ROWS(kElements)
   }
+#undef GS_F32_ROWS
 #undef GS_F32
+}
+
+// Whether a block of M rows runs a layer in the launches below (see RowNorm).  fp32: one row chunk; the tiles of the QKV
+// and gate/up projections come in pairs, the sums of squares in whole 16-byte loads.
+bool rows_fused(int dtype, int M, int d, int F) {
+  if (M <= 0 || d > kRowNormMaxWidth || d % 64 != 0) return false;
+  if (dtype == GS_F32) return M <= 64 && F % 16 == 0;
+  return false;
+}
+gs_status launch_rows_qkv(int dtype, const void* h, const void* w, const RowNorm& norm, const QkvOut& out, int M, int K,
+                          hipStream_t stream) {
+  const int N = (out.n_heads + 2 * out.n_kv) * out.hd;
+  launch_f32<kF32Qkv>(static_cast<const float*>(h), static_cast<const float*>(w), nullptr, M, N, K, norm, out, ResidualOut{}, stream);
+  GS_LAUNCH_CHECK("rows_qkv");
+  return GS_OK;
+}
+gs_status launch_rows_gate_up(int dtype, const void* h, const void* w, const RowNorm& norm, void* act, int M, int F, int K,
+                              hipStream_t stream) {
+  launch_f32<kF32GateUp>(static_cast<const float*>(h), static_cast<const float*>(w), static_cast<float*>(act), M, 2 * F, K, norm,
+                         QkvOut{}, ResidualOut{}, stream);
+  GS_LAUNCH_CHECK("rows_gate_up");
+  return GS_OK;
+}
+gs_status launch_rows_residual(int dtype, const void* in, const void* w, const ResidualOut& out, int M, int N, int K,
+                               hipStream_t stream) {
+  launch_f32<kF32Residual>(static_cast<const float*>(in), static_cast<const float*>(w), nullptr, M, N, K, RowNorm{}, QkvOut{}, out,
+                           stream);
+  GS_LAUNCH_CHECK("rows_residual");
+  return GS_OK;
 }
 
 // P [splits][M][N] fp32 partial sums of X [M][K] * W[N][K]^T (W tile-packed for bf16, packed 4-bit for
@@ -457,7 +587,7 @@ gs_status launch_gemm(int dtype, const void* X, const void* W, float* P, int M, 
     launch_skinny<false>(p, x, w, P, M, N, K, nullptr, 0, stream);
     GS_LAUNCH_CHECK("gemm_bf16");
   } else {
-    launch_f32(static_cast<const float*>(X), static_cast<const float*>(W), P, M, N, K, stream);
+    launch_f32<kF32Plain>(static_cast<const float*>(X), static_cast<const float*>(W), P, M, N, K, RowNorm{}, QkvOut{}, ResidualOut{}, stream);
     GS_LAUNCH_CHECK("gemm_f32");
   }
   return GS_OK;

@@ -34,6 +34,82 @@ __device__ __forceinline__ float row16_sum(float v) {
   return v + dpp_move<0x140>(v);
 }
 
+// Sum over a wave, the same on every lane.
+__device__ __forceinline__ float wave_sum(float v) {
+  v = row16_sum(v);
+  v += __shfl_xor(v, 16);
+  return v + __shfl_xor(v, 32);
+}
+
+// Blocks of a few rows run a layer in five launches: the norms and the rotation are part of the projections.  The projection
+// that completes the residual stream x stores h = x * norm weight, not yet divided by the row's root mean square (one rounding
+// to the storage type, as with the division), and the sums of x^2 over its 16-column tiles; the projection that reads h forms
+// the row's factor from those sums while its first weights are on their way, and applies it to its own sums.
+struct RowNorm {       // input side: x^2 sums [rows][blocks], blocks = d / 16
+  const float* squares;
+  int blocks;
+  float inv_d, eps;
+};
+struct QkvOut {        // rotated Q [rows][heads][hd], K and V into the pages (rope_append_kernel)
+  const int4* row_slot;
+  const float2* rope;
+  void* q;
+  void* k_pages;
+  void* v_pages;
+  int page_size, n_heads, n_kv, hd;
+};
+struct ResidualOut {   // x += result; h = x * norm (of the next projection's input); squares as in RowNorm
+  float* x;
+  const float* norm;
+  void* h;
+  float* squares;
+};
+constexpr int kRowNormMaxWidth = 8192;      // d: eight 16-byte loads per lane
+
+// Row factors of a workgroup's rows, 16 lanes to a row (their sum is four row moves): load() early, store() into LDS where the
+// loads may be waited for.  Branch-free loads, so that the wait does not cover the loads issued after them.
+template <int ROWS, int WAVES>
+struct RowFactors {
+  static constexpr int PASSES = (ROWS + 4 * WAVES - 1) / (4 * WAVES), J = kRowNormMaxWidth / 1024;
+  float4 v[PASSES][J];
+  __device__ __forceinline__ void load(const RowNorm& n, int wave, int lane, int m0, int rows) {
+#pragma unroll
+    for (int p = 0; p < PASSES; ++p) {
+      const float* src = n.squares + (size_t)(m0 + min((p * WAVES + wave) * 4 + (lane >> 4), rows - 1)) * n.blocks;
+#pragma unroll
+      for (int j = 0; j < J; ++j) v[p][j] = *reinterpret_cast<const float4*>(src + min((lane & 15) * 4 + j * 64, n.blocks - 4));
+    }
+  }
+  __device__ __forceinline__ void store(const RowNorm& n, int wave, int lane, float* factor) {
+#pragma unroll
+    for (int p = 0; p < PASSES; ++p) {
+      float s = 0.f;
+#pragma unroll
+      for (int j = 0; j < J; ++j)
+        s += (lane & 15) * 4 + j * 64 < n.blocks ? (v[p][j].x + v[p][j].y) + (v[p][j].z + v[p][j].w) : 0.f;
+      s = row16_sum(s);
+      const int row = (p * WAVES + wave) * 4 + (lane >> 4);
+      if ((lane & 15) == 0 && row < ROWS) factor[row] = 1.0f / sqrtf(s * n.inv_d + n.eps);
+    }
+  }
+};
+
+// Rotates and stores the pair (a, b) = elements (i, i + hd / 2) of a head of the fused QKV result.
+template <typename T>
+__device__ __forceinline__ void store_qkv_pair(const QkvOut& o, int row, int head, int i, float a, float b, const int4& ps, const float2& cs) {
+  const int half = o.hd >> 1;
+  if (head < o.n_heads + o.n_kv) {
+    T* dst = head < o.n_heads ? static_cast<T*>(o.q) + ((size_t)row * o.n_heads + head) * o.hd
+                              : static_cast<T*>(o.k_pages) + (((size_t)ps.x * o.n_kv + (head - o.n_heads)) * o.page_size + ps.y) * o.hd;
+    Storage<T>::store(dst + i, a * cs.x - b * cs.y);
+    Storage<T>::store(dst + i + half, b * cs.x + a * cs.y);
+  } else {
+    T* dst = static_cast<T*>(o.v_pages) + ((size_t)ps.x * o.n_kv + (head - o.n_heads - o.n_kv)) * o.hd * o.page_size + ps.y;
+    Storage<T>::store(dst + (size_t)i * o.page_size, a);
+    Storage<T>::store(dst + (size_t)(i + half) * o.page_size, b);
+  }
+}
+
 // Launch of gemm_bf16_wide_kernel: wm x wn waves of mt x nt tiles, kg groups of them, n_blocks column blocks.
 struct WidePlan {
   int wm, wn, kg, mt, nt, m_chunks, n_blocks, splits, k_per;
@@ -44,6 +120,9 @@ gs_status launch_wide(const WidePlan& p, const bf16_t* x, const bf16_t* w, float
                       hipStream_t stream);
 gs_status launch_wide_gate_up(const WidePlan& p, const bf16_t* x, const bf16_t* w, bf16_t* act, int M, int N, int K,
                               hipStream_t stream);
+// h not yet divided by its root mean square: up to 16 rows
+gs_status launch_wide_gate_up_norm(const WidePlan& p, const bf16_t* x, const bf16_t* w, const RowNorm& norm, bf16_t* act, int M,
+                                   int N, int K, hipStream_t stream);
 gs_status launch_wide_stats(const WidePlan& p, const bf16_t* x, const bf16_t* w, float* y, float2* stats, int M, int N,
                             int K, hipStream_t stream);
 

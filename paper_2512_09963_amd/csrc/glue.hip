@@ -103,7 +103,7 @@ __global__ __launch_bounds__(1024) void add_rmsnorm_kernel(float* __restrict__ x
 // Everything of a step that precedes the first projection, in one launch (five dependent-looking launches of 3 to 17 us
 // otherwise: 27 us of a 53-row step, 6 now; the roles are independent of each other).  Workgroups by index:
 //   [0, R)       embedding row r into the residual stream (storage type -> fp32, 4 elements per lane and pass) and its
-//                first RMSNorm h[r] = x[r] * w / sqrt(mean(x[r]^2) + eps)
+//                first RMSNorm h[r] = x[r] * w / sqrt(mean(x[r]^2) + eps), or x[r] * w and the row's sum of squares
 //   [R, 2 R)     per-row facts that every layer shares: where the row's K/V go (page, slot), how many keys its attention
 //                query group (group_tokens consecutive tokens of the block) sees, and the rotary sine/cosine of its
 //                position, rope [R][hd/2] (cos, sin).  The angle pos * theta^(-2i/hd) reaches thousands of radians: it
@@ -123,6 +123,7 @@ struct StepBegin {
   float2* rope;
   int* draft_tokens;
   int* attn_work;
+  float* squares;      // or null: h complete
   double log2_theta;
   float eps;
   int n_rows, d, vocab, n_servers, max_blocks, page_size, hd, group_tokens, steps_per_split, work_capacity;
@@ -153,7 +154,11 @@ __global__ __launch_bounds__(kWorkThreads) void step_begin_kernel(StepBegin a) {
       ss += (v.x * v.x + v.y * v.y) + (v.z * v.z + v.w * v.w);
     }
     const float tot = block_sum(ss, reinterpret_cast<float*>(shared));
-    const float inv = 1.0f / sqrtf(tot / (float)a.d + a.eps);
+    float inv = 1.0f / sqrtf(tot / (float)a.d + a.eps);
+    if (a.squares) {      // the row's factor is left to the projection that reads h (RowNorm)
+      inv = 1.0f;
+      for (int i = tid; i < a.d >> 4; i += kWorkThreads) a.squares[(size_t)r * (a.d >> 4) + i] = i == 0 ? tot : 0.f;
+    }
     for (int i = tid; i < d4; i += kWorkThreads) {
       const float4 v = i == tid ? v0 : xr[i], w = i == tid ? w0 : wr[i];
       Storage<T>::store(hr + 4 * i + 0, v.x * inv * w.x);
@@ -265,9 +270,9 @@ gs_status launch_step_begin(int dtype, const void* embed, const int* tokens, flo
                             int n_rows, int d, int vocab, const int* cu_rows, const int* ctx_len, int n_servers,
                             const int* block_table, int max_blocks, int page_size, int hd, float rope_theta,
                             int group_tokens, int steps_per_split, int work_capacity, bool work_list, void* row_slot,
-                            void* rope, int* draft_tokens, int* attn_work, hipStream_t stream) {
+                            void* rope, int* draft_tokens, int* attn_work, float* squares, hipStream_t stream) {
   const StepBegin a{embed, tokens, x, norm, h, cu_rows, ctx_len, block_table, static_cast<int4*>(row_slot),
-                    static_cast<float2*>(rope), draft_tokens, attn_work, log2((double)rope_theta), eps, n_rows, d, vocab,
+                    static_cast<float2*>(rope), draft_tokens, attn_work, squares, log2((double)rope_theta), eps, n_rows, d, vocab,
                     n_servers, max_blocks, page_size, hd, group_tokens, steps_per_split, work_capacity};
   const unsigned grid = 2u * (unsigned)n_rows + (work_list ? 1u : 0u);
   GS_DISPATCH_T(dtype, step_begin_kernel<T><<<grid, kWorkThreads, 0, stream>>>(a);)

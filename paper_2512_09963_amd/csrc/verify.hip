@@ -8,6 +8,7 @@
 #include <new>
 #include <vector>
 #include "common.h"
+#include "gemm_common.h"
 
 namespace gs {
 
@@ -19,11 +20,18 @@ gs_status launch_pack_weight_w4(const void* q, const void* scales, const void* z
 gs_status launch_gemm(int dtype, const void* X, const void* W, float* P, int M, int N, int K, hipStream_t stream);
 bool gate_up_fused(int dtype, int M, int F, int K);
 gs_status launch_gemm_gate_up(int dtype, const void* X, const void* W, void* act, int M, int F, int K, hipStream_t stream);
+bool rows_fused(int dtype, int M, int d, int F);
+gs_status launch_rows_qkv(int dtype, const void* h, const void* w, const RowNorm& norm, const QkvOut& out, int M, int K,
+                          hipStream_t stream);
+gs_status launch_rows_gate_up(int dtype, const void* h, const void* w, const RowNorm& norm, void* act, int M, int F, int K,
+                              hipStream_t stream);
+gs_status launch_rows_residual(int dtype, const void* in, const void* w, const ResidualOut& out, int M, int N, int K,
+                               hipStream_t stream);
 gs_status launch_step_begin(int dtype, const void* embed, const int* tokens, float* x, const float* norm, float eps, void* h,
                             int n_rows, int d, int vocab, const int* cu_rows, const int* ctx_len, int n_servers,
                             const int* block_table, int max_blocks, int page_size, int hd, float rope_theta,
                             int group_tokens, int steps_per_split, int work_capacity, bool work_list, void* row_slot,
-                            void* rope, int* draft_tokens, int* attn_work, hipStream_t stream);
+                            void* rope, int* draft_tokens, int* attn_work, float* squares, hipStream_t stream);
 gs_status launch_add_rmsnorm(int dtype, float* x, const float* partial, int n_splits, int n_rows, const float* w,
                              float eps, void* h, int d, hipStream_t stream);
 gs_status launch_rope_append(int dtype, const float* qkv, int n_splits, int n_rows, const void* row_slot,
@@ -92,6 +100,7 @@ struct Plan {
   int attn_work_capacity;
   void* accept_ws;
   size_t accept_bytes;
+  float* squares;   // [R][d / 16] sums of x^2 (few rows, see RowNorm)
   void* lm_stats;   // [R][column blocks] (max, sum exp) pairs from the LM-head projection's epilogue
   size_t bytes;
 };
@@ -117,6 +126,8 @@ size_t max_partial_floats(const gs_ctx* ctx, int max_rows) {
   for (int tiles = (int)best.size(); tiles <= max_rows / 16; ++tiles) best.push_back(std::max(best.back(), floats(16 * tiles)));
   return max_rows % 16 ? std::max(best[max_rows / 16], floats(max_rows)) : best[max_rows / 16];
 }
+
+constexpr int kMaxFusedRows = 64;      // rows_fused never accepts more
 
 Plan make_plan(const gs_ctx* ctx, int max_rows, int max_servers, int max_ctx, void* ws) {
   const gs_model_desc& m = ctx->desc;
@@ -145,6 +156,7 @@ Plan make_plan(const gs_ctx* ctx, int max_rows, int max_servers, int max_ctx, vo
   for (int n = 1; n <= max_servers; ++n) p.accept_bytes = std::max(p.accept_bytes, gs::accept_min_bytes(n, max_rows, m.vocab));
   p.accept_ws = c.take<char>(p.accept_bytes);
   p.lm_stats = c.take<float>(2 * R * (size_t)(m.vocab / 64 + 1));     // at least 64 columns per block
+  p.squares = c.take<float>((size_t)std::min(max_rows, kMaxFusedRows) * (m.d_model / 16));
   p.bytes = c.used();
   return p;
 }
@@ -426,6 +438,8 @@ extern "C" gs_status gs_verify_batch(gs_ctx* ctx, const gs_kv_cache* kv, const g
   const long attn_items = gs::attention_items(n, b->gamma_host, b->ctx_len_host, group_tokens, attn_sps);
   if (attn_items > p.attn_work_capacity) return gs::fail(GS_ECAPACITY, "attention work list overflow");
 
+  const bool fused = gs::rows_fused(m.dtype, rows, d, F);      // norms, rotation and residual inside the projections
+  const gs::RowNorm norm{p.squares, d / 16, 1.0f / (float)d, m.rms_eps};
   StageTimer timer(ctx, stream);
 #define GS_STAGE(stage, call)   \
   do {                          \
@@ -436,23 +450,38 @@ extern "C" gs_status gs_verify_batch(gs_ctx* ctx, const gs_kv_cache* kv, const g
   GS_STAGE(GS_STAGE_GLUE, gs::launch_step_begin(act, ctx->embed, b->tokens, p.x, ctx->norm1[0], m.rms_eps, p.h, rows, d, m.vocab,
                                                 b->cu_rows, b->ctx_len, n, b->block_table, b->max_blocks, kv->page_size,
                                                 m.head_dim, m.rope_theta, group_tokens, attn_sps, p.attn_work_capacity,
-                                                act == GS_BF16, p.row_slot, p.rope, p.draft_tokens, p.attn_work, stream));
+                                                act == GS_BF16, p.row_slot, p.rope, p.draft_tokens, p.attn_work,
+                                                fused ? p.squares : nullptr, stream));
   const float* pending = nullptr;   // split-K partials of the projection whose result is still to be added to x
   int pending_splits = 0;
   for (int l = 0; l < m.n_layers; ++l) {
-    if (l > 0)      // (the first norm comes with the embedding)
+    if (l > 0 && !fused)      // (the first norm comes with the embedding)
       GS_STAGE(GS_STAGE_GLUE, gs::launch_add_rmsnorm(act, p.x, pending, pending_splits, rows, ctx->norm1[l], m.rms_eps, p.h, d, stream));
     if (ctx->residual_trace)   // residual stream entering layer l (complete once the pending partials are added)
       GS_HIP_CHECK(hipMemcpyAsync(ctx->residual_trace + (size_t)l * rows * d, p.x, sizeof(float) * rows * d,
                                   hipMemcpyDeviceToDevice, stream));
-    GS_STAGE(GS_STAGE_GEMM, gs::launch_gemm(m.dtype, p.h, ctx->wqkv[l], p.partial, rows, qkv, d, stream));
     char* kl = static_cast<char*>(kv->k_pages) + layer_stride * l;
     char* vl = static_cast<char*>(kv->v_pages) + layer_stride * l;
-    GS_STAGE(GS_STAGE_GLUE, gs::launch_rope_append(act, p.partial, gs::gemm_splits(m.dtype, rows, qkv, d), rows, p.row_slot,
-                                  p.rope, kv->page_size, m.n_heads, m.n_kv_heads, m.head_dim, p.q, kl, vl, stream));
+    if (fused) {
+      const gs::QkvOut out{static_cast<const int4*>(p.row_slot), static_cast<const float2*>(p.rope), p.q, kl, vl, kv->page_size,
+                           m.n_heads, m.n_kv_heads, m.head_dim};
+      GS_STAGE(GS_STAGE_GEMM, gs::launch_rows_qkv(m.dtype, p.h, ctx->wqkv[l], norm, out, rows, d, stream));
+    } else {
+      GS_STAGE(GS_STAGE_GEMM, gs::launch_gemm(m.dtype, p.h, ctx->wqkv[l], p.partial, rows, qkv, d, stream));
+      GS_STAGE(GS_STAGE_GLUE, gs::launch_rope_append(act, p.partial, gs::gemm_splits(m.dtype, rows, qkv, d), rows, p.row_slot,
+                                    p.rope, kv->page_size, m.n_heads, m.n_kv_heads, m.head_dim, p.q, kl, vl, stream));
+    }
     GS_STAGE(GS_STAGE_ATTENTION, gs::launch_attention(act, p.q, kl, vl, b->block_table, b->max_blocks, b->cu_rows, b->ctx_len, n, rows,
                                 kv->page_size, m.n_heads, m.n_kv_heads, m.head_dim, attn_waves, attn_sps, attn_splits,
                                 attn_split, p.row_slot, p.attn_work, (int)attn_items, p.attn_scratch, p.attn, stream));
+    if (fused) {
+      const bool top = l + 1 == m.n_layers;
+      GS_STAGE(GS_STAGE_GEMM, gs::launch_rows_residual(m.dtype, p.attn, ctx->wo[l], {p.x, ctx->norm2[l], p.h, p.squares}, rows, d, hq, stream));
+      GS_STAGE(GS_STAGE_GEMM, gs::launch_rows_gate_up(m.dtype, p.h, ctx->wgu[l], norm, p.act, rows, F, d, stream));
+      GS_STAGE(GS_STAGE_GEMM, gs::launch_rows_residual(m.dtype, p.act, ctx->wd[l],
+                                                       {p.x, top ? ctx->final_norm : ctx->norm1[l + 1], p.h, p.squares}, rows, d, F, stream));
+      continue;
+    }
     GS_STAGE(GS_STAGE_GEMM, gs::launch_gemm(m.dtype, p.attn, ctx->wo[l], p.partial, rows, d, hq, stream));
     GS_STAGE(GS_STAGE_GLUE, gs::launch_add_rmsnorm(act, p.x, p.partial, gs::gemm_splits(m.dtype, rows, d, hq), rows,
                                                    ctx->norm2[l], m.rms_eps, p.h, d, stream));

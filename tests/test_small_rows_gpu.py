@@ -1,4 +1,5 @@
-"""Edges of the kernels that serve blocks of a few rows: the fp32 attention's chunks of 128 keys and its page sizes."""
+"""Edges of the kernels that serve blocks of a few rows: the fp32 attention (chunks of 128 keys, page sizes) and the layers of
+five launches (norms, rotation and residual inside the projections)."""
 import numpy as np
 import pytest
 
@@ -19,3 +20,20 @@ def test_f32_attention_chunks_and_page_sizes(hd, page, gamma, ctx):
     """Against the float64 oracle within 1e-4 of the row scale (float32 sums of at most a few hundred terms: about 1e-6)."""
     ms = synth.ModelShape(2, 4 * hd, 4, 2, hd, 384, 320, 10000.0, dtype="f32")
     _run_case(ms, 41 + page, np.array(gamma, np.int32), np.array(ctx, np.int32), page, 0.05)
+
+
+@pytest.mark.parametrize("d,heads,n_kv,hd,ffn,rows", [
+    (64, 1, 1, 64, 16, 2),             # the narrowest: 4 column tiles, one pair of gate and up
+    (64, 2, 1, 128, 48, 16),           # head size 128: 4 pairs of tiles a head; 16 rows: the last of one row tile
+    (128, 4, 2, 64, 400, 17),
+    (320, 4, 4, 64, 1040, 33),         # K of 20 steps in slices of unequal length
+    (192, 2, 2, 64, 72, 48),           # features that are no multiple of 16: the separate kernels
+    (100, 2, 1, 64, 64, 9),            # a width that is no multiple of 64: the separate kernels
+    (256, 4, 4, 64, 1024, 64),
+    (256, 4, 4, 64, 1024, 65),         # past the last fused row
+    (4160, 1, 1, 64, 32, 3),           # sums of squares in two loads per lane
+])
+def test_f32_layer_of_five_launches(d, heads, n_kv, hd, ffn, rows):
+    ms = synth.ModelShape(2, d, heads, n_kv, hd, ffn, 272, 10000.0, dtype="f32")
+    gamma = np.array([rows - 1 - rows // 3, rows // 3 - 1] if rows >= 3 else [rows - 1], np.int32)
+    _run_case(ms, 300 + rows, gamma, np.array([37, 5][:gamma.size], np.int32), 16, 0.06)
