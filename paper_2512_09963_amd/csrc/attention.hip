@@ -233,7 +233,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NW == 1
                                                          int n_heads, int n_kv, int steps_per_split,
                                                          int max_splits, float* __restrict__ partial_o,
                                                          float* __restrict__ partial_ml,
-                                                         bf16_t* __restrict__ attn_out) {
+                                                         bf16_t* __restrict__ attn_out, bool packed) {
   constexpr int KS = HD / 32;            // 1 KB loads per part
   constexpr int KK = HD / 16;            // k steps of the first product
   constexpr int DT = HD / 32;            // 32-channel tiles of the second product
@@ -486,12 +486,13 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NW == 1
   // ---- lane l holds query row l%32, channels 32 dt + 8 b + 4 h + (0..3)
   if (!my_ok) return;
   if (n_splits == 1) {      // the group is not split: the result is final
-    bf16_t* dst = attn_out + ((size_t)(row0 + my_j) * n_heads + kh * G + my_hg) * HD + 4 * h;
+    const int row = row0 + my_j, col0 = (kh * G + my_hg) * HD + 4 * h, width = n_heads * HD;
 #pragma unroll
     for (int dt = 0; dt < DT; ++dt)
 #pragma unroll
       for (int b = 0; b < 4; ++b)
-        *reinterpret_cast<uint2*>(dst + dt * 32 + b * 8) =
+        *reinterpret_cast<uint2*>(attn_out + (packed ? packed_index(row, col0 + dt * 32 + b * 8, width)
+                                                     : (size_t)row * width + col0 + dt * 32 + b * 8)) =
             make_uint2(pack_bf16x2(oacc[dt][4 * b] / l_run, oacc[dt][4 * b + 1] / l_run),
                        pack_bf16x2(oacc[dt][4 * b + 2] / l_run, oacc[dt][4 * b + 3] / l_run));
     return;
@@ -515,7 +516,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NW == 1
 template <int HD>
 __global__ void attn_combine_kernel(const float* __restrict__ partial_o, const float* __restrict__ partial_ml,
                                     int max_splits, int steps_per_split, const int4* __restrict__ row_info,
-                                    int n_heads, bf16_t* __restrict__ attn_out) {
+                                    int n_heads, bf16_t* __restrict__ attn_out, bool packed) {
   const size_t rh = blockIdx.x;
   const int d = threadIdx.x;
   const int n_keys = row_info[rh / n_heads].z;      // keys of the row's query group (per-row table of the step)
@@ -535,7 +536,8 @@ __global__ void attn_combine_kernel(const float* __restrict__ partial_o, const f
     acc = acc * c + o * f;
     M = Mn;
   }
-  attn_out[rh * HD + d] = float_to_bf16(acc / Lsum);
+  const int row = (int)(rh / n_heads);
+  attn_out[packed ? packed_index(row, (int)(rh - (size_t)row * n_heads) * HD + d, n_heads * HD) : rh * HD + d] = float_to_bf16(acc / Lsum);
 }
 
 }  // namespace
@@ -718,12 +720,12 @@ template <int HD, int G>
 static gs_status launch_mfma_g(const bf16_t* q, const bf16_t* k_pages, const bf16_t* v_pages, const int* block_table,
                                int max_blocks, const int* work, int n_work, int page_size,
                                int n_heads, int n_kv, int waves, int steps_per_split, int max_splits,
-                               float* po, float* pml, bf16_t* attn_out, hipStream_t stream) {
+                               float* po, float* pml, bf16_t* attn_out, bool packed, hipStream_t stream) {
   dim3 grid((unsigned)n_work * (unsigned)n_kv);      // one workgroup per (entry, KV head) item, see item_of_workgroup
 #define GS_RING(NW_)                                                                                              \
   attn_kernel<HD, G, NW_><<<grid, 64 * NW_, 0, stream>>>(q, k_pages, v_pages, block_table, max_blocks, work,      \
                                                          n_work, page_size, n_heads, n_kv, steps_per_split, max_splits,   \
-                                                         po, pml, attn_out)
+                                                         po, pml, attn_out, packed)
   switch (waves) {
     case 1: GS_RING(1); break;
     case 2: GS_RING(2); break;
@@ -744,12 +746,13 @@ size_t attention_work_ints(int capacity) { return 8 + 8 * (size_t)capacity; }
 
 // attn_out [R][H*hd] (storage type).  scratch: attention_workspace_floats floats; work, n_work: the step's work
 // list and its length as the host computes it from its copy of the batch geometry (bf16 path only).  waves: per
-// workgroup (attention_groups).  split: whether any group has more than one split.
+// workgroup (attention_groups).  split: whether any group has more than one split.  packed: bf16 result in
+// fragment order (packed_index).
 gs_status launch_attention(int dtype, const void* q, const void* k_pages, const void* v_pages,
                            const int* block_table, int max_blocks, const int* cu_rows, const int* ctx_len,
                            int n_servers, int n_rows, int page_size, int n_heads, int n_kv, int hd,
                            int waves, int steps_per_split, int max_splits, bool split, const void* row_info,
-                           const int* work, int n_work, float* scratch, void* attn_out, hipStream_t stream) {
+                           const int* work, int n_work, float* scratch, void* attn_out, bool packed, hipStream_t stream) {
   if (dtype == GS_F32) {
     dim3 grid(n_rows, n_heads);
     const float* qf = static_cast<const float*>(q);
@@ -781,7 +784,7 @@ gs_status launch_attention(int dtype, const void* q, const void* k_pages, const 
   if (hd == HD_ && G == G_)                                                                                       \
     st = launch_mfma_g<HD_, G_>(qb, kb, vb, block_table, max_blocks, work, n_work, page_size, n_heads, n_kv,     \
                                 waves, steps_per_split, max_splits, po, pml, static_cast<bf16_t*>(attn_out),       \
-                                stream);
+                                packed, stream);
   GS_ATTN_CASE(128, 1) GS_ATTN_CASE(128, 2) GS_ATTN_CASE(128, 4) GS_ATTN_CASE(128, 8)
   GS_ATTN_CASE(64, 1) GS_ATTN_CASE(64, 2) GS_ATTN_CASE(64, 4) GS_ATTN_CASE(64, 8)
 #undef GS_ATTN_CASE
@@ -789,11 +792,11 @@ gs_status launch_attention(int dtype, const void* q, const void* k_pages, const 
   if (hd == 128)
     attn_combine_kernel<128><<<n_rows * n_heads, 128, 0, stream>>>(po, pml, max_splits, steps_per_split,
                                                                    static_cast<const int4*>(row_info), n_heads,
-                                                                   static_cast<bf16_t*>(attn_out));
+                                                                   static_cast<bf16_t*>(attn_out), packed);
   else
     attn_combine_kernel<64><<<n_rows * n_heads, 64, 0, stream>>>(po, pml, max_splits, steps_per_split,
                                                                  static_cast<const int4*>(row_info), n_heads,
-                                                                 static_cast<bf16_t*>(attn_out));
+                                                                 static_cast<bf16_t*>(attn_out), packed);
   GS_LAUNCH_CHECK("attn_combine");
   return GS_OK;
 }

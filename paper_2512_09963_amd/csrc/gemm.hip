@@ -550,10 +550,17 @@ static void launch_f32(const float* x, const float* w, float* y, int M, int N, i
 bool rows_fused(int dtype, int M, int d, int F) {
   if (M <= 0 || d > kRowNormMaxWidth || d % 64 != 0) return false;
   if (dtype == GS_F32) return M <= 64 && F % 16 == 0;
+  // (a K of more than eight times the columns wants K splits: few workgroups would stream it alone)
+  if (dtype == GS_BF16) return M <= kMaxRows && F <= 8 * d;
   return false;
 }
+gs_status launch_bf16_rows_qkv(const bf16_t* h, const bf16_t* w, const RowNorm& norm, const QkvOut& out, int M, int K, hipStream_t stream);
+gs_status launch_bf16_rows_residual(const bf16_t* in, const bf16_t* w, const ResidualOut& out, int M, int N, int K, hipStream_t stream);
+// bf16: h, attn and act of these calls are in fragment order, but for the h that the gate/up projection reads
 gs_status launch_rows_qkv(int dtype, const void* h, const void* w, const RowNorm& norm, const QkvOut& out, int M, int K,
                           hipStream_t stream) {
+  if (dtype == GS_BF16)
+    return launch_bf16_rows_qkv(static_cast<const bf16_t*>(h), static_cast<const bf16_t*>(w), norm, out, M, K, stream);
   const int N = (out.n_heads + 2 * out.n_kv) * out.hd;
   launch_f32<kF32Qkv>(static_cast<const float*>(h), static_cast<const float*>(w), nullptr, M, N, K, norm, out, ResidualOut{}, stream);
   GS_LAUNCH_CHECK("rows_qkv");
@@ -561,6 +568,9 @@ gs_status launch_rows_qkv(int dtype, const void* h, const void* w, const RowNorm
 }
 gs_status launch_rows_gate_up(int dtype, const void* h, const void* w, const RowNorm& norm, void* act, int M, int F, int K,
                               hipStream_t stream) {
+  if (dtype == GS_BF16)
+    return launch_wide_gate_up_norm(wide_plan(M, 2 * F, K, true), static_cast<const bf16_t*>(h), static_cast<const bf16_t*>(w), norm,
+                                    static_cast<bf16_t*>(act), M, 2 * F, K, stream);
   launch_f32<kF32GateUp>(static_cast<const float*>(h), static_cast<const float*>(w), static_cast<float*>(act), M, 2 * F, K, norm,
                          QkvOut{}, ResidualOut{}, stream);
   GS_LAUNCH_CHECK("rows_gate_up");
@@ -568,6 +578,8 @@ gs_status launch_rows_gate_up(int dtype, const void* h, const void* w, const Row
 }
 gs_status launch_rows_residual(int dtype, const void* in, const void* w, const ResidualOut& out, int M, int N, int K,
                                hipStream_t stream) {
+  if (dtype == GS_BF16)
+    return launch_bf16_rows_residual(static_cast<const bf16_t*>(in), static_cast<const bf16_t*>(w), out, M, N, K, stream);
   launch_f32<kF32Residual>(static_cast<const float*>(in), static_cast<const float*>(w), nullptr, M, N, K, RowNorm{}, QkvOut{}, out,
                            stream);
   GS_LAUNCH_CHECK("rows_residual");

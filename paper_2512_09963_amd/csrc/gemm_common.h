@@ -63,7 +63,15 @@ struct ResidualOut {   // x += result; h = x * norm (of the next projection's in
   const float* norm;
   void* h;
   float* squares;
+  bool packed;         // h in fragment order
 };
+// bf16 activations in fragment order: the 16-byte pieces of a 16 x 64 tile in the order in which lanes and MFMAs take them,
+// [row / 16][k / 64][half][lane][8] with lane (g, c) = row c, k = 16 g + 8 half of the tile.
+__device__ __forceinline__ size_t packed_index(int row, int k, int K) {
+  const size_t tile = (size_t)(row >> 4) * (K >> 6) + (k >> 6);
+  return ((tile * 2 + ((k >> 3) & 1)) * 64 + ((k >> 4) & 3) * 16 + (row & 15)) * 8 + (k & 7);
+}
+constexpr int kMaxRows = 32;      // of the bf16 kernels that read it
 constexpr int kRowNormMaxWidth = 8192;      // d: eight 16-byte loads per lane
 
 // Row factors of a workgroup's rows, 16 lanes to a row (their sum is four row moves): load() early, store() into LDS where the
@@ -120,7 +128,7 @@ gs_status launch_wide(const WidePlan& p, const bf16_t* x, const bf16_t* w, float
                       hipStream_t stream);
 gs_status launch_wide_gate_up(const WidePlan& p, const bf16_t* x, const bf16_t* w, bf16_t* act, int M, int N, int K,
                               hipStream_t stream);
-// h not yet divided by its root mean square: up to 16 rows
+// x not yet divided by its root mean square, act in fragment order; up to kMaxRows rows
 gs_status launch_wide_gate_up_norm(const WidePlan& p, const bf16_t* x, const bf16_t* w, const RowNorm& norm, bf16_t* act, int M,
                                    int N, int K, hipStream_t stream);
 gs_status launch_wide_stats(const WidePlan& p, const bf16_t* x, const bf16_t* w, float* y, float2* stats, int M, int N,

@@ -46,11 +46,11 @@ namespace {
 
 typedef unsigned int uintx4_t __attribute__((ext_vector_type(4)));
 
-enum { kPlain = 0, kGateUp = 1, kStats = 2 };
+enum { kPlain = 0, kGateUp = 1, kStats = 2, kGateUpNorm = 3 };
 
 // MODE: kPlain stores the fp32 sums [split][M][N] at P; kGateUp (one split): the wave's tiles are NT / 2 feature tiles of
 // the gate half and the same ones of the up half of a [2F][K] matrix (N = 2F), and act[M][F] = silu(gate) * up is
-// stored as bf16 at P; kStats (one split): also (max, sum exp) of every row over the workgroup's columns.
+// stored as bf16 at P; kGateUpNorm: the same of rows that still need their factor (RowNorm), act in fragment order; kStats (one split): also (max, sum exp) of every row over the workgroup's columns.
 // DB, DA: steps of weights and of activations held in registers.  POL: cache policy of the weight loads (2: do not
 // displace other lines; for weights that one workgroup reads once).
 // grid (column blocks, rounded up to a multiple of 8, times row chunks; K splits).  Row chunks of one column block are separate
@@ -60,7 +60,8 @@ enum { kPlain = 0, kGateUp = 1, kStats = 2 };
 template <int WM, int WN, int KG, int MT, int NT, int DB, int DA, int POL, int WPE, int MODE>
 __global__ __launch_bounds__(64 * WM * WN * KG) __attribute__((amdgpu_waves_per_eu(WPE, WPE))) void gemm_bf16_wide_kernel(
     const bf16_t* __restrict__ X, const bf16_t* __restrict__ Wp, float* __restrict__ P, int M, int N, int K,
-    int k_per_split, int m_chunks, float2* __restrict__ stats, int n_stat_blocks) {
+    int k_per_split, int m_chunks, float2* __restrict__ stats, int n_stat_blocks, RowNorm norm) {
+  constexpr bool GATE_UP = MODE == kGateUp || MODE == kGateUpNorm;
   static_assert(MT >= 2, "fragments are read two row tiles ahead");
   static_assert(DB % DA == 0, "the unrolled ring addresses the activation slots statically");
   static_assert(KG == 1 || (KG == 2 && MODE != kStats), "sums of two K groups");
@@ -79,7 +80,7 @@ __global__ __launch_bounds__(64 * WM * WN * KG) __attribute__((amdgpu_waves_per_
   const int n_block = (t / m_chunks) * 8 + xcd;
   if (n_block * (16 * NT * WN) >= N) return;      // padding of the grid to a multiple of 8 column blocks
   const int wm = wave / WN, wn = wave % WN;
-  const int n_tile0 = (n_block * WN + wn) * (MODE == kGateUp ? NT / 2 : NT);
+  const int n_tile0 = (n_block * WN + wn) * (GATE_UP ? NT / 2 : NT);
   const int split = blockIdx.y;
   const int m0 = m_chunk * ROWS;
   const int split_begin = split * k_per_split, split_end = min(K, split_begin + k_per_split);
@@ -113,15 +114,18 @@ __global__ __launch_bounds__(64 * WM * WN * KG) __attribute__((amdgpu_waves_per_
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(wbase + (size_t)min(step, last) * w_stride), 0,
                                              (KG == 1 || step < own_steps) ? w_bytes : 0u, 0x00020000);
   };
+  __shared__ float factor[MODE == kGateUpNorm ? ROWS : 1];
+  RowFactors<MODE == kGateUpNorm ? ROWS : 4, WM * WN * KG> factors;      // (one row chunk)
+  if constexpr (MODE == kGateUpNorm) factors.load(norm, wave_all, lane, 0, M);
   uintx4_t xreg[DA][PASSES];
   uintx4_t wreg[DB][NT][2];
   const unsigned woff = lane * 16;
-  const unsigned up_off = MODE == kGateUp ? (unsigned)(N / 32) * 2048u - (unsigned)(NT / 2) * 2048u : 0u;
+  const unsigned up_off = GATE_UP ? (unsigned)(N / 32) * 2048u - (unsigned)(NT / 2) * 2048u : 0u;
 #define GS_LOAD_X(slot, p, r) xreg[slot][p] = __builtin_amdgcn_raw_buffer_load_b128(r, xoff[p], 0, 0)
   // piece i of the wave's weights of a step: tile i / 2, half i % 2
 #define GS_LOAD_W(slot, i, r)                                                                                       \
   wreg[slot][(i) >> 1][(i) & 1] = __builtin_amdgcn_raw_buffer_load_b128(                                            \
-      r, woff + (i) * 1024, (MODE == kGateUp && (i) >= NT) ? up_off : 0u, POL)
+      r, woff + (i) * 1024, (GATE_UP && (i) >= NT) ? up_off : 0u, POL)
   floatx4_t acc[MT][NT];
 #pragma unroll
   for (int mt = 0; mt < MT; ++mt)
@@ -151,6 +155,7 @@ __global__ __launch_bounds__(64 * WM * WN * KG) __attribute__((amdgpu_waves_per_
     }
 #pragma unroll
     for (int p = 0; p < PASSES; ++p) *reinterpret_cast<uintx4_t*>(&xs[loff[p]]) = r0[p];
+    if constexpr (MODE == kGateUpNorm) factors.store(norm, wave_all, lane, factor);
 #pragma unroll
     for (int p = 0; p < PASSES; ++p) *reinterpret_cast<uintx4_t*>(&xs[TILE + loff[p]]) = r1[p];
   }
@@ -226,7 +231,7 @@ __global__ __launch_bounds__(64 * WM * WN * KG) __attribute__((amdgpu_waves_per_
       for (int nt = 0; nt < NT; ++nt) acc[mt][nt] += sums[(mt * NT + nt) * THREADS + tid];
   }
   const int row0 = m0 + wm * MT * 16;
-  if constexpr (MODE == kGateUp) {
+  if constexpr (GATE_UP) {
     bf16_t* act = reinterpret_cast<bf16_t*>(P);
     const int F = N / 2;
 #pragma unroll
@@ -237,9 +242,12 @@ __global__ __launch_bounds__(64 * WM * WN * KG) __attribute__((amdgpu_waves_per_
         if (row < M) {
 #pragma unroll
           for (int ft = 0; ft < NT / 2; ++ft) {
-            const float gt = acc[mt][ft][i];
-            act[(size_t)row * F + (n_tile0 + ft) * 16 + c] =
-                float_to_bf16(gt / (1.0f + expf(-gt)) * acc[mt][NT / 2 + ft][i]);
+            const float f = MODE == kGateUpNorm ? factor[row - m0] : 1.0f;
+            const float gt = MODE == kGateUpNorm ? acc[mt][ft][i] * f : acc[mt][ft][i];
+            const float up = MODE == kGateUpNorm ? acc[mt][NT / 2 + ft][i] * f : acc[mt][NT / 2 + ft][i];
+            const int col = (n_tile0 + ft) * 16 + c;
+            act[MODE == kGateUpNorm ? packed_index(row, col, F) : (size_t)row * F + col] =
+                float_to_bf16(gt / (1.0f + expf(-gt)) * up);
           }
         }
       }
@@ -375,11 +383,18 @@ WidePlan wide_plan(int M, int N, int K, bool one_split) {
 
 template <int MODE>
 static gs_status launch_mode(const WidePlan& p, const bf16_t* x, const bf16_t* w, float* out, int M, int N, int K,
-                             float2* stats, hipStream_t stream) {
+                             float2* stats, const RowNorm& norm, hipStream_t stream) {
   const dim3 grid(ceil_div(p.n_blocks, 8) * 8 * p.m_chunks, p.splits, 1);
 #define GS_WIDE(WM, WN, KG, MT, NT, DB, DA, POL, WPE)                                                              \
   gemm_bf16_wide_kernel<WM, WN, KG, MT, NT, DB, DA, POL, WPE, MODE>                                                 \
-      <<<grid, 64 * WM * WN * KG, 0, stream>>>(x, w, out, M, N, K, p.k_per, p.m_chunks, stats, p.n_blocks)
+      <<<grid, 64 * WM * WN * KG, 0, stream>>>(x, w, out, M, N, K, p.k_per, p.m_chunks, stats, p.n_blocks, norm)
+  if constexpr (MODE == kGateUpNorm) {
+    if (p.wn == 8) GS_WIDE(1, 8, 1, 2, 2, 4, 2, 2, 2);
+    else GS_WIDE(1, 4, 2, 2, 2, 4, 2, 2, 2);
+    GS_LAUNCH_CHECK("gemm_bf16_wide");
+    return GS_OK;
+  }
+  if constexpr (MODE != kGateUpNorm) {
   if (p.wm == 1 && p.nt == 4) {
     GS_WIDE(1, 4, 1, 8, 4, 2, 1, 0, 2);
   } else if (p.wm == 2) {
@@ -418,6 +433,7 @@ static gs_status launch_mode(const WidePlan& p, const bf16_t* x, const bf16_t* w
       default: GS_WIDE(1, 4, 1, 12, 2, 4, 2, 0, 2);
     }
   }
+  }
 #undef GS_WIDE
   GS_LAUNCH_CHECK("gemm_bf16_wide");
   return GS_OK;
@@ -425,15 +441,19 @@ static gs_status launch_mode(const WidePlan& p, const bf16_t* x, const bf16_t* w
 
 gs_status launch_wide(const WidePlan& p, const bf16_t* x, const bf16_t* w, float* out, int M, int N, int K,
                       hipStream_t stream) {
-  return launch_mode<kPlain>(p, x, w, out, M, N, K, nullptr, stream);
+  return launch_mode<kPlain>(p, x, w, out, M, N, K, nullptr, RowNorm{}, stream);
 }
 gs_status launch_wide_gate_up(const WidePlan& p, const bf16_t* x, const bf16_t* w, bf16_t* act, int M, int N, int K,
                               hipStream_t stream) {
-  return launch_mode<kGateUp>(p, x, w, reinterpret_cast<float*>(act), M, N, K, nullptr, stream);
+  return launch_mode<kGateUp>(p, x, w, reinterpret_cast<float*>(act), M, N, K, nullptr, RowNorm{}, stream);
+}
+gs_status launch_wide_gate_up_norm(const WidePlan& p, const bf16_t* x, const bf16_t* w, const RowNorm& norm, bf16_t* act, int M,
+                                   int N, int K, hipStream_t stream) {
+  return launch_mode<kGateUpNorm>(p, x, w, reinterpret_cast<float*>(act), M, N, K, nullptr, norm, stream);
 }
 gs_status launch_wide_stats(const WidePlan& p, const bf16_t* x, const bf16_t* w, float* y, float2* stats, int M, int N,
                             int K, hipStream_t stream) {
-  return launch_mode<kStats>(p, x, w, y, M, N, K, stats, stream);
+  return launch_mode<kStats>(p, x, w, y, M, N, K, stats, RowNorm{}, stream);
 }
 
 }  // namespace gs

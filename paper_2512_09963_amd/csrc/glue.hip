@@ -5,6 +5,7 @@
 #include "common.h"
 #include "attn_work.h"
 #include "device_types.h"
+#include "gemm_common.h"
 
 namespace gs {
 namespace {
@@ -159,12 +160,14 @@ __global__ __launch_bounds__(kWorkThreads) void step_begin_kernel(StepBegin a) {
       inv = 1.0f;
       for (int i = tid; i < a.d >> 4; i += kWorkThreads) a.squares[(size_t)r * (a.d >> 4) + i] = i == 0 ? tot : 0.f;
     }
+    const bool packed = a.squares && sizeof(T) == 2;      // (bf16 rows in fragment order)
     for (int i = tid; i < d4; i += kWorkThreads) {
       const float4 v = i == tid ? v0 : xr[i], w = i == tid ? w0 : wr[i];
-      Storage<T>::store(hr + 4 * i + 0, v.x * inv * w.x);
-      Storage<T>::store(hr + 4 * i + 1, v.y * inv * w.y);
-      Storage<T>::store(hr + 4 * i + 2, v.z * inv * w.z);
-      Storage<T>::store(hr + 4 * i + 3, v.w * inv * w.w);
+      T* dst = packed ? static_cast<T*>(a.h) + packed_index(r, 4 * i, a.d) : hr + 4 * i;
+      Storage<T>::store(dst + 0, v.x * inv * w.x);
+      Storage<T>::store(dst + 1, v.y * inv * w.y);
+      Storage<T>::store(dst + 2, v.z * inv * w.z);
+      Storage<T>::store(dst + 3, v.w * inv * w.w);
     }
   } else if ((int)blockIdx.x < 2 * a.n_rows) {
     if (tid >= 64) return;

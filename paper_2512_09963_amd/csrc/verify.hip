@@ -50,7 +50,7 @@ gs_status launch_attention(int dtype, const void* q, const void* k_pages, const 
                            const int* block_table, int max_blocks, const int* cu_rows, const int* ctx_len,
                            int n_servers, int n_rows, int page_size, int n_heads, int n_kv, int hd,
                            int waves, int steps_per_split, int max_splits, bool split, const void* row_info,
-                           const int* work, int n_work, float* scratch, void* attn_out, hipStream_t stream);
+                           const int* work, int n_work, float* scratch, void* attn_out, bool packed, hipStream_t stream);
 size_t attention_work_ints(int capacity);
 gs_status launch_accept(int n_servers, int n_rows, const int* cu_rows, int vocab, int elem, const void* target_logits,
                         const void* q_probs, const int* draft_tokens, const float* u_accept,
@@ -131,16 +131,16 @@ constexpr int kMaxFusedRows = 64;      // rows_fused never accepts more
 
 Plan make_plan(const gs_ctx* ctx, int max_rows, int max_servers, int max_ctx, void* ws) {
   const gs_model_desc& m = ctx->desc;
-  const size_t R = max_rows;
+  const size_t R = max_rows, R16 = gs::align_up(R, 16);      // (bf16 activations in fragment order have whole row tiles)
   const int hq = m.n_heads * m.head_dim;
   gs::Carver c(ws);
   Plan p;
   p.x = c.take<float>(R * m.d_model);
-  p.h = c.take<char>(R * m.d_model * ctx->elem);
+  p.h = c.take<char>(R16 * m.d_model * ctx->elem);
   p.partial = c.take<float>(max_partial_floats(ctx, max_rows));
   p.q = c.take<char>(R * hq * ctx->elem);
-  p.attn = c.take<char>(R * hq * ctx->elem);
-  p.act = c.take<char>(R * m.d_ffn * ctx->elem);
+  p.attn = c.take<char>(R16 * hq * ctx->elem);
+  p.act = c.take<char>(R16 * m.d_ffn * ctx->elem);
   // the planner never uses more than 32 splits per server and never fewer than 6 steps per split
   const int max_steps = (max_ctx + 31) / 32;
   const int max_splits = std::max(1, std::min(32, (max_steps + 5) / 6)) | 1;   // odd, like the planner's
@@ -439,6 +439,7 @@ extern "C" gs_status gs_verify_batch(gs_ctx* ctx, const gs_kv_cache* kv, const g
   if (attn_items > p.attn_work_capacity) return gs::fail(GS_ECAPACITY, "attention work list overflow");
 
   const bool fused = gs::rows_fused(m.dtype, rows, d, F);      // norms, rotation and residual inside the projections
+  const bool packed = fused && act == GS_BF16;                   // bf16 activations of such layers in fragment order
   const gs::RowNorm norm{p.squares, d / 16, 1.0f / (float)d, m.rms_eps};
   StageTimer timer(ctx, stream);
 #define GS_STAGE(stage, call)   \
@@ -473,13 +474,13 @@ extern "C" gs_status gs_verify_batch(gs_ctx* ctx, const gs_kv_cache* kv, const g
     }
     GS_STAGE(GS_STAGE_ATTENTION, gs::launch_attention(act, p.q, kl, vl, b->block_table, b->max_blocks, b->cu_rows, b->ctx_len, n, rows,
                                 kv->page_size, m.n_heads, m.n_kv_heads, m.head_dim, attn_waves, attn_sps, attn_splits,
-                                attn_split, p.row_slot, p.attn_work, (int)attn_items, p.attn_scratch, p.attn, stream));
+                                attn_split, p.row_slot, p.attn_work, (int)attn_items, p.attn_scratch, p.attn, packed, stream));
     if (fused) {
       const bool top = l + 1 == m.n_layers;
-      GS_STAGE(GS_STAGE_GEMM, gs::launch_rows_residual(m.dtype, p.attn, ctx->wo[l], {p.x, ctx->norm2[l], p.h, p.squares}, rows, d, hq, stream));
+      GS_STAGE(GS_STAGE_GEMM, gs::launch_rows_residual(m.dtype, p.attn, ctx->wo[l], {p.x, ctx->norm2[l], p.h, p.squares, false}, rows, d, hq, stream));
       GS_STAGE(GS_STAGE_GEMM, gs::launch_rows_gate_up(m.dtype, p.h, ctx->wgu[l], norm, p.act, rows, F, d, stream));
       GS_STAGE(GS_STAGE_GEMM, gs::launch_rows_residual(m.dtype, p.act, ctx->wd[l],
-                                                       {p.x, top ? ctx->final_norm : ctx->norm1[l + 1], p.h, p.squares}, rows, d, F, stream));
+                                                       {p.x, top ? ctx->final_norm : ctx->norm1[l + 1], p.h, p.squares, packed}, rows, d, F, stream));
       continue;
     }
     GS_STAGE(GS_STAGE_GEMM, gs::launch_gemm(m.dtype, p.attn, ctx->wo[l], p.partial, rows, d, hq, stream));

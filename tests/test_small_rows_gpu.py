@@ -37,3 +37,26 @@ def test_f32_layer_of_five_launches(d, heads, n_kv, hd, ffn, rows):
     ms = synth.ModelShape(2, d, heads, n_kv, hd, ffn, 272, 10000.0, dtype="f32")
     gamma = np.array([rows - 1 - rows // 3, rows // 3 - 1] if rows >= 3 else [rows - 1], np.int32)
     _run_case(ms, 300 + rows, gamma, np.array([37, 5][:gamma.size], np.int32), 16, 0.06)
+
+
+@pytest.mark.parametrize("d,heads,n_kv,hd,ffn,rows", [
+    (64, 1, 1, 64, 64, 2),             # one k step: three waves of four have none
+    (128, 2, 1, 128, 192, 16),
+    (192, 4, 2, 64, 576, 17),          # 3 and 9 steps over 4 and 8 waves; head size 64: 2 tiles a half
+    (320, 8, 1, 64, 2496, 31),         # 39 steps: past the ring of 8 x 4 and of 4 x 8 steps
+    (256, 8, 8, 128, 1024, 32),
+    (256, 8, 8, 128, 1024, 33),        # past the last row of these kernels
+    (128, 4, 4, 64, 1088, 9),          # F > 8 d: the kernels with K splits
+    (256, 64, 8, 128, 512, 12),        # 10240 columns: two pairs of tiles per workgroup
+    (256, 63, 63, 64, 512, 20),        # 12096 columns: 189 workgroups of two pairs
+    (4160, 2, 2, 64, 128, 7),          # 260 column tiles: two per workgroup; sums of squares of 260 tiles
+    (4160, 2, 2, 64, 128, 27),
+])
+def test_bf16_layer_of_five_launches(d, heads, n_kv, hd, ffn, rows):
+    """Against the oracle within 2e-2 of the row scale, K and V rows as well (one bf16 rounding of h, before instead of after the
+    division by the root mean square, is as large as the one it replaces)."""
+    ms = synth.ModelShape(2, d, heads, n_kv, hd, ffn, 384, 10000.0, dtype="bf16")
+    gamma = np.array([rows - 1 - rows // 3, rows // 3 - 1] if rows >= 3 else [rows - 1], np.int32)
+    # scores have a standard deviation of d std^2 sqrt(hd), and a rounding of q or k is amplified by that factor: at most
+    # 1.44 sqrt(hd) = 16 (0.05 at d = 4160 would be 83, where softmax is nearly an argmax)
+    _run_case(ms, 500 + rows, gamma, np.array([250, 5][:gamma.size], np.int32), 16, min(0.05, 1.2 / d ** 0.5))
