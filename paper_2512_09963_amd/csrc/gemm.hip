@@ -398,10 +398,10 @@ gs_status launch_pack_weight(const void* src, void* dst, int N, int K, hipStream
 // Which bf16 kernel serves a shape, and how the launch is cut.
 struct GemmPlan {
   enum Kind {
-    kSkinny,      // up to 64 rows where K is split over workgroups (inside a step at 53 rows: QKV of the 8B shape 13.7 us,
-                  // 15.2 with the wide kernel, O and down 17.8 on average, 18.1), and column counts that are no
-                  // multiple of 128
-    kWide         // gemm_wide.hip: everything else
+    kSkinny,      // column counts that are no multiple of 128
+    kWide         // gemm_wide.hip: everything else.  (Up to 64 rows the K-split projections too: with its four K groups, or two
+                  // where four splits are enough, steps of 4 layers of the 8B shape at 24 / 32 / 60 rows 649 / 648 / 707 us ->
+                  // 615 / 630 / 688, of 2 layers of the 70B shape at 24 / 60 rows 996 / 1049 -> 912 / 989.)
   } kind;
   int mt;         // row tiles per workgroup
   int m_chunks;   // row chunks (separate workgroups)
@@ -415,7 +415,7 @@ static GemmPlan gemm_plan(int M, int N, int K) {
   const int tiles = ceil_div(M, 16);
   int n_blocks;
   if (N % 128 == 0) p.wide = wide_plan(M, N, K, false);
-  if (N % 128 == 0 && (tiles > 4 || p.wide.splits == 1)) {
+  if (N % 128 == 0) {
     p.kind = GemmPlan::kWide;
     p.mt = p.wide.mt;
     p.m_chunks = p.wide.m_chunks;
@@ -550,10 +550,10 @@ static void launch_f32(const float* x, const float* w, float* y, int M, int N, i
 bool rows_fused(int dtype, int M, int d, int F) {
   if (M <= 0 || d > kRowNormMaxWidth || d % 64 != 0) return false;
   if (dtype == GS_F32) return M <= 64 && F % 16 == 0;
-  // (a K of more than eight times the columns wants K splits: few workgroups would stream it alone)
-  // (8B shape, 4 layers, against the K splits: 16 rows 614 -> 593 us, 24 rows 649 -> 638, 32 rows 648 -> 655; 70B shape, 2 layers,
-  // 32 columns per workgroup: 16 rows 979 -> 923, 32 rows 996 -> 977)
-  if (dtype == GS_BF16) return M <= (d <= 4096 ? kMaxRows * 3 / 4 : kMaxRows) && F <= 8 * d;
+  // bf16: up to 16 rows, 8 where a workgroup has 32 columns; beyond, K splits and separate norms are faster (8B shape, 4 layers, us
+  // fused and not: 5 rows 545 / 590, 16 rows 590 / 600, 20 rows 623 / 609; 70B shape, 2 layers: 5 rows 898 / 904, 12 rows
+  // 927 / 912).  A K of more than eight times the columns wants K splits: few workgroups would stream it alone.
+  if (dtype == GS_BF16) return M <= (d <= 4096 ? kMaxRows : kMaxRows / 2) && F <= 8 * d;
   return false;
 }
 gs_status launch_bf16_rows_qkv(const bf16_t* h, const bf16_t* w, const RowNorm& norm, const QkvOut& out, int M, int K, hipStream_t stream);

@@ -71,7 +71,7 @@ __device__ __forceinline__ size_t packed_index(int row, int k, int K) {
   const size_t tile = (size_t)(row >> 4) * (K >> 6) + (k >> 6);
   return ((tile * 2 + ((k >> 3) & 1)) * 64 + ((k >> 4) & 3) * 16 + (row & 15)) * 8 + (k & 7);
 }
-constexpr int kMaxRows = 32;      // of the bf16 kernels that read it
+constexpr int kMaxRows = 16;      // of the bf16 kernels that read it
 constexpr int kRowNormMaxWidth = 8192;      // d: eight 16-byte loads per lane
 
 // Row factors of a workgroup's rows, 16 lanes to a row (their sum is four row moves): load() early, store() into LDS where the

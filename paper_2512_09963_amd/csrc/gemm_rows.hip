@@ -6,12 +6,13 @@
 // workgroup owns NT column tiles for all of K, its NW waves take the k steps in turn (so that all waves of the launch
 // sweep the packed weights band by band) and their sums meet in LDS.  Weights and activations go from global memory
 // straight into the MFMA operands, D steps ahead; an activation fragment is used by one wave of a workgroup, so LDS would not
-// save a load, but every workgroup reads all activations: M x K x 2 bytes per compute unit beside 32 x NT x K of weights.  Up
-// to 16 rows that is at most as much, at 32 rows twice as much, and beyond the K splits are faster (53 rows: 40 us for the
-// 4096 x 14336 projection against 24 and a norm).  The activations are stored in fragment order (packed_index), so that such a
-// load is one kilobyte in a row: row-major 34.7 us against 28.9 at 32 rows.
-// Per launch, us, 8B shape, 5 / 16 / 32 rows, this kernel and in brackets the K splits with their norm or rotation kernel:
-//   6144 x 4096  11.2 / 12.0 / 13.9 (16.0 at 5 rows)    4096 x 4096  8.2 / 9.6 / 11.3 (15.0)    4096 x 14336  21.1 / 25.1 / 28.9 (26.2)
+// save a load, but every workgroup reads all activations: M x K x 2 bytes per compute unit beside 32 x NT x K of weights.  A compute
+// unit takes 23 GB/s of its share of the HBM stream and 94 GB/s from L2, but not both at once (54 GB/s in all at two parts of
+// activations to one of weights, whatever the number of loads in flight), so beyond 16 rows the K splits are faster
+// (53 rows: 40 us for the 4096 x 14336 projection, 24 and a norm with them).  The activations are stored in fragment
+// order (packed_index), so that such a load is one kilobyte in a row (row-major 34.7 us against 28.9 at 32 rows).
+// Per launch, us, 8B shape, 5 / 16 rows, and in brackets the K splits with their norm or rotation kernel at 5 rows:
+//   6144 x 4096  11.2 / 12.0 (16.0)    4096 x 4096  8.2 / 9.6 (15.0)    4096 x 14336  21.1 / 25.1 (26.2)
 #include "common.h"
 #include "device_types.h"
 #include "gemm_common.h"
@@ -150,21 +151,11 @@ gs_status launch(const bf16_t* x, const bf16_t* w, int M, int N, int K, const Ro
   const unsigned grid = ceil_div(N / 16, nt);
 #define GS_ROWS(MT, NT, D, NW) gemm_bf16_rows_kernel<MT, NT, D, NW, MODE><<<grid, 64 * NW, 0, stream>>>(x, w, M, N, K, norm, qkv, res)
   if constexpr (MODE == kQkv) {
-    if (M <= 16) {
-      if (nt == 2) GS_ROWS(1, 2, 4, 8);
-      else GS_ROWS(1, 4, 4, 8);
-    } else {
-      if (nt == 2) GS_ROWS(2, 2, 4, 8);
-      else GS_ROWS(2, 4, 3, 8);
-    }
+    if (nt == 2) GS_ROWS(1, 2, 4, 8);
+    else GS_ROWS(1, 4, 4, 8);
   } else {
-    if (M <= 16) {
-      if (nt == 1) GS_ROWS(1, 1, 8, 4);
-      else GS_ROWS(1, 2, 4, 8);
-    } else {
-      if (nt == 1) GS_ROWS(2, 1, 8, 4);
-      else GS_ROWS(2, 2, 4, 8);
-    }
+    if (nt == 1) GS_ROWS(1, 1, 8, 4);
+    else GS_ROWS(1, 2, 4, 8);
   }
 #undef GS_ROWS
   GS_LAUNCH_CHECK("gemm_bf16_rows");

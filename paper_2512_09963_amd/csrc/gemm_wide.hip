@@ -22,6 +22,7 @@
 //   1 x 4 (128 columns) with KG = 2, all rows (up to 160) in one workgroup: the two halves of K in one workgroup, their sums meet
 //     in LDS: as many waves as 1 x 8 without halving the workgroups of a narrower matrix, and half the partial results of a
 //     further K split (which the gate/up projection, whose epilogue applies the SwiGLU, must not have)
+//   1 x 2 (64 columns) with KG = 4, up to 64 rows: the same for matrices of 4096 columns or so, which would need eight K splits
 //   1 x 4 (128 columns) in row chunks of 64 to 192 rows, two workgroups per compute unit: narrow matrices and middling row counts,
 //     where the time of one workgroup is the time of the launch
 //   2 x 2 (128 columns, up to 352 rows in one workgroup): both row halves load the weights, the second time from L1
@@ -64,7 +65,7 @@ __global__ __launch_bounds__(64 * WM * WN * KG) __attribute__((amdgpu_waves_per_
   constexpr bool GATE_UP = MODE == kGateUp || MODE == kGateUpNorm;
   static_assert(MT >= 2, "fragments are read two row tiles ahead");
   static_assert(DB % DA == 0, "the unrolled ring addresses the activation slots statically");
-  static_assert(KG == 1 || (KG == 2 && MODE != kStats), "sums of two K groups");
+  static_assert(KG == 1 || MODE != kStats, "whole sums");
   constexpr int ROWS = WM * MT * 16, THREADS = 64 * WM * WN;       // of one K group
   constexpr int PASSES = (ROWS * 8 + THREADS - 1) / THREADS;
   constexpr int TILE = ROWS * 128;                                 // bytes of one activation buffer
@@ -212,23 +213,34 @@ __global__ __launch_bounds__(64 * WM * WN * KG) __attribute__((amdgpu_waves_per_
 #undef GS_LOAD_X
 #undef GS_LOAD_W
 
-  if constexpr (KG == 2) {
+  // The K groups share the epilogue: group mt % KG owns row tile mt, takes its sums from all groups in a fixed order and stores it.
+  auto owned = [&](int mt) { return KG == 1 || mt % KG == kg; };
+  if constexpr (KG > 1) {
     // (the last step's barrier: all reads of the activation buffers are done but for fragments nobody uses)
-    static_assert(KG * 3 * TILE >= MT * NT * 16 * THREADS, "the sums of one K group fit the activation buffers");
+    static_assert(KG * 3 * TILE >= MT * NT * (KG - 1) * 16 * THREADS, "the sums that change hands fit the activation buffers");
     __syncthreads();
     floatx4_t* sums = reinterpret_cast<floatx4_t*>(xs_all);
-    if (kg == 1) {
-#pragma unroll
-      for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-        for (int nt = 0; nt < NT; ++nt) sums[(mt * NT + nt) * THREADS + tid] = acc[mt][nt];
-    }
-    __syncthreads();
-    if (kg == 1) return;
+    auto place = [&](int src, int mt, int nt) {      // what group src hands to the owner of row tile mt
+      const int o = mt % KG;
+      return ((mt * (KG - 1) + (src < o ? src : src - 1)) * NT + nt) * THREADS + tid;
+    };
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt)
+      if (!owned(mt))
 #pragma unroll
-      for (int nt = 0; nt < NT; ++nt) acc[mt][nt] += sums[(mt * NT + nt) * THREADS + tid];
+        for (int nt = 0; nt < NT; ++nt) sums[place(kg, mt, nt)] = acc[mt][nt];
+    __syncthreads();
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt)
+      if (owned(mt))
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) {
+          const floatx4_t own = acc[mt][nt];
+          floatx4_t v = mt % KG == 0 ? own : sums[place(0, mt, nt)];
+#pragma unroll
+          for (int src = 1; src < KG; ++src) v += mt % KG == src ? own : sums[place(src, mt, nt)];
+          acc[mt][nt] = v;
+        }
   }
   const int row0 = m0 + wm * MT * 16;
   if constexpr (GATE_UP) {
@@ -239,7 +251,7 @@ __global__ __launch_bounds__(64 * WM * WN * KG) __attribute__((amdgpu_waves_per_
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         const int row = row0 + mt * 16 + g * 4 + i;
-        if (row < M) {
+        if (owned(mt) && row < M) {
 #pragma unroll
           for (int ft = 0; ft < NT / 2; ++ft) {
             const float f = MODE == kGateUpNorm ? factor[row - m0] : 1.0f;
@@ -259,7 +271,7 @@ __global__ __launch_bounds__(64 * WM * WN * KG) __attribute__((amdgpu_waves_per_
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const int row = row0 + mt * 16 + g * 4 + i;
-      if (row < M) {
+      if (owned(mt) && row < M) {
 #pragma unroll
         for (int nt = 0; nt < NT; ++nt) out[(size_t)row * N + (n_tile0 + nt) * 16 + c] = acc[mt][nt][i];
       }
@@ -376,6 +388,15 @@ WidePlan wide_plan(int M, int N, int K, bool one_split) {
     p.kg = p.wn == 8 ? 1 : 2;
     p.n_blocks = N / (32 * p.wn);
     cut_k(p, K, one_split ? 1 : std::max(1, std::min(256 / p.n_blocks, K / 512)));
+    // Four K groups of 64 columns where that fills the chip with half of the K splits: half of the partial results
+    // (four and fewer are not worth the larger share of the activations: 8192 x 28672 wants the two groups)
+    const int blocks = N / 64, s4 = std::min(256 / blocks, K / 1024);
+    if (p.splits > 4 && s4 > 1 && blocks * s4 >= 224) {
+      p.wn = 2;
+      p.kg = 4;
+      p.n_blocks = blocks;
+      cut_k(p, K, s4);
+    }
     return p;
   }
   return fastest_shape(tiles, N, K, one_split);
@@ -411,6 +432,11 @@ static gs_status launch_mode(const WidePlan& p, const bf16_t* x, const bf16_t* w
       case 8: GS_WIDE(1, 8, 1, 8, 2, 4, 2, 2, 2); break;
       case 10: GS_WIDE(1, 8, 1, 10, 2, 4, 2, 2, 2); break;
       default: GS_WIDE(1, 8, 1, 12, 2, 4, 2, 2, 2);
+    }
+  } else if (MODE == kPlain && p.kg == 4) {
+    if constexpr (MODE == kPlain) {
+      if (p.mt == 2) GS_WIDE(1, 2, 4, 2, 2, 4, 2, 2, 2);
+      else GS_WIDE(1, 2, 4, 4, 2, 4, 2, 2, 2);
     }
   } else if (MODE == kStats && p.m_chunks == 1 && p.mt == 12) {
     if constexpr (MODE == kStats) GS_WIDE(1, 4, 1, 12, 2, 4, 2, 2, 1);      // (spills where two workgroups share the registers)

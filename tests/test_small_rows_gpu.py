@@ -60,3 +60,13 @@ def test_bf16_layer_of_five_launches(d, heads, n_kv, hd, ffn, rows):
     # scores have a standard deviation of d std^2 sqrt(hd), and a rounding of q or k is amplified by that factor: at most
     # 1.44 sqrt(hd) = 16 (0.05 at d = 4160 would be 83, where softmax is nearly an argmax)
     _run_case(ms, 500 + rows, gamma, np.array([250, 5][:gamma.size], np.int32), 16, min(0.05, 1.2 / d ** 0.5))
+
+
+@pytest.mark.parametrize("rows", [17, 32, 33, 49, 64, 65])
+def test_bf16_projections_with_four_k_groups(rows):
+    """5120 x 3584 in 3 K splits of 19, 19 and 18 steps (groups of 5, 5, 5 and 4 or 3 steps) and 3584 x 4096 in 4 of 16; two and four row
+    tiles, of which a K group owns none, one or two; 65 rows: past them.  The down projection (K = 192) has no split."""
+    ms = synth.ModelShape(1, 3584, 32, 4, 128, 192, 512, 10000.0, dtype="bf16")
+    gamma = np.array([rows - 20, 11, 6] if rows > 20 else [rows - 3, 0, 1], np.int32)
+    # (std: see above)
+    _run_case(ms, 700 + rows, gamma, np.array([40, 0, 19], np.int32), 16, 0.02)
