@@ -458,15 +458,19 @@ static W4Plan w4_plan(int M, int N, int K) {
       if (blocks >= 192 || K / 64 >= 16 * p.kg * s) p.nt = 2;
     }
   }
-  if (N % (32 * p.waves * p.nt) != 0) {      // N is a multiple of 64
+  // narrow matrices at 33 to 64 rows: 64 columns and four K groups per workgroup, down to four steps each, so that the chip is full
+  // with half of the K splits (8B shape, 8 layers, 53 rows 952 -> 934 us; at 8192 columns and more the larger share of the
+  // activations costs more: 70B shape, 2 layers, 45 rows 587 -> 604)
+  const bool narrow = p.mt == 2 && p.nt == 1 && N < 8192;
+  if (narrow || N % (32 * p.waves * p.nt) != 0) {      // N is a multiple of 64
     p.waves = 2;
     p.kg = p.mt == 4 ? 2 : 4;      // (LDS: kg x 3 activation buffers)
   }
   p.n_blocks = N / (32 * p.waves * p.nt);
   // K splits: every one adds an M x N fp32 partial result to write and re-read, so as many as fill the chip once, with
-  // at least 8 steps per K group
+  // at least 8 steps per K group (4 in narrow matrices)
   const int wgs = p.n_blocks * p.m_chunks;
-  const int s = std::max(1, std::min(target / wgs, K / (512 * p.kg)));
+  const int s = std::max(1, std::min(target / wgs, K / ((narrow ? 256 : 512) * p.kg)));
   p.k_per = ceil_div(ceil_div(K, s), kGroup) * kGroup;      // whole scale groups per split
   p.splits = ceil_div(K, p.k_per);
   return p;
