@@ -217,14 +217,14 @@ __device__ __forceinline__ float4 load4_f32(const float* __restrict__ row, int k
 }
 // MODE: kF32Plain stores Y [M][N].  The others (gemm_common.h; up to 64 rows, one row chunk) take pairs of column tiles, or
 // whole tiles, through LDS: kF32Qkv and kF32GateUp, whose input rows still need their factor, the two halves of a head's
-// rotation pairs and the gate and up tile of 16 features, kF32Residual the tiles of the residual stream.
-enum { kF32Plain = 0, kF32Qkv = 1, kF32GateUp = 2, kF32Residual = 3 };
+// rotation pairs and the gate and up tile of 16 features, kF32Head tiles of the logits, kF32Residual of the residual stream.
+enum { kF32Plain = 0, kF32Qkv = 1, kF32GateUp = 2, kF32Residual = 3, kF32Head = 4 };
 template <int MT, int LOADS, int MODE>
 __global__ __launch_bounds__(64 * kF32Waves) void gemm_f32_kernel(const float* __restrict__ X,
                                                                   const float* __restrict__ W, float* __restrict__ Y,
                                                                   int M, int N, int K, int ks_log2, int k_per, RowNorm norm,
                                                                   QkvOut qkv, ResidualOut res) {
-  constexpr bool PAIRS = MODE == kF32Qkv || MODE == kF32GateUp;
+  constexpr bool PAIRS = MODE == kF32Qkv || MODE == kF32GateUp, NORM = PAIRS || MODE == kF32Head;
   __shared__ float red[kF32Waves][MT * 256];
   __shared__ float factor[MT * 16];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -247,7 +247,7 @@ __global__ __launch_bounds__(64 * kF32Waves) void gemm_f32_kernel(const float* _
   const int m0 = blockIdx.y * (MT * 16);
   const int k_begin = slice * k_per, k_end = min(K, k_begin + k_per);
   RowFactors<MT * 16, kF32Waves> factors;
-  if constexpr (PAIRS) factors.load(norm, wave, lane, m0, M - m0);
+  if constexpr (NORM) factors.load(norm, wave, lane, m0, M - m0);
   // what the epilogue needs from memory for this lane's first element, fetched before the products
   const int e_t = tid / (MT * 256), e_o = tid - e_t * (MT * 256), e_row = m0 + (e_o >> 4);
   int4 e_slot = make_int4(0, 0, 0, 0);
@@ -289,7 +289,7 @@ __global__ __launch_bounds__(64 * kF32Waves) void gemm_f32_kernel(const float* _
     }
   };
   if (k_begin < k_end) load_steps(k_begin);
-  if constexpr (PAIRS) factors.store(norm, wave, lane, factor);
+  if constexpr (NORM) factors.store(norm, wave, lane, factor);
   for (int k0 = k_begin; k0 < k_end; k0 += 16 * U) {
 #pragma unroll
     for (int u = 0; u < U; ++u)
@@ -364,7 +364,7 @@ __global__ __launch_bounds__(64 * kF32Waves) void gemm_f32_kernel(const float* _
       const float sq = row16_sum(v * v);      // (16 lanes share a row and a tile)
       if ((o & 15) == 0 && row < M && col < N) res.squares[(size_t)row * (N >> 4) + (col >> 4)] = sq;
     } else {
-      if (row < M && col < N) Y[(size_t)row * N + col] = sum;
+      if (row < M && col < N) Y[(size_t)row * N + col] = MODE == kF32Head ? sum * factor[o >> 4] : sum;
     }
   }
 }
@@ -576,6 +576,12 @@ gs_status launch_rows_gate_up(int dtype, const void* h, const void* w, const Row
   launch_f32<kF32GateUp>(static_cast<const float*>(h), static_cast<const float*>(w), static_cast<float*>(act), M, 2 * F, K, norm,
                          QkvOut{}, ResidualOut{}, stream);
   GS_LAUNCH_CHECK("rows_gate_up");
+  return GS_OK;
+}
+// Logits of rows that still need their factor: fp32 (the others take a norm of their own, their LM heads being the plain ones).
+gs_status launch_rows_head_f32(const float* h, const float* w, const RowNorm& norm, float* logits, int M, int N, int K, hipStream_t stream) {
+  launch_f32<kF32Head>(h, w, logits, M, N, K, norm, QkvOut{}, ResidualOut{}, stream);
+  GS_LAUNCH_CHECK("rows_head");
   return GS_OK;
 }
 gs_status launch_rows_residual(int dtype, const void* in, const void* w, const ResidualOut& out, int M, int N, int K,

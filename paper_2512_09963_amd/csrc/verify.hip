@@ -25,6 +25,7 @@ gs_status launch_rows_qkv(int dtype, const void* h, const void* w, const RowNorm
                           hipStream_t stream);
 gs_status launch_rows_gate_up(int dtype, const void* h, const void* w, const RowNorm& norm, void* act, int M, int F, int K,
                               hipStream_t stream);
+gs_status launch_rows_head_f32(const float* h, const float* w, const RowNorm& norm, float* logits, int M, int N, int K, hipStream_t stream);
 gs_status launch_rows_residual(int dtype, const void* in, const void* w, const ResidualOut& out, int M, int N, int K,
                                hipStream_t stream);
 gs_status launch_step_begin(int dtype, const void* embed, const int* tokens, float* x, const float* norm, float eps, void* h,
@@ -496,7 +497,9 @@ extern "C" gs_status gs_verify_batch(gs_ctx* ctx, const gs_kv_cache* kv, const g
     pending = p.partial;
     pending_splits = gs::gemm_splits(m.dtype, rows, d, F);
   }
-  GS_STAGE(GS_STAGE_GLUE, gs::launch_add_rmsnorm(act, p.x, pending, pending_splits, rows, ctx->final_norm, m.rms_eps, p.h, d, stream));
+  const bool fused_head = fused && m.dtype == GS_F32;
+  if (!fused_head)
+    GS_STAGE(GS_STAGE_GLUE, gs::launch_add_rmsnorm(act, p.x, pending, pending_splits, rows, ctx->final_norm, m.rms_eps, p.h, d, stream));
   if (ctx->residual_trace)
     GS_HIP_CHECK(hipMemcpyAsync(ctx->residual_trace + (size_t)m.n_layers * rows * d, p.x, sizeof(float) * rows * d,
                                 hipMemcpyDeviceToDevice, stream));
@@ -505,7 +508,10 @@ extern "C" gs_status gs_verify_batch(gs_ctx* ctx, const gs_kv_cache* kv, const g
   // Where the LM-head projection runs as one bf16 launch, its epilogue also leaves the softmax statistics of
   // every row per column block, and the accept stage does not read the logits again for them.
   const int stat_blocks = do_accept ? gs::gemm_stat_blocks(m.dtype, rows, m.vocab, d) : 0;
-  if (stat_blocks > 0) {
+  if (fused_head) {
+    GS_STAGE(GS_STAGE_GEMM, gs::launch_rows_head_f32(static_cast<const float*>(p.h), static_cast<const float*>(ctx->lm_head), norm, logits,
+                                                     rows, m.vocab, d, stream));
+  } else if (stat_blocks > 0) {
     GS_STAGE(GS_STAGE_GEMM, gs::launch_gemm_stats(p.h, ctx->lm_head, logits, p.lm_stats, rows, m.vocab, d, stream));
   } else if (lm_splits == 1) {
     GS_STAGE(GS_STAGE_GEMM, gs::launch_gemm(m.dtype, p.h, ctx->lm_head, logits, rows, m.vocab, d, stream));
