@@ -40,11 +40,6 @@ constexpr float kNegBig = -1.0e30f;
 // ------------------------------------------------------------------------------------------
 constexpr int kRowThreads = 256;
 constexpr int kRowKeys = 128;
-__device__ __forceinline__ float wave_max(float v) {
-  v = row16_max(v);
-  v = fmaxf(v, __shfl_xor(v, 16));
-  return fmaxf(v, __shfl_xor(v, 32));
-}
 template <int HD, bool VEC>
 __global__ __launch_bounds__(kRowThreads) void attn_rowwise_kernel(const float* __restrict__ q,
                                                                    const float* __restrict__ k_pages,

@@ -34,7 +34,12 @@ __device__ __forceinline__ float row16_sum(float v) {
   return v + dpp_move<0x140>(v);
 }
 
-// Sum over a wave, the same on every lane.
+// Maximum and sum over a wave, the same on every lane.
+__device__ __forceinline__ float wave_max(float v) {
+  v = row16_max(v);
+  v = fmaxf(v, __shfl_xor(v, 16));
+  return fmaxf(v, __shfl_xor(v, 32));
+}
 __device__ __forceinline__ float wave_sum(float v) {
   v = row16_sum(v);
   v += __shfl_xor(v, 16);
