@@ -130,17 +130,24 @@ def _check(code):
         raise GsError(code, lib().gs_last_error().decode())
 
 
+# A call's marshalling is host time in front of its launches (a small accept call is bound by it): addresses are passed as the
+# integers that ctypes converts itself, and the raw stream is asked for without a Stream object.
 def _ptr(t):
-    return None if t is None else C.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
 def _host_i32(a):
     return np.ascontiguousarray(a, dtype=np.int32)
 
 
+def _host_ptr(a):
+    return a.__array_interface__["data"][0]
+
+
 def _stream(stream):
-    s = torch.cuda.current_stream() if stream is None else stream
-    return C.c_void_p(s.cuda_stream)
+    if stream is not None:
+        return stream.cuda_stream
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
 
 def gs_accept_workspace_bytes(n_servers, n_rows, vocab):
@@ -166,7 +173,7 @@ def gs_accept_reject(gamma_host, cu_rows, vocab, target_logits, q_probs, draft_t
     """Enqueues accept/reject + resample; `out` is a dict from make_accept_out, `workspace` a uint8 device tensor."""
     g = _host_i32(gamma_host)
     st = _accept_out_struct(out)
-    _check(lib().gs_accept_reject(int(g.size), g.ctypes.data, _ptr(cu_rows), int(vocab), _ptr(target_logits),
+    _check(lib().gs_accept_reject(int(g.size), _host_ptr(g), _ptr(cu_rows), int(vocab), _ptr(target_logits),
                                   _ptr(q_probs), _ptr(draft_tokens), _ptr(u_accept), _ptr(u_resample),
                                   C.byref(st), _ptr(workspace), workspace.numel() if workspace is not None else 0,
                                   _stream(stream)))
@@ -179,7 +186,7 @@ def gs_accept_reject_bf16(gamma_host, cu_rows, vocab, target_logits, q_probs, dr
     assert target_logits.dtype == torch.bfloat16 and (q_probs is None or q_probs.dtype == torch.bfloat16)
     g = _host_i32(gamma_host)
     st = _accept_out_struct(out)
-    _check(lib().gs_accept_reject_bf16(int(g.size), g.ctypes.data, _ptr(cu_rows), int(vocab), _ptr(target_logits),
+    _check(lib().gs_accept_reject_bf16(int(g.size), _host_ptr(g), _ptr(cu_rows), int(vocab), _ptr(target_logits),
                                        _ptr(q_probs), _ptr(draft_tokens), _ptr(u_accept), _ptr(u_resample),
                                        C.byref(st), _ptr(workspace), workspace.numel() if workspace is not None else 0,
                                        _stream(stream)))
@@ -191,7 +198,7 @@ def gs_accept_reject_static(gamma_host, cu_rows, vocab, target_logits, q_probs, 
     """gs_accept_reject on the library's static scratch array: no workspace argument, nothing allocated."""
     g = _host_i32(gamma_host)
     st = _accept_out_struct(out)
-    _check(lib().gs_accept_reject_static(int(g.size), g.ctypes.data, _ptr(cu_rows), int(vocab), _ptr(target_logits),
+    _check(lib().gs_accept_reject_static(int(g.size), _host_ptr(g), _ptr(cu_rows), int(vocab), _ptr(target_logits),
                                          _ptr(q_probs), _ptr(draft_tokens), _ptr(u_accept), _ptr(u_resample),
                                          C.byref(st), _stream(stream)))
     return out
@@ -321,8 +328,8 @@ class Verifier:
         g = _host_i32(gamma_host)
         cl = _host_i32(ctx_len_host)
         kv = gs_kv_cache(_ptr(k_pages), _ptr(v_pages), int(page_size), int(n_pages))
-        b = gs_batch(int(g.size), g.ctypes.data, cl.ctypes.data, _ptr(cu_rows).value, _ptr(ctx_len).value,
-                     _ptr(tokens).value, _ptr(block_table).value, int(block_table.shape[1]), None, None, None)
+        b = gs_batch(int(g.size), _host_ptr(g), _host_ptr(cl), _ptr(cu_rows), _ptr(ctx_len),
+                     _ptr(tokens), _ptr(block_table), int(block_table.shape[1]), None, None, None)
         _check(lib().gs_check_batch(self._ctx, C.byref(kv), C.byref(b), _ptr(workspace), workspace.numel(),
                                     _stream(stream)))
 
@@ -331,8 +338,8 @@ class Verifier:
         g = _host_i32(gamma_host)
         cl = _host_i32(ctx_len_host)
         kv = gs_kv_cache(_ptr(k_pages), _ptr(v_pages), int(page_size), int(n_pages))
-        b = gs_batch(int(g.size), g.ctypes.data, cl.ctypes.data, _ptr(cu_rows).value, _ptr(ctx_len).value,
-                     _ptr(tokens).value, _ptr(block_table).value, int(block_table.shape[1]),
+        b = gs_batch(int(g.size), _host_ptr(g), _host_ptr(cl), _ptr(cu_rows), _ptr(ctx_len),
+                     _ptr(tokens), _ptr(block_table), int(block_table.shape[1]),
                      None if q_probs is None else q_probs.data_ptr(),
                      None if u_accept is None else u_accept.data_ptr(),
                      None if u_resample is None else u_resample.data_ptr())
