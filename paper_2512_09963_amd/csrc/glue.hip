@@ -12,7 +12,7 @@ namespace {
 
 // Sum over the workgroup (any multiple of 64 threads up to 1024), fixed order.
 __device__ __forceinline__ float block_sum(float v, float* sh /*[16]*/) {
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_down(v, off);
+  v = wave_sum(v);
   if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = v;
   __syncthreads();
   float t = 0.f;
