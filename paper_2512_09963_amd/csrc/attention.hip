@@ -507,32 +507,41 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NW == 1
 }
 
 // attn_out[r][h*HD + d] = sum_s o_s * 2^(m_s - M) / sum_s l_s * 2^(m_s - M) over the splits of the row's query
-// group; the rows of a group that is not split are final already.  grid (R*H), block HD.
+// group; the rows of a group that is not split are final already.  HD / 4 lanes to a (row, head), 16 bytes per lane and split
+// (324 rows of 32 heads 6.1 us, 53 rows 4.7; a workgroup per (row, head) with a lane per channel 7.8 and 4.9).  grid ceil(R * H / (1024 / HD)).
+constexpr int kCombineThreads = 256;
 template <int HD>
-__global__ void attn_combine_kernel(const float* __restrict__ partial_o, const float* __restrict__ partial_ml,
-                                    int max_splits, int steps_per_split, const int4* __restrict__ row_info,
-                                    int n_heads, bf16_t* __restrict__ attn_out, bool packed) {
-  const size_t rh = blockIdx.x;
-  const int d = threadIdx.x;
-  const int n_keys = row_info[rh / n_heads].z;      // keys of the row's query group (per-row table of the step)
+__global__ __launch_bounds__(kCombineThreads) void attn_combine_kernel(const float* __restrict__ partial_o, const float* __restrict__ partial_ml,
+                                                                       int max_splits, int steps_per_split, const int4* __restrict__ row_info,
+                                                                       int n_rows, int n_heads, bf16_t* __restrict__ attn_out, bool packed) {
+  constexpr int LANES = HD / 4, PER_WG = kCombineThreads / LANES;
+  const int rh = blockIdx.x * PER_WG + threadIdx.x / LANES, d = threadIdx.x % LANES * 4;
+  if (rh >= n_rows * n_heads) return;
+  const int row = rh / n_heads;
+  const int n_keys = row_info[row].z;      // keys of the row's query group (per-row table of the step)
   const int n_splits = (((n_keys + 31) >> 5) + steps_per_split - 1) / steps_per_split;
   if (n_splits == 1) return;
   // one pass with a running maximum, so that no load waits for the maximum over all splits
-  const float2* ml = reinterpret_cast<const float2*>(partial_ml) + rh * max_splits;
-  const float* po = partial_o + rh * max_splits * HD + d;
-  float M = kNegBig, Lsum = 0.f, acc = 0.f;
+  const float2* ml = reinterpret_cast<const float2*>(partial_ml) + (size_t)rh * max_splits;
+  const float* po = partial_o + (size_t)rh * max_splits * HD + d;
+  float M = kNegBig, Lsum = 0.f;
+  float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll 4
   for (int s = 0; s < n_splits; ++s) {
     const float2 st = ml[s];
-    const float o = po[(size_t)s * HD];
+    const float4 o = *reinterpret_cast<const float4*>(po + (size_t)s * HD);
     const float Mn = fmaxf(M, st.x);
     const float c = exp2f(M - Mn), f = exp2f(st.x - Mn);
     Lsum = Lsum * c + st.y * f;
-    acc = acc * c + o * f;
+    acc.x = acc.x * c + o.x * f;
+    acc.y = acc.y * c + o.y * f;
+    acc.z = acc.z * c + o.z * f;
+    acc.w = acc.w * c + o.w * f;
     M = Mn;
   }
-  const int row = (int)(rh / n_heads);
-  attn_out[packed ? packed_index(row, (int)(rh - (size_t)row * n_heads) * HD + d, n_heads * HD) : rh * HD + d] = float_to_bf16(acc / Lsum);
+  const int col = (rh - row * n_heads) * HD + d;
+  *reinterpret_cast<uint2*>(attn_out + (packed ? packed_index(row, col, n_heads * HD) : (size_t)rh * HD + d)) =
+      make_uint2(pack_bf16x2(acc.x / Lsum, acc.y / Lsum), pack_bf16x2(acc.z / Lsum, acc.w / Lsum));
 }
 
 }  // namespace
@@ -784,14 +793,15 @@ gs_status launch_attention(int dtype, const void* q, const void* k_pages, const 
   GS_ATTN_CASE(64, 1) GS_ATTN_CASE(64, 2) GS_ATTN_CASE(64, 4) GS_ATTN_CASE(64, 8)
 #undef GS_ATTN_CASE
   if (st != GS_OK || !split) return st;
+  const unsigned combine_grid = (unsigned)ceil_div(n_rows * n_heads, kCombineThreads * 4 / hd);
   if (hd == 128)
-    attn_combine_kernel<128><<<n_rows * n_heads, 128, 0, stream>>>(po, pml, max_splits, steps_per_split,
-                                                                   static_cast<const int4*>(row_info), n_heads,
-                                                                   static_cast<bf16_t*>(attn_out), packed);
+    attn_combine_kernel<128><<<combine_grid, kCombineThreads, 0, stream>>>(po, pml, max_splits, steps_per_split,
+                                                                           static_cast<const int4*>(row_info), n_rows, n_heads,
+                                                                           static_cast<bf16_t*>(attn_out), packed);
   else
-    attn_combine_kernel<64><<<n_rows * n_heads, 64, 0, stream>>>(po, pml, max_splits, steps_per_split,
-                                                                 static_cast<const int4*>(row_info), n_heads,
-                                                                 static_cast<bf16_t*>(attn_out), packed);
+    attn_combine_kernel<64><<<combine_grid, kCombineThreads, 0, stream>>>(po, pml, max_splits, steps_per_split,
+                                                                          static_cast<const int4*>(row_info), n_rows, n_heads,
+                                                                          static_cast<bf16_t*>(attn_out), packed);
   GS_LAUNCH_CHECK("attn_combine");
   return GS_OK;
 }
