@@ -148,7 +148,8 @@ __global__ __launch_bounds__(kRowThreads) void attn_rowwise_kernel(const float* 
 }
 
 // ------------------------------------------------------------------------------------------
-// bf16 MFMA path.  1-D grid over the (work list entry, KV head) items (item_of_workgroup), NW waves per workgroup.
+// bf16 MFMA path.  1-D grid over the (work list entry, KV head) items (item_of_workgroup), NW waves per workgroup, or KW key
+// groups of NW waves that take the steps of the split in turn (kKeyGroups).
 //
 // A workgroup owns one split of one (server, query group, KV head): a group's steps are dealt evenly to its
 // ceil(steps / steps_per_split) splits; a step is 32
@@ -219,8 +220,8 @@ __device__ __forceinline__ float halves_sum(float x) {
 
 // (164 vector registers: three waves per SIMD, i.e. up to four 3-wave workgroups per CU, which hides a
 // workgroup's start-up and barrier stalls behind the others' loads)
-template <int HD, int G, int NW>
-__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NW == 1 ? 2 : 3))) void attn_kernel(const bf16_t* __restrict__ q,
+template <int HD, int G, int NW, int KW>
+__global__ __launch_bounds__(64 * NW * KW) __attribute__((amdgpu_waves_per_eu(KW > 1 ? 1 : NW == 1 ? 2 : 3))) void attn_kernel(const bf16_t* __restrict__ q,
                                                          const bf16_t* __restrict__ k_pages,
                                                          const bf16_t* __restrict__ v_pages,
                                                          const int* __restrict__ block_table, int max_blocks,
@@ -234,7 +235,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NW == 1
   constexpr int DT = HD / 32;            // 32-channel tiles of the second product
   constexpr int PART = HD * 32;          // bytes of K (or V) of one 16-key tile
   constexpr int STAGE = 4 * PART;        // K tile 0, K tile 1, V tile 0, V tile 1
-  __shared__ __attribute__((aligned(16))) unsigned char ring[2 * STAGE];
+  __shared__ __attribute__((aligned(16))) unsigned char rings[KW * 2 * STAGE];
 
   int entry, kh;
   item_of_workgroup(blockIdx.x, n_work * n_kv, n_kv, entry, kh);
@@ -244,7 +245,9 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NW == 1
   const int srv = wk.srv, split = wk.split, row0 = wk.row0, T = wk.n_tokens, L = wk.ctx;
   const int first_pages[2] = {wk.page0, wk.page1};
   const int lane = threadIdx.x & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wave_all = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int key_group = KW > 1 ? wave_all / NW : 0, wave = KW > 1 ? wave_all % NW : wave_all;
+  unsigned char* ring = rings + key_group * 2 * STAGE;
   const int h = lane >> 5, c32 = lane & 31;
   const int g = lane >> 4, c = lane & 15;            // loader roles
   const int n_keys = L + T;
@@ -254,8 +257,10 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NW == 1
   const int n_splits = (n_steps_all + steps_per_split - 1) / steps_per_split;
   if (split >= n_splits) return;
   const int base_steps = n_steps_all / n_splits, extra = n_steps_all - base_steps * n_splits;
-  const int step_begin = split * base_steps + min(split, extra);
-  const int n = base_steps + (split < extra ? 1 : 0);
+  const int n_wg = base_steps + (split < extra ? 1 : 0);
+  // the key groups take the steps of the split in turn
+  const int step_begin = split * base_steps + min(split, extra) + key_group;
+  const int n = KW > 1 ? (n_wg - key_group + KW - 1) / KW : n_wg;
   const int* bt = block_table + (size_t)srv * max_blocks;
   const bool page_pow2 = (page_size & (page_size - 1)) == 0;
   const int page_shift = 31 - __builtin_clz(page_size);
@@ -335,27 +340,30 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NW == 1
   };
 
   int pg_next[2], sl_next[2];
-  {
+  if (key_group == 0) {
     int blk[2];
     locate(step_begin, blk, sl_next);
     issue(0, first_pages, sl_next);
+  } else if (n > 0) {
+    lookup(step_begin, pg_next, sl_next);
+    issue(0, pg_next, sl_next);
   }
-  if (1 < n) lookup(step_begin + 1, pg_next, sl_next);
+  if (1 < n) lookup(step_begin + KW, pg_next, sl_next);
 
   // K fragment of k step kk for this lane: tile c32/16, fragment kk/2, lane group 2 (kk%2) + h, key c32%16
   const int k_lane = ((c32 >> 4) * KS * 64 + h * 16 + (c32 & 15)) * 16;
   // V: channel c32 of a 32-channel tile is 32 bytes per 16-key tile; this lane's runs start at slot 4h and 8 + 4h
   const int v_lane = 2 * PART + c32 * 32 + h * 8;
 
-  for (int s = 0; s < n; ++s) {
-    const int step = step_begin + s;
+  for (int s = 0; s < (KW > 1 ? (n_wg + KW - 1) / KW : n); ++s) {
+    const int step = step_begin + s * KW;
     wait_all_vector_loads();     // this wave's parts of stage s have landed
     __syncthreads();             // stage s complete for all waves; the other stage is free
     if (s + 1 < n) {
       issue((s + 1) & 1, pg_next, sl_next);
-      if (s + 2 < n) lookup(step + 2, pg_next, sl_next);     // for the next iteration's issue
+      if (s + 2 < n) lookup(step + 2 * KW, pg_next, sl_next);     // for the next iteration's issue
     }
-    if (step >= my_step_end) continue;
+    if (s >= n || step >= my_step_end) continue;
 
     const unsigned char* base = ring + (s & 1) * STAGE;
     bf16x8_t kf[KK];
@@ -478,6 +486,46 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NW == 1
     }
   }
 
+  // ---- the key groups' states meet in LDS, half of them handing theirs to the other half
+  if constexpr (KW > 1) {
+    static_assert(KW * 2 * STAGE >= KW / 2 * NW * (HD * 128 + 512), "the states of half of the key groups fit the rings");
+#pragma unroll
+    for (int half = KW / 2; half >= 1; half /= 2) {
+      __syncthreads();      // (all fragment reads, or the reads of the round before, are done)
+      float4* state = reinterpret_cast<float4*>(rings);
+      float2* ml = reinterpret_cast<float2*>(rings + KW / 2 * NW * HD * 128);
+      if (key_group >= half && key_group < 2 * half) {
+        const int slot = (key_group - half) * NW + wave;
+        ml[slot * 64 + lane] = make_float2(m_run, l_run);
+#pragma unroll
+        for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+          for (int b = 0; b < 4; ++b)
+            state[(slot * DT * 4 + dt * 4 + b) * 64 + lane] =
+                make_float4(oacc[dt][4 * b], oacc[dt][4 * b + 1], oacc[dt][4 * b + 2], oacc[dt][4 * b + 3]);
+      }
+      __syncthreads();
+      if (key_group < half) {
+        const int slot = key_group * NW + wave;
+        const float2 other = ml[slot * 64 + lane];
+        const float m_new = fmaxf(m_run, other.x);
+        const float f = __builtin_amdgcn_exp2f(m_run - m_new), f_other = __builtin_amdgcn_exp2f(other.x - m_new);
+        l_run = l_run * f + other.y * f_other;
+        m_run = m_new;
+#pragma unroll
+        for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+          for (int b = 0; b < 4; ++b) {
+            const float4 v = state[(slot * DT * 4 + dt * 4 + b) * 64 + lane];
+            oacc[dt][4 * b] = oacc[dt][4 * b] * f + v.x * f_other;
+            oacc[dt][4 * b + 1] = oacc[dt][4 * b + 1] * f + v.y * f_other;
+            oacc[dt][4 * b + 2] = oacc[dt][4 * b + 2] * f + v.z * f_other;
+            oacc[dt][4 * b + 3] = oacc[dt][4 * b + 3] * f + v.w * f_other;
+          }
+      }
+    }
+    if (key_group != 0) return;
+  }
   // ---- lane l holds query row l%32, channels 32 dt + 8 b + 4 h + (0..3)
   if (!my_ok) return;
   if (n_splits == 1) {      // the group is not split: the result is final
@@ -554,6 +602,13 @@ __global__ __launch_bounds__(kCombineThreads) void attn_combine_kernel(const flo
 // 8 prompts of 128 tokens: 30 us and 14 us, now 14 us.)
 constexpr int kMaxWaves = 8;
 constexpr int kGroupWaves = 4;
+// Key groups: where a launch leaves compute units idle and a block is one tile of query rows, four waves of a workgroup take the
+// steps of its split in turn (0.85 us a step), each with a ring of its own, and merge their states in LDS.  8B shape, 4 layers, one
+// server at 700 / 2048 keys 395 -> 385 and 400 -> 393 us, two servers 408 -> 397 and 415 -> 408.  A workgroup then fills the LDS of a
+// compute unit: with 256 of them 8 servers at 2048 keys take 499 instead of 492; two tiles of rows gain nothing.  (Fewer splits
+// instead, as the key groups would allow, are slower: a compute unit alone streams 26 GB/s, 700 keys unsplit take 22 us, in four
+// splits with the merge 15.)
+constexpr int kKeyGroups = 4, kKeyGroupItems = 192;
 void attention_groups(int group, long max_block_tokens, int* waves, int* group_tokens) {
   const long tiles = (max_block_tokens * group + 31) / 32;
   *waves = tiles > kMaxWaves ? kGroupWaves : tiles > 0 ? (int)tiles : 1;
@@ -656,7 +711,7 @@ static long group_steps_per_split(int n_kv, int n_servers, const int* gamma_host
 // results few; a floor on the steps per split bounds what the partial results cost on small batches.
 // Prompt blocks whose unsplit groups already give every compute unit a workgroup: see group_steps_per_split.
 void attention_plan(int n_kv, int group, long max_block_tokens, int n_servers, const int* gamma_host,
-                    const int* ctx_len_host, int* steps_per_split, int* max_splits) {
+                    const int* ctx_len_host, int* steps_per_split, int* max_splits, int* key_groups) {
   int waves, group_tokens;
   attention_groups(group, max_block_tokens, &waves, &group_tokens);
   constexpr int kWavesPerCu = 12;    // by registers (three waves per SIMD)
@@ -710,6 +765,7 @@ void attention_plan(int n_kv, int group, long max_block_tokens, int n_servers, c
     if (sps > max_steps) sps = max_steps;
   }
   *steps_per_split = (int)sps;
+  *key_groups = waves == 1 && n_groups == n_servers && sps > 1 && workgroups(sps) <= kKeyGroupItems ? kKeyGroups : 1;
   // the split count is also the stride (in 512-byte partial rows) between the partial results of
   // neighbouring (row, head) pairs: kept odd, because a power-of-two stride sends all partial stores of a
   // workgroup to the same few memory channels (measured: 110 instead of 81 us per layer at a stride of 32)
@@ -723,13 +779,19 @@ size_t attention_workspace_floats(int n_rows, int n_heads, int hd, int max_split
 template <int HD, int G>
 static gs_status launch_mfma_g(const bf16_t* q, const bf16_t* k_pages, const bf16_t* v_pages, const int* block_table,
                                int max_blocks, const int* work, int n_work, int page_size,
-                               int n_heads, int n_kv, int waves, int steps_per_split, int max_splits,
+                               int n_heads, int n_kv, int waves, int key_groups, int steps_per_split, int max_splits,
                                float* po, float* pml, bf16_t* attn_out, bool packed, hipStream_t stream) {
   dim3 grid((unsigned)n_work * (unsigned)n_kv);      // one workgroup per (entry, KV head) item, see item_of_workgroup
-#define GS_RING(NW_)                                                                                              \
-  attn_kernel<HD, G, NW_><<<grid, 64 * NW_, 0, stream>>>(q, k_pages, v_pages, block_table, max_blocks, work,      \
+#define GS_RING(NW_) GS_RINGS(NW_, 1)
+#define GS_RINGS(NW_, KW_)                                                                                        \
+  attn_kernel<HD, G, NW_, KW_><<<grid, 64 * NW_ * KW_, 0, stream>>>(q, k_pages, v_pages, block_table, max_blocks, work,      \
                                                          n_work, page_size, n_heads, n_kv, steps_per_split, max_splits,   \
                                                          po, pml, attn_out, packed)
+  if (key_groups > 1) {
+    GS_RINGS(1, kKeyGroups);      // (one wave of query rows)
+    GS_LAUNCH_CHECK("attn");
+    return GS_OK;
+  }
   switch (waves) {
     case 1: GS_RING(1); break;
     case 2: GS_RING(2); break;
@@ -741,6 +803,7 @@ static gs_status launch_mfma_g(const bf16_t* q, const bf16_t* k_pages, const bf1
     default: GS_RING(8); break;
   }
 #undef GS_RING
+#undef GS_RINGS
   GS_LAUNCH_CHECK("attn");
   return GS_OK;
 }
@@ -755,7 +818,7 @@ size_t attention_work_ints(int capacity) { return 8 + 8 * (size_t)capacity; }
 gs_status launch_attention(int dtype, const void* q, const void* k_pages, const void* v_pages,
                            const int* block_table, int max_blocks, const int* cu_rows, const int* ctx_len,
                            int n_servers, int n_rows, int page_size, int n_heads, int n_kv, int hd,
-                           int waves, int steps_per_split, int max_splits, bool split, const void* row_info,
+                           int waves, int key_groups, int steps_per_split, int max_splits, bool split, const void* row_info,
                            const int* work, int n_work, float* scratch, void* attn_out, bool packed, hipStream_t stream) {
   if (dtype == GS_F32) {
     dim3 grid(n_rows, n_heads);
@@ -787,7 +850,7 @@ gs_status launch_attention(int dtype, const void* q, const void* k_pages, const 
 #define GS_ATTN_CASE(HD_, G_)                                                                                     \
   if (hd == HD_ && G == G_)                                                                                       \
     st = launch_mfma_g<HD_, G_>(qb, kb, vb, block_table, max_blocks, work, n_work, page_size, n_heads, n_kv,     \
-                                waves, steps_per_split, max_splits, po, pml, static_cast<bf16_t*>(attn_out),       \
+                                waves, key_groups, steps_per_split, max_splits, po, pml, static_cast<bf16_t*>(attn_out),       \
                                 packed, stream);
   GS_ATTN_CASE(128, 1) GS_ATTN_CASE(128, 2) GS_ATTN_CASE(128, 4) GS_ATTN_CASE(128, 8)
   GS_ATTN_CASE(64, 1) GS_ATTN_CASE(64, 2) GS_ATTN_CASE(64, 4) GS_ATTN_CASE(64, 8)

@@ -40,7 +40,7 @@ gs_status launch_rope_append(int dtype, const float* qkv, int n_splits, int n_ro
                              void* k_pages, void* v_pages, hipStream_t stream);
 gs_status launch_swiglu(int dtype, const float* gu, int n_splits, int n_rows, int F, void* act, hipStream_t stream);
 void attention_plan(int n_kv, int group, long max_block_tokens, int n_servers, const int* gamma_host,
-                    const int* ctx_len_host, int* steps_per_split, int* max_splits);
+                    const int* ctx_len_host, int* steps_per_split, int* max_splits, int* key_groups);
 void attention_groups(int group, long max_block_tokens, int* waves, int* group_tokens);
 long attention_items(int n_servers, const int* gamma_host, const int* ctx_len_host, int group_tokens, int steps_per_split);
 long attention_max_groups(int max_rows, int max_servers);
@@ -50,7 +50,7 @@ size_t attention_workspace_floats(int n_rows, int n_heads, int hd, int max_split
 gs_status launch_attention(int dtype, const void* q, const void* k_pages, const void* v_pages,
                            const int* block_table, int max_blocks, const int* cu_rows, const int* ctx_len,
                            int n_servers, int n_rows, int page_size, int n_heads, int n_kv, int hd,
-                           int waves, int steps_per_split, int max_splits, bool split, const void* row_info,
+                           int waves, int key_groups, int steps_per_split, int max_splits, bool split, const void* row_info,
                            const int* work, int n_work, float* scratch, void* attn_out, bool packed, hipStream_t stream);
 size_t attention_work_ints(int capacity);
 gs_status launch_accept(int n_servers, int n_rows, const int* cu_rows, int vocab, int elem, const void* target_logits,
@@ -423,10 +423,10 @@ extern "C" gs_status gs_verify_batch(gs_ctx* ctx, const gs_kv_cache* kv, const g
   const int rows = (int)R, d = m.d_model, hq = m.n_heads * m.head_dim, qkv = (m.n_heads + 2 * m.n_kv_heads) * m.head_dim;
   const int F = m.d_ffn;
   const size_t layer_stride = (size_t)kv->n_pages * m.n_kv_heads * kv->page_size * m.head_dim * ctx->elem;
-  int attn_sps = 1, attn_splits = 1, attn_waves = 1, group_tokens = 1;
+  int attn_sps = 1, attn_splits = 1, attn_waves = 1, attn_key_groups = 1, group_tokens = 1;
   gs::attention_groups(m.n_heads / m.n_kv_heads, max_t, &attn_waves, &group_tokens);
   gs::attention_plan(m.n_kv_heads, m.n_heads / m.n_kv_heads, max_t, n, b->gamma_host, b->ctx_len_host, &attn_sps,
-                     &attn_splits);
+                     &attn_splits, &attn_key_groups);
   bool attn_split = max_ctx > 32L * attn_sps;      // any group with more than one split
   gs_status st;
 #define GS_TRY(call)          \
@@ -474,7 +474,7 @@ extern "C" gs_status gs_verify_batch(gs_ctx* ctx, const gs_kv_cache* kv, const g
                                     p.rope, kv->page_size, m.n_heads, m.n_kv_heads, m.head_dim, p.q, kl, vl, stream));
     }
     GS_STAGE(GS_STAGE_ATTENTION, gs::launch_attention(act, p.q, kl, vl, b->block_table, b->max_blocks, b->cu_rows, b->ctx_len, n, rows,
-                                kv->page_size, m.n_heads, m.n_kv_heads, m.head_dim, attn_waves, attn_sps, attn_splits,
+                                kv->page_size, m.n_heads, m.n_kv_heads, m.head_dim, attn_waves, attn_key_groups, attn_sps, attn_splits,
                                 attn_split, p.row_slot, p.attn_work, (int)attn_items, p.attn_scratch, p.attn, packed, stream));
     if (fused) {
       const bool top = l + 1 == m.n_layers;
@@ -579,9 +579,9 @@ extern "C" gs_status gs_plan_attention(int n_kv_heads, int group, int n_servers,
       return gs::fail(GS_EINVAL, "server %d: gamma = %d, ctx_len = %d", i, gamma_host[i], ctx_len_host[i]);
     max_t = std::max(max_t, gamma_host[i] + 1L);
   }
-  int sps = 1, splits = 1, waves = 1, group_tokens = 1;
+  int sps = 1, splits = 1, waves = 1, key_groups = 1, group_tokens = 1;
   gs::attention_groups(group, max_t, &waves, &group_tokens);
-  gs::attention_plan(n_kv_heads, group, max_t, n_servers, gamma_host, ctx_len_host, &sps, &splits);
+  gs::attention_plan(n_kv_heads, group, max_t, n_servers, gamma_host, ctx_len_host, &sps, &splits, &key_groups);
   long items = 0;
   const long busiest = gs::attention_busiest_cu(n_kv_heads, n_servers, gamma_host, ctx_len_host, group_tokens, sps, &items);
   *steps_per_split = sps;

@@ -70,3 +70,16 @@ def test_bf16_projections_with_four_k_groups(rows):
     gamma = np.array([rows - 20, 11, 6] if rows > 20 else [rows - 3, 0, 1], np.int32)
     # (std: see above)
     _run_case(ms, 700 + rows, gamma, np.array([40, 0, 19], np.int32), 16, 0.02)
+
+
+@pytest.mark.parametrize("heads,n_kv,hd,gamma,ctx,page", [
+    (4, 1, 128, [7], [0], 16),                          # one step: three key groups have none
+    (4, 2, 128, [3, 0], [40, 90], 16),                  # two and three steps
+    (8, 2, 64, [4, 2], [700, 129], 32),                 # splits of six and five steps
+    (8, 1, 128, [3], [8190], 16),                       # 32 splits, the longest context here; a block across a step's end
+    (2, 2, 64, [31, 5, 0], [333, 64, 1], 48),           # a full tile of rows; page size that is no power of two
+])
+def test_bf16_attention_with_key_groups(heads, n_kv, hd, gamma, ctx, page):
+    """Few workgroups of one tile of query rows: four waves share the steps of a split."""
+    ms = synth.ModelShape(1, 128, heads, n_kv, hd, 192, 320, 10000.0, dtype="bf16")
+    _run_case(ms, 900 + page + heads, np.array(gamma, np.int32), np.array(ctx, np.int32), page, 0.08)
