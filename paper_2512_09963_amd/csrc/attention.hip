@@ -530,14 +530,15 @@ __global__ __launch_bounds__(64 * NW * KW) __attribute__((amdgpu_waves_per_eu(KW
   if (!my_ok) return;
   if (n_splits == 1) {      // the group is not split: the result is final
     const int row = row0 + my_j, col0 = (kh * G + my_hg) * HD + 4 * h, width = n_heads * HD;
+    const float inv = 1.0f / l_run;
 #pragma unroll
     for (int dt = 0; dt < DT; ++dt)
 #pragma unroll
       for (int b = 0; b < 4; ++b)
         *reinterpret_cast<uint2*>(attn_out + (packed ? packed_index(row, col0 + dt * 32 + b * 8, width)
                                                      : (size_t)row * width + col0 + dt * 32 + b * 8)) =
-            make_uint2(pack_bf16x2(oacc[dt][4 * b] / l_run, oacc[dt][4 * b + 1] / l_run),
-                       pack_bf16x2(oacc[dt][4 * b + 2] / l_run, oacc[dt][4 * b + 3] / l_run));
+            make_uint2(pack_bf16x2(oacc[dt][4 * b] * inv, oacc[dt][4 * b + 1] * inv),
+                       pack_bf16x2(oacc[dt][4 * b + 2] * inv, oacc[dt][4 * b + 3] * inv));
     return;
   }
   const size_t out_idx = ((size_t)(row0 + my_j) * n_heads + kh * G + my_hg) * max_splits + split;
