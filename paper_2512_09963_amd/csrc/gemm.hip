@@ -195,7 +195,7 @@ __global__ __launch_bounds__(64 * NW) void gemm_bf16_skinny_kernel(const bf16_t*
 // 16 bytes of row c at k + 4 g, the k order inside a 16-wide step being permuted alike in both operands), two to eight steps
 // in flight, and the slices' sums meet in LDS in a fixed order.  2-layer model of width 256 / 1024 at 16 rows: a plain launch
 // 4 us, with the rotation or the SwiGLU and the rows' factors 5.7, the residual forms 4.6 (K = 256) and 6 (K = 1024); the whole
-// step 86 -> 76 us against separate kernels for norms, rotation and SwiGLU (25 launches, 16 now).
+// step 86 -> 74 us against separate kernels for norms, rotation and SwiGLU (25 launches, 15 now).
 // grid (column groups, row chunks of MT * 16).
 constexpr int kF32Waves = 8;
 // LOADS: kWholeSteps where K is a multiple of 16 and the operands are 16-byte aligned, kVec4 where K is a multiple of 4,
