@@ -31,7 +31,7 @@ def test_f32_attention_chunks_and_page_sizes(hd, page, gamma, ctx):
     (100, 2, 1, 64, 64, 9),            # a width that is no multiple of 64: the separate kernels
     (256, 4, 4, 64, 1024, 64),
     (256, 4, 4, 64, 1024, 65),         # past the last fused row
-    (4160, 1, 1, 64, 32, 3),           # sums of squares in two loads per lane
+    (4160, 1, 1, 64, 32, 3),           # sums of squares of 260 tiles: five loads per lane
 ])
 def test_f32_layer_of_five_launches(d, heads, n_kv, hd, ffn, rows):
     ms = synth.ModelShape(2, d, heads, n_kv, hd, ffn, 272, 10000.0, dtype="f32")
@@ -42,13 +42,16 @@ def test_f32_layer_of_five_launches(d, heads, n_kv, hd, ffn, rows):
 @pytest.mark.parametrize("d,heads,n_kv,hd,ffn,rows", [
     (64, 1, 1, 64, 64, 2),             # one k step: three waves of four have none
     (128, 2, 1, 128, 192, 16),
-    (192, 4, 2, 64, 576, 17),          # 3 and 9 steps over 4 and 8 waves; head size 64: 2 tiles a half
-    (320, 8, 1, 64, 2496, 31),         # 39 steps: past the ring of 8 x 4 and of 4 x 8 steps
+    (192, 4, 2, 64, 576, 11),          # 3 and 9 steps over 8 and 4 waves; head size 64: 2 tiles a half
+    (320, 8, 1, 64, 2496, 15),         # 39 steps: past the ring of 8 x 4 steps
+    (192, 4, 2, 64, 576, 17),          # past the last row: K splits and separate norms
+    (320, 8, 1, 64, 2496, 31),
     (256, 8, 8, 128, 1024, 32),
-    (256, 8, 8, 128, 1024, 33),        # past the last row of these kernels
+    (256, 8, 8, 128, 1024, 33),
     (128, 4, 4, 64, 1088, 9),          # F > 8 d: the kernels with K splits
     (256, 64, 8, 128, 512, 12),        # 10240 columns: two pairs of tiles per workgroup
-    (256, 63, 63, 64, 512, 20),        # 12096 columns: 189 workgroups of two pairs
+    (256, 63, 63, 64, 512, 13),        # 12096 columns: 189 workgroups of two pairs
+    (256, 63, 63, 64, 512, 20),
     (4160, 2, 2, 64, 128, 7),          # 260 column tiles: two per workgroup; sums of squares of 260 tiles
     (4160, 2, 2, 64, 128, 27),
 ])
