@@ -398,10 +398,8 @@ gs_status launch_pack_weight(const void* src, void* dst, int N, int K, hipStream
 // Which bf16 kernel serves a shape, and how the launch is cut.
 struct GemmPlan {
   enum Kind {
-    kSkinny,      // column counts that are no multiple of 128
-    kWide         // gemm_wide.hip: everything else.  (Up to 64 rows the K-split projections too: with its four K groups, or two
-                  // where four splits are enough, steps of 4 layers of the 8B shape at 24 / 32 / 60 rows 649 / 648 / 707 us ->
-                  // 615 / 630 / 688, of 2 layers of the 70B shape at 24 / 60 rows 996 / 1049 -> 912 / 989.)
+    kSkinny,      // column counts that are no multiple of 128, and small matrices of a few rows (wide_serves)
+    kWide         // gemm_wide.hip: everything else
   } kind;
   int mt;         // row tiles per workgroup
   int m_chunks;   // row chunks (separate workgroups)
@@ -410,12 +408,24 @@ struct GemmPlan {
   WidePlan wide;
 };
 
+// Whether the wide kernel serves a shape.  Up to 64 rows it takes the projections without K splits and the large ones: where the
+// 64-column workgroups and 512-element K splits of the skinny kernel leave at most one workgroup to a compute unit, a launch is
+// over before the wide kernel's three buffers and exchange of K groups pay.  Isolated launches, skinny and wide, us at 20 / 64 rows:
+// 1024 x 4096 5.3 / 6.0 and 6.7 / 8.1, 2048 x 2048 5.3 / 6.0 and 6.6 / 8.0, 4096 x 2048 7.2 / 7.8 and 7.5 / 8.8; beyond the line 1536 x 6144
+// 7.9 / 9.3 and 7.5 / 9.1, 3072 x 3072 7.9 / 9.6 and 7.6 / 9.1.  Larger ones gain in the step as well by fewer partial results: 4 layers of the 8B
+// shape at 24 / 32 / 60 rows 649 / 648 / 707 us -> 615 / 630 / 688, 2 layers of the 70B shape at 24 / 60 rows 996 / 1049 -> 912 / 989.
+bool wide_serves(int M, int N, int K) {
+  if (N % 128 != 0) return false;
+  if (M > 64 || wide_plan(M, N, K, false).splits == 1) return true;
+  return (long)(N / 64) * (K / 512) > 256;
+}
+
 static GemmPlan gemm_plan(int M, int N, int K) {
   GemmPlan p;
   const int tiles = ceil_div(M, 16);
   int n_blocks;
   if (N % 128 == 0) p.wide = wide_plan(M, N, K, false);
-  if (N % 128 == 0) {
+  if (wide_serves(M, N, K)) {
     p.kind = GemmPlan::kWide;
     p.mt = p.wide.mt;
     p.m_chunks = p.wide.m_chunks;

@@ -75,6 +75,15 @@ def test_bf16_projections_with_four_k_groups(rows):
     _run_case(ms, 700 + rows, gamma, np.array([40, 0, 19], np.int32), 16, 0.02)
 
 
+@pytest.mark.parametrize("rows", [17, 33, 64, 65])
+def test_bf16_projections_of_small_matrices(rows):
+    """2048 x 1024, 1024 x 1024 and 1024 x 2048 in two, two and four K splits of the skinny kernel, two and four row tiles; 65 rows: past
+    them."""
+    ms = synth.ModelShape(1, 1024, 8, 4, 128, 2048, 512, 10000.0, dtype="bf16")
+    gamma = np.array([rows - 12, 0, 9], np.int32)
+    _run_case(ms, 600 + rows, gamma, np.array([40, 0, 19], np.int32), 16, 0.035)
+
+
 @pytest.mark.parametrize("heads,n_kv,hd,gamma,ctx,page", [
     (4, 1, 128, [7], [0], 16),                          # one step: three key groups have none
     (4, 2, 128, [3, 0], [40, 90], 16),                  # two and three steps
