@@ -608,8 +608,11 @@ constexpr int kGroupWaves = 4;
 // server at 700 / 2048 keys 395 -> 385 and 400 -> 393 us, two servers 408 -> 397 and 415 -> 408.  A workgroup then fills the LDS of a
 // compute unit: with 256 of them 8 servers at 2048 keys take 499 instead of 492; two tiles of rows gain nothing.  (Fewer splits
 // instead, as the key groups would allow, are slower: a compute unit alone streams 26 GB/s, 700 keys unsplit take 22 us, in four
-// splits with the merge 15.)
-constexpr int kKeyGroups = 4, kKeyGroupItems = 192;
+// splits with the merge 15.)  On short contexts, whose only split has fewer than kKeyGroupSteps steps, the start of four rings and
+// the merge cost more than the steps they save: 16 layers of 32 heads of 128 over 8, 1 to 24 servers, whole call against one key
+// group: 2 steps 1.02 to 1.08 times as long, 3 steps 1.01 to 1.05, 4 and 5 steps 0.99 to 1.02, 6 steps 0.95 to 0.985; 7 steps and
+// more, in splits of up to 6, 0.95 to 0.985.
+constexpr int kKeyGroups = 4, kKeyGroupItems = 192, kKeyGroupSteps = 6;
 void attention_groups(int group, long max_block_tokens, int* waves, int* group_tokens) {
   const long tiles = (max_block_tokens * group + 31) / 32;
   *waves = tiles > kMaxWaves ? kGroupWaves : tiles > 0 ? (int)tiles : 1;
@@ -766,7 +769,7 @@ void attention_plan(int n_kv, int group, long max_block_tokens, int n_servers, c
     if (sps > max_steps) sps = max_steps;
   }
   *steps_per_split = (int)sps;
-  *key_groups = waves == 1 && n_groups == n_servers && sps > 1 && workgroups(sps) <= kKeyGroupItems ? kKeyGroups : 1;
+  *key_groups = waves == 1 && n_groups == n_servers && sps >= kKeyGroupSteps && workgroups(sps) <= kKeyGroupItems ? kKeyGroups : 1;
   // the split count is also the stride (in 512-byte partial rows) between the partial results of
   // neighbouring (row, head) pairs: kept odd, because a power-of-two stride sends all partial stores of a
   // workgroup to the same few memory channels (measured: 110 instead of 81 us per layer at a stride of 32)

@@ -2,6 +2,7 @@
 (no GPU needed).  The lines lie where both sides were measured; the figures stand beside the rules."""
 import ctypes as C
 
+import numpy as np
 import pytest
 
 from paper_2512_09963_amd import binding as gsb
@@ -33,3 +34,32 @@ def test_bf16_projections_of_up_to_64_rows(M, N, K, wide):
 @pytest.mark.parametrize("N,K", [(1024, 1024), (1024, 4096), (2048, 2048), (4096, 14336)])
 def test_bf16_projections_of_more_rows_are_wide(N, K):
     assert _wide_serves(65, N, K) and _wide_serves(2047, N, K) and not _wide_serves(65, N + 64, K)
+
+
+def attention_key_groups(n_kv, group, gamma, ctx):
+    """(key groups per workgroup, steps per split) of the attention launch."""
+    g, c = np.ascontiguousarray(gamma, np.int32), np.ascontiguousarray(ctx, np.int32)
+    sps, splits, groups = C.c_int(), C.c_int(), C.c_int()
+    ip = C.POINTER(C.c_int)
+    plan = _rule("_ZN2gs14attention_planEiiliPKiS1_PiS2_S2_", None, C.c_int, C.c_int, C.c_long, C.c_int, C.c_void_p, C.c_void_p, ip, ip, ip)
+    plan(n_kv, group, int(g.max()) + 1, g.size, g.ctypes.data, c.ctypes.data, C.byref(sps), C.byref(splits), C.byref(groups))
+    return groups.value, sps.value
+
+
+@pytest.mark.parametrize("n", [1, 2, 8, 16, 24])
+def test_attention_of_short_contexts_has_one_key_group(n):
+    """A split of fewer than six steps of 32 keys is over before the start of four rings and their merge pay."""
+    for keys in range(1, 161):
+        assert attention_key_groups(8, 4, [0] * n, [keys - 1] * n)[0] == 1
+    for keys in range(161, 193):
+        assert attention_key_groups(8, 4, [0] * n, [keys - 1] * n) == (4, 6)
+
+
+@pytest.mark.parametrize("gamma,ctx,groups", [
+    ([0], [700], 4), ([7], [2040], 4), ([3] * 4, [500] * 4, 4),
+    ([3] * 8, [2048] * 8, 1),      # more than 192 workgroups
+    ([8], [700], 1),               # 36 query rows: two tiles
+    ([40], [700], 1),
+])
+def test_attention_key_groups(gamma, ctx, groups):
+    assert attention_key_groups(8, 4, gamma, ctx)[0] == groups

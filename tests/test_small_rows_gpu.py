@@ -4,6 +4,7 @@ import numpy as np
 import pytest
 
 from paper_2512_09963_amd import synth
+from tests.test_routes import attention_key_groups
 from tests.test_verify_gpu import _run_case
 
 pytestmark = pytest.mark.gpu
@@ -84,14 +85,16 @@ def test_bf16_projections_of_small_matrices(rows):
     _run_case(ms, 600 + rows, gamma, np.array([40, 0, 19], np.int32), 16, 0.035)
 
 
-@pytest.mark.parametrize("heads,n_kv,hd,gamma,ctx,page", [
-    (4, 1, 128, [7], [0], 16),                          # one step: three key groups have none
-    (4, 2, 128, [3, 0], [40, 90], 16),                  # two and three steps
-    (8, 2, 64, [4, 2], [700, 129], 32),                 # splits of six and five steps
-    (8, 1, 128, [3], [8190], 16),                       # 32 splits, the longest context here; a block across a step's end
-    (2, 2, 64, [31, 5, 0], [333, 64, 1], 48),           # a full tile of rows; page size that is no power of two
+@pytest.mark.parametrize("heads,n_kv,hd,gamma,ctx,page,key_groups", [
+    (4, 1, 128, [7], [0], 16, 1),                          # short contexts: one wave and one ring
+    (4, 1, 128, [7, 0], [0, 300], 16, 4),                  # one step (three key groups have none) beside splits of five
+    (4, 2, 128, [3, 0], [40, 190], 16, 4),                 # two and six steps
+    (8, 2, 64, [4, 2], [700, 129], 32, 4),                 # splits of six and five steps
+    (8, 1, 128, [3], [8190], 16, 4),                       # 29 splits of nine and eight, the longest context here; a block across a step's end
+    (2, 2, 64, [31, 5, 0], [333, 64, 1], 48, 4),           # a full tile of rows; page size that is no power of two
 ])
-def test_bf16_attention_with_key_groups(heads, n_kv, hd, gamma, ctx, page):
+def test_bf16_attention_with_key_groups(heads, n_kv, hd, gamma, ctx, page, key_groups):
     """Few workgroups of one tile of query rows: four waves share the steps of a split."""
+    assert attention_key_groups(n_kv, heads // n_kv, gamma, ctx)[0] == key_groups
     ms = synth.ModelShape(1, 128, heads, n_kv, hd, 192, 320, 10000.0, dtype="bf16")
     _run_case(ms, 900 + page + heads, np.array(gamma, np.int32), np.array(ctx, np.int32), page, 0.08)
