@@ -555,15 +555,21 @@ static void launch_f32(const float* x, const float* w, float* y, int M, int N, i
 #undef GS_F32
 }
 
-// Whether a block of M rows runs a layer in the launches below (see RowNorm).  fp32: one row chunk; the tiles of the QKV
-// and gate/up projections come in pairs, the sums of squares in whole 16-byte loads.
-bool rows_fused(int dtype, int M, int d, int F) {
+// Whether a block of M rows runs a layer in the launches below (see RowNorm); hq = heads x head size, qkv: columns of the QKV
+// projection.  fp32: one row chunk; the tiles of the QKV and gate/up projections come in pairs, the sums of squares in whole
+// 16-byte loads.
+bool rows_fused(int dtype, int M, int d, int hq, int qkv, int F) {
   if (M <= 0 || d > kRowNormMaxWidth || d % 64 != 0) return false;
   if (dtype == GS_F32) return M <= 64 && F % 16 == 0;
   // bf16: up to 16 rows, 8 where a workgroup has 32 columns; beyond, K splits and separate norms are faster (8B shape, 4 layers, us
   // fused and not: 5 rows 545 / 590, 16 rows 590 / 600, 20 rows 623 / 609; 70B shape, 2 layers: 5 rows 898 / 904, 12 rows
-  // 927 / 912).  A K of more than eight times the columns wants K splits: few workgroups would stream it alone.
-  if (dtype == GS_BF16) return M <= (d <= 4096 ? kMaxRows : kMaxRows / 2) && F <= 8 * d;
+  // 927 / 912).  A K of many times the columns wants K splits, few workgroups would stream it alone: F up to eight times d, and
+  // heads and F together up to nine times, or 9216 on narrow matrices (4 layers, F = 4 d, whole calls at 1 / 16 rows, fused to not:
+  // hq = 4 d 0.91 / 0.98 at d = 1024 and 0.90 / 0.97 at 2048; 8 d 1.01 / 1.07 and 0.99 / 1.06; 16 d 1.17 / 1.26 at 1024; 32 d 1.19 / 1.30 at 512).
+  // A QKV projection of up to 16384 columns is one workgroup per compute unit; more start a second round, which only the
+  // savings of wide models outweigh (18432 columns: d = 512 1.07 / 1.09, 2048 1.03 / 1.04, 3072 0.96 / 1.00, 4096 0.92 / 0.96).
+  if (dtype == GS_BF16)
+    return M <= (d <= 4096 ? kMaxRows : kMaxRows / 2) && F <= 8 * d && hq + F <= 9 * std::max(d, 1024) && (qkv <= 16384 || d >= 3072);
   return false;
 }
 gs_status launch_bf16_rows_qkv(const bf16_t* h, const bf16_t* w, const RowNorm& norm, const QkvOut& out, int M, int K, hipStream_t stream);

@@ -20,7 +20,7 @@ gs_status launch_pack_weight_w4(const void* q, const void* scales, const void* z
 gs_status launch_gemm(int dtype, const void* X, const void* W, float* P, int M, int N, int K, hipStream_t stream);
 bool gate_up_fused(int dtype, int M, int F, int K);
 gs_status launch_gemm_gate_up(int dtype, const void* X, const void* W, void* act, int M, int F, int K, hipStream_t stream);
-bool rows_fused(int dtype, int M, int d, int F);
+bool rows_fused(int dtype, int M, int d, int hq, int qkv, int F);
 gs_status launch_rows_qkv(int dtype, const void* h, const void* w, const RowNorm& norm, const QkvOut& out, int M, int K,
                           hipStream_t stream);
 gs_status launch_rows_gate_up(int dtype, const void* h, const void* w, const RowNorm& norm, void* act, int M, int F, int K,
@@ -439,7 +439,7 @@ extern "C" gs_status gs_verify_batch(gs_ctx* ctx, const gs_kv_cache* kv, const g
   const long attn_items = gs::attention_items(n, b->gamma_host, b->ctx_len_host, group_tokens, attn_sps);
   if (attn_items > p.attn_work_capacity) return gs::fail(GS_ECAPACITY, "attention work list overflow");
 
-  const bool fused = gs::rows_fused(m.dtype, rows, d, F);      // norms, rotation and residual inside the projections
+  const bool fused = gs::rows_fused(m.dtype, rows, d, hq, qkv, F);      // norms, rotation and residual inside the projections
   const bool packed = fused && act == GS_BF16;                   // bf16 activations of such layers in fragment order
   const gs::RowNorm norm{p.squares, d / 16, 1.0f / (float)d, m.rms_eps};
   StageTimer timer(ctx, stream);

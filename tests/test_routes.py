@@ -63,3 +63,20 @@ def test_attention_of_short_contexts_has_one_key_group(n):
 ])
 def test_attention_key_groups(gamma, ctx, groups):
     assert attention_key_groups(8, 4, gamma, ctx)[0] == groups
+
+
+@pytest.mark.parametrize("dtype,M,d,hq,qkv,F,fused", [
+    (1, 16, 4096, 4096, 6144, 14336, True), (1, 17, 4096, 4096, 6144, 14336, False),
+    (1, 8, 8192, 8192, 10240, 28672, True), (1, 9, 8192, 8192, 10240, 28672, False),
+    (1, 1, 256, 8192, 10240, 1024, True), (1, 1, 256, 8192, 10240, 1088, False),              # heads and features: 9216
+    (1, 1, 1024, 4096, 5120, 4096, True), (1, 1, 1024, 8192, 10240, 4096, False), (1, 1, 1024, 1024, 2048, 8192, True),
+    (1, 1, 2048, 10240, 12800, 8192, True), (1, 1, 2048, 16384, 20480, 8192, False),
+    (1, 1, 512, 16384, 20480, 2048, False), (1, 1, 2048, 6144, 16384, 8192, True), (1, 1, 2048, 6144, 18432, 8192, False),
+    (1, 1, 3072, 6144, 18432, 8192, True), (1, 1, 512, 512, 1024, 4096, True), (1, 1, 512, 512, 1024, 4160, False),
+    (1, 1, 8256, 8192, 10240, 28672, False), (1, 1, 4128, 4096, 6144, 14336, False),
+    (0, 64, 256, 256, 768, 1024, True), (0, 65, 256, 256, 768, 1024, False), (0, 64, 256, 32768, 98304, 1024, True),
+    (0, 1, 192, 128, 384, 72, False), (2, 1, 4096, 4096, 6144, 14336, False),
+])
+def test_layers_of_a_few_rows_in_five_launches(dtype, M, d, hq, qkv, F, fused):
+    rule = _rule("_ZN2gs10rows_fusedEiiiiii", C.c_bool, *[C.c_int] * 6)
+    assert rule(dtype, M, d, hq, qkv, F) == fused and not rule(dtype, 0, d, hq, qkv, F)
