@@ -36,11 +36,14 @@ constexpr float kNegBig = -1.0e30f;
 // keys): all loads of K and V of a chunk are issued before the first score, so a chunk costs two dependent trips to memory
 // (pages, then K and V), and the softmax state is formed by every wave for itself from the scores in LDS.  A lane per key
 // with the lanes' states merged at the end took 13.6 us at 16 rows of 4 heads, 69 keys and head size 64, this takes 6.9.
-// VEC: 16-byte loads (16-byte aligned pages, page size a multiple of 4).  Writes attn_out [R][H*hd].
+// VEC: 16-byte loads (16-byte aligned pages, page size a multiple of 4).  AHEAD: the pages of the next chunk are looked up while
+// this one is computed, one dependent trip per chunk; for launches of at most two workgroups per compute unit, which wait
+// for loads and not for the units (kRowAheadItems).  Writes attn_out [R][H*hd].
 // ------------------------------------------------------------------------------------------
 constexpr int kRowThreads = 256;
 constexpr int kRowKeys = 128;
-template <int HD, bool VEC>
+constexpr int kRowAheadItems = 512;
+template <int HD, bool VEC, bool AHEAD>
 __global__ __launch_bounds__(kRowThreads) void attn_rowwise_kernel(const float* __restrict__ q,
                                                                    const float* __restrict__ k_pages,
                                                                    const float* __restrict__ v_pages,
@@ -68,13 +71,24 @@ __global__ __launch_bounds__(kRowThreads) void attn_rowwise_kernel(const float* 
   float o[C4];
 #pragma unroll
   for (int j = 0; j < C4; ++j) o[j] = 0.f;
+  static_assert(VEC || !AHEAD, "one page per four keys");
+  int k_page[KP], v_page[KP];      // AHEAD
+  auto look_up = [&](int base) {
+#pragma unroll
+    for (int p = 0; p < KP; ++p) {
+      k_page[p] = bt[min(base + p * 16 + kl, n_keys - 1) / page_size];
+      v_page[p] = bt[min(base + p * 16 + vq, n_keys - 1) / page_size];
+    }
+  };
+  if constexpr (AHEAD) look_up(0);
   for (int base = 0; base < n_keys; base += kRowKeys) {
     float4 kv[KP][C4], vv[KP][C4];
 #pragma unroll
     for (int p = 0; p < KP; ++p) {
       const int key = min(base + p * 16 + kl, n_keys - 1);      // (keys past the end re-read the last one)
       const int blk = key / page_size;
-      const float* kp = k_pages + (((size_t)bt[blk] * n_kv + kh) * page_size + (key - blk * page_size)) * HD + cl;
+      const int page = AHEAD ? k_page[p] : bt[blk];
+      const float* kp = k_pages + (((size_t)page * n_kv + kh) * page_size + (key - blk * page_size)) * HD + cl;
 #pragma unroll
       for (int j = 0; j < C4; ++j)
         kv[p][j] = VEC ? *reinterpret_cast<const float4*>(kp + j * 64)
@@ -89,7 +103,8 @@ __global__ __launch_bounds__(kRowThreads) void attn_rowwise_kernel(const float* 
       if constexpr (VEC) {
         if (key0 < n_keys) {
           const int blk = key0 / page_size;
-          const float* vp = v_pages + (((size_t)bt[blk] * n_kv + kh) * HD + vd) * page_size + (key0 - blk * page_size);
+          const int page = AHEAD ? v_page[p] : bt[blk];
+          const float* vp = v_pages + (((size_t)page * n_kv + kh) * HD + vd) * page_size + (key0 - blk * page_size);
 #pragma unroll
           for (int j = 0; j < C4; ++j) vv[p][j] = *reinterpret_cast<const float4*>(vp + (size_t)j * 64 * page_size);
         }
@@ -104,6 +119,7 @@ __global__ __launch_bounds__(kRowThreads) void attn_rowwise_kernel(const float* 
           }
       }
     }
+    if (AHEAD && base + kRowKeys < n_keys) look_up(base + kRowKeys);
 #pragma unroll
     for (int p = 0; p < KP; ++p) {
       float s = 0.f;
@@ -832,14 +848,19 @@ gs_status launch_attention(int dtype, const void* q, const void* k_pages, const 
     float* of = static_cast<float*>(attn_out);
     const bool vec = page_size % 4 == 0 && reinterpret_cast<uintptr_t>(k_pages) % 16 == 0 &&
                      reinterpret_cast<uintptr_t>(v_pages) % 16 == 0;
-#define GS_ROWWISE(HD_, VEC_)                                                                                     \
-  attn_rowwise_kernel<HD_, VEC_><<<grid, kRowThreads, 0, stream>>>(qf, kf, vf, block_table, max_blocks,           \
+    // Looking ahead: 4 layers of 4 heads of 64 over 2, whole call, us without and with: 64 rows on 8000 keys 1268 and 980, 128 rows
+    // 1425 and 1243 (1356 with a lane per key); 8 heads over 1, 256 rows on 8000 keys 3073 and 3577.
+    const bool ahead = vec && (long)n_rows * n_heads <= kRowAheadItems;
+#define GS_ROWWISE(HD_, VEC_, AHEAD_)                                                                             \
+  attn_rowwise_kernel<HD_, VEC_, AHEAD_><<<grid, kRowThreads, 0, stream>>>(qf, kf, vf, block_table, max_blocks,           \
                                                                    static_cast<const int4*>(row_info), cu_rows, ctx_len, \
                                                                    page_size, n_heads, n_kv, of)
-    if (hd == 64 && vec) GS_ROWWISE(64, true);
-    else if (hd == 64) GS_ROWWISE(64, false);
-    else if (vec) GS_ROWWISE(128, true);
-    else GS_ROWWISE(128, false);
+    if (hd == 64 && ahead) GS_ROWWISE(64, true, true);
+    else if (hd == 64 && vec) GS_ROWWISE(64, true, false);
+    else if (hd == 64) GS_ROWWISE(64, false, false);
+    else if (ahead) GS_ROWWISE(128, true, true);
+    else if (vec) GS_ROWWISE(128, true, false);
+    else GS_ROWWISE(128, false, false);
 #undef GS_ROWWISE
     GS_LAUNCH_CHECK("attn_rowwise");
     return GS_OK;

@@ -16,6 +16,9 @@ pytestmark = pytest.mark.gpu
     (128, 1, [2, 1], [3, 130]),
     (128, 12, [4, 6], [253, 40]),                      # a multiple of 4 but not of 16
     (128, 64, [1, 15], [512, 1]),
+    (64, 16, [127], [300]),                            # 128 rows of 4 heads: the last launch that looks its pages up ahead
+    (64, 16, [128], [300]),
+    (128, 4, [100, 27, 2], [130, 0, 513]),             # past it
 ])
 def test_f32_attention_chunks_and_page_sizes(hd, page, gamma, ctx):
     """Against the float64 oracle within 1e-4 of the row scale (float32 sums of at most a few hundred terms: about 1e-6)."""
