@@ -234,6 +234,13 @@ __device__ __forceinline__ float halves_sum(float x) {
   return __uint_as_float(b[0]) + __uint_as_float(b[1]);
 }
 
+// a / l correctly rounded, with inv = 1 / l correctly rounded: a product whose remainder is divided as well (Markstein, IBM J. Res.
+// Dev. 34, 1990).  The 64 quotients of a lane share l: half of the instructions of 64 divisions.  Infinities stay what they are.
+__device__ __forceinline__ float quotient(float a, float l, float inv) {
+  const float q = a * inv;
+  return fabsf(q) < INFINITY ? fmaf(fmaf(-q, l, a), inv, q) : q;
+}
+
 // (164 vector registers: three waves per SIMD, i.e. up to four 3-wave workgroups per CU, which hides a
 // workgroup's start-up and barrier stalls behind the others' loads)
 template <int HD, int G, int NW, int KW>
@@ -547,14 +554,14 @@ __global__ __launch_bounds__(64 * NW * KW) __attribute__((amdgpu_waves_per_eu(KW
   if (n_splits == 1) {      // the group is not split: the result is final
     const int row = row0 + my_j, col0 = (kh * G + my_hg) * HD + 4 * h, width = n_heads * HD;
     const float inv = 1.0f / l_run;
+    auto o = [&](int dt, int i) { return quotient(oacc[dt][i], l_run, inv); };
 #pragma unroll
     for (int dt = 0; dt < DT; ++dt)
 #pragma unroll
       for (int b = 0; b < 4; ++b)
         *reinterpret_cast<uint2*>(attn_out + (packed ? packed_index(row, col0 + dt * 32 + b * 8, width)
                                                      : (size_t)row * width + col0 + dt * 32 + b * 8)) =
-            make_uint2(pack_bf16x2(oacc[dt][4 * b] * inv, oacc[dt][4 * b + 1] * inv),
-                       pack_bf16x2(oacc[dt][4 * b + 2] * inv, oacc[dt][4 * b + 3] * inv));
+            make_uint2(pack_bf16x2(o(dt, 4 * b), o(dt, 4 * b + 1)), pack_bf16x2(o(dt, 4 * b + 2), o(dt, 4 * b + 3)));
     return;
   }
   const size_t out_idx = ((size_t)(row0 + my_j) * n_heads + kh * G + my_hg) * max_splits + split;

@@ -101,3 +101,44 @@ def test_bf16_attention_with_key_groups(heads, n_kv, hd, gamma, ctx, page, key_g
     assert attention_key_groups(n_kv, heads // n_kv, gamma, ctx)[0] == key_groups
     ms = synth.ModelShape(1, 128, heads, n_kv, hd, 192, 320, 10000.0, dtype="bf16")
     _run_case(ms, 900 + page + heads, np.array(gamma, np.int32), np.array(ctx, np.int32), page, 0.08)
+
+
+@pytest.mark.parametrize("rows,page", [(1, 16), (12, 16), (40, 32)])
+def test_bf16_attention_quotient_is_correctly_rounded(rows, page):
+    """Attention of equal scores is the mean of V.  Here every mean is an integer plus one half, halfway between two bf16 values from
+    128 on, and the float32 sums are exact, so a quotient that is off by one bit in float32 is off by one bf16 step in the result.
+    Among the key counts are those (14, 30, 56, 60, 126, ...) whose rounded reciprocal times the sum is not the quotient."""
+    import torch
+    from paper_2512_09963_amd import binding as gsb
+    d, hd, vocab = 256, 128, 64
+    dev = torch.device("cuda:0")
+    counts = [14, 30, 56, 60, 122, 126, 120, 112, 28, 52, 104, 26, 110, 94, 4, 6, 100, 128, 64][:rows]
+    counts += [10 + 2 * i for i in range(rows - len(counts))]
+    bf = dict(dtype=torch.bfloat16, device=dev)
+    zeros = lambda n, k: gsb.gs_pack_weight(torch.zeros(n, k, **bf))
+    layer = dict(wqkv=zeros(2 * d + d, d), wo=gsb.gs_pack_weight(torch.eye(d, **bf)), wgu=zeros(2 * 64, d), wd=zeros(d, 64),
+                 norm1=torch.ones(d, device=dev), norm2=torch.ones(d, device=dev))
+    top = dict(embed=torch.zeros(vocab, d, **bf), lm_head=zeros(vocab, d), final_norm=torch.ones(d, device=dev))
+    desc = dict(n_layers=1, d_model=d, n_heads=2, n_kv_heads=2, head_dim=hd, d_ffn=64, vocab=vocab, rope_theta=10000.0, rms_eps=1e-5,
+                dtype="bf16")
+    ver = gsb.Verifier(desc, top, [layer])
+    gamma, ctx = np.zeros(rows, np.int32), np.array([n - 1 for n in counts], np.int32)
+    batch = synth.make_batch(3, gamma, ctx, page, permute_pages=True)
+    k = torch.zeros(1, batch.n_pages, 2, page, hd, **bf)
+    v = torch.zeros(1, batch.n_pages, 2, hd, page, **bf)
+    a = torch.arange(128, 256, device=dev, dtype=torch.float32).repeat(2).view(2, hd)
+    for i, n in enumerate(counts):      # the block's own value is 0: n / 2 values a + 1, n / 2 - 2 values a and one 2 a
+        vals = [a + 1] * (n // 2) + [a] * (n // 2 - 2) + [2 * a]
+        assert len(vals) == n - 1
+        for p, val in enumerate(vals):
+            v[0, int(batch.block_table[i, p // page]), :, :, p % page] = val.to(torch.bfloat16)
+    trace = torch.empty(2, rows, d, device=dev)
+    ver.gs_trace_residual(trace)
+    logits = torch.empty(rows, vocab, device=dev)
+    ws = torch.empty(ver.gs_workspace_bytes(rows, rows, int(max(counts))), dtype=torch.uint8, device=dev)
+    ver.gs_verify_batch(k, v, page, batch.n_pages, gamma, ctx, torch.from_numpy(batch.cu_rows).to(dev), torch.from_numpy(ctx).to(dev),
+                        torch.zeros(rows, dtype=torch.int32, device=dev), torch.from_numpy(batch.block_table).to(dev), None, None, None,
+                        None, logits, ws)
+    torch.cuda.synchronize()
+    want = (a + 0.5).view(1, d).to(torch.bfloat16).float().expand(rows, d)
+    assert torch.equal(trace[1], want)
