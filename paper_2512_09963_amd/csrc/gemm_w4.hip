@@ -458,10 +458,12 @@ static W4Plan w4_plan(int M, int N, int K) {
       if (blocks >= 192 || K / 64 >= 16 * p.kg * s) p.nt = 2;
     }
   }
-  // narrow matrices at 33 to 64 rows: 64 columns and four K groups per workgroup, down to four steps each, so that the chip is full
-  // with half of the K splits (8B shape, 8 layers, 53 rows 952 -> 934 us; at 8192 columns and more the larger share of the
-  // activations costs more: 70B shape, 2 layers, 45 rows 587 -> 604)
-  const bool narrow = p.mt == 2 && p.nt == 1 && N < 8192;
+  // narrow matrices at 33 to 64 rows: 64 columns and four K groups per workgroup, down to four steps each, where that gives seven
+  // compute units in eight a workgroup with half of the K splits, or as many splits as K allows (8B shape, 8 layers, 53 rows 952 -> 934 us;
+  // 1024 x 4096 8.6 -> 7.0 us; but 6144 x 12288, 5 splits on 240 workgroups, 18.6 -> 21.9 with 2 on 192).  From 128 blocks on the
+  // larger share of the activations costs more: 70B shape, 2 layers, 45 rows 587 -> 604.
+  const int blocks64 = N / 64, splits64 = std::max(1, std::min(target / blocks64, K / 1024));
+  const bool narrow = p.mt == 2 && p.nt == 1 && blocks64 < 128 && (blocks64 * splits64 >= 224 || splits64 >= K / 1024);
   if (narrow || N % (32 * p.waves * p.nt) != 0) {      // N is a multiple of 64
     p.waves = 2;
     p.kg = p.mt == 4 ? 2 : 4;      // (LDS: kg x 3 activation buffers)

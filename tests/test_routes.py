@@ -80,3 +80,17 @@ def test_attention_key_groups(gamma, ctx, groups):
 def test_layers_of_a_few_rows_in_five_launches(dtype, M, d, hq, qkv, F, fused):
     rule = _rule("_ZN2gs10rows_fusedEiiiiii", C.c_bool, *[C.c_int] * 6)
     assert rule(dtype, M, d, hq, qkv, F) == fused and not rule(dtype, 0, d, hq, qkv, F)
+
+
+def gemm_splits(dtype, M, N, K):
+    return _rule("_ZN2gs11gemm_splitsEiiii", C.c_int, *[C.c_int] * 4)({"f32": 0, "bf16": 1, "w4": 2}[dtype], M, N, K)
+
+
+@pytest.mark.parametrize("N,K,splits", [
+    (4096, 14336, 4), (4096, 4096, 4), (3072, 12288, 5), (5120, 5120, 3), (7168, 5120, 2),       # 64 columns, four K groups
+    (1024, 2048, 2), (1024, 16384, 16), (6144, 2048, 2), (512, 640, 1),                          # as many splits as K allows
+    (6144, 4096, 4), (6144, 6144, 5), (6144, 12288, 5),      # 192 workgroups of 64 columns: 128 columns and two K groups
+    (8192, 8192, 4),
+])
+def test_w4_splits_at_33_to_64_rows(N, K, splits):
+    assert [gemm_splits("w4", M, N, K) for M in (33, 53, 64)] == [splits] * 3

@@ -169,3 +169,13 @@ def test_w4_shapes_are_validated():
     with pytest.raises(gsb.GsError):
         gsb.gs_pack_weight_w4(codes, torch.zeros(64, 1, dtype=torch.bfloat16, device=dev),
                               torch.zeros(64, 1, dtype=torch.uint8, device=dev))
+
+
+@pytest.mark.parametrize("rows", [33, 49, 64])
+def test_w4_narrow_projections_with_unequal_splits(rows):
+    """384 x 3200 (O and down) in three K splits of 9, 9 and 7 scale groups, which the four K groups of a workgroup take 3, 3, 3 and 0,
+    or 3, 3, 1 and 0 at a time; 6400 x 384 (gate/up): three scale groups, the fourth K group has none."""
+    from tests.test_routes import gemm_splits
+    assert gemm_splits("w4", rows, 384, 3200) == 3
+    ms = synth.ModelShape(1, 384, 25, 25, 128, 3200, 512, 10000.0, dtype="bf16")
+    _run(ms, 400 + rows, np.array([rows - 11, 0, 8], np.int32), np.array([40, 0, 19], np.int32), std=0.05)
