@@ -527,6 +527,7 @@ gs_status launch_gemm_stats(const void* X, const void* W, float* Y, void* stats,
 template <int MODE>
 static void launch_f32(const float* x, const float* w, float* y, int M, int N, int K, const RowNorm& norm, const QkvOut& qkv,
                        const ResidualOut& res, hipStream_t stream) {
+  static_assert(kMaxRowsF32 <= 64, "one row chunk of four tiles");
   const int mt = M <= 16 ? 1 : M <= 32 ? 2 : 4;
   const int chunks = ceil_div(M, 16 * mt), tiles = ceil_div(N, 16);
   // K slices: doubled until the launch has a workgroup per CU, as long as a slice keeps a 16-wide step of its own (and a
@@ -560,7 +561,7 @@ static void launch_f32(const float* x, const float* w, float* y, int M, int N, i
 // 16-byte loads.
 bool rows_fused(int dtype, int M, int d, int hq, int qkv, int F) {
   if (M <= 0 || d > kRowNormMaxWidth || d % 64 != 0) return false;
-  if (dtype == GS_F32) return M <= 64 && F % 16 == 0;
+  if (dtype == GS_F32) return M <= kMaxRowsF32 && F % 16 == 0;
   // bf16: up to 16 rows, 8 where a workgroup has 32 columns; beyond, K splits and separate norms are faster (8B shape, 4 layers, us
   // fused and not: 5 rows 545 / 590, 16 rows 590 / 600, 20 rows 623 / 609; 70B shape, 2 layers: 5 rows 898 / 904, 12 rows
   // 927 / 912).  A K of many times the columns wants K splits, few workgroups would stream it alone: F up to eight times d, and
@@ -574,9 +575,15 @@ bool rows_fused(int dtype, int M, int d, int hq, int qkv, int F) {
 }
 gs_status launch_bf16_rows_qkv(const bf16_t* h, const bf16_t* w, const RowNorm& norm, const QkvOut& out, int M, int K, hipStream_t stream);
 gs_status launch_bf16_rows_residual(const bf16_t* in, const bf16_t* w, const ResidualOut& out, int M, int N, int K, hipStream_t stream);
+// More rows would be left out, or overrun the sums of squares.
+static gs_status check_rows(int dtype, int M) {
+  const int most = dtype == GS_BF16 ? kMaxRows : kMaxRowsF32;
+  return M <= most ? GS_OK : fail(GS_EUNSUPPORTED, "%d rows in a layer of at most %d", M, most);
+}
 // bf16: h, attn and act of these calls are in fragment order, but for the h that the gate/up projection reads
 gs_status launch_rows_qkv(int dtype, const void* h, const void* w, const RowNorm& norm, const QkvOut& out, int M, int K,
                           hipStream_t stream) {
+  if (gs_status st = check_rows(dtype, M); st != GS_OK) return st;
   if (dtype == GS_BF16)
     return launch_bf16_rows_qkv(static_cast<const bf16_t*>(h), static_cast<const bf16_t*>(w), norm, out, M, K, stream);
   const int N = (out.n_heads + 2 * out.n_kv) * out.hd;
@@ -586,6 +593,7 @@ gs_status launch_rows_qkv(int dtype, const void* h, const void* w, const RowNorm
 }
 gs_status launch_rows_gate_up(int dtype, const void* h, const void* w, const RowNorm& norm, void* act, int M, int F, int K,
                               hipStream_t stream) {
+  if (gs_status st = check_rows(dtype, M); st != GS_OK) return st;
   if (dtype == GS_BF16)
     return launch_wide_gate_up_norm(wide_plan(M, 2 * F, K, true), static_cast<const bf16_t*>(h), static_cast<const bf16_t*>(w), norm,
                                     static_cast<bf16_t*>(act), M, 2 * F, K, stream);
@@ -596,12 +604,14 @@ gs_status launch_rows_gate_up(int dtype, const void* h, const void* w, const Row
 }
 // Logits of rows that still need their factor: fp32 (the others take a norm of their own, their LM heads being the plain ones).
 gs_status launch_rows_head_f32(const float* h, const float* w, const RowNorm& norm, float* logits, int M, int N, int K, hipStream_t stream) {
+  if (gs_status st = check_rows(GS_F32, M); st != GS_OK) return st;
   launch_f32<kF32Head>(h, w, logits, M, N, K, norm, QkvOut{}, ResidualOut{}, stream);
   GS_LAUNCH_CHECK("rows_head");
   return GS_OK;
 }
 gs_status launch_rows_residual(int dtype, const void* in, const void* w, const ResidualOut& out, int M, int N, int K,
                                hipStream_t stream) {
+  if (gs_status st = check_rows(dtype, M); st != GS_OK) return st;
   if (dtype == GS_BF16)
     return launch_bf16_rows_residual(static_cast<const bf16_t*>(in), static_cast<const bf16_t*>(w), out, M, N, K, stream);
   launch_f32<kF32Residual>(static_cast<const float*>(in), static_cast<const float*>(w), nullptr, M, N, K, RowNorm{}, QkvOut{}, out,

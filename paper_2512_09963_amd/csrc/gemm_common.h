@@ -76,7 +76,8 @@ __device__ __forceinline__ size_t packed_index(int row, int k, int K) {
   const size_t tile = (size_t)(row >> 4) * (K >> 6) + (k >> 6);
   return ((tile * 2 + ((k >> 3) & 1)) * 64 + ((k >> 4) & 3) * 16 + (row & 15)) * 8 + (k & 7);
 }
-constexpr int kMaxRows = 16;      // of the bf16 kernels that read it
+// Most rows of such a block: what one row tile of gemm_rows.hip, and one row chunk of gemm_f32_kernel, holds.
+constexpr int kMaxRows = 16, kMaxRowsF32 = 64;
 constexpr int kRowNormMaxWidth = 8192;      // d: eight 16-byte loads per lane
 
 // Row factors of a workgroup's rows, 16 lanes to a row (their sum is four row moves): load() early, store() into LDS where the
@@ -133,7 +134,7 @@ gs_status launch_wide(const WidePlan& p, const bf16_t* x, const bf16_t* w, float
                       hipStream_t stream);
 gs_status launch_wide_gate_up(const WidePlan& p, const bf16_t* x, const bf16_t* w, bf16_t* act, int M, int N, int K,
                               hipStream_t stream);
-// x not yet divided by its root mean square, act in fragment order; up to kMaxRows rows
+// x not yet divided by its root mean square, act in fragment order; up to kMaxRows rows (two row tiles)
 gs_status launch_wide_gate_up_norm(const WidePlan& p, const bf16_t* x, const bf16_t* w, const RowNorm& norm, bf16_t* act, int M,
                                    int N, int K, hipStream_t stream);
 gs_status launch_wide_stats(const WidePlan& p, const bf16_t* x, const bf16_t* w, float* y, float2* stats, int M, int N,

@@ -144,6 +144,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 2)))
 template <int MODE>
 gs_status launch(const bf16_t* x, const bf16_t* w, int M, int N, int K, const RowNorm& norm, const QkvOut& qkv, const ResidualOut& res,
                  hipStream_t stream) {
+  static_assert(kMaxRows <= 16, "one row tile");
   // one workgroup per compute unit: 16 columns where that is enough, otherwise 32; pairs of tiles, two where one would need
   // a second round (10240 x 8192 at 16 rows: 37.7 us with one)
   const int blocks = MODE == kQkv ? N / 32 : N / 16;

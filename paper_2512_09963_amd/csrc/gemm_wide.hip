@@ -410,6 +410,7 @@ static gs_status launch_mode(const WidePlan& p, const bf16_t* x, const bf16_t* w
   gemm_bf16_wide_kernel<WM, WN, KG, MT, NT, DB, DA, POL, WPE, MODE>                                                 \
       <<<grid, 64 * WM * WN * KG, 0, stream>>>(x, w, out, M, N, K, p.k_per, p.m_chunks, stats, p.n_blocks, norm)
   if constexpr (MODE == kGateUpNorm) {
+    static_assert(kMaxRows <= 32, "two row tiles in one row chunk");
     if (p.wn == 8) GS_WIDE(1, 8, 1, 2, 2, 4, 2, 2, 2);
     else GS_WIDE(1, 4, 2, 2, 2, 4, 2, 2, 2);
     GS_LAUNCH_CHECK("gemm_bf16_wide");

@@ -128,8 +128,6 @@ size_t max_partial_floats(const gs_ctx* ctx, int max_rows) {
   return max_rows % 16 ? std::max(best[max_rows / 16], floats(max_rows)) : best[max_rows / 16];
 }
 
-constexpr int kMaxFusedRows = 64;      // rows_fused never accepts more
-
 Plan make_plan(const gs_ctx* ctx, int max_rows, int max_servers, int max_ctx, void* ws) {
   const gs_model_desc& m = ctx->desc;
   const size_t R = max_rows, R16 = gs::align_up(R, 16);      // (bf16 activations in fragment order have whole row tiles)
@@ -157,7 +155,7 @@ Plan make_plan(const gs_ctx* ctx, int max_rows, int max_servers, int max_ctx, vo
   for (int n = 1; n <= max_servers; ++n) p.accept_bytes = std::max(p.accept_bytes, gs::accept_min_bytes(n, max_rows, m.vocab));
   p.accept_ws = c.take<char>(p.accept_bytes);
   p.lm_stats = c.take<float>(2 * R * (size_t)(m.vocab / 64 + 1));     // at least 64 columns per block
-  p.squares = c.take<float>((size_t)std::min(max_rows, kMaxFusedRows) * (m.d_model / 16));
+  p.squares = c.take<float>((size_t)std::min(max_rows, std::max(gs::kMaxRows, gs::kMaxRowsF32)) * (m.d_model / 16));
   p.bytes = c.used();
   return p;
 }

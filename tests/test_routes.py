@@ -94,3 +94,19 @@ def gemm_splits(dtype, M, N, K):
 ])
 def test_w4_splits_at_33_to_64_rows(N, K, splits):
     assert [gemm_splits("w4", M, N, K) for M in (33, 53, 64)] == [splits] * 3
+
+
+@pytest.mark.parametrize("dtype,most", [(1, 16), (0, 64)])
+def test_layers_of_five_launches_refuse_more_rows(dtype, most):
+    """The launchers hold one row tile (bf16) or one row chunk (fp32): more rows are refused before anything is launched."""
+    args = [C.c_int, C.c_void_p, C.c_void_p, C.c_void_p, C.c_int, C.c_int, C.c_int, C.c_void_p]
+    residual = _rule("_ZN2gs20launch_rows_residualEiPKvS1_RKNS_11ResidualOutEiiiP12ihipStream_t", C.c_int, *args)
+    out = (C.c_char * 64)()
+    assert residual(dtype, None, None, C.addressof(out), most + 1, 256, 256, None) == -5      # GS_EUNSUPPORTED
+    assert b"at most %d" % most in gsb.lib().gs_last_error()
+    gate_up = _rule("_ZN2gs19launch_rows_gate_upEiPKvS1_RKNS_7RowNormEPviiiP12ihipStream_t", C.c_int,
+                    C.c_int, C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p, C.c_int, C.c_int, C.c_int, C.c_void_p)
+    assert gate_up(dtype, None, None, C.addressof(out), None, most + 1, 256, 256, None) == -5
+    qkv = _rule("_ZN2gs15launch_rows_qkvEiPKvS1_RKNS_7RowNormERKNS_6QkvOutEiiP12ihipStream_t", C.c_int,
+                C.c_int, C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p, C.c_int, C.c_int, C.c_void_p)
+    assert qkv(dtype, None, None, C.addressof(out), C.addressof(out), most + 1, 256, None) == -5
