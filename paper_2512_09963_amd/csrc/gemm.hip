@@ -199,7 +199,7 @@ __global__ __launch_bounds__(64 * NW) void gemm_bf16_skinny_kernel(const bf16_t*
 // grid (column groups, row chunks of MT * 16).
 constexpr int kF32Waves = 8;
 // LOADS: kWholeSteps where K is a multiple of 16 and the operands are 16-byte aligned, kVec4 where K is a multiple of 4,
-// kElements otherwise.
+// kElements otherwise.  (The modes of fused layers never have a K that is no multiple of 16.)
 enum { kElements = 0, kVec4 = 1, kWholeSteps = 2 };
 template <int LOADS>
 __device__ __forceinline__ float4 load4_f32(const float* __restrict__ row, int k, int K) {
@@ -547,9 +547,13 @@ static void launch_f32(const float* x, const float* w, float* y, int M, int N, i
   else GS_F32(4, LOADS_);
   if (aligned && K % 16 == 0) {
     GS_F32_ROWS(kWholeSteps)
-  } else if (aligned && K % 4 == 0) {
-    GS_F32_ROWS(kVec4)
   } else {
+    if constexpr (MODE == kF32Plain) {
+      if (aligned && K % 4 == 0) {
+        GS_F32_ROWS(kVec4)
+        return;
+      }
+    }
     GS_F32_ROWS(kElements)
   }
 #undef GS_F32_ROWS

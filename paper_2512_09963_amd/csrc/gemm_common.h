@@ -63,7 +63,7 @@ struct QkvOut {        // rotated Q [rows][heads][hd], K and V into the pages (r
   void* v_pages;
   int page_size, n_heads, n_kv, hd;
 };
-struct ResidualOut {   // x += result; h = x * norm (of the next projection's input); squares as in RowNorm
+struct ResidualOut {   // x += result; h = x * norm (of the next projection's input); squares as in RowNorm; h null: x alone (bf16)
   float* x;
   const float* norm;
   void* h;

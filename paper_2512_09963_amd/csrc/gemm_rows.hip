@@ -25,14 +25,15 @@ typedef unsigned int uintx4_t __attribute__((ext_vector_type(4)));
 enum { kQkv = 0, kResidual = 1 };
 
 // X: activations in fragment order; Wp: packed weights.  kQkv: tiles 2 p and 2 p + 1 of a workgroup are the halves of 16
-// rotation pairs of a head.  grid: ceil(N / 16 / NT) workgroups.
-template <int MT, int NT, int D, int NW, int MODE>
+// rotation pairs of a head.  grid: ceil(N / 16 / NT) workgroups.  One row tile: M up to 16.
+template <int NT, int D, int NW, int MODE>
 __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 2))) void gemm_bf16_rows_kernel(
     const bf16_t* __restrict__ X, const bf16_t* __restrict__ Wp, int M, int N, int K, RowNorm norm, QkvOut qkv, ResidualOut res) {
   static_assert(MODE != kQkv || NT % 2 == 0, "both halves of the rotation pairs");
+  static_assert(kMaxRows <= 16, "one row tile");
   constexpr int W = NT * 16, THREADS = 64 * NW;
-  __shared__ float red[NW][MT * 16][W];
-  __shared__ float factor[MT * 16];
+  __shared__ float red[NW][16][W];
+  __shared__ float factor[16];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int c = lane & 15;
@@ -46,18 +47,17 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 2)))
       return (int)blockIdx.x * NT + t;
     }
   };
-  RowFactors<MT * 16, NW> factors;
+  RowFactors<16, NW> factors;
   if constexpr (MODE == kQkv) factors.load(norm, wave, lane, 0, M);
 
   // lanes whose row or column does not exist read zeros (offset past the descriptor's range)
-  unsigned woff[NT], aoff[MT];
+  unsigned woff[NT];
 #pragma unroll
   for (int n = 0; n < NT; ++n) woff[n] = column_tile(n) * 16 < N ? (unsigned)column_tile(n) * 2048u + lane * 16u : 0x80000000u;
-#pragma unroll
-  for (int m = 0; m < MT; ++m) aoff[m] = m * 16 + c < M ? (unsigned)(m * steps) * 2048u + lane * 16u : 0x80000000u;
+  const unsigned aoff = c < M ? lane * 16u : 0x80000000u;
   const size_t w_stride = (size_t)(N / 16) * 2048;
-  const unsigned a_bytes = (unsigned)((M + 15) / 16 * steps) * 2048u;
-  uintx4_t wr[D][NT][2], ar[D][MT][2];
+  const unsigned a_bytes = (unsigned)steps * 2048u;
+  uintx4_t wr[D][NT][2], ar[D][2];
   // a step past the wave's last has empty descriptors: zeros
 #define GS_LOAD(slot, s)                                                                                                     \
   {                                                                                                                          \
@@ -71,16 +71,12 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 2)))
       wr[slot][n][0] = __builtin_amdgcn_raw_buffer_load_b128(rw, woff[n], 0, 2);                                             \
       wr[slot][n][1] = __builtin_amdgcn_raw_buffer_load_b128(rw, woff[n] + 1024, 0, 2);                                      \
     }                                                                                                                        \
-    _Pragma("unroll") for (int m = 0; m < MT; ++m) {                                                                         \
-      ar[slot][m][0] = __builtin_amdgcn_raw_buffer_load_b128(ra, aoff[m], 0, 0);                                             \
-      ar[slot][m][1] = __builtin_amdgcn_raw_buffer_load_b128(ra, aoff[m] + 1024, 0, 0);                                      \
-    }                                                                                                                        \
+    ar[slot][0] = __builtin_amdgcn_raw_buffer_load_b128(ra, aoff, 0, 0);                                                     \
+    ar[slot][1] = __builtin_amdgcn_raw_buffer_load_b128(ra, aoff + 1024, 0, 0);                                              \
   }
-  floatx4_t acc[MT][NT];
+  floatx4_t acc[NT];
 #pragma unroll
-  for (int m = 0; m < MT; ++m)
-#pragma unroll
-    for (int n = 0; n < NT; ++n) acc[m][n] = floatx4_t{0.f, 0.f, 0.f, 0.f};
+  for (int n = 0; n < NT; ++n) acc[n] = floatx4_t{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
   for (int d = 0; d < D; ++d) GS_LOAD(d, d);
   __builtin_amdgcn_sched_barrier(0);
@@ -91,11 +87,9 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 2)))
 #pragma unroll
       for (int h = 0; h < 2; ++h)
 #pragma unroll
-        for (int m = 0; m < MT; ++m)
-#pragma unroll
-          for (int n = 0; n < NT; ++n)
-            acc[m][n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(*reinterpret_cast<const bf16x8_t*>(&ar[d][m][h]),
-                                                                *reinterpret_cast<const bf16x8_t*>(&wr[d][n][h]), acc[m][n], 0, 0, 0);
+        for (int n = 0; n < NT; ++n)
+          acc[n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(*reinterpret_cast<const bf16x8_t*>(&ar[d][h]),
+                                                           *reinterpret_cast<const bf16x8_t*>(&wr[d][n][h]), acc[n], 0, 0, 0);
       __builtin_amdgcn_sched_barrier(0);
       GS_LOAD(d, base + d + D);
       __builtin_amdgcn_sched_barrier(0);
@@ -103,11 +97,9 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 2)))
   }
 #undef GS_LOAD
 #pragma unroll
-  for (int m = 0; m < MT; ++m)
+  for (int n = 0; n < NT; ++n)
 #pragma unroll
-    for (int n = 0; n < NT; ++n)
-#pragma unroll
-      for (int i = 0; i < 4; ++i) red[wave][m * 16 + (lane >> 4) * 4 + i][n * 16 + c] = acc[m][n][i];
+    for (int i = 0; i < 4; ++i) red[wave][(lane >> 4) * 4 + i][n * 16 + c] = acc[n][i];
   __syncthreads();
   auto sum_of = [&](int row, int col) {      // the waves' sums, in a fixed order
     float s = red[0][row][col];
@@ -116,7 +108,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 2)))
     return s;
   };
   if constexpr (MODE == kQkv) {
-    for (int e = tid; e < MT * 16 * (W / 2); e += THREADS) {
+    for (int e = tid; e < 16 * (W / 2); e += THREADS) {
       const int row = e / (W / 2), q = e - row * (W / 2), p = q >> 4;      // pair of tiles, lane of the tile
       const int pair = blockIdx.x * (NT / 2) + p;
       if (row >= M || pair * 32 >= N) continue;
@@ -126,15 +118,17 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 2)))
                              qkv.row_slot[row], qkv.rope[(size_t)row * (qkv.hd >> 1) + i]);
     }
   } else {
-    for (int e = tid; e < MT * 16 * W; e += THREADS) {
+    for (int e = tid; e < 16 * W; e += THREADS) {
       const int row = e / W, q = e - row * W, col = blockIdx.x * W + q;
       const bool ok = row < M && col < N;
       float v = 0.f;
       if (ok) {
         v = res.x[(size_t)row * N + col] + sum_of(row, q);
         res.x[(size_t)row * N + col] = v;
-        static_cast<bf16_t*>(res.h)[res.packed ? packed_index(row, col, N) : (size_t)row * N + col] = float_to_bf16(v * res.norm[col]);
+        if (res.h)
+          static_cast<bf16_t*>(res.h)[res.packed ? packed_index(row, col, N) : (size_t)row * N + col] = float_to_bf16(v * res.norm[col]);
       }
+      if (!res.h) continue;
       const float sq = row16_sum(v * v);      // (16 lanes share a row and a tile)
       if (ok && (q & 15) == 0) res.squares[(size_t)row * (N >> 4) + (col >> 4)] = sq;
     }
@@ -144,19 +138,18 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 2)))
 template <int MODE>
 gs_status launch(const bf16_t* x, const bf16_t* w, int M, int N, int K, const RowNorm& norm, const QkvOut& qkv, const ResidualOut& res,
                  hipStream_t stream) {
-  static_assert(kMaxRows <= 16, "one row tile");
   // one workgroup per compute unit: 16 columns where that is enough, otherwise 32; pairs of tiles, two where one would need
   // a second round (10240 x 8192 at 16 rows: 37.7 us with one)
   const int blocks = MODE == kQkv ? N / 32 : N / 16;
   const int nt = MODE == kQkv ? (blocks <= 256 ? 2 : 4) : (blocks <= 256 ? 1 : 2);
   const unsigned grid = ceil_div(N / 16, nt);
-#define GS_ROWS(MT, NT, D, NW) gemm_bf16_rows_kernel<MT, NT, D, NW, MODE><<<grid, 64 * NW, 0, stream>>>(x, w, M, N, K, norm, qkv, res)
+#define GS_ROWS(NT, D, NW) gemm_bf16_rows_kernel<NT, D, NW, MODE><<<grid, 64 * NW, 0, stream>>>(x, w, M, N, K, norm, qkv, res)
   if constexpr (MODE == kQkv) {
-    if (nt == 2) GS_ROWS(1, 2, 4, 8);
-    else GS_ROWS(1, 4, 4, 8);
+    if (nt == 2) GS_ROWS(2, 4, 8);
+    else GS_ROWS(4, 4, 8);
   } else {
-    if (nt == 1) GS_ROWS(1, 1, 8, 4);
-    else GS_ROWS(1, 2, 4, 8);
+    if (nt == 1) GS_ROWS(1, 8, 4);
+    else GS_ROWS(2, 4, 8);
   }
 #undef GS_ROWS
   GS_LAUNCH_CHECK("gemm_bf16_rows");

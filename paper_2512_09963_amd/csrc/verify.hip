@@ -478,8 +478,10 @@ extern "C" gs_status gs_verify_batch(gs_ctx* ctx, const gs_kv_cache* kv, const g
       const bool top = l + 1 == m.n_layers;
       GS_STAGE(GS_STAGE_GEMM, gs::launch_rows_residual(m.dtype, p.attn, ctx->wo[l], {p.x, ctx->norm2[l], p.h, p.squares, false}, rows, d, hq, stream));
       GS_STAGE(GS_STAGE_GEMM, gs::launch_rows_gate_up(m.dtype, p.h, ctx->wgu[l], norm, p.act, rows, F, d, stream));
+      // (the bf16 LM head takes complete rows from a norm of its own)
       GS_STAGE(GS_STAGE_GEMM, gs::launch_rows_residual(m.dtype, p.act, ctx->wd[l],
-                                                       {p.x, top ? ctx->final_norm : ctx->norm1[l + 1], p.h, p.squares, packed}, rows, d, F, stream));
+                                                       {p.x, top ? ctx->final_norm : ctx->norm1[l + 1], top && packed ? nullptr : p.h, p.squares, packed},
+                                                       rows, d, F, stream));
       continue;
     }
     GS_STAGE(GS_STAGE_GEMM, gs::launch_gemm(m.dtype, p.attn, ctx->wo[l], p.partial, rows, d, hq, stream));
