@@ -55,7 +55,7 @@ struct RowNorm {       // input side: x^2 sums [rows][blocks], blocks = d / 16
   int blocks;
   float inv_d, eps;
 };
-struct QkvOut {        // rotated Q [rows][heads][hd], K and V into the pages (rope_append_kernel)
+struct QkvOut {        // where the fused QKV result goes (store_qkv_pair)
   const int4* row_slot;
   const float2* rope;
   void* q;
@@ -108,15 +108,17 @@ struct RowFactors {
   }
 };
 
-// Rotates and stores the pair (a, b) = elements (i, i + hd / 2) of a head of the fused QKV result.
+// Rotates and stores the pair (a, b) = elements (i, i + hd / 2) of a head of the fused QKV result: Q [R][H][hd], K ([page][H_kv][slot][hd])
+// and V ([page][H_kv][hd][slot]) into the layer's pages.
 template <typename T>
 __device__ __forceinline__ void store_qkv_pair(const QkvOut& o, int row, int head, int i, float a, float b, const int4& ps, const float2& cs) {
   const int half = o.hd >> 1;
   if (head < o.n_heads + o.n_kv) {
     T* dst = head < o.n_heads ? static_cast<T*>(o.q) + ((size_t)row * o.n_heads + head) * o.hd
                               : static_cast<T*>(o.k_pages) + (((size_t)ps.x * o.n_kv + (head - o.n_heads)) * o.page_size + ps.y) * o.hd;
-    Storage<T>::store(dst + i, a * cs.x - b * cs.y);
-    Storage<T>::store(dst + i + half, b * cs.x + a * cs.y);
+    // (explicit multiply-adds: the same rounding in every kernel)
+    Storage<T>::store(dst + i, fmaf(a, cs.x, -(b * cs.y)));
+    Storage<T>::store(dst + i + half, fmaf(b, cs.x, a * cs.y));
   } else {
     T* dst = static_cast<T*>(o.v_pages) + ((size_t)ps.x * o.n_kv + (head - o.n_heads - o.n_kv)) * o.hd * o.page_size + ps.y;
     Storage<T>::store(dst + (size_t)i * o.page_size, a);

@@ -192,41 +192,25 @@ __global__ __launch_bounds__(kWorkThreads) void step_begin_kernel(StepBegin a) {
   }
 }
 
-// Sums the QKV partials, rotates Q and K at the row's position, stores Q [R][H][hd] and
-// appends K ([page][H_kv][slot][hd]) and V ([page][H_kv][hd][slot]) to the layer's pages.
-// grid (R, (H + 2 H_kv) * hd/2 / 256): a thread owns the element pair (i, i + hd/2) of one head.
+// Sums the QKV partials and hands the element pair (i, i + hd/2) of a head to store_qkv_pair.
+// grid (R, (H + 2 H_kv) * hd/2 / 256): a thread owns one pair.
 template <typename T>
-__global__ __launch_bounds__(256) void rope_append_kernel(const float* __restrict__ qkv, int n_splits, int n_rows,
-                                                          const int4* __restrict__ row_slot,
-                                                          const float2* __restrict__ rope, int page_size,
-                                                          int n_heads, int n_kv, int hd, T* __restrict__ q_out,
-                                                          T* __restrict__ k_pages, T* __restrict__ v_pages) {
+__global__ __launch_bounds__(256) void rope_append_kernel(const float* __restrict__ qkv, int n_splits, int n_rows, QkvOut out) {
   const int r = blockIdx.x;
-  const int half = hd >> 1;
+  const int half = out.hd >> 1;
   const int item = blockIdx.y * 256 + threadIdx.x;
   const int head = item / half, i = item - head * half;
-  if (head >= n_heads + 2 * n_kv) return;
-  const int width = (n_heads + 2 * n_kv) * hd;
+  if (head >= out.n_heads + 2 * out.n_kv) return;
+  const int width = (out.n_heads + 2 * out.n_kv) * out.hd;
   const size_t split_stride = (size_t)n_rows * width;
-  const float* src = qkv + (size_t)r * width + head * hd + i;
+  const float* src = qkv + (size_t)r * width + head * out.hd + i;
   float a = 0.f, b = 0.f;
   for (int s = 0; s < n_splits; ++s) {
     a += src[(size_t)s * split_stride];
     b += src[(size_t)s * split_stride + half];
   }
-  const int4 ps = row_slot[r];
-  if (head < n_heads + n_kv) {
-    const float2 cs = rope[(size_t)r * half + i];
-    const float ra = a * cs.x - b * cs.y, rb = b * cs.x + a * cs.y;
-    T* dst = (head < n_heads) ? q_out + ((size_t)r * n_heads + head) * hd
-                              : k_pages + (((size_t)ps.x * n_kv + (head - n_heads)) * page_size + ps.y) * hd;
-    Storage<T>::store(dst + i, ra);
-    Storage<T>::store(dst + i + half, rb);
-  } else {
-    T* dst = v_pages + ((size_t)ps.x * n_kv + (head - n_heads - n_kv)) * hd * page_size + ps.y;
-    Storage<T>::store(dst + (size_t)i * page_size, a);
-    Storage<T>::store(dst + (size_t)(i + half) * page_size, b);
-  }
+  const bool rotated = head < out.n_heads + out.n_kv;
+  store_qkv_pair<T>(out, r, head, i, a, b, out.row_slot[r], rotated ? out.rope[(size_t)r * half + i] : make_float2(1.f, 0.f));
 }
 
 // act[r][f] = silu(gate) * up with gate = sum_s gu[s][r][f], up = sum_s gu[s][r][F + f].
@@ -293,14 +277,9 @@ gs_status launch_add_rmsnorm(int dtype, float* x, const float* partial, int n_sp
   return GS_OK;
 }
 
-gs_status launch_rope_append(int dtype, const float* qkv, int n_splits, int n_rows, const void* row_slot,
-                             const void* rope, int page_size, int n_heads, int n_kv, int hd, void* q_out,
-                             void* k_pages, void* v_pages, hipStream_t stream) {
-  const dim3 grid(n_rows, ceil_div((n_heads + 2 * n_kv) * (hd / 2), 256));
-  GS_DISPATCH_T(dtype, rope_append_kernel<T><<<grid, 256, 0, stream>>>(
-                           qkv, n_splits, n_rows, static_cast<const int4*>(row_slot),
-                           static_cast<const float2*>(rope), page_size, n_heads, n_kv, hd, static_cast<T*>(q_out),
-                           static_cast<T*>(k_pages), static_cast<T*>(v_pages));)
+gs_status launch_rope_append(int dtype, const float* qkv, int n_splits, int n_rows, const QkvOut& out, hipStream_t stream) {
+  const dim3 grid(n_rows, ceil_div((out.n_heads + 2 * out.n_kv) * (out.hd / 2), 256));
+  GS_DISPATCH_T(dtype, rope_append_kernel<T><<<grid, 256, 0, stream>>>(qkv, n_splits, n_rows, out);)
   GS_LAUNCH_CHECK("rope_append");
   return GS_OK;
 }

@@ -35,9 +35,7 @@ gs_status launch_step_begin(int dtype, const void* embed, const int* tokens, flo
                             void* rope, int* draft_tokens, int* attn_work, float* squares, hipStream_t stream);
 gs_status launch_add_rmsnorm(int dtype, float* x, const float* partial, int n_splits, int n_rows, const float* w,
                              float eps, void* h, int d, hipStream_t stream);
-gs_status launch_rope_append(int dtype, const float* qkv, int n_splits, int n_rows, const void* row_slot,
-                             const void* rope, int page_size, int n_heads, int n_kv, int hd, void* q_out,
-                             void* k_pages, void* v_pages, hipStream_t stream);
+gs_status launch_rope_append(int dtype, const float* qkv, int n_splits, int n_rows, const QkvOut& out, hipStream_t stream);
 gs_status launch_swiglu(int dtype, const float* gu, int n_splits, int n_rows, int F, void* act, hipStream_t stream);
 void attention_plan(int n_kv, int group, long max_block_tokens, int n_servers, const int* gamma_host,
                     const int* ctx_len_host, int* steps_per_split, int* max_splits, int* key_groups);
@@ -462,14 +460,13 @@ extern "C" gs_status gs_verify_batch(gs_ctx* ctx, const gs_kv_cache* kv, const g
                                   hipMemcpyDeviceToDevice, stream));
     char* kl = static_cast<char*>(kv->k_pages) + layer_stride * l;
     char* vl = static_cast<char*>(kv->v_pages) + layer_stride * l;
+    const gs::QkvOut out{static_cast<const int4*>(p.row_slot), static_cast<const float2*>(p.rope), p.q, kl, vl, kv->page_size,
+                         m.n_heads, m.n_kv_heads, m.head_dim};
     if (fused) {
-      const gs::QkvOut out{static_cast<const int4*>(p.row_slot), static_cast<const float2*>(p.rope), p.q, kl, vl, kv->page_size,
-                           m.n_heads, m.n_kv_heads, m.head_dim};
       GS_STAGE(GS_STAGE_GEMM, gs::launch_rows_qkv(m.dtype, p.h, ctx->wqkv[l], norm, out, rows, d, stream));
     } else {
       GS_STAGE(GS_STAGE_GEMM, gs::launch_gemm(m.dtype, p.h, ctx->wqkv[l], p.partial, rows, qkv, d, stream));
-      GS_STAGE(GS_STAGE_GLUE, gs::launch_rope_append(act, p.partial, gs::gemm_splits(m.dtype, rows, qkv, d), rows, p.row_slot,
-                                    p.rope, kv->page_size, m.n_heads, m.n_kv_heads, m.head_dim, p.q, kl, vl, stream));
+      GS_STAGE(GS_STAGE_GLUE, gs::launch_rope_append(act, p.partial, gs::gemm_splits(m.dtype, rows, qkv, d), rows, out, stream));
     }
     GS_STAGE(GS_STAGE_ATTENTION, gs::launch_attention(act, p.q, kl, vl, b->block_table, b->max_blocks, b->cu_rows, b->ctx_len, n, rows,
                                 kv->page_size, m.n_heads, m.n_kv_heads, m.head_dim, attn_waves, attn_key_groups, attn_sps, attn_splits,
