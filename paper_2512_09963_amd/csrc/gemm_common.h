@@ -53,7 +53,7 @@ __device__ __forceinline__ float wave_sum(float v) {
 struct RowNorm {       // input side: x^2 sums [rows][blocks], blocks = d / 16
   const float* squares;
   int blocks;
-  float inv_d, eps;
+  float d, eps;
 };
 struct QkvOut {        // where the fused QKV result goes (store_qkv_pair)
   const int4* row_slot;
@@ -103,7 +103,7 @@ struct RowFactors {
         s += (lane & 15) * 4 + j * 64 < n.blocks ? (v[p][j].x + v[p][j].y) + (v[p][j].z + v[p][j].w) : 0.f;
       s = row16_sum(s);
       const int row = (p * WAVES + wave) * 4 + (lane >> 4);
-      if ((lane & 15) == 0 && row < ROWS) factor[row] = 1.0f / sqrtf(s * n.inv_d + n.eps);
+      if ((lane & 15) == 0 && row < ROWS) factor[row] = 1.0f / sqrtf(s / n.d + n.eps);
     }
   }
 };

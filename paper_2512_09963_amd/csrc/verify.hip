@@ -437,7 +437,7 @@ extern "C" gs_status gs_verify_batch(gs_ctx* ctx, const gs_kv_cache* kv, const g
 
   const bool fused = gs::rows_fused(m.dtype, rows, d, hq, qkv, F);      // norms, rotation and residual inside the projections
   const bool packed = fused && act == GS_BF16;                   // bf16 activations of such layers in fragment order
-  const gs::RowNorm norm{p.squares, d / 16, 1.0f / (float)d, m.rms_eps};
+  const gs::RowNorm norm{p.squares, d / 16, (float)d, m.rms_eps};
   StageTimer timer(ctx, stream);
 #define GS_STAGE(stage, call)   \
   do {                          \

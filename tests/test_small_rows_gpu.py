@@ -142,3 +142,32 @@ def test_bf16_attention_quotient_is_correctly_rounded(rows, page):
     torch.cuda.synchronize()
     want = (a + 0.5).view(1, d).to(torch.bfloat16).float().expand(rows, d)
     assert torch.equal(trace[1], want)
+
+
+@pytest.mark.parametrize("rows", [1, 20, 64, 70])
+def test_f32_row_factor_is_that_of_a_quotient(rows):
+    """Rows of ones have a mean square of exactly 1 and a factor of exactly 1, whatever the width.  2624 is 41 * 64: its rounded reciprocal times
+    2624 is one bit below 1, and the factor would be one bit above it."""
+    import torch
+    from paper_2512_09963_amd import binding as gsb
+    d, hd, vocab = 2624, 64, 96
+    dev = torch.device("cuda:0")
+    f32 = dict(dtype=torch.float32, device=dev)
+    pick = torch.zeros(vocab, d, **f32)
+    pick[torch.arange(vocab), torch.arange(vocab) * 27] = 1.0      # logit j is element 27 j of the normed row
+    layer = dict(wqkv=torch.zeros(3 * hd, d, **f32), wo=torch.zeros(d, hd, **f32), wgu=torch.zeros(2 * 16, d, **f32),
+                 wd=torch.zeros(d, 16, **f32), norm1=torch.ones(d, **f32), norm2=torch.ones(d, **f32))
+    top = dict(embed=torch.ones(vocab, d, **f32), lm_head=pick, final_norm=torch.ones(d, **f32))
+    desc = dict(n_layers=1, d_model=d, n_heads=1, n_kv_heads=1, head_dim=hd, d_ffn=16, vocab=vocab, rope_theta=10000.0, rms_eps=0.0,
+                dtype="f32")
+    ver = gsb.Verifier(desc, top, [layer])
+    gamma, ctx = np.array([rows - 1], np.int32), np.zeros(1, np.int32)
+    batch = synth.make_batch(5, gamma, ctx, 16)
+    k, v = torch.zeros(1, batch.n_pages, 1, 16, hd, **f32), torch.zeros(1, batch.n_pages, 1, hd, 16, **f32)
+    logits = torch.empty(rows, vocab, **f32)
+    ws = torch.empty(ver.gs_workspace_bytes(rows, 1, rows), dtype=torch.uint8, device=dev)
+    ver.gs_verify_batch(k, v, 16, batch.n_pages, gamma, ctx, torch.from_numpy(batch.cu_rows).to(dev), torch.from_numpy(ctx).to(dev),
+                        torch.zeros(rows, dtype=torch.int32, device=dev), torch.from_numpy(batch.block_table).to(dev), None, None, None,
+                        None, logits, ws)
+    torch.cuda.synchronize()
+    assert torch.equal(logits, torch.ones_like(logits))
