@@ -171,3 +171,106 @@ def test_f32_row_factor_is_that_of_a_quotient(rows):
                         None, logits, ws)
     torch.cuda.synchronize()
     assert torch.equal(logits, torch.ones_like(logits))
+
+
+def _small_model(dtype):
+    return synth.ModelShape(2, 256, 4, 2, 64, 512, 1024, 10000.0, dtype=dtype)
+
+
+def _prepare(ms, seed, gamma, ctx, std=0.08):
+    """(verifier, KV cache, device batch, workspace) and what the oracle starts from."""
+    import torch
+    from paper_2512_09963_amd import workload as wl
+    top = synth.top_weights(ms, seed, std=std)
+    layers = [synth.layer_weights(ms, seed, l, std=std) for l in range(ms.n_layers)]
+    batch = synth.make_batch(seed, np.array(gamma, np.int32), np.array(ctx, np.int32), 16, permute_pages=True)
+    tokens, q, ua, ur = synth.verify_side_inputs(seed, ms.vocab, batch.gamma, sigma=0.5)
+    ver = wl.upload_model(ms, top, lambda l: layers[l])
+    kv = wl.KVCache(ms, batch.n_pages, 16)
+    cache = [(synth.kv_layer_cache(ms, seed, l, "k", batch.n_pages, 16), synth.kv_layer_cache(ms, seed, l, "v", batch.n_pages, 16))
+             for l in range(ms.n_layers)]
+    for l in range(ms.n_layers):
+        kv.set_layer(l, *cache[l])
+    db = wl.DeviceBatch(batch, tokens, q, ua, ur)
+    ws = torch.empty(ver.gs_workspace_bytes(db.n_rows, db.n_servers, db.max_ctx), dtype=torch.uint8, device="cuda:0")
+    return ver, kv, db, ws, (top, layers, batch, tokens, cache)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_layers_of_five_launches_under_capture(dtype):
+    """Replays, with eager work and synchronisations between them, give the eager result bit for bit."""
+    import torch
+    from paper_2512_09963_amd import binding as gsb, workload as wl
+    ms = _small_model(dtype)
+    ver, kv, db, ws, _ = _prepare(ms, 61, [4, 0, 2, 5], [37, 5, 260, 0])
+    ref_out, ref_logits, _ = wl.verify(ver, kv, db, workspace=ws)
+    torch.cuda.synchronize()
+    ref_out, ref_logits = {k: v.clone() for k, v in ref_out.items()}, ref_logits.clone()
+    out, logits = gsb.make_accept_out(db.n_servers, db.n_draft, torch.device("cuda:0")), torch.empty_like(ref_logits)
+    args = (kv.k, kv.v, kv.page_size, kv.n_pages, db.gamma, db.ctx_len_host, db.cu_rows, db.ctx_len, db.tokens, db.block_table,
+            db.q_probs, db.u_accept, db.u_resample, out, logits, ws)
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        ver.gs_verify_batch(*args)
+    torch.cuda.current_stream().wait_stream(side)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        ver.gs_verify_batch(*args)
+    for rep in range(3):
+        logits.zero_()
+        ws.fill_(0xff)
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(logits, ref_logits), f"replay {rep}"
+        for k, v in ref_out.items():
+            assert torch.equal(out[k], v), f"replay {rep}: {k}"
+        wl.verify(ver, kv, db, workspace=ws)
+        torch.cuda.synchronize()
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_residual_trace_of_layers_of_five_launches(dtype):
+    """Entry l is the residual stream that enters layer l.  The last entry, normed and multiplied by the LM head on the host, gives the
+    logits: to 1e-5 of the row scale in fp32, to the rounding of the normed row in bf16 (2^-9 an element, 1e-2 with 256 of them)."""
+    import torch
+    from paper_2512_09963_amd import workload as wl
+    ms = _small_model(dtype)
+    ver, kv, db, ws, (top, layers, batch, tokens, _) = _prepare(ms, 62, [4, 0, 2, 5], [37, 5, 260, 0])
+    trace = torch.full((ms.n_layers + 1, db.n_rows, ms.d_model), float("nan"), device="cuda:0")
+    ver.gs_trace_residual(trace)
+    _, logits, _ = wl.verify(ver, kv, db, workspace=ws)
+    torch.cuda.synchronize()
+    ver.gs_trace_residual(None)
+    tr = trace.cpu().numpy().astype(np.float64)
+    np.testing.assert_array_equal(tr[0], np.asarray(top["embed"], np.float64)[tokens])
+    assert np.isfinite(tr).all() and (np.abs(tr[1:] - tr[:-1]).max(axis=(1, 2)) > 0).all()
+    x = tr[-1]
+    h = x * np.asarray(top["final_norm"], np.float64) / np.sqrt((x * x).mean(axis=1, keepdims=True) + ms.rms_eps)
+    want = h @ np.asarray(top["lm_head"], np.float64).T
+    err = np.abs(logits.cpu().numpy() - want) / np.abs(want).max(axis=1, keepdims=True)
+    assert err.max() <= (1e-5 if dtype == "f32" else 1e-2)
+
+
+def test_f32_weights_that_are_not_16_byte_aligned():
+    """Matrices four bytes past an aligned address take scalar loads; the sums are formed in the same order."""
+    import torch
+    from paper_2512_09963_amd import binding as gsb, workload as wl
+    ms = _small_model("f32")
+    ver, kv, db, ws, _ = _prepare(ms, 63, [4, 0, 2, 5], [37, 5, 260, 0])
+    _, want, _ = wl.verify(ver, kv, db, workspace=ws)
+    want = want.clone()
+
+    def moved(t):
+        m = torch.empty(t.numel() + 1, dtype=t.dtype, device=t.device)[1:]
+        m.view(t.shape).copy_(t)
+        assert m.data_ptr() % 16 == 4
+        return m
+    top, layers = ver._keep
+    mats = ("wqkv", "wo", "wgu", "wd")
+    other = gsb.Verifier(ver.desc, dict(top, lm_head=moved(top["lm_head"])),
+                         [dict(l, **{k: moved(l[k]) for k in mats}) for l in layers])
+    _, got, _ = wl.verify(other, kv, db, workspace=ws)
+    torch.cuda.synchronize()
+    assert float((got - want).abs().max()) <= 1e-6 * float(want.abs().max())
