@@ -412,12 +412,13 @@ struct GemmPlan {
 // 64-column workgroups and 512-element K splits of the skinny kernel leave at most one workgroup to a compute unit, a launch is
 // over before the wide kernel's three buffers and exchange of K groups pay.  Isolated launches, skinny and wide, us at 20 / 64 rows:
 // 1024 x 4096 5.3 / 6.0 and 6.7 / 8.1, 2048 x 2048 5.3 / 6.0 and 6.6 / 8.0, 4096 x 2048 7.2 / 7.8 and 7.5 / 8.8; beyond the line 1536 x 6144
-// 7.9 / 9.3 and 7.5 / 9.1, 3072 x 3072 7.9 / 9.6 and 7.6 / 9.1.  Larger ones gain in the step as well by fewer partial results: 4 layers of the 8B
+// 7.9 / 9.3 and 7.5 / 9.1, 3072 x 3072 7.9 / 9.6 and 7.6 / 9.1.  Nor with fewer than eight blocks of 128 columns, which its grid leaves
+// on as many XCDs (512 x 20480 8.8 / 11.3 and 12.9 / 16.3).  Larger ones gain in the step as well by fewer partial results: 4 layers of the 8B
 // shape at 24 / 32 / 60 rows 649 / 648 / 707 us -> 615 / 630 / 688, 2 layers of the 70B shape at 24 / 60 rows 996 / 1049 -> 912 / 989.
 bool wide_serves(int M, int N, int K) {
   if (N % 128 != 0) return false;
   if (M > 64 || wide_plan(M, N, K, false).splits == 1) return true;
-  return (long)(N / 64) * (K / 512) > 256;
+  return N >= 1024 && (long)(N / 64) * (K / 512) > 256;
 }
 
 static GemmPlan gemm_plan(int M, int N, int K) {

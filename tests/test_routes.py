@@ -25,6 +25,7 @@ def _wide_serves(M, N, K):
     (4224, 2048, True), (1536, 6144, True), (3072, 3072, True), (2048, 8192, True),          # more
     (4096, 4096, True), (6144, 4096, True), (4096, 14336, True), (8192, 28672, True),
     (1024, 512, True), (28672, 4096, True), (128256, 4096, True),                            # no K split
+    (512, 20480, False), (896, 20480, False), (1024, 20480, True),                           # fewer than eight column blocks
     (1088, 4096, False),                                                                     # no multiple of 128 columns
 ])
 def test_bf16_projections_of_up_to_64_rows(M, N, K, wide):
