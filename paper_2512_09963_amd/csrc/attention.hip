@@ -16,7 +16,8 @@
 // workgroup), so ragged batches stay balanced.  Partial results of the splits are merged by
 // attn_combine_kernel; the result of a group that is not split is final and stored by the kernel itself.
 //
-// fp32 path: one workgroup per (row, head), lanes over keys, online softmax per lane.
+// fp32 path (attn_rowwise_kernel): one workgroup per (row, head), 128 keys at a time, 16 lanes to a key; the softmax state is one per
+// workgroup.
 #include "common.h"
 #include "attn_work.h"
 #include "device_types.h"
@@ -35,7 +36,7 @@ constexpr float kNegBig = -1.0e30f;
 // products read memory in whole lines; the four lanes of a channel are neighbours.  Latency bound (a few dozen rows and
 // keys): all loads of K and V of a chunk are issued before the first score, so a chunk costs two dependent trips to memory
 // (pages, then K and V), and the softmax state is formed by every wave for itself from the scores in LDS.  A lane per key
-// with the lanes' states merged at the end took 13.6 us at 16 rows of 4 heads, 69 keys and head size 64, this takes 6.9.
+// with the lanes' states merged at the end took 13.6 us at 16 rows of 4 heads, 69 keys and head size 64, this takes 5.6.
 // VEC: 16-byte loads (16-byte aligned pages, page size a multiple of 4).  AHEAD: the pages of the next chunk are looked up while
 // this one is computed, one dependent trip per chunk; for launches of at most two workgroups per compute unit, which wait
 // for loads and not for the units (kRowAheadItems).  Writes attn_out [R][H*hd].

@@ -8,8 +8,8 @@
 // straight into the MFMA operands, D steps ahead; an activation fragment is used by one wave of a workgroup, so LDS would not
 // save a load, but every workgroup reads all activations: M x K x 2 bytes per compute unit beside 32 x NT x K of weights.  A compute
 // unit takes 23 GB/s of its share of the HBM stream and 94 GB/s from L2, but not both at once (54 GB/s in all at two parts of
-// activations to one of weights, whatever the number of loads in flight), so beyond 16 rows the K splits are faster
-// (53 rows: 40 us for the 4096 x 14336 projection, 24 and a norm with them).  The activations are stored in fragment
+// activations to one of weights, whatever the number of loads in flight: a loop of the same loads alone), so beyond 16 rows
+// the K splits are faster (53 rows: 40 us for the 4096 x 14336 projection, 24 and a norm with them).  The activations are stored in fragment
 // order (packed_index), so that such a load is one kilobyte in a row (row-major 34.7 us against 28.9 at 32 rows).
 // Per launch, us, 8B shape, 5 / 16 rows, and in brackets the K splits with their norm or rotation kernel at 5 rows:
 //   6144 x 4096  11.2 / 12.0 (16.0)    4096 x 4096  8.2 / 9.6 (15.0)    4096 x 14336  21.1 / 25.1 (26.2)

@@ -428,14 +428,14 @@ gs_status launch_pack_weight_w4(const void* q, const void* scales, const void* z
 //   up to 32 rows: the weight stream is all there is; 8 waves side by side, K splits for two workgroups per compute unit up to
 //     16 rows, for one beyond, where the partial results weigh more (32 rows, 8192 x 8192: 14.5 us and 16.8 MB with two, 13.8 us
 //     and 8.4 MB with one)
-//   33 to 96 rows: 4 waves x 2 K groups; two column tiles per wave (a fragment read from LDS feeds two MFMAs) for matrices of
+//   33 to 96 rows: 4 waves x 2 K groups, or 2 x 4 (narrow matrices, below); two column tiles per wave (a fragment read from LDS feeds two MFMAs) for matrices of
 //     192 blocks of 256 columns and more, and where every wave still gets 16 steps; otherwise one
 //     (92 rows, isolated: 8192 x 28672 49 us with two, 54 with one; 8192 x 8192 22.0 and 20.8; 10240 x 8192 26.5 and 25.8)
 //   more rows: chunks of 128; 8 waves side by side with one tile (two do not fit the registers)
 // Inside a verification step, us per launch (predecessor, with two LDS buffers and one burst of loads per step, in
-// brackets): 92 rows, 70B shape: gate/up 102 (123, and 8.5 for the separate SwiGLU), 8192 x 28672 51, 8192 x 8192 22.5 (67
-// on average), QKV 26.8 (33.5), LM head 202 (250); 53 rows, 8B shape: gate/up 28.6 (32, and 6), 4096 x 14336 15.6 (18.5),
-// QKV 12.2 (15.1), 4096 x 4096 10.8 (11.3), LM head 85.5 (89.6).
+// brackets): 92 rows, 70B shape: gate/up 101 (123, and 8.5 for the separate SwiGLU), 8192 x 28672 52, 8192 x 8192 22.9 (67
+// on average), QKV 27.3 (33.5), LM head 205 (250); 53 rows, 8B shape: gate/up 26.3 (32, and 6), 4096 x 14336 and 4096 x 4096 13.2 on
+// average (14.9), QKV 10.7 (15.1), LM head 83.5 (89.6).
 struct W4Plan {
   int mt, m_chunks, waves, kg, nt, n_blocks, splits, k_per;
 };
@@ -481,7 +481,7 @@ static W4Plan w4_plan(int M, int N, int K) {
 int gemm_w4_splits(int M, int N, int K) { return M <= 0 ? 1 : w4_plan(M, N, K).splits; }
 
 // Whether the gate/up projection runs unsplit with the SwiGLU in its epilogue: up to 64 rows with 2 waves x 4 K groups
-// (128 columns per workgroup; 53 rows of the 8B shape 28 us, against 25 and a separate SwiGLU of 6), up to 96 with 4 x 2
+// (128 columns per workgroup; 53 rows of the 8B shape 26 us, against 25 and a separate SwiGLU of 6), up to 96 with 4 x 2
 // (256 columns), where that fills more than half of the compute units.
 static int w4_gate_up_blocks(int M, int F) {
   if (M <= 64) return F % 64 == 0 ? F / 64 : 0;

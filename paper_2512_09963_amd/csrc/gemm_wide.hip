@@ -23,6 +23,7 @@
 //     in LDS: as many waves as 1 x 8 without halving the workgroups of a narrower matrix, and half the partial results of a
 //     further K split (which the gate/up projection, whose epilogue applies the SwiGLU, must not have)
 //   1 x 2 (64 columns) with KG = 4, up to 64 rows: the same for matrices of 4096 columns or so, which would need eight K splits
+//     (small matrices of up to 64 rows stay on the kernel of gemm.hip: wide_serves)
 //   1 x 4 (128 columns) in row chunks of 64 to 192 rows, two workgroups per compute unit: narrow matrices and middling row counts,
 //     where the time of one workgroup is the time of the launch
 //   2 x 2 (128 columns, up to 352 rows in one workgroup): both row halves load the weights, the second time from L1

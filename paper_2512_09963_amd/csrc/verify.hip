@@ -2,7 +2,12 @@
 // rejection-verification, enqueued on one stream without host synchronisation.
 // First one launch for the embedding, the first norm, the per-row tables and the attention work list; then
 // per layer: add+RMSNorm -> QKV projection -> rotary + KV append -> attention -> O projection
-//            -> add+RMSNorm -> gate/up projection -> SwiGLU -> down projection.
+//            -> add+RMSNorm -> gate/up projection -> SwiGLU -> down projection
+// where the attention may be two launches (merge of KV splits) and the gate/up projection apply the SwiGLU itself;
+// in blocks of a few rows (rows_fused):
+//            QKV projection (with the norm, rotary and KV append) -> attention -> O projection (with the residual sum)
+//            -> gate/up projection (with the norm and the SwiGLU) -> down projection (with the residual sum).
+// At last the final norm, where the LM head does not apply it, the LM head and rejection-verification.
 // The residual stream and the logits are fp32; tensors fed to a projection and the KV
 // pages are in the model's storage type.
 #include <new>
