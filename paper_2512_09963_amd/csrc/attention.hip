@@ -632,11 +632,11 @@ constexpr int kGroupWaves = 4;
 // server at 700 / 2048 keys 395 -> 385 and 400 -> 393 us, two servers 408 -> 397 and 415 -> 408.  A workgroup then fills the LDS of a
 // compute unit: with 256 of them 8 servers at 2048 keys take 499 instead of 492; two tiles of rows gain nothing.  (Fewer splits
 // instead, as the key groups would allow, are slower: a compute unit alone streams 26 GB/s, 700 keys unsplit take 22 us, in four
-// splits with the merge 15.)  On short contexts, whose only split has fewer than kKeyGroupSteps steps, the start of four rings and
-// the merge cost more than the steps they save: 16 layers of 32 heads of 128 over 8, 1 to 24 servers, whole call against one key
-// group: 2 steps 1.02 to 1.08 times as long, 3 steps 1.01 to 1.05, 4 and 5 steps 0.99 to 1.02, 6 steps 0.95 to 0.985; 7 steps and
-// more, in splits of up to 6, 0.95 to 0.985.
-constexpr int kKeyGroups = 4, kKeyGroupItems = 192, kKeyGroupSteps = 6;
+// splits with the merge 15.)  On contexts of two steps the start of four rings and the merge cost more than the step they save.
+// Replayed calls of 8 layers on 64 / 96 / 128 / 160 keys, one key group and four, us: one server, 32 heads of 128 over 8 217 / 226 / 236 /
+// 245 and 221 / 225 / 228 / 238; 4 heads of 64 over 2 183 / 188 / 196 / 203 and 186 / 185 / 187 / 193; 16 servers of the latter 261 / 268 / 275 /
+// 282 and 262 / 265 / 269 / 275.
+constexpr int kKeyGroups = 4, kKeyGroupItems = 192, kKeyGroupSteps = 3;
 void attention_groups(int group, long max_block_tokens, int* waves, int* group_tokens) {
   const long tiles = (max_block_tokens * group + 31) / 32;
   *waves = tiles > kMaxWaves ? kGroupWaves : tiles > 0 ? (int)tiles : 1;

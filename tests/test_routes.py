@@ -49,11 +49,11 @@ def attention_key_groups(n_kv, group, gamma, ctx):
 
 @pytest.mark.parametrize("n", [1, 2, 8, 16, 24])
 def test_attention_of_short_contexts_has_one_key_group(n):
-    """A split of fewer than six steps of 32 keys is over before the start of four rings and their merge pay."""
-    for keys in range(1, 161):
+    """A split of two steps of 32 keys is over before the start of four rings and their merge pay."""
+    for keys in range(1, 65):
         assert attention_key_groups(8, 4, [0] * n, [keys - 1] * n)[0] == 1
-    for keys in range(161, 193):
-        assert attention_key_groups(8, 4, [0] * n, [keys - 1] * n) == (4, 6)
+    for keys in range(65, 193):
+        assert attention_key_groups(8, 4, [0] * n, [keys - 1] * n) == (4, (keys + 31) // 32)
 
 
 @pytest.mark.parametrize("gamma,ctx,groups", [

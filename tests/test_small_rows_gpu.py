@@ -89,7 +89,8 @@ def test_bf16_projections_of_small_matrices(rows):
 
 
 @pytest.mark.parametrize("heads,n_kv,hd,gamma,ctx,page,key_groups", [
-    (4, 1, 128, [7], [0], 16, 1),                          # short contexts: one wave and one ring
+    (4, 1, 128, [7, 0], [0, 60], 16, 1),                   # short contexts: one wave and one ring
+    (4, 1, 128, [7, 0], [80, 60], 16, 4),                  # three and two steps: a key group has none
     (4, 1, 128, [7, 0], [0, 300], 16, 4),                  # one step (three key groups have none) beside splits of five
     (4, 2, 128, [3, 0], [40, 190], 16, 4),                 # two and six steps
     (8, 2, 64, [4, 2], [700, 129], 32, 4),                 # splits of six and five steps
