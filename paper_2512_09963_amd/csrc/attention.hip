@@ -236,10 +236,12 @@ __device__ __forceinline__ float halves_sum(float x) {
 }
 
 // a / l correctly rounded, with inv = 1 / l correctly rounded: a product whose remainder is divided as well (Markstein, IBM J. Res.
-// Dev. 34, 1990).  The 64 quotients of a lane share l: half of the instructions of 64 divisions.  Infinities stay what they are.
+// Dev. 34, 1990).  The 64 quotients of a lane share l: four instructions each instead of ten.  The remainder of an infinity is NaN, which
+// the median turns into a finite number, so that infinities stay what they are.  8 layers of 32 heads of 128 over 8, one server on 20 tokens,
+// replayed: product alone 208 us, this 212, with a comparison and a selection instead of the median 214.
 __device__ __forceinline__ float quotient(float a, float l, float inv) {
   const float q = a * inv;
-  return fabsf(q) < INFINITY ? fmaf(fmaf(-q, l, a), inv, q) : q;
+  return fmaf(__builtin_amdgcn_fmed3f(fmaf(-q, l, a), -3.0e38f, 3.0e38f), inv, q);
 }
 
 // (164 vector registers: three waves per SIMD, i.e. up to four 3-wave workgroups per CU, which hides a
