@@ -841,13 +841,13 @@ static gs_status launch_mfma_g(const bf16_t* q, const bf16_t* k_pages, const bf1
 // Number of ints of a work list with room for `capacity` entries.
 size_t attention_work_ints(int capacity) { return 8 + 8 * (size_t)capacity; }
 
-// attn_out [R][H*hd] (storage type).  scratch: attention_workspace_floats floats; work, n_work: the step's work
+// attn_out [R][H*hd] (storage type).  max_keys: the most keys any row sees.  scratch: attention_workspace_floats floats; work, n_work: the step's work
 // list and its length as the host computes it from its copy of the batch geometry (bf16 path only).  waves: per
 // workgroup (attention_groups).  split: whether any group has more than one split.  packed: bf16 result in
 // fragment order (packed_index).
 gs_status launch_attention(int dtype, const void* q, const void* k_pages, const void* v_pages,
                            const int* block_table, int max_blocks, const int* cu_rows, const int* ctx_len,
-                           int n_servers, int n_rows, int page_size, int n_heads, int n_kv, int hd,
+                           int n_servers, int n_rows, int max_keys, int page_size, int n_heads, int n_kv, int hd,
                            int waves, int key_groups, int steps_per_split, int max_splits, bool split, const void* row_info,
                            const int* work, int n_work, float* scratch, void* attn_out, bool packed, hipStream_t stream) {
   if (dtype == GS_F32) {
@@ -859,8 +859,9 @@ gs_status launch_attention(int dtype, const void* q, const void* k_pages, const 
     const bool vec = page_size % 4 == 0 && reinterpret_cast<uintptr_t>(k_pages) % 16 == 0 &&
                      reinterpret_cast<uintptr_t>(v_pages) % 16 == 0;
     // Looking ahead: 4 layers of 4 heads of 64 over 2, whole call, us without and with: 64 rows on 8000 keys 1268 and 980, 128 rows
-    // 1425 and 1243 (1356 with a lane per key); 8 heads over 1, 256 rows on 8000 keys 3073 and 3577.
-    const bool ahead = vec && (long)n_rows * n_heads <= kRowAheadItems;
+    // 1425 and 1243 (1356 with a lane per key); 8 heads over 1, 256 rows on 8000 keys 3073 and 3577.  Up to 32 keys
+    // there is nothing to wait for (8 layers, 8 servers on 8 keys 208 and 211, on 32 the same, on 60 217 and 212).
+    const bool ahead = vec && (long)n_rows * n_heads <= kRowAheadItems && max_keys > 32;
 #define GS_ROWWISE(HD_, VEC_, AHEAD_)                                                                             \
   attn_rowwise_kernel<HD_, VEC_, AHEAD_><<<grid, kRowThreads, 0, stream>>>(qf, kf, vf, block_table, max_blocks,           \
                                                                    static_cast<const int4*>(row_info), cu_rows, ctx_len, \

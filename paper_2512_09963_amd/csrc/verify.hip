@@ -52,7 +52,7 @@ long attention_busiest_cu(int n_kv, int n_servers, const int* gamma_host, const 
 size_t attention_workspace_floats(int n_rows, int n_heads, int hd, int max_splits);
 gs_status launch_attention(int dtype, const void* q, const void* k_pages, const void* v_pages,
                            const int* block_table, int max_blocks, const int* cu_rows, const int* ctx_len,
-                           int n_servers, int n_rows, int page_size, int n_heads, int n_kv, int hd,
+                           int n_servers, int n_rows, int max_keys, int page_size, int n_heads, int n_kv, int hd,
                            int waves, int key_groups, int steps_per_split, int max_splits, bool split, const void* row_info,
                            const int* work, int n_work, float* scratch, void* attn_out, bool packed, hipStream_t stream);
 size_t attention_work_ints(int capacity);
@@ -474,7 +474,7 @@ extern "C" gs_status gs_verify_batch(gs_ctx* ctx, const gs_kv_cache* kv, const g
       GS_STAGE(GS_STAGE_GLUE, gs::launch_rope_append(act, p.partial, gs::gemm_splits(m.dtype, rows, qkv, d), rows, out, stream));
     }
     GS_STAGE(GS_STAGE_ATTENTION, gs::launch_attention(act, p.q, kl, vl, b->block_table, b->max_blocks, b->cu_rows, b->ctx_len, n, rows,
-                                kv->page_size, m.n_heads, m.n_kv_heads, m.head_dim, attn_waves, attn_key_groups, attn_sps, attn_splits,
+                                max_ctx, kv->page_size, m.n_heads, m.n_kv_heads, m.head_dim, attn_waves, attn_key_groups, attn_sps, attn_splits,
                                 attn_split, p.row_slot, p.attn_work, (int)attn_items, p.attn_scratch, p.attn, packed, stream));
     if (fused) {
       const bool top = l + 1 == m.n_layers;

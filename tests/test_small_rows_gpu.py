@@ -16,6 +16,8 @@ pytestmark = pytest.mark.gpu
     (128, 1, [2, 1], [3, 130]),
     (128, 12, [4, 6], [253, 40]),                      # a multiple of 4 but not of 16
     (128, 64, [1, 15], [512, 1]),
+    (64, 16, [1, 0], [30, 12]),                        # 32 keys: no look-up ahead
+    (64, 16, [1, 0], [31, 12]),                        # 33
     (64, 16, [127], [300]),                            # 128 rows of 4 heads: the last launch that looks its pages up ahead
     (64, 16, [128], [300]),
     (128, 4, [100, 27, 2], [130, 0, 513]),             # past it
