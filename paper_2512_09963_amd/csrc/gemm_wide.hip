@@ -55,10 +55,12 @@ enum { kPlain = 0, kGateUp = 1, kStats = 2, kGateUpNorm = 3 };
 // stored as bf16 at P; kGateUpNorm: the same of rows that still need their factor (RowNorm), act in fragment order; kStats (one split): also (max, sum exp) of every row over the workgroup's columns.
 // DB, DA: steps of weights and of activations held in registers.  POL: cache policy of the weight loads (2: do not
 // displace other lines; for weights that one workgroup reads once).
-// grid (column blocks, rounded up to a multiple of 8, times row chunks; K splits).  Row chunks of one column block are separate
-// workgroups that read the same weights: workgroups are handed to the 8 XCDs round robin by their linear index, so the
-// chunks of a column block get indices that are 8 apart and land on the same XCD one after the other, and all but the first
-// find the weights in that XCD's L2.
+// 1-D grid: K splits x column blocks x row chunks.  Workgroups are handed to the 8 XCDs round robin by their index; an XCD takes a
+// contiguous range of (split, column block, row chunk), so the row chunks of a column block run on one XCD, and all but the first find
+// the weights in its L2.  No XCD has more than one workgroup more than another.  (Column blocks dealt to the XCDs one by one, rounded up
+// to a multiple of 8, left XCDs idle where a matrix has a few: replayed launches of 304 / 1024 rows, us, that way -> this one:
+// 1536 x 6144 17.2 -> 12.2 / 36.3 -> 25.5, 3584 x 3584 at 304 rows 23.6 -> 16.8, 512 x 20480 23.5 -> 15.3 / 49.3 -> 28.4; column counts that
+// divide evenly are within 2 % but for the LM head 128256 x 4096, 53 rows 180 -> 172.5; 15 matrices x 13 rows 1.07 on average.)
 template <int WM, int WN, int KG, int MT, int NT, int DB, int DA, int POL, int WPE, int MODE>
 __global__ __launch_bounds__(64 * WM * WN * KG) __attribute__((amdgpu_waves_per_eu(WPE, WPE))) void gemm_bf16_wide_kernel(
     const bf16_t* __restrict__ X, const bf16_t* __restrict__ Wp, float* __restrict__ P, int M, int N, int K,
@@ -77,13 +79,12 @@ __global__ __launch_bounds__(64 * WM * WN * KG) __attribute__((amdgpu_waves_per_
   const int tid = threadIdx.x - kg * THREADS;
   unsigned char* xs = xs_all + kg * 3 * TILE;
   const int g = lane >> 4, c = lane & 15;
-  const int xcd = blockIdx.x & 7, t = blockIdx.x >> 3;
-  const int m_chunk = t % m_chunks;
-  const int n_block = (t / m_chunks) * 8 + xcd;
-  if (n_block * (16 * NT * WN) >= N) return;      // padding of the grid to a multiple of 8 column blocks
+  const int per_xcd = gridDim.x >> 3, more = gridDim.x & 7, xcd = blockIdx.x & 7;
+  const int item = xcd * per_xcd + min(xcd, more) + (blockIdx.x >> 3);
+  const int m_chunk = item % m_chunks, column = item / m_chunks, n_blocks = N / (16 * NT * WN);
+  const int split = column / n_blocks, n_block = column - split * n_blocks;
   const int wm = wave / WN, wn = wave % WN;
   const int n_tile0 = (n_block * WN + wn) * (GATE_UP ? NT / 2 : NT);
-  const int split = blockIdx.y;
   const int m0 = m_chunk * ROWS;
   const int split_begin = split * k_per_split, split_end = min(K, split_begin + k_per_split);
   // the K groups take the halves of the split, rounded to steps; both run the same number of steps (barriers), a
@@ -406,7 +407,7 @@ WidePlan wide_plan(int M, int N, int K, bool one_split) {
 template <int MODE>
 static gs_status launch_mode(const WidePlan& p, const bf16_t* x, const bf16_t* w, float* out, int M, int N, int K,
                              float2* stats, const RowNorm& norm, hipStream_t stream) {
-  const dim3 grid(ceil_div(p.n_blocks, 8) * 8 * p.m_chunks, p.splits, 1);
+  const int grid = p.n_blocks * p.m_chunks * p.splits;
 #define GS_WIDE(WM, WN, KG, MT, NT, DB, DA, POL, WPE)                                                              \
   gemm_bf16_wide_kernel<WM, WN, KG, MT, NT, DB, DA, POL, WPE, MODE>                                                 \
       <<<grid, 64 * WM * WN * KG, 0, stream>>>(x, w, out, M, N, K, p.k_per, p.m_chunks, stats, p.n_blocks, norm)
