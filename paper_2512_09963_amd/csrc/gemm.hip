@@ -3,7 +3,7 @@
 // bf16 path (MFMA): the verify step has few rows (tens to a few hundred) against
 // matrices of 10^7..10^9 weights, so every weight byte is used by only M rows: the kernels
 // are weight-streaming kernels bound by HBM, and the layout serves the stream.  Most shapes go to the pipelined
-// kernel of gemm_wide.hip (same packed weights); the one here serves what GemmPlan says:
+// kernels of gemm_wide.hip and gemm_block.hip (same packed weights); the one here serves what GemmPlan says:
 //   * the weights are stored tile-packed (gs_pack_weight): the 2 KB that one wavefront needs
 //     per 64-wide k step for its 16 output columns is contiguous, and the blocks are ordered
 //     [k_step][n_tile][half][lane][8 bf16]: at one k step the blocks of neighbouring column tiles
@@ -417,15 +417,15 @@ struct GemmPlan {
 // shape at 24 / 32 / 60 rows 649 / 648 / 707 us -> 615 / 630 / 688, 2 layers of the 70B shape at 24 / 60 rows 996 / 1049 -> 912 / 989.
 bool wide_serves(int M, int N, int K) {
   if (N % 128 != 0) return false;
-  if (M > 64 || wide_plan(M, N, K, false).splits == 1) return true;
+  if (M > 64 || wide_plan(M, N, K, kForSums).splits == 1) return true;
   return N >= 1024 && (long)(N / 64) * (K / 512) > 256;
 }
 
-static GemmPlan gemm_plan(int M, int N, int K) {
+static GemmPlan gemm_plan(int M, int N, int K, PlanFor use = kForSums) {
   GemmPlan p;
   const int tiles = ceil_div(M, 16);
   int n_blocks;
-  if (N % 128 == 0) p.wide = wide_plan(M, N, K, false);
+  if (N % 128 == 0) p.wide = wide_plan(M, N, K, use);
   if (wide_serves(M, N, K)) {
     p.kind = GemmPlan::kWide;
     p.mt = p.wide.mt;
@@ -482,13 +482,11 @@ static void launch_skinny(const GemmPlan& p, const bf16_t* x, const bf16_t* w, f
 }
 
 // Whether the gate/up projection of this shape runs with the SwiGLU fused: 4-bit where its kernel does; bf16 up to 64 rows
-// and where the kernel needs no K split anyway.
+// and where the whole sums take no longer.
 bool gate_up_fused(int dtype, int M, int F, int K) {
   if (dtype == GS_W4) return M > 0 && w4_gate_up_fused(M, F);
   if (dtype != GS_BF16 || M <= 0 || F % 64 != 0 || K % kBK != 0) return false;
-  if (M <= 64) return true;
-  const GemmPlan p = gemm_plan(M, 2 * F, K);
-  return p.kind != GemmPlan::kSkinny && p.splits == 1;
+  return wide_gate_up_fused(M, 2 * F, K);      // (2 F is a multiple of 128)
 }
 
 // act [M][F] (bf16) = silu(X Wg^T) * (X Wu^T), W = [Wg; Wu] packed; only for shapes gate_up_fused accepts.
@@ -498,14 +496,14 @@ gs_status launch_gemm_gate_up(int dtype, const void* X, const void* W, void* act
   const bf16_t* x = static_cast<const bf16_t*>(X);
   const bf16_t* w = static_cast<const bf16_t*>(W);
   // (2 F is a multiple of 128)
-  return launch_wide_gate_up(wide_plan(M, 2 * F, K, true), x, w, static_cast<bf16_t*>(act), M, 2 * F, K, stream);
+  return launch_wide_gate_up(wide_plan(M, 2 * F, K, kForWholeSums), x, w, static_cast<bf16_t*>(act), M, 2 * F, K, stream);
 }
 
 // Number of column blocks per row of the statistics that launch_gemm_stats writes for this shape, or 0 where
 // the projection of this shape does not emit them (fp32 and 4-bit models, shapes that need a K split).
 int gemm_stat_blocks(int dtype, int M, int N, int K) {
   if (dtype != GS_BF16 || M <= 0) return 0;
-  const GemmPlan p = gemm_plan(M, N, K);
+  const GemmPlan p = gemm_plan(M, N, K, kForStats);
   if (p.splits != 1) return 0;
   return p.kind == GemmPlan::kWide ? p.wide.n_blocks : N / (16 * kSkinnyWaves);
 }
@@ -513,7 +511,7 @@ int gemm_stat_blocks(int dtype, int M, int N, int K) {
 // Y [M][N] = X W^T (one K split) and stats [M][gemm_stat_blocks] = per row and column block (max, sum exp(y - max)).
 gs_status launch_gemm_stats(const void* X, const void* W, float* Y, void* stats, int M, int N, int K,
                             hipStream_t stream) {
-  const GemmPlan p = gemm_plan(M, N, K);
+  const GemmPlan p = gemm_plan(M, N, K, kForStats);
   const bf16_t* x = static_cast<const bf16_t*>(X);
   const bf16_t* w = static_cast<const bf16_t*>(W);
   float2* st = static_cast<float2*>(stats);
@@ -604,7 +602,7 @@ gs_status launch_rows_gate_up(int dtype, const void* h, const void* w, const Row
                               hipStream_t stream) {
   if (gs_status st = check_rows(dtype, M); st != GS_OK) return st;
   if (dtype == GS_BF16)
-    return launch_wide_gate_up_norm(wide_plan(M, 2 * F, K, true), static_cast<const bf16_t*>(h), static_cast<const bf16_t*>(w), norm,
+    return launch_wide_gate_up_norm(wide_plan(M, 2 * F, K, kForWholeSums), static_cast<const bf16_t*>(h), static_cast<const bf16_t*>(w), norm,
                                     static_cast<bf16_t*>(act), M, 2 * F, K, stream);
   launch_f32<kF32GateUp>(static_cast<const float*>(h), static_cast<const float*>(w), static_cast<float*>(act), M, 2 * F, K, norm,
                          QkvOut{}, ResidualOut{}, stream);

@@ -126,12 +126,24 @@ __device__ __forceinline__ void store_qkv_pair(const QkvOut& o, int row, int hea
   }
 }
 
-// Launch of gemm_bf16_wide_kernel: wm x wn waves of mt x nt tiles, kg groups of them, n_blocks column blocks.
+// What a projection kernel stores.  kPlain: the fp32 sums [split][M][N]; kGateUp (one split): act[M][F] = silu(gate) * up as bf16, of a
+// [2F][K] matrix (N = 2F); kGateUpNorm: the same of rows that still need their factor (RowNorm), act in fragment order; kStats (one
+// split): the sums and (max, sum exp) of every row over the workgroup's columns.
+enum { kPlain = 0, kGateUp = 1, kStats = 2, kGateUpNorm = 3 };
+
+// Launch of gemm_bf16_wide_kernel or (block) gemm_bf16_block_kernel: wm x wn waves of mt x nt tiles, kg groups of them, n_blocks
+// column blocks.
 struct WidePlan {
   int wm, wn, kg, mt, nt, m_chunks, n_blocks, splits, k_per;
+  bool block;
+  float us;      // modelled time, for more than 64 rows
 };
-// one_split: the projection must not be split over workgroups (its epilogue needs the whole sums).
-WidePlan wide_plan(int M, int N, int K, bool one_split);
+// kForWholeSums: the projection must not be split over workgroups (its epilogue needs the whole sums); kForStats: it leaves statistics
+// where it needs no split.
+enum PlanFor { kForSums, kForWholeSums, kForStats };
+WidePlan wide_plan(int M, int N, int K, PlanFor use);
+// Whether gate/up (N = 2 F, a multiple of 128) is better unsplit with the SwiGLU in its epilogue than in the K splits of its plan.
+bool wide_gate_up_fused(int M, int N, int K);
 gs_status launch_wide(const WidePlan& p, const bf16_t* x, const bf16_t* w, float* out, int M, int N, int K,
                       hipStream_t stream);
 gs_status launch_wide_gate_up(const WidePlan& p, const bf16_t* x, const bf16_t* w, bf16_t* act, int M, int N, int K,
@@ -139,6 +151,9 @@ gs_status launch_wide_gate_up(const WidePlan& p, const bf16_t* x, const bf16_t* 
 // x not yet divided by its root mean square, act in fragment order; up to kMaxRows rows (two row tiles)
 gs_status launch_wide_gate_up_norm(const WidePlan& p, const bf16_t* x, const bf16_t* w, const RowNorm& norm, bf16_t* act, int M,
                                    int N, int K, hipStream_t stream);
+// (mode: kPlain, kGateUp or kStats)
+gs_status launch_block(int mode, const WidePlan& p, const bf16_t* x, const bf16_t* w, float* out, int M, int N, int K, float2* stats,
+                       hipStream_t stream);
 gs_status launch_wide_stats(const WidePlan& p, const bf16_t* x, const bf16_t* w, float* y, float2* stats, int M, int N,
                             int K, hipStream_t stream);
 

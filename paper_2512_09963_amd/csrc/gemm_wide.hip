@@ -3,7 +3,7 @@
 //
 // What bounds it: up to about 130 rows the weight stream (HBM), above the matrix pipe together with the LDS
 // reads of the activations: a 1 KB activation fragment feeds NT MFMAs of 16 cycles, so at NT = 2 the LDS delivers its
-// limit of 128 bytes per cycle and compute unit; where the matrix pipe is the bound (more than 12 row tiles) NT is 4.
+// limit of 128 bytes per cycle and compute unit.
 // The predecessor of this kernel (two LDS buffers, fragments read where they are used, all loads of a step in one
 // burst behind the barrier) was held up by neither: the loads' addresses, the LDS stores and the first fragment reads
 // of a step ran while the matrix pipe was idle, and the compiler sank the loads to the end of the step, where the
@@ -26,18 +26,11 @@
 //     (small matrices of up to 64 rows stay on the kernel of gemm.hip: wide_serves)
 //   1 x 4 (128 columns) in row chunks of 64 to 192 rows, two workgroups per compute unit: narrow matrices and middling row counts,
 //     where the time of one workgroup is the time of the launch
-//   2 x 2 (128 columns, up to 352 rows in one workgroup): both row halves load the weights, the second time from L1
-//   1 x 4 of 128 x 64 (256 columns, chunks of 128 rows) for many rows, where the matrix pipe and the power it draws are
-//     the bound: 1.0 to 1.1 PFLOP/s, 1.25 to 1.3 on matrices of zeros, 1.86 with the global loads of the loop taken out
-//     (rates of a work copy at 2048 x 28672 x 4096; more weights or activations in flight change nothing)
+// More rows, where what the waves load for themselves is the bound: gemm_block.hip.
 // Measured inside a verification step (us per launch; predecessor in brackets), N x K:
 //   50 rows    gate/up 28672 x 4096 38.4 (46.0) = 6.1 TB/s, LM head 128256 x 4096 179 (188)
 //   98 rows    gate/up 57344 x 8192 142 (181) = 6.6 TB/s, 8192 x 28672 and 8192 x 8192 55 (60) on average, 10240 x 8192
 //              36.4 (37.9), LM head 128256 x 8192 331 (455) = 6.3 TB/s
-//   312 rows   gate/up 28672 x 4096 81 to 86 (124) = 0.85 to 0.9 PFLOP/s, 4096 x 14336 and 4096 x 4096 33.2 (38) on average,
-//              6144 x 4096 28.3 (39), LM head 128256 x 4096 341 to 362 (440)
-//   1024 rows  gate/up 213 to 220, 4096 x 14336 109, 6144 x 4096 64.8, 4096 x 4096 43.6
-// (two figures: the same kernel on two machines; the matrix-bound launches are the ones that differ)
 #include "common.h"
 #include "device_types.h"
 #include "gemm_common.h"
@@ -47,8 +40,6 @@ namespace gs {
 namespace {
 
 typedef unsigned int uintx4_t __attribute__((ext_vector_type(4)));
-
-enum { kPlain = 0, kGateUp = 1, kStats = 2, kGateUpNorm = 3 };
 
 // MODE: kPlain stores the fp32 sums [split][M][N] at P; kGateUp (one split): the wave's tiles are NT / 2 feature tiles of
 // the gate half and the same ones of the up half of a [2F][K] matrix (N = 2F), and act[M][F] = silu(gate) * up is
@@ -309,77 +300,79 @@ __global__ __launch_bounds__(64 * WM * WN * KG) __attribute__((amdgpu_waves_per_
 
 }  // namespace
 
-// The shapes for more than 64 rows and what a launch takes with them (us), over 18 matrices of 1024 x 1024 to 28672 x 8192 and
-// 65 to 2047 rows in every shape and K split (rms 8 %):
+// The shapes for more than 64 rows, of this kernel and (block) of gemm_block.hip, and what a launch takes with them (us), fitted to 18000
+// launches of 22 matrices of 768 x 3072 to 57344 x 8192 and 70 to 2047 rows in every shape and several K splits (rms 7 %):
 //   the larger of loop = steps x step time of the workgroups a compute unit has one after the other, and stream = weight bytes /
-//   5.5 TB/s; 0.2 of the smaller; 0.063 x tiles per SIMD and workgroup for the epilogue; 0.46 per MB of partial results (written
+//   7.8 TB/s; 0.45 of the smaller; 0.085 x tiles per SIMD and workgroup for the epilogue; 0.39 per MB of partial results (written
 //   here, read by the next kernel).
-// A step takes fixed_us + tile_us x tiles of 16 x 16 per SIMD, of two workgroups at once (shapes that fit a compute unit twice)
-// pair_fixed_us + pair_tile_us x tiles.  Row chunks read the weights again, from L2 for the most part: 0.19 of the stream each.
-// The fixed part is what a step's barrier and loads cost whatever the tile: few rows on a narrow matrix want small workgroups in
-// several row chunks, wide matrices and many rows large tiles.  Against one shape per range of rows (K groups up to 192 rows,
-// 2 x 2 waves up to 639, 128 x 64 per wave from there), isolated launches are faster by a factor of 1.19 on average and 0.96 at
-// worst: at 180 rows 2048 x 2048 14.8 -> 6.6 us and 6144 x 4096 21.4 -> 18.1, at 384 rows 10240 x 8192 115 -> 68.
+// A step takes single_us, of two workgroups at once (shapes that fit a compute unit twice) pair_us.  Row chunks read the weights again,
+// from L2 for the most part: 0.27 of the stream each.  The shape of least modelled time is within 1 % of the fastest one on average over
+// those matrices (worst 1.2), and 1.048x as fast as the shape that the same rule chose before the shapes of gemm_block.hip (worst 0.945:
+// 8192 x 28672 at 160 rows 94.7 -> 100.2 us; best 1.37: 57344 x 8192 at 256 rows 257 -> 203).
 struct WideShape {
+  bool block;
   int wm, wn, kg, mt, nt;
-  float tile_us, fixed_us, pair_tile_us, pair_fixed_us;      // pair: 0 where a compute unit holds one workgroup
+  float single_us, pair_us;      // pair: 0 where a compute unit holds one workgroup
 };
 static const WideShape kWideShapes[] = {
-    {1, 4, 2, 6, 2, 0.0146f, 0.256f, 0.f, 0.f},         {1, 4, 2, 8, 2, 0.0146f, 0.256f, 0.f, 0.f},
-    {1, 4, 2, 10, 2, 0.0146f, 0.256f, 0.f, 0.f},        {1, 4, 1, 4, 2, 0.0152f, 0.271f, 0.0354f, 0.34f},
-    {1, 4, 1, 6, 2, 0.0152f, 0.271f, 0.0354f, 0.34f},   {1, 4, 1, 8, 2, 0.0152f, 0.271f, 0.0354f, 0.34f},
-    {1, 4, 1, 10, 2, 0.0152f, 0.271f, 0.0354f, 0.34f},  {1, 4, 1, 12, 2, 0.0152f, 0.271f, 0.0354f, 0.34f},
-    {1, 8, 1, 6, 2, 0.012f, 0.527f, 0.f, 0.f},          {1, 8, 1, 8, 2, 0.012f, 0.527f, 0.f, 0.f},
-    {1, 8, 1, 10, 2, 0.012f, 0.527f, 0.f, 0.f},         {1, 8, 1, 12, 2, 0.012f, 0.527f, 0.f, 0.f},
-    {2, 2, 1, 8, 4, 0.0153f, 0.311f, 0.f, 0.f},         {2, 2, 1, 10, 4, 0.0153f, 0.311f, 0.f, 0.f},
-    {2, 2, 1, 11, 4, 0.0153f, 0.311f, 0.f, 0.f},        {1, 4, 1, 8, 4, 0.f, 0.77f, 0.f, 1.22f}};
+    {false, 1, 4, 2, 6, 2, 0.394f, 0.f},     {false, 1, 4, 2, 8, 2, 0.490f, 0.f},     {false, 1, 4, 2, 10, 2, 0.578f, 0.f},
+    {false, 1, 4, 1, 4, 2, 0.322f, 0.500f},  {false, 1, 4, 1, 6, 2, 0.389f, 0.601f},  {false, 1, 4, 1, 8, 2, 0.436f, 0.737f},
+    {false, 1, 4, 1, 10, 2, 0.498f, 0.848f}, {false, 1, 4, 1, 12, 2, 0.563f, 0.992f}, {false, 1, 8, 1, 6, 2, 0.637f, 0.f},
+    {false, 1, 8, 1, 8, 2, 0.719f, 0.f},     {false, 1, 8, 1, 10, 2, 0.854f, 0.f},    {false, 1, 8, 1, 12, 2, 0.936f, 0.f},
+    {true, 2, 2, 1, 4, 4, 0.428f, 0.671f},   {true, 2, 2, 1, 4, 6, 0.450f, 0.f},      {true, 1, 4, 2, 8, 4, 0.585f, 0.f},
+    {true, 1, 4, 2, 10, 4, 0.677f, 0.f},     {true, 1, 4, 2, 11, 4, 0.718f, 0.f},     {true, 4, 2, 1, 4, 7, 0.948f, 0.f},
+    {true, 4, 2, 1, 4, 8, 0.949f, 0.f}};
 
 static void cut_k(WidePlan& p, int K, int s) {
   p.k_per = ceil_div(ceil_div(K, s), 64) * 64;
   p.splits = ceil_div(K, p.k_per);
 }
 
+constexpr float kPartialUs = 0.39f * 64e-6f;      // of the 16 x 4 bytes that a column has per row tile and split
+
 // The shape of kWideShapes and the K splits with the least time for more than 4 row tiles (N a multiple of 128).
-static WidePlan fastest_shape(int tiles, int N, int K, bool one_split) {
+static WidePlan fastest_shape(int tiles, int N, int K, PlanFor use) {
   constexpr long kCus = 256;
-  float least = 0.f;
   WidePlan best{};
   for (const WideShape& w : kWideShapes) {
     const int cols = 16 * w.nt * w.wn;
-    if (N % cols != 0) continue;
-    WidePlan p{w.wm, w.wn, w.kg, w.mt, w.nt, ceil_div(tiles, w.wm * w.mt), N / cols, 1, 0};
-    const bool halves = w.wm == 1 && w.nt == 4;      // 128 x 64 outputs per wave
-    // where one workgroup has all rows, K groups are better than the same tile without; they are not for weights that several
-    // workgroups read, nor 1 x 8 waves for more than two; 128 rows per wave pad few rows
-    if (p.m_chunks > 1 ? w.kg == 2 || (w.wn == 8 && p.m_chunks > 2) : w.wn == 4 && w.nt == 2 && w.kg == 1 && tiles <= 10) continue;
-    if (halves && tiles <= 12) continue;
-    const bool pairs = w.pair_fixed_us > 0.f && tiles > 12;
+    if (N % cols != 0 || (use == kForStats && cols % 128 != 0)) continue;
+    WidePlan p{w.wm, w.wn, w.kg, w.mt, w.nt, ceil_div(tiles, w.wm * w.mt), N / cols, 1, 0, w.block, 0.f};
+    if (!w.block) {
+      // where one workgroup has all rows, K groups are better than the same tile without; they are not for weights that several
+      // workgroups read, nor 1 x 8 waves for more than two
+      if (p.m_chunks > 1 ? w.kg == 2 || (w.wn == 8 && p.m_chunks > 2) : w.wn == 4 && w.kg == 1 && tiles <= 10) continue;
+    } else if (tiles <= 8 && (cols > 128 || (long)N * K > 1L << 26)) {
+      // one row chunk whose weights are the bound: straight into the registers (57344 x 8192 at 80 rows 142 us, here 155 to 167; 28672 x
+      // 4096 at 112 rows 47 and 46, 4096 x 4096 at 80 rows 14.4 and 13.1)
+      continue;
+    }
+    const bool pairs = w.pair_us > 0.f && (w.block || tiles > 12);
     const float units = 0.25f * (float)(w.mt * w.nt * w.wm * w.wn);
-    const float single_us = w.fixed_us + w.tile_us * units, pair_us = w.pair_fixed_us + w.pair_tile_us * units;
-    const float stream = 2e-6f / 5.54f * (float)N * (float)K * (1.f + 0.195f * (float)(p.m_chunks - 1));
+    const float stream = 2e-6f / 7.83f * (float)N * (float)K * (1.f + 0.267f * (float)(p.m_chunks - 1));
     const long blocks = (long)p.n_blocks * p.m_chunks;
-    // K splits: as many as give every compute unit one workgroup (the largest tile also two), at least 8 steps each
-    for (long target = kCus; target <= (halves && !one_split && K >= 1024 ? 2 * kCus : kCus); target += kCus) {
-      cut_k(p, K, one_split ? 1 : std::max(1, std::min((int)(target / blocks), K / 512)));
+    // K splits: as many as give every compute unit one workgroup (two where it holds two), at least 8 steps each
+    for (long target = kCus; target <= (w.block && pairs && use != kForWholeSums && K >= 1024 ? 2 * kCus : kCus); target += kCus) {
+      cut_k(p, K, use == kForWholeSums ? 1 : std::max(1, std::min((int)(target / blocks), K / 512)));
       const long wgs = blocks * p.splits, per_cu = (wgs + kCus - 1) / kCus, last = wgs % (2 * kCus);
-      const float steps_us = !pairs ? (float)per_cu * single_us
-                                    : (float)(wgs / (2 * kCus)) * pair_us + (last == 0 ? 0.f : last <= kCus ? single_us : pair_us);
+      const float steps_us = !pairs ? (float)per_cu * w.single_us
+                                    : (float)(wgs / (2 * kCus)) * w.pair_us + (last == 0 ? 0.f : last <= kCus ? w.single_us : w.pair_us);
       const float loop = (float)(p.k_per / 64) * steps_us;
-      const float us = std::max(loop, stream) + 0.197f * std::min(loop, stream) + 0.0626f * units * (float)per_cu +
-                       0.46f * 64e-6f * (float)p.splits * (float)tiles * (float)N;
-      if (best.splits == 0 || us < least) {
-        least = us;
+      const float us = std::max(loop, stream) + 0.446f * std::min(loop, stream) + 0.0855f * units * (float)per_cu +
+                       kPartialUs * (float)p.splits * (float)tiles * (float)N;
+      if (best.splits == 0 || us < best.us) {
         best = p;
+        best.us = us;
       }
     }
   }
   return best;
 }
 
-WidePlan wide_plan(int M, int N, int K, bool one_split) {
+WidePlan wide_plan(int M, int N, int K, PlanFor use) {
   const int tiles = ceil_div(M, 16);
   if (tiles <= 4) {
-    WidePlan p;
+    WidePlan p{};
     p.wm = 1;
     p.nt = 2;
     p.mt = std::max(2, (tiles + 1) / 2 * 2);
@@ -389,7 +382,7 @@ WidePlan wide_plan(int M, int N, int K, bool one_split) {
     p.wn = (N % 256 == 0 && N / 256 >= 192) ? 8 : 4;
     p.kg = p.wn == 8 ? 1 : 2;
     p.n_blocks = N / (32 * p.wn);
-    cut_k(p, K, one_split ? 1 : std::max(1, std::min(256 / p.n_blocks, K / 512)));
+    cut_k(p, K, use == kForWholeSums ? 1 : std::max(1, std::min(256 / p.n_blocks, K / 512)));
     // Four K groups of 64 columns where that fills the chip with half of the K splits: half of the partial results
     // (four and fewer are not worth the larger share of the activations: 8192 x 28672 wants the two groups)
     const int blocks = N / 64, s4 = std::min(256 / blocks, K / 1024);
@@ -401,12 +394,29 @@ WidePlan wide_plan(int M, int N, int K, bool one_split) {
     }
     return p;
   }
-  return fastest_shape(tiles, N, K, one_split);
+  return fastest_shape(tiles, N, K, use);
+}
+
+bool wide_gate_up_fused(int M, int N, int K) {
+  if (M <= 64) return true;
+  const WidePlan whole = wide_plan(M, N, K, kForWholeSums), split = wide_plan(M, N, K, kForSums);
+  // fused: no fp32 sums and one launch less (3 us)
+  return split.splits == 1 || whole.us - kPartialUs * (float)ceil_div(M, 16) * (float)N <= split.us + 3.f;
 }
 
 template <int MODE>
-static gs_status launch_mode(const WidePlan& p, const bf16_t* x, const bf16_t* w, float* out, int M, int N, int K,
+static gs_status launch_mode(const WidePlan& plan, const bf16_t* x, const bf16_t* w, float* out, int M, int N, int K,
                              float2* stats, const RowNorm& norm, hipStream_t stream) {
+  WidePlan p = plan;
+  if constexpr (MODE != kGateUpNorm) {
+    if (p.block) {
+      // (direct loads of 16 bytes into LDS want their addresses aligned; loads into registers do not)
+      if (reinterpret_cast<uintptr_t>(x) % 16 == 0 && reinterpret_cast<uintptr_t>(w) % 16 == 0)
+        return launch_block(MODE, p, x, w, out, M, N, K, stats, stream);
+      const int wn = MODE == kStats && p.n_blocks * 256 == N ? 8 : 4;      // (as many column blocks of statistics as planned)
+      p = WidePlan{1, wn, 1, 8, 2, ceil_div(M, 128), N / (32 * wn), p.splits, p.k_per, false, 0.f};
+    }
+  }
   const int grid = p.n_blocks * p.m_chunks * p.splits;
 #define GS_WIDE(WM, WN, KG, MT, NT, DB, DA, POL, WPE)                                                              \
   gemm_bf16_wide_kernel<WM, WN, KG, MT, NT, DB, DA, POL, WPE, MODE>                                                 \
@@ -419,15 +429,7 @@ static gs_status launch_mode(const WidePlan& p, const bf16_t* x, const bf16_t* w
     return GS_OK;
   }
   if constexpr (MODE != kGateUpNorm) {
-  if (p.wm == 1 && p.nt == 4) {
-    GS_WIDE(1, 4, 1, 8, 4, 2, 1, 0, 2);
-  } else if (p.wm == 2) {
-    switch (p.mt) {
-      case 8: GS_WIDE(2, 2, 1, 8, 4, 2, 1, 0, 1); break;
-      case 10: GS_WIDE(2, 2, 1, 10, 4, 2, 1, 0, 1); break;
-      default: GS_WIDE(2, 2, 1, 11, 4, 2, 1, 0, 1);
-    }
-  } else if (p.wn == 8) {
+  if (p.wn == 8) {
     switch (p.mt) {
       case 2: GS_WIDE(1, 8, 1, 2, 2, 4, 2, 2, 2); break;
       case 4: GS_WIDE(1, 8, 1, 4, 2, 4, 2, 2, 2); break;
