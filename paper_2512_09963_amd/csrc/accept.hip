@@ -2,7 +2,7 @@
 // test, and the residual / bonus draw (paper Section II-A-2; the per-server
 // statistic is the sum inside the acceptance-rate update of Section III-C).
 //
-// Three launches on one stream, no host synchronisation:
+// Two or three launches on one stream, no host synchronisation:
 //   row_stats   every target row is read once, with non-temporal 16-byte loads, four per lane
 //               in flight; each workgroup reduces one chunk of one row to an online-softmax
 //               pair (max, sum exp(l - max))
@@ -11,7 +11,8 @@
 //               accept tests, m, statistic: a few hundred bytes out of L2), then sums
 //               max(0, p - q) (or p for the bonus draw) over its 2048-token tiles of the one
 //               row the extra token is drawn from
-//   pick_token  one workgroup per server: scans the tile sums, then the one tile, for the
+//   pick_token  one workgroup per server, the last one of draw_tiles where a server has few of them, else of a
+//               launch of its own: scans the tile sums, then the one tile, for the
 //               token whose running sum first exceeds u * total
 // Bandwidth-bound: row_stats streams 4*V bytes per target row; the draw touches O(N*V) bytes.
 #include "common.h"
@@ -34,12 +35,15 @@ constexpr int kMaxChunks = 64;
 constexpr long kMaxAcceptRows = 1L << 22;
 namespace {
 
-struct Decision {    // per server, written by decide, read by the draw kernels
+struct Decision {    // per server
   int row;           // target row the extra token is drawn from (first row + m)
   int q_row;         // draft row whose q is subtracted, or -1 for the bonus draw from p
   float row_max;     // softmax statistics of that row
   float inv_z;
 };
+// Where the workgroups that draw for a server also pick, its record is not stored; its first word counts those that are done, from zero
+// (set by the kernel before).
+__device__ __forceinline__ unsigned* groups_done(Decision* record) { return reinterpret_cast<unsigned*>(&record->row); }
 
 __device__ __forceinline__ void merge_pair(float& m, float& s, float m2, float s2) {
   float M = fmaxf(m, m2);
@@ -125,9 +129,11 @@ __device__ __forceinline__ float sum_exp_of(const float (&v)[W], float mm) {
 template <typename T, bool VEC>
 __global__ __launch_bounds__(kStatsThreads) void row_stats_kernel(const T* __restrict__ logits, int vocab,
                                                                    int chunk_len, int n_chunks,
-                                                                   float2* __restrict__ partial) {
+                                                                   float2* __restrict__ partial, int n_servers,
+                                                                   Decision* __restrict__ decision) {
   constexpr int W = Pack<T>::W;
   const int row = blockIdx.x / n_chunks, chunk = blockIdx.x - row * n_chunks;
+  if (chunk == 0 && row < n_servers && threadIdx.x == 0) *groups_done(decision + row) = 0;      // (a server has a row or more)
   const int begin = chunk * chunk_len;
   const int end = min(vocab, begin + chunk_len);
   const T* base = logits + (size_t)row * vocab;
@@ -195,8 +201,10 @@ __global__ __launch_bounds__(kStatsThreads) void row_stats_kernel(const T* __res
 // (stats [rows][n_blocks]).  grid rows, 256 lanes: every lane issues its (up to four at a time) loads back to
 // back, then a fixed-order merge over the lanes of a wave and over the waves.
 __global__ __launch_bounds__(256) void merge_stats_kernel(const float2* __restrict__ stats, int n_blocks,
-                                                          float2* __restrict__ row_stat) {
+                                                          float2* __restrict__ row_stat, int n_servers,
+                                                          Decision* __restrict__ decision) {
   const int row = blockIdx.x, tid = threadIdx.x;
+  if (row < n_servers && tid == 0) *groups_done(decision + row) = 0;
   const float2* p = stats + (size_t)row * n_blocks;
   float m = -INFINITY, s = 0.f;
   for (int b0 = tid; b0 < n_blocks; b0 += 4 * 256) {
@@ -378,8 +386,31 @@ __device__ __forceinline__ Decision decide_server(int srv, const int* __restrict
 // consecutive 2048-token tiles; group 0 also stores the server's outputs and its decision.  Every workgroup repeats the
 // decision (5 us of dependent loads), so it takes four tiles, unless even single tiles leave compute units without a
 // workgroup: then the time of one workgroup is the time of the launch.
+// PICK: the last workgroup of a server also picks the token.  Counting a server's workgroups costs each of them a store that
+// the whole chip sees, a wait and an atomic add on one address: less than a launch and its boundary where they are few.  Replayed calls, us,
+// as two launches and in one: 8 servers over 32000 tokens (16 workgroups each) 11.5 and 10.9, 8 over 1024 10.8 and 10.1, 4 over 128256 (63 each)
+// 13.6 and 14.4, 4 over 151936 14.7 and 16.0; 64 over 151936 (19 of four tiles each, several to a compute unit) 75.6 and 76.8.  So: single tiles,
+// and at most 32 of them per server.  Eager calls for 8 servers over 32000 tokens, which their launches bound, 13.4 -> 11.5.
 // ---------------------------------------------------------------------------------------
-template <typename T, bool VEC, int TILES>
+
+// Tile sums change hands between workgroups of one launch, whose compute dies do not share an L2: they are stored and loaded as relaxed
+// atomics at agent scope, which go through to the memory that all dies see, and a wave has waited for its stores before it counts its
+// workgroup as done.  (A release fence instead would write back the L2 of the die.)
+__device__ __forceinline__ void store_for_all(double* p, double v) {
+  __hip_atomic_store(reinterpret_cast<unsigned long long*>(p), (unsigned long long)__double_as_longlong(v), __ATOMIC_RELAXED,
+                     __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ double load_from_all(const double* p) {
+  return __longlong_as_double((long long)__hip_atomic_load(
+      reinterpret_cast<unsigned long long*>(const_cast<double*>(p)), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+}
+
+template <typename T, bool VEC, bool SAME_LAUNCH>
+__device__ __forceinline__ void pick_token(int srv, const Decision& d, int vocab, int n_tiles, const T* __restrict__ logits,
+                                           const T* __restrict__ q_probs, const double* sums, const float* __restrict__ u_resample,
+                                           int* __restrict__ next_token);
+
+template <typename T, bool VEC, int TILES, bool PICK>
 __global__ __launch_bounds__(kTileThreads) void draw_tiles_kernel(const int* __restrict__ cu_rows, int vocab,
                                                                   int n_chunks, int n_tiles, int n_groups,
                                                                   const float2* __restrict__ partial,
@@ -387,11 +418,13 @@ __global__ __launch_bounds__(kTileThreads) void draw_tiles_kernel(const int* __r
                                                                   const T* __restrict__ q_probs,
                                                                   const int* __restrict__ draft_tokens,
                                                                   const float* __restrict__ u_accept,
+                                                                  const float* __restrict__ u_resample,
                                                                   int* __restrict__ accepted_len,
+                                                                  int* __restrict__ next_token,
                                                                   float* __restrict__ accept_stat,
                                                                   float* __restrict__ ratio_out,
                                                                   Decision* __restrict__ decision,
-                                                                  double* __restrict__ tile_sums) {
+                                                                  double* tile_sums) {
   const int srv = blockIdx.x / n_groups, group = blockIdx.x - srv * n_groups;
   __shared__ Decision sh_d;
   __shared__ double part[TILES][kTileThreads / 64];
@@ -400,7 +433,7 @@ __global__ __launch_bounds__(kTileThreads) void draw_tiles_kernel(const int* __r
                                       group == 0, accepted_len, accept_stat, ratio_out);
     if (threadIdx.x == 0) {
       sh_d = dd;
-      if (group == 0) decision[srv] = dd;
+      if (!PICK && group == 0) decision[srv] = dd;
     }
   }
   __syncthreads();
@@ -427,41 +460,47 @@ __global__ __launch_bounds__(kTileThreads) void draw_tiles_kernel(const int* __r
 #pragma unroll
     for (int k = 0; k < TILES; ++k) part[k][threadIdx.x >> 6] = acc[k];
   __syncthreads();
+  double* sums = tile_sums + (size_t)srv * n_tiles;
   const int k = threadIdx.x, tile = group * TILES + k;
   if (k < TILES && tile < n_tiles) {
     double t = part[k][0];
     for (int wv = 1; wv < kTileThreads / 64; ++wv) t += part[k][wv];
-    tile_sums[(size_t)srv * n_tiles + tile] = t;
+    if constexpr (PICK) store_for_all(&sums[tile], t);
+    else sums[tile] = t;
+  }
+  if constexpr (PICK) {
+    __shared__ bool last_group;
+    if (threadIdx.x == 0) {
+      static_assert(TILES == 1, "the wave that stores the sums counts the workgroup");
+      __atomic_signal_fence(__ATOMIC_SEQ_CST);
+      __builtin_amdgcn_s_waitcnt((7 << 4) | (15 << 8));      // vmcnt(0): the sum is where all dies see it
+      __atomic_signal_fence(__ATOMIC_SEQ_CST);
+      last_group = __hip_atomic_fetch_add(groups_done(decision + srv), 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (unsigned)n_groups - 1;
+    }
+    __syncthreads();
+    if (last_group) pick_token<T, VEC, true>(srv, d, vocab, n_tiles, logits, q_probs, sums, u_resample, next_token);
   }
 }
 
-// ---------------------------------------------------------------------------------------
-// pick_token: one workgroup per server.  Two trips to memory and two scans in a row; with the scans as lane moves instead of
-// shuffles of doubles, and the last token with mass looked for only where no sum crosses (it was an LDS atomic of every
-// lane), 7.1 -> 4.6 us.
-// ---------------------------------------------------------------------------------------
-template <typename T, bool VEC>
-__global__ __launch_bounds__(kTileThreads) void pick_token_kernel(const Decision* __restrict__ decision, int vocab,
-                                                                   int n_tiles, const T* __restrict__ logits,
-                                                                   const T* __restrict__ q_probs,
-                                                                   const double* __restrict__ tile_sums,
-                                                                   const float* __restrict__ u_resample,
-                                                                   int* __restrict__ next_token) {
-  const int srv = blockIdx.x;
-  const Decision d = decision[srv];
+// The token of server srv, by one workgroup (with the scans as lane moves instead of shuffles of doubles, and the last token with mass
+// looked for only where no sum crosses: it was an LDS atomic of every lane, 7.1 -> 4.6 us).
+template <typename T, bool VEC, bool SAME_LAUNCH>
+__device__ __forceinline__ void pick_token(int srv, const Decision& d, int vocab, int n_tiles, const T* __restrict__ logits,
+                                           const T* __restrict__ q_probs, const double* sums, const float* __restrict__ u_resample,
+                                           int* __restrict__ next_token) {
   bool residual = d.q_row >= 0;
   const T* lrow = logits + (size_t)d.row * vocab;
   const T* qrow = residual ? q_probs + (size_t)d.q_row * vocab : nullptr;
+  auto sum_of_tile = [&](int t) { return t >= n_tiles ? 0.0 : SAME_LAUNCH ? load_from_all(&sums[t]) : sums[t]; };
   __shared__ double wave_tot[kTileThreads / 64];
   __shared__ double sh_prefix;
   __shared__ int sh_tile, sh_found, sh_last_pos;
   float w[8];
 
-  const double* sums = tile_sums + (size_t)srv * n_tiles;
   const double u = (double)u_resample[srv];
   double total = 0.0;
   // Up to 256 tiles (a vocabulary of 524288 tokens): every wave scans all tile sums by itself, four per lane, so that the
-  // tile is found without a barrier; the sums and the uniform are loaded beside the decision.
+  // tile is found without a barrier.
   constexpr int kPerLane = 4;
   const bool small = n_tiles <= 64 * kPerLane;
   const int lane = threadIdx.x & 63;
@@ -470,7 +509,7 @@ __global__ __launch_bounds__(kTileThreads) void pick_token_kernel(const Decision
     double sum = 0.0;
 #pragma unroll
     for (int k = 0; k < kPerLane; ++k) {
-      own[k] = lane * kPerLane + k < n_tiles ? sums[lane * kPerLane + k] : 0.0;
+      own[k] = sum_of_tile(lane * kPerLane + k);
       sum += own[k];
     }
     incl = wave_scan(sum);
@@ -481,7 +520,7 @@ __global__ __launch_bounds__(kTileThreads) void pick_token_kernel(const Decision
   for (int base = 0; !small && base < n_tiles; base += kTileThreads) {
     const int t = base + threadIdx.x;
     double ex;
-    const double incl = block_scan(t < n_tiles ? sums[t] : 0.0, wave_tot, ex);
+    const double incl = block_scan(sum_of_tile(t), wave_tot, ex);
     if (threadIdx.x == kTileThreads - 1) sh_prefix = incl;
     __syncthreads();
     total += sh_prefix;
@@ -556,7 +595,7 @@ __global__ __launch_bounds__(kTileThreads) void pick_token_kernel(const Decision
     double carry = 0.0;
     for (int base = 0; base < n_tiles; base += kTileThreads) {
       const int t = base + threadIdx.x;
-      const double v = t < n_tiles ? sums[t] : 0.0;
+      const double v = sum_of_tile(t);
       double ex;
       const double incl = block_scan(v, wave_tot, ex);
       if ((carry + incl > target) && !(carry + ex > target)) {
@@ -576,7 +615,7 @@ __global__ __launch_bounds__(kTileThreads) void pick_token_kernel(const Decision
       for (int base = 0; base < n_tiles; base += kTileThreads) {
         const int t = base + threadIdx.x;
         double ex;
-        const double incl = block_scan(t < n_tiles ? sums[t] : 0.0, wave_tot, ex);
+        const double incl = block_scan(sum_of_tile(t), wave_tot, ex);
         if (t == sh_last_tile) sh_prefix = carry + ex;
         if (threadIdx.x == kTileThreads - 1) sh_carry = carry + incl;
         __syncthreads();
@@ -630,6 +669,15 @@ __global__ __launch_bounds__(kTileThreads) void pick_token_kernel(const Decision
     }
     ++tile;
   }
+}
+
+template <typename T, bool VEC>
+__global__ __launch_bounds__(kTileThreads) void pick_token_kernel(const Decision* __restrict__ decision, int vocab, int n_tiles,
+                                                                  const T* __restrict__ logits, const T* __restrict__ q_probs,
+                                                                  const double* __restrict__ tile_sums,
+                                                                  const float* __restrict__ u_resample, int* __restrict__ next_token) {
+  const int srv = blockIdx.x;
+  pick_token<T, VEC, false>(srv, decision[srv], vocab, n_tiles, logits, q_probs, tile_sums + (size_t)srv * n_tiles, u_resample, next_token);
 }
 
 // Chunks per row of the statistics pass: about 4096 workgroups in all, chunks of at least 4096 tokens ...
@@ -688,25 +736,30 @@ gs_status launch_accept_t(const AcceptPlan& p, int n_servers, int n_rows, const 
                           const void* row_stats, int n_stat_blocks) {
   int n_chunks = p.n_chunks;
   if (row_stats) {      // one pair per row, merged from the producer's column-block pairs
-    merge_stats_kernel<<<n_rows, 256, 0, stream>>>(static_cast<const float2*>(row_stats), n_stat_blocks, p.partial);
+    merge_stats_kernel<<<n_rows, 256, 0, stream>>>(static_cast<const float2*>(row_stats), n_stat_blocks, p.partial, n_servers,
+                                                   p.decision);
     GS_LAUNCH_CHECK("merge_stats");
     n_chunks = 1;
   } else {
     const unsigned g1 = (unsigned)p.n_chunks * (unsigned)n_rows;
-    row_stats_kernel<T, VEC><<<g1, kStatsThreads, 0, stream>>>(target_logits, vocab, p.chunk_len, p.n_chunks, p.partial);
+    row_stats_kernel<T, VEC><<<g1, kStatsThreads, 0, stream>>>(target_logits, vocab, p.chunk_len, p.n_chunks, p.partial, n_servers,
+                                                               p.decision);
     GS_LAUNCH_CHECK("row_stats");
   }
   const int tiles = (long)n_servers * p.n_tiles <= 512 ? 1 : 4;      // (two workgroups per compute unit)
   const int n_groups = ceil_div(p.n_tiles, tiles);
   const unsigned g2 = (unsigned)n_groups * (unsigned)n_servers;
-#define GS_DRAW(TILES)                                                                                              \
-  draw_tiles_kernel<T, VEC, TILES><<<g2, kTileThreads, 0, stream>>>(                                                \
+#define GS_DRAW(TILES, PICK)                                                                                       \
+  draw_tiles_kernel<T, VEC, TILES, PICK><<<g2, kTileThreads, 0, stream>>>(                                          \
       cu_rows, vocab, n_chunks, p.n_tiles, n_groups, p.partial, target_logits, q_probs, draft_tokens, u_accept,     \
-      out->accepted_len, out->accept_stat, out->ratio, p.decision, p.tile_sums)
-  if (tiles == 1) GS_DRAW(1);
-  else GS_DRAW(4);
+      u_resample, out->accepted_len, out->next_token, out->accept_stat, out->ratio, p.decision, p.tile_sums)
+  const bool pick = tiles == 1 && p.n_tiles <= 32;
+  if (pick) GS_DRAW(1, true);
+  else if (tiles == 1) GS_DRAW(1, false);
+  else GS_DRAW(4, false);
 #undef GS_DRAW
   GS_LAUNCH_CHECK("draw_tiles");
+  if (pick) return GS_OK;
   pick_token_kernel<T, VEC><<<n_servers, kTileThreads, 0, stream>>>(p.decision, vocab, p.n_tiles, target_logits, q_probs,
                                                                     p.tile_sums, u_resample, out->next_token);
   GS_LAUNCH_CHECK("pick_token");

@@ -244,3 +244,20 @@ def test_workspace_sized_for_the_coarse_chunks():
     with pytest.raises(gsb.GsError) as e:
         _run_gpu(inp, ws_bytes=coarse - 1)
     assert e.value.code == -3
+
+
+@pytest.mark.parametrize("n,vocab", [(1, 1000), (16, 65536), (15, 65537), (16, 65540), (17, 61440)])
+@pytest.mark.parametrize("where", ["spread", "last"])
+def test_pick_by_the_last_workgroup(n, vocab, where):
+    """One workgroup per server, 32 and 33 tiles (the last count that picks inside the draw, the first that does not), 510 tiles in all;
+    repeated calls on one workspace give the same tokens."""
+    inp = synth.accept_inputs(1000 + n, np.ones(n, dtype=np.int32), vocab, 0.5)
+    if where == "last":
+        inp.target_logits[:, :-1] = -np.inf
+    inp.u_accept[:] = np.where(np.arange(n) % 2 == 0, 1.5, inp.u_accept)
+    got = _run_gpu(inp)
+    bands = _check(inp, got)
+    assert bands["n_band_m"] + bands["n_band_tok"] <= (2 if where == "spread" else 0)
+    for _ in range(3):
+        again = _run_gpu(inp)
+        np.testing.assert_array_equal(again["next_token"], got["next_token"])
