@@ -183,10 +183,13 @@ __global__ __launch_bounds__(kRowThreads) void attn_rowwise_kernel(const float* 
 // chip):
 //   S^T (32 keys x 32 queries) = K Q^T : A = K, lane l holds key l%32 (tile l%32/16 of the step),
 //       channels 16 kk + 8 (l/32) .. of k step kk; B = Q^T, lane l holds query row l%32, same channels.
-//       Result register v of lane l is key 8 (v/4) + 4 (l/32) + v%4 of query l%32.
+//       Result register v of lane l is row 8 (v/4) + 4 (l/32) + v%4 of query l%32; row r is key r with bits 2 and 3
+//       exchanged, so that registers 8 kk' .. 8 kk' + 7 are the keys 16 kk' + 8 (l/32) .. + 7.
 //   O^T (hd x 32 queries) += V^T P : B = P straight from the result registers of the first product:
-//       k slot i of k step kk' (16 keys) is register 8 kk' + i, i.e. key 16 kk' + 8 (i/4) + 4 (l/32) + i%4;
-//       A = V^T in the same key order: channel 32 dt + l%32, two 8-byte runs of the transposed page.
+//       k slot i of k step kk' (16 keys) is register 8 kk' + i, i.e. key 16 kk' + 8 (l/32) + i;
+//       A = V^T in the same key order: channel 32 dt + l%32, 16 contiguous bytes of the transposed page (rows in
+//       key order would make it two runs of 8 bytes, with half of the LDS banks idle: a 2047-token prompt 114 us per layer, so
+//       104; 16 servers of the 70B shape 58.2 and 56.6, 8 of the 8B shape 18.0 and 17.5).
 // A query row lives in lanes l and l + 32: one lane swap finishes its max and its sum, and the
 // accumulator rescale is a per-lane multiply.  P enters the second product as a two-term bf16 sum.
 // partial_o [R][H][max_splits][HD] fp32, partial_ml [R][H][max_splits][2]; splits beyond a group's own
@@ -222,7 +225,7 @@ __device__ __forceinline__ void wait_all_vector_loads() {
   __builtin_amdgcn_s_waitcnt((7 << 4) | (15 << 8));
 }
 
-typedef unsigned int uintx2_t __attribute__((ext_vector_type(2)));
+typedef unsigned int uintx4_t __attribute__((ext_vector_type(4)));
 
 typedef __attribute__((__vector_size__(16 * sizeof(float)))) float floatx16_t;
 
@@ -376,10 +379,10 @@ __global__ __launch_bounds__(64 * NW * KW) __attribute__((amdgpu_waves_per_eu(KW
   }
   if (1 < n) lookup(step_begin + KW, pg_next, sl_next);
 
-  // K fragment of k step kk for this lane: tile c32/16, fragment kk/2, lane group 2 (kk%2) + h, key c32%16
-  const int k_lane = ((c32 >> 4) * KS * 64 + h * 16 + (c32 & 15)) * 16;
-  // V: channel c32 of a 32-channel tile is 32 bytes per 16-key tile; this lane's runs start at slot 4h and 8 + 4h
-  const int v_lane = 2 * PART + c32 * 32 + h * 8;
+  // K fragment of k step kk for this lane: tile c32/16, fragment kk/2, lane group 2 (kk%2) + h, key c32%16 with bits 2 and 3 exchanged
+  const int k_lane = ((c32 >> 4) * KS * 64 + h * 16 + ((c32 & 3) | ((c32 & 4) << 1) | ((c32 & 8) >> 1))) * 16;
+  // V: channel c32 of a 32-channel tile is 32 bytes per 16-key tile; this lane's run starts at slot 8h
+  const int v_lane = 2 * PART + c32 * 32 + h * 16;
 
   for (int s = 0; s < (KW > 1 ? (n_wg + KW - 1) / KW : n); ++s) {
     const int step = step_begin + s * KW;
@@ -424,7 +427,7 @@ __global__ __launch_bounds__(64 * NW * KW) __attribute__((amdgpu_waves_per_eu(KW
       float mx = kNegBig;
 #pragma unroll
       for (int e = 0; e < 16; ++e) {
-        const int key = step * 32 + (e >> 2) * 8 + h * 4 + (e & 3);
+        const int key = step * 32 + (e >> 3) * 16 + h * 8 + (e & 7);
         sv[e] = key <= limit ? sacc[e] * scale_log2 : kNegBig;
         mx = fmaxf(mx, sv[e]);
       }
@@ -472,7 +475,7 @@ __global__ __launch_bounds__(64 * NW * KW) __attribute__((amdgpu_waves_per_eu(KW
       // keys past the end of the sequence inside the last page hold stale data: zero their V
 #pragma unroll
       for (int kk = 0; kk < 2; ++kk) {
-        const int kb0 = step * 32 + 16 * kk + 4 * h, kb1 = kb0 + 8;
+        const int kb0 = step * 32 + 16 * kk + 8 * h, kb1 = kb0 + 4;
         keep[kk].x = (kb0 + 0 < n_keys ? 0x0000ffffu : 0u) | (kb0 + 1 < n_keys ? 0xffff0000u : 0u);
         keep[kk].y = (kb0 + 2 < n_keys ? 0x0000ffffu : 0u) | (kb0 + 3 < n_keys ? 0xffff0000u : 0u);
         keep[kk].z = (kb1 + 0 < n_keys ? 0x0000ffffu : 0u) | (kb1 + 1 < n_keys ? 0xffff0000u : 0u);
@@ -489,9 +492,8 @@ __global__ __launch_bounds__(64 * NW * KW) __attribute__((amdgpu_waves_per_eu(KW
           const unsigned char* vp = base + v_lane + kk * PART + (d0 + dd) * 1024;
           // (native vector type: an LDS read without type metadata makes the compiler wait for every
           // outstanding global->LDS load first, which would drain the prefetched stage in mid-step)
-          const uintx2_t a = *reinterpret_cast<const uintx2_t*>(vp);
-          const uintx2_t b = *reinterpret_cast<const uintx2_t*>(vp + 16);
-          vv[dd][kk] = make_uint4(a.x, a.y, b.x, b.y);
+          const uintx4_t a = *reinterpret_cast<const uintx4_t*>(vp);
+          vv[dd][kk] = make_uint4(a.x, a.y, a.z, a.w);
         }
       if (tail) {
 #pragma unroll
