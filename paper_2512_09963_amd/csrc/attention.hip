@@ -203,6 +203,7 @@ __global__ __launch_bounds__(kRowThreads) void attn_rowwise_kernel(const float* 
 // length, the sums of the items that meet on a compute unit are nearly equal, and the compute units that get
 // one item more get the shortest ones on top of the smaller sums.
 constexpr int kComputeUnits = 256;
+constexpr int kGroupWaves = 4;      // of the query groups of a prompt (attention_groups)
 __device__ __forceinline__ void item_of_workgroup(int wg, int n_items, int n_kv, int& entry, int& kh) {
   const int rounds = (n_items + kComputeUnits - 1) / kComputeUnits;
   const int round = wg / kComputeUnits, c = wg - round * kComputeUnits;
@@ -218,6 +219,11 @@ __device__ __forceinline__ void item_of_workgroup(int wg, int n_items, int n_kv,
 // of its keys, and the policy costs them nothing: 112 to 114 us per layer with and without it for a prompt of 2047
 // tokens, 15.4 with and without for 8 of 128; 149 with, 176 without for one of 256 beside 24 blocks on 8192.
 constexpr int kKvLoadPolicy = 2;
+
+// The reference that a row's exponentials are taken against follows its maximum only when that is 2^8 above it: the weights are up to
+// 256 instead of 1, with the same relative precision in all sums (and in their two-term bf16 form), and most steps neither multiply the
+// accumulators nor wait for the factor.  us per layer: 8 servers at 2048 tokens 17.5 -> 16.5, 16 of the 70B shape 56.6 -> 54.2.
+constexpr float kRescaleAt = 8.f;
 
 __device__ __forceinline__ void wait_all_vector_loads() {
   // s_waitcnt vmcnt(0) alone (gfx9 encoding: vmcnt in bits 3:0 and 15:14, expcnt 6:4, lgkmcnt 11:8;
@@ -247,10 +253,10 @@ __device__ __forceinline__ float quotient(float a, float l, float inv) {
   return fmaf(__builtin_amdgcn_fmed3f(fmaf(-q, l, a), -3.0e38f, 3.0e38f), inv, q);
 }
 
-// (164 vector registers: three waves per SIMD, i.e. up to four 3-wave workgroups per CU, which hides a
+// (165 vector registers: three waves per SIMD, i.e. up to four 3-wave workgroups per CU, which hides a
 // workgroup's start-up and barrier stalls behind the others' loads)
 template <int HD, int G, int NW, int KW>
-__global__ __launch_bounds__(64 * NW * KW) __attribute__((amdgpu_waves_per_eu(KW > 1 ? 1 : NW == 1 ? 2 : 3))) void attn_kernel(const bf16_t* __restrict__ q,
+__global__ __launch_bounds__(64 * NW * KW) __attribute__((amdgpu_waves_per_eu(NW * KW == 4 && KW > 1 ? 1 : NW == 1 || KW > 1 ? 2 : 3))) void attn_kernel(const bf16_t* __restrict__ q,
                                                          const bf16_t* __restrict__ k_pages,
                                                          const bf16_t* __restrict__ v_pages,
                                                          const int* __restrict__ block_table, int max_blocks,
@@ -264,7 +270,8 @@ __global__ __launch_bounds__(64 * NW * KW) __attribute__((amdgpu_waves_per_eu(KW
   constexpr int DT = HD / 32;            // 32-channel tiles of the second product
   constexpr int PART = HD * 32;          // bytes of K (or V) of one 16-key tile
   constexpr int STAGE = 4 * PART;        // K tile 0, K tile 1, V tile 0, V tile 1
-  __shared__ __attribute__((aligned(16))) unsigned char rings[KW * 2 * STAGE];
+  constexpr int STATES = KW / 2 * NW * (HD * 128 + 512);      // of half of the key groups, see the merge
+  __shared__ __attribute__((aligned(16))) unsigned char rings[KW * 2 * STAGE > STATES ? KW * 2 * STAGE : STATES];
 
   int entry, kh;
   item_of_workgroup(blockIdx.x, n_work * n_kv, n_kv, entry, kh);
@@ -303,6 +310,7 @@ __global__ __launch_bounds__(64 * NW * KW) __attribute__((amdgpu_waves_per_eu(KW
   const bool my_ok = c32 < rows;
   const int my_j = my_ok ? my_lr / G : 0, my_hg = my_ok ? my_lr - my_j * G : 0;
   const int limit = my_ok ? L + my_j : -1;
+  const int first_limit = L + tile_row0 / G;      // every row of the wave sees the keys up to here
   const int j_max = min(T - 1, (tile_row0 + 31) / G);
   const int my_step_end = has_rows ? ((L + j_max) >> 5) + 1 : 0;
   const float scale_log2 = 1.4426950408889634f / sqrtf((float)HD);
@@ -407,12 +415,12 @@ __global__ __launch_bounds__(64 * NW * KW) __attribute__((amdgpu_waves_per_eu(KW
 
     float p[16];
     float corr;
-    if (step * 32 + 31 <= L) {
+    if (step * 32 + 31 <= first_limit) {
       float mx = sacc[0];
 #pragma unroll
       for (int e = 1; e < 16; ++e) mx = fmaxf(mx, sacc[e]);
-      mx = halves_max(mx);
-      const float m_new = fmaxf(m_run, mx * scale_log2);
+      mx = halves_max(mx) * scale_log2;
+      const float m_new = mx > m_run + kRescaleAt ? mx : m_run;
       corr = __builtin_amdgcn_exp2f(m_run - m_new);
       float sum = 0.f;
 #pragma unroll
@@ -432,7 +440,7 @@ __global__ __launch_bounds__(64 * NW * KW) __attribute__((amdgpu_waves_per_eu(KW
         mx = fmaxf(mx, sv[e]);
       }
       mx = halves_max(mx);
-      const float m_new = fmaxf(m_run, mx);
+      const float m_new = mx > m_run + kRescaleAt ? mx : m_run;
       corr = __builtin_amdgcn_exp2f(m_run - m_new);
       float sum = 0.f;
 #pragma unroll
@@ -460,8 +468,8 @@ __global__ __launch_bounds__(64 * NW * KW) __attribute__((amdgpu_waves_per_eu(KW
       pf[kk] = *reinterpret_cast<const bf16x8_t*>(&hi);
       pf_lo[kk] = *reinterpret_cast<const bf16x8_t*>(&lo);
     }
-    // the rescale factor of a query row sits in the lanes that hold the row: a per-lane multiply,
-    // skipped once the running maxima have settled
+    // the rescale factor of a query row sits in the lanes that hold the row: a per-lane multiply, skipped while no
+    // row's maximum has passed its reference by 2^8
     if (__any(corr != 1.0f)) {
 #pragma unroll
       for (int dt = 0; dt < DT; ++dt)
@@ -516,7 +524,6 @@ __global__ __launch_bounds__(64 * NW * KW) __attribute__((amdgpu_waves_per_eu(KW
 
   // ---- the key groups' states meet in LDS, half of them handing theirs to the other half
   if constexpr (KW > 1) {
-    static_assert(KW * 2 * STAGE >= KW / 2 * NW * (HD * 128 + 512), "the states of half of the key groups fit the rings");
 #pragma unroll
     for (int half = KW / 2; half >= 1; half /= 2) {
       __syncthreads();      // (all fragment reads, or the reads of the round before, are done)
@@ -627,10 +634,10 @@ __global__ __launch_bounds__(kCombineThreads) void attn_combine_kernel(const flo
 // head) a block is one group of as many waves.  Longer blocks (prompts) are cut into groups of 4 waves: the groups are
 // workgroups of one launch, each with the keys up to its own last token, which halves the work of a causal prompt
 // and needs no KV splits to fill the chip.  (One launch per 8 tiles, every one of them over all keys in up to 11
-// splits, took 720 us per layer for a 2047-token prompt at 32 heads and 107 us to merge the partials; now 116 us.
-// 8 prompts of 128 tokens: 30 us and 14 us, now 14 us.)
+// splits, took 720 us per layer for a 2047-token prompt at 32 heads and 107 us to merge the partials; now 70 us: 114 in groups, 104 with
+// contiguous reads of the values, 87 with the mask only in the steps that some row of the wave does not see in full and fewer
+// rescales, 70 with two key groups.  8 prompts of 128 tokens: 30 us and 14 us, now 12.7 us.)
 constexpr int kMaxWaves = 8;
-constexpr int kGroupWaves = 4;
 // Key groups: where a launch leaves compute units idle and a block is one tile of query rows, four waves of a workgroup take the
 // steps of its split in turn (0.85 us a step), each with a ring of its own, and merge their states in LDS.  8B shape, 4 layers, one
 // server at 700 / 2048 keys 395 -> 385 and 400 -> 393 us, two servers 408 -> 397 and 415 -> 408.  A workgroup then fills the LDS of a
@@ -641,6 +648,11 @@ constexpr int kGroupWaves = 4;
 // 245 and 221 / 225 / 228 / 238; 4 heads of 64 over 2 183 / 188 / 196 / 203 and 186 / 185 / 187 / 193; 16 servers of the latter 261 / 268 / 275 /
 // 282 and 262 / 265 / 269 / 275.
 constexpr int kKeyGroups = 4, kKeyGroupItems = 192, kKeyGroupSteps = 3;
+// Prompts: the groups of a causal prompt have 1, 2, 3, ... times the steps of the first, and a compute unit that is dealt the longest and
+// the shortest has one wave per SIMD most of the time, whose loads, products and exponentials follow each other.  Two key groups
+// give every SIMD two waves.  us per layer, one and two: a prompt of 2047 tokens 87.1 and 70.4; 8 of 128 tokens (one to four steps) 12.7 and
+// 12.9: so where the longest split has 8 steps or more.
+constexpr int kPromptKeyGroups = 2, kPromptKeyGroupSteps = 8;
 void attention_groups(int group, long max_block_tokens, int* waves, int* group_tokens) {
   const long tiles = (max_block_tokens * group + 31) / 32;
   *waves = tiles > kMaxWaves ? kGroupWaves : tiles > 0 ? (int)tiles : 1;
@@ -797,7 +809,9 @@ void attention_plan(int n_kv, int group, long max_block_tokens, int n_servers, c
     if (sps > max_steps) sps = max_steps;
   }
   *steps_per_split = (int)sps;
-  *key_groups = waves == 1 && n_groups == n_servers && sps >= kKeyGroupSteps && workgroups(sps) <= kKeyGroupItems ? kKeyGroups : 1;
+  *key_groups = waves == 1 && n_groups == n_servers && sps >= kKeyGroupSteps && workgroups(sps) <= kKeyGroupItems ? kKeyGroups
+                : waves == kGroupWaves && n_groups > n_servers && std::min(sps, max_steps) >= kPromptKeyGroupSteps ? kPromptKeyGroups
+                                                                                                                   : 1;
   // the split count is also the stride (in 512-byte partial rows) between the partial results of
   // neighbouring (row, head) pairs: kept odd, because a power-of-two stride sends all partial stores of a
   // workgroup to the same few memory channels (measured: 110 instead of 81 us per layer at a stride of 32)
@@ -820,7 +834,8 @@ static gs_status launch_mfma_g(const bf16_t* q, const bf16_t* k_pages, const bf1
                                                          n_work, page_size, n_heads, n_kv, steps_per_split, max_splits,   \
                                                          po, pml, attn_out, packed)
   if (key_groups > 1) {
-    GS_RINGS(1, kKeyGroups);      // (one wave of query rows)
+    if (waves == 1) GS_RINGS(1, kKeyGroups);
+    else GS_RINGS(kGroupWaves, kPromptKeyGroups);
     GS_LAUNCH_CHECK("attn");
     return GS_OK;
   }

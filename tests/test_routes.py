@@ -115,3 +115,12 @@ def test_layers_of_five_launches_refuse_more_rows(dtype, most):
     qkv = _rule("_ZN2gs15launch_rows_qkvEiPKvS1_RKNS_7RowNormERKNS_6QkvOutEiiP12ihipStream_t", C.c_int,
                 C.c_int, C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p, C.c_int, C.c_int, C.c_void_p)
     assert qkv(dtype, None, None, C.addressof(out), C.addressof(out), most + 1, 256, None) == -5
+
+
+@pytest.mark.parametrize("gamma,ctx,groups", [
+    ([2046], [0], 2), ([127] * 8, [0] * 8, 1), ([300] * 4, [500] * 4, 2),      # the longest split of a prompt has 64, 4 and 26 steps
+    ([223] * 5, [0] * 5, 1), ([255] * 5, [0] * 5, 2),                          # 7 and 8
+    ([120], [700], 1),                                                         # groups that leave compute units idle are split instead
+])
+def test_attention_key_groups_of_prompts(gamma, ctx, groups):
+    assert attention_key_groups(8, 4, gamma, ctx)[0] == groups
