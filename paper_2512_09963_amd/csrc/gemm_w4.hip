@@ -95,7 +95,7 @@ enum { kPlain = 0, kGateUp = 1 };
 // Pipeline, as in gemm_wide.hip: a step is four blocks, one per k group of 16, each of which reads the activation
 // fragments of two blocks ahead from LDS (three buffers), dequantises the weights of the next block, moves its share of
 // the next activation tile and weights, and issues its MT * NT MFMAs.
-// grid (column blocks, rounded up to a multiple of 8, times row chunks; K splits).
+// 1-D grid: K splits x column blocks x row chunks, an even contiguous range of them for every XCD (as in gemm_wide.hip).
 template <int WN, int KG, int MT, int NT, int DB, int DA, int WPE, int MODE>
 __global__ __launch_bounds__(64 * WN * KG) __attribute__((amdgpu_waves_per_eu(WPE, WPE))) void gemm_w4_kernel(
     const bf16_t* __restrict__ X, const uint4* __restrict__ codes, const uint32_t* __restrict__ meta,
@@ -114,12 +114,11 @@ __global__ __launch_bounds__(64 * WN * KG) __attribute__((amdgpu_waves_per_eu(WP
   const int tid = threadIdx.x - kg * THREADS;
   unsigned char* xs = xs_all + kg * 3 * TILE;
   const int h = lane >> 5, c32 = lane & 31;
-  const int xcd = blockIdx.x & 7, t = blockIdx.x >> 3;
-  const int m_chunk = t % m_chunks;
-  const int n_block = (t / m_chunks) * 8 + xcd;
-  if (n_block * (32 * NT * WN) >= N) return;      // padding of the grid to a multiple of 8 column blocks
+  const int per_xcd = gridDim.x >> 3, more = gridDim.x & 7, xcd = blockIdx.x & 7;
+  const int item = xcd * per_xcd + min(xcd, more) + (blockIdx.x >> 3);
+  const int m_chunk = item % m_chunks, column = item / m_chunks, n_blocks = N / (32 * NT * WN);
+  const int split = column / n_blocks, n_block = column - split * n_blocks;
   const int n_tile0 = (n_block * WN + wn) * (MODE == kGateUp ? NT / 2 : NT);
-  const int split = blockIdx.y;
   const int m0 = m_chunk * ROWS;
   const int split_begin = split * k_per_split, split_end = min(K, split_begin + k_per_split);
   // the K groups take whole scale groups (two steps) and run the same number of steps (barriers); a step past a group's
@@ -499,7 +498,7 @@ gs_status launch_gemm_w4_gate_up(const void* X, const void* Wpacked, void* act, 
   const uint4* codes = static_cast<const uint4*>(Wpacked);
   const uint32_t* meta = reinterpret_cast<const uint32_t*>(static_cast<const char*>(Wpacked) + w4_code_bytes(N, K));
   float* P = static_cast<float*>(act);
-  const dim3 grid(ceil_div(w4_gate_up_blocks(M, F), 8) * 8, 1, 1);
+  const int grid = w4_gate_up_blocks(M, F);
   if (M <= 32) GS_W4(2, 4, 1, 2, 2, kGateUp);
   else if (M <= 64) GS_W4(2, 4, 2, 2, 2, kGateUp);
   else GS_W4(4, 2, 3, 2, 2, kGateUp);
@@ -515,7 +514,7 @@ gs_status launch_gemm_w4(const void* X, const void* Wpacked, float* P, int M, in
   const uint4* codes = static_cast<const uint4*>(Wpacked);
   const uint32_t* meta = reinterpret_cast<const uint32_t*>(static_cast<const char*>(Wpacked) + w4_code_bytes(N, K));
   const int k_per = p.k_per, chunks = p.m_chunks;
-  const dim3 grid(ceil_div(p.n_blocks, 8) * 8 * p.m_chunks, p.splits, 1);
+  const int grid = p.n_blocks * p.m_chunks * p.splits;
   switch (p.mt) {
     case 1:
       if (p.waves == 8) GS_W4(8, 1, 1, 1, 4, kPlain);
