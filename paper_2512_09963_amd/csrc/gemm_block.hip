@@ -61,8 +61,7 @@ __global__ __launch_bounds__(64 * WM * WN * KG) __attribute__((amdgpu_waves_per_
   const int kg = KG == 1 ? 0 : wave / (WM * WN), wv = wave - kg * (WM * WN);
   const int wm = wv / WN, wn = wv % WN;
   const int g = lane >> 4, c = lane & 15;
-  const int per_xcd = gridDim.x >> 3, more = gridDim.x & 7, xcd = blockIdx.x & 7;
-  const int item = xcd * per_xcd + min(xcd, more) + (blockIdx.x >> 3);
+  const int item = xcd_item();
   const int m_chunk = item % m_chunks, column = item / m_chunks;
   const int split = column / n_blocks, n_block = column - split * n_blocks;
   const int m0 = m_chunk * ROWS;

@@ -46,6 +46,13 @@ __device__ __forceinline__ float wave_sum(float v) {
   return v + __shfl_xor(v, 32);
 }
 
+// The item of a workgroup of a 1-D grid.  Workgroups are handed to the 8 XCDs round robin by their index; here an XCD takes a contiguous
+// range of the items, at most one more than another.
+__device__ __forceinline__ int xcd_item() {
+  const int per_xcd = gridDim.x >> 3, more = gridDim.x & 7, xcd = blockIdx.x & 7;
+  return xcd * per_xcd + min(xcd, more) + (int)(blockIdx.x >> 3);
+}
+
 // Blocks of a few rows run a layer in five launches: the norms and the rotation are part of the projections.  The projection
 // that completes the residual stream x stores h = x * norm weight, not yet divided by the row's root mean square (one rounding
 // to the storage type, as with the division), and the sums of x^2 over its 16-column tiles; the projection that reads h forms

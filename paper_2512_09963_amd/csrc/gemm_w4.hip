@@ -18,6 +18,7 @@
 // Rows beyond 128 are served in chunks of 128 by separate workgroups (XCD-aware order, see the bf16 kernel).
 #include "common.h"
 #include "device_types.h"
+#include "gemm_common.h"
 #include <algorithm>
 #include <type_traits>
 
@@ -85,8 +86,6 @@ __device__ __forceinline__ bf16x8_t dequant8_large(uint32_t word, const DequantS
 
 typedef unsigned int uintx4_t __attribute__((ext_vector_type(4)));
 
-enum { kPlain = 0, kGateUp = 1 };
-
 // WN waves side by side, each with NT 32-column tiles and all MT 32-row tiles; KG groups of them take K slices of the
 // workgroup's range, and their sums meet in LDS.  DB, DA: steps (64 of k) of weights and of activations in
 // registers.
@@ -114,8 +113,7 @@ __global__ __launch_bounds__(64 * WN * KG) __attribute__((amdgpu_waves_per_eu(WP
   const int tid = threadIdx.x - kg * THREADS;
   unsigned char* xs = xs_all + kg * 3 * TILE;
   const int h = lane >> 5, c32 = lane & 31;
-  const int per_xcd = gridDim.x >> 3, more = gridDim.x & 7, xcd = blockIdx.x & 7;
-  const int item = xcd * per_xcd + min(xcd, more) + (blockIdx.x >> 3);
+  const int item = xcd_item();
   const int m_chunk = item % m_chunks, column = item / m_chunks, n_blocks = N / (32 * NT * WN);
   const int split = column / n_blocks, n_block = column - split * n_blocks;
   const int n_tile0 = (n_block * WN + wn) * (MODE == kGateUp ? NT / 2 : NT);

@@ -70,8 +70,7 @@ __global__ __launch_bounds__(64 * WM * WN * KG) __attribute__((amdgpu_waves_per_
   const int tid = threadIdx.x - kg * THREADS;
   unsigned char* xs = xs_all + kg * 3 * TILE;
   const int g = lane >> 4, c = lane & 15;
-  const int per_xcd = gridDim.x >> 3, more = gridDim.x & 7, xcd = blockIdx.x & 7;
-  const int item = xcd * per_xcd + min(xcd, more) + (blockIdx.x >> 3);
+  const int item = xcd_item();
   const int m_chunk = item % m_chunks, column = item / m_chunks, n_blocks = N / (16 * NT * WN);
   const int split = column / n_blocks, n_block = column - split * n_blocks;
   const int wm = wave / WN, wn = wave % WN;
