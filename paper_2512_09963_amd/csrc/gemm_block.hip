@@ -12,7 +12,7 @@
 //     buffer of this step (refilled at once for the step after the next) and publishes the next step.  Weights have three buffers
 //     and are loaded from the start of a step, for the step after the next: their way from memory is the longer one, and the
 //     loads of a step are spread over it (all of them behind the barrier: 400 us against 318 for 2048 x 28672 x 4096 of zeros)
-//   * activation rows are 128 bytes in LDS, their 16-byte pieces XOR-swizzled by the row pair; since a direct load places the
+//   * activation rows are 128 bytes in LDS, their 16-byte pieces XOR-swizzled (row_swizzle); since a direct load places the
 //     lanes' pieces one after the other, the swizzle is in the lanes' addresses
 // Workgroups are dealt to the XCDs in contiguous ranges of (split, column block, row chunk), row chunks next to each other: those of
 // an XCD share weights and activations in its L2, and no XCD gets more than one workgroup more than another.
@@ -79,7 +79,7 @@ __global__ __launch_bounds__(64 * WM * WN * KG) __attribute__((amdgpu_waves_per_
   for (int i = 0; i < LA; ++i) {
     a_piece[i] = min(wave + i * WAVES, A_BYTES / 1024 - 1);
     const int r = a_piece[i] * 8 + (lane >> 3);
-    a_off[i] = (unsigned)min(r, M - 1 - m0) * (unsigned)K * 2u + (((lane & 7) ^ ((r >> 1) & 7)) << 4);
+    a_off[i] = (unsigned)min(r, M - 1 - m0) * (unsigned)K * 2u + (((lane & 7) ^ row_swizzle(r)) << 4);
   }
 #pragma unroll
   for (int i = 0; i < LB; ++i) {
@@ -106,8 +106,8 @@ __global__ __launch_bounds__(64 * WM * WN * KG) __attribute__((amdgpu_waves_per_
 
   // fragments: lane (g, c) holds row (column) c, k = 16 g + 8 h .. of the step for half h
   constexpr bool PAIRED = GATE_UP && NT % 2 == 0;      // a wave has NT / 2 gate tiles and the same up tiles; else gate or up tiles
-  const int a0 = (wm * MT * 16 + c) * 128 + (((2 * g + kg) ^ ((c >> 1) & 7)) << 4);
-  const int a1 = (wm * MT * 16 + c) * 128 + (((2 * g + 1) ^ ((c >> 1) & 7)) << 4);
+  const int a0 = (wm * MT * 16 + c) * 128 + (((2 * g + kg) ^ row_swizzle(c)) << 4);
+  const int a1 = (wm * MT * 16 + c) * 128 + (((2 * g + 1) ^ row_swizzle(c)) << 4);
   const int b0 = (PAIRED ? wn * (NT / 2) : wn * NT) * 2048 + kg * 1024 + lane16;
   auto frag = [&](bool b, int buf, int slot, int tile, int h) {
     if (!b) return *reinterpret_cast<const bf16x8_t*>(&lds[buf * A_BYTES + (h ? a1 : a0) + tile * 2048]);

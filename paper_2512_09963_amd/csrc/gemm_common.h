@@ -133,6 +133,12 @@ __device__ __forceinline__ void store_qkv_pair(const QkvOut& o, int row, int hea
   }
 }
 
+// Activation rows of the bf16 kernels are 128 bytes in LDS; their 16-byte pieces are XOR-swizzled by this value of the row.  A 16-byte
+// read serves its lanes in sixteens, the first being lanes 0-3, 12-15 and 20-27: rows 0-3 and 12-15 of one piece and rows 4-11 of
+// the piece two further on.  With the row pair itself these met on the same banks (40 % of the LDS cycles of 1 x 4 x 2 waves of
+// 11 x 4 tiles were conflicts); exchanging the upper and the lower half of the pieces in every second two pairs keeps them apart.
+__device__ __forceinline__ int row_swizzle(int row) { return ((row >> 1) & 7) ^ (row & 4); }
+
 // What a projection kernel stores.  kPlain: the fp32 sums [split][M][N]; kGateUp (one split): act[M][F] = silu(gate) * up as bf16, of a
 // [2F][K] matrix (N = 2F); kGateUpNorm: the same of rows that still need their factor (RowNorm), act in fragment order; kStats (one
 // split): the sums and (max, sum exp) of every row over the workgroup's columns.

@@ -14,7 +14,7 @@
 //     every block keeps the compiler from undoing that order
 //   * the activation tile lives in three LDS buffers, so that the fragments of the next step's first two blocks can be
 //     read before the barrier that ends the step (the buffer they come from was published one barrier earlier)
-//   * activation rows are 128 bytes in LDS, their 16-byte pieces XOR-swizzled by the row pair: conflict-free reads
+//   * activation rows are 128 bytes in LDS, their 16-byte pieces XOR-swizzled (row_swizzle): conflict-free reads
 //   * loads are buffer loads: the descriptor moves with k on the scalar unit and the lane offsets are constant, so a
 //     load costs no vector instruction for its address; rows past the end read as zero by the descriptor's range
 // The shapes: WM x WN waves, each with MT x NT tiles of 16 x 16, KG groups of them that share K (which one a launch takes: kWideShapes):
@@ -95,7 +95,7 @@ __global__ __launch_bounds__(64 * WM * WN * KG) __attribute__((amdgpu_waves_per_
     // (a last pass with fewer pieces than lanes moves the last piece several times)
     const int ch = min(tid + p * THREADS, ROWS * 8 - 1), row = ch >> 3, piece = ch & 7;
     xoff[p] = (unsigned)row * (unsigned)K * 2u + piece * 16u;
-    loff[p] = row * 128 + ((piece ^ ((row >> 1) & 7)) << 4);
+    loff[p] = row * 128 + ((piece ^ row_swizzle(row)) << 4);
   }
   // a step past the K group's own end has an empty descriptor: it reads zeros
   auto x_rsrc = [&](int step) {
@@ -125,8 +125,8 @@ __global__ __launch_bounds__(64 * WM * WN * KG) __attribute__((amdgpu_waves_per_
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt) acc[mt][nt] = floatx4_t{0.f, 0.f, 0.f, 0.f};
   // fragment of row tile mt: lane (g, c) holds row c, pieces 2 g (first MFMA) and 2 g + 1 (second)
-  const int a0 = (wm * MT * 16 + c) * 128 + (((2 * g) ^ ((c >> 1) & 7)) << 4);
-  const int a1 = (wm * MT * 16 + c) * 128 + (((2 * g + 1) ^ ((c >> 1) & 7)) << 4);
+  const int a0 = (wm * MT * 16 + c) * 128 + (((2 * g) ^ row_swizzle(c)) << 4);
+  const int a1 = (wm * MT * 16 + c) * 128 + (((2 * g + 1) ^ row_swizzle(c)) << 4);
   {
     uintx4_t r0[PASSES], r1[PASSES];
     auto rx0 = x_rsrc(0), rx1 = x_rsrc(1);
