@@ -489,6 +489,21 @@ bool gate_up_fused(int dtype, int M, int F, int K) {
   return wide_gate_up_fused(M, 2 * F, K);      // (2 F is a multiple of 128)
 }
 
+// Whether the QKV projection of this shape leaves Q, K and V in their places (launch_gemm_qkv): bf16 of many rows, operands that direct
+// loads of 16 bytes into LDS can take, places that its stores of 4 bytes (Q, K) and 8 bytes (V) can.
+bool qkv_fused(int dtype, const void* X, const void* W, const QkvOut& out, int M, int K) {
+  auto aligned = [](const void* p, int bytes) { return reinterpret_cast<uintptr_t>(p) % bytes == 0; };
+  return dtype == GS_BF16 && K % kBK == 0 && aligned(X, 16) && aligned(W, 16) && aligned(out.q, 4) && aligned(out.k_pages, 4) &&
+         aligned(out.v_pages, 8) && block_qkv_fused(M, (out.n_heads + 2 * out.n_kv) * out.hd, K);
+}
+
+// Q, K and V of M rows, rotated and stored; only for shapes qkv_fused accepts.
+gs_status launch_gemm_qkv(const void* X, const void* W, const QkvOut& out, int M, int K, hipStream_t stream) {
+  const int N = (out.n_heads + 2 * out.n_kv) * out.hd;
+  return launch_block_qkv(wide_plan(M, N, K, kForHeads), static_cast<const bf16_t*>(X),
+                          static_cast<const bf16_t*>(W), out, M, N, K, stream);
+}
+
 // act [M][F] (bf16) = silu(X Wg^T) * (X Wu^T), W = [Wg; Wu] packed; only for shapes gate_up_fused accepts.
 gs_status launch_gemm_gate_up(int dtype, const void* X, const void* W, void* act, int M, int F, int K,
                               hipStream_t stream) {

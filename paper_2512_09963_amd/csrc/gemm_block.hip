@@ -18,6 +18,8 @@
 // an XCD share weights and activations in its L2, and no XCD gets more than one workgroup more than another.
 // Shapes (kBlockShapes in gemm_wide.hip): WM x WN waves of MT x NT tiles of 16 x 16; KG = 2: two K groups, each takes one half of
 // every 64-wide step, so that tiles of 176 x 64 leave room for two waves per SIMD.
+// kQkvHeads: the QKV projection stores Q and the K and V pages itself.  The fp32 sums (25 MB at 1024 rows of 6144 columns) were written and read
+// again by a launch of 15 us a layer, 27 at 2047 rows; whole passes 4212 -> 4135 (8 prompts of 128 tokens) and 4994 -> 4934 us (2047 tokens).
 // Isolated launches, us, gemm_wide.hip before and this one (one machine):
 //   1024 rows  gate/up 28672 x 4096 217 -> 190, 4096 x 14336 104 -> 91, 6144 x 4096 50 -> 45, LM head 128256 x 4096 932 -> 831
 //   2047 rows  385 -> 358, 189 -> 172, 97 -> 79, 1810 -> 1614
@@ -42,11 +44,11 @@ namespace {
 
 constexpr int kBlockAhead = 2;      // streamed tiles read ahead (3: within 2 %)
 
-// MODE as in gemm_wide.hip.  1-D grid: splits x column blocks x row chunks.
+// MODE as in gemm_wide.hip; qkv: kQkvHeads.  1-D grid: splits x column blocks x row chunks.
 template <int WM, int WN, int KG, int MT, int NT, bool STATIONARY_B, int MODE>
 __global__ __launch_bounds__(64 * WM * WN * KG) __attribute__((amdgpu_waves_per_eu(WM * WN * KG == 4 && NT > 4 ? 1 : 2))) void gemm_bf16_block_kernel(
     const bf16_t* __restrict__ X, const bf16_t* __restrict__ Wp, float* __restrict__ P, int M, int N, int K, int k_per_split,
-    int m_chunks, int n_blocks, float2* __restrict__ stats) {
+    int m_chunks, int n_blocks, float2* __restrict__ stats, QkvOut qkv) {
   constexpr bool GATE_UP = MODE == kGateUp;
   constexpr int WAVES = WM * WN * KG, ROWS = WM * MT * 16, COL_TILES = WN * NT;
   constexpr int NO = STATIONARY_B ? MT : NT, NI = STATIONARY_B ? NT : MT, NH = 2 / KG;
@@ -73,6 +75,9 @@ __global__ __launch_bounds__(64 * WM * WN * KG) __attribute__((amdgpu_waves_per_
   const char* wbase = reinterpret_cast<const char*>(Wp) + (size_t)(k_begin / 64) * w_stride;
   // pieces of 1 KB (eight activation rows; half a column tile) that this wave moves, the last one more than once where they do
   // not divide among the waves; rows past the end re-read the last one
+  constexpr bool HEADS = MODE == kQkvHeads;
+  static_assert(!HEADS || NT % 2 == 0, "both halves of the rotation pairs");
+  const int half_tiles = HEADS ? qkv.hd >> 5 : 1, pair0 = n_block * (COL_TILES / 2);      // column tiles of half a head; first pair of tiles
   int a_piece[LA], b_piece[LB];
   unsigned a_off[LA], b_off[LB];
 #pragma unroll
@@ -86,7 +91,12 @@ __global__ __launch_bounds__(64 * WM * WN * KG) __attribute__((amdgpu_waves_per_
     b_piece[i] = min(wave + i * WAVES, B_BYTES / 1024 - 1);
     // gate/up: the first half of the workgroup's column tiles are gate features, the second the same ones of the up half
     const int t = b_piece[i] >> 1;
-    const int tile = GATE_UP ? n_block * (COL_TILES / 2) + (t < COL_TILES / 2 ? t : t - COL_TILES / 2 + N / 32) : n_block * COL_TILES + t;
+    int tile = GATE_UP ? n_block * (COL_TILES / 2) + (t < COL_TILES / 2 ? t : t - COL_TILES / 2 + N / 32) : n_block * COL_TILES + t;
+    if constexpr (HEADS) {
+      // the first half of a wave's tiles are first halves of rotation pairs, the others the second halves of the same ones
+      const int u = t % NT, pair = pair0 + t / NT * (NT / 2) + u % (NT / 2);
+      tile = pair / half_tiles * 2 * half_tiles + pair % half_tiles + (u < NT / 2 ? 0 : half_tiles);
+    }
     b_off[i] = (unsigned)tile * 2048u + (b_piece[i] & 1) * 1024u;
   }
   const unsigned lane16 = lane * 16;
@@ -253,6 +263,84 @@ __global__ __launch_bounds__(64 * WM * WN * KG) __attribute__((amdgpu_waves_per_
     }
     return;
   }
+  if constexpr (HEADS) {
+    // pair of column tiles after pair, row tile after row tile: the factors and places of the next one are loaded while this one is stored
+    // (loaded where they are used, and stores of 2 bytes: a 2047-token prompt 33 us a layer slower)
+    const int half = qkv.hd >> 1;
+    const bool odd = c & 1;
+    auto pair_of = [&](int p) { return pair0 + wn * (NT / 2) + p; };
+    float2 cs[2][4];
+    int2 at[2][4];
+    auto fetch = [&](int b, int p, int mt) {
+      const int i = pair_of(p) % half_tiles * 16 + c;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int row = min(row0 + mt * 16 + r, M - 1);
+        cs[b][r] = qkv.rope[(size_t)row * half + i];
+        at[b][r] = *reinterpret_cast<const int2*>(qkv.row_slot + row);
+      }
+    };
+    static_assert(!HEADS || MT / KG % 2 == 0, "the two sets of a pair's row tiles end on the second one");
+    fetch(0, 0, kg);
+#pragma unroll
+    for (int p = 0; p < NT / 2; ++p) {
+      const int pair = pair_of(p), head = pair / half_tiles, i0 = pair % half_tiles * 16 + c;
+#pragma unroll
+      for (int mt = 0; mt < MT; ++mt) {
+        if (!owned(mt)) continue;
+        const int b = mt / KG & 1;
+        if (mt + KG < MT) fetch(b ^ 1, p, mt + KG);
+        else if (p + 1 < NT / 2) fetch(0, p + 1, kg);
+        const floatx4_t u = sum(mt, p), v = sum(mt, NT / 2 + p);
+        const int row = row0 + mt * 16;
+        if (head < qkv.n_heads + qkv.n_kv) {
+          // neighbouring columns share their stores: the even lane takes the first row of two, the odd one the second, 4 bytes each
+#pragma unroll
+          for (int j = 0; j < 2; ++j) {
+            float lo[2], hi[2];
+#pragma unroll
+            for (int k = 0; k < 2; ++k) {
+              const float2 f = cs[b][2 * j + k];
+              lo[k] = fmaf(u[2 * j + k], f.x, -(v[2 * j + k] * f.y));      // (as in store_qkv_pair)
+              hi[k] = fmaf(v[2 * j + k], f.x, u[2 * j + k] * f.y);
+            }
+            const float lo_n = dpp_move<0xB1>(odd ? lo[0] : lo[1]), hi_n = dpp_move<0xB1>(odd ? hi[0] : hi[1]);
+            const int2 ps = odd ? at[b][2 * j + 1] : at[b][2 * j];
+            const int r = row + 2 * j + (int)odd;
+            bf16_t* dst = head < qkv.n_heads
+                              ? static_cast<bf16_t*>(qkv.q) + ((size_t)r * qkv.n_heads + head) * qkv.hd
+                              : static_cast<bf16_t*>(qkv.k_pages) + (((size_t)ps.x * qkv.n_kv + (head - qkv.n_heads)) * qkv.page_size + ps.y) * qkv.hd;
+            dst += i0 - (int)odd;
+            if (r < M) {
+              *reinterpret_cast<uint32_t*>(dst) = odd ? pack_bf16x2(lo_n, lo[1]) : pack_bf16x2(lo[0], lo_n);
+              *reinterpret_cast<uint32_t*>(dst + half) = odd ? pack_bf16x2(hi_n, hi[1]) : pack_bf16x2(hi[0], hi_n);
+            }
+          }
+        } else {
+          // four rows of a lane are four slots of a channel, next to each other in most cases: one store of 8 bytes
+          bool run = row + 3 < M && at[b][0].y % 4 == 0 && qkv.page_size % 4 == 0;
+#pragma unroll
+          for (int r = 1; r < 4; ++r) run = run && at[b][r].x == at[b][0].x && at[b][r].y == at[b][0].y + r;
+          auto place = [&](int r, int channel) {
+            return static_cast<bf16_t*>(qkv.v_pages) +
+                   (((size_t)at[b][r].x * qkv.n_kv + (head - qkv.n_heads - qkv.n_kv)) * qkv.hd + channel) * qkv.page_size + at[b][r].y;
+          };
+          if (run) {
+            *reinterpret_cast<uint2*>(place(0, i0)) = make_uint2(pack_bf16x2(u[0], u[1]), pack_bf16x2(u[2], u[3]));
+            *reinterpret_cast<uint2*>(place(0, i0 + half)) = make_uint2(pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3]));
+          } else {
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+              if (row + r < M) {
+                *place(r, i0) = float_to_bf16(u[r]);
+                *place(r, i0 + half) = float_to_bf16(v[r]);
+              }
+          }
+        }
+      }
+    }
+    return;
+  }
   float* out = P + (size_t)split * M * N + (size_t)(n_block * COL_TILES + wn * NT) * 16 + c;
 #pragma unroll
   for (int mt = 0; mt < MT; ++mt)
@@ -299,14 +387,18 @@ __global__ __launch_bounds__(64 * WM * WN * KG) __attribute__((amdgpu_waves_per_
 
 template <int MODE>
 static gs_status launch_mode(const WidePlan& p, const bf16_t* x, const bf16_t* w, float* out, int M, int N, int K, float2* stats,
-                             hipStream_t stream) {
+                             hipStream_t stream, const QkvOut& qkv = QkvOut{}) {
   const int grid = p.n_blocks * p.m_chunks * p.splits;
 #define GS_BLOCK(WM, WN, KG, MT, NT, STATIONARY_B)                                                                     \
   gemm_bf16_block_kernel<WM, WN, KG, MT, NT, STATIONARY_B, MODE><<<grid, 64 * WM * WN * KG, 0, stream>>>(               \
-      x, w, out, M, N, K, p.k_per, p.m_chunks, p.n_blocks, stats)
+      x, w, out, M, N, K, p.k_per, p.m_chunks, p.n_blocks, stats, qkv)
   if (p.wm == 4 && p.nt == 8) GS_BLOCK(4, 2, 1, 4, 8, false);
   else if (p.wm == 2 && p.nt == 4) GS_BLOCK(2, 2, 1, 4, 4, true);
   else if (p.wm == 1 && p.mt == 8) GS_BLOCK(1, 4, 2, 8, 4, true);
+  else if constexpr (MODE == kQkvHeads) {
+    if (p.wm != 2) return fail(GS_EUNSUPPORTED, "no heads of %d x %d tiles", p.mt, p.nt);
+    GS_BLOCK(2, 2, 1, 4, 6, false);
+  }
   else if (p.wm == 1 && p.mt == 10) GS_BLOCK(1, 4, 2, 10, 4, true);
   else if (p.wm == 1 && p.mt == 11) GS_BLOCK(1, 4, 2, 11, 4, true);
   else if (MODE == kStats) return fail(GS_EUNSUPPORTED, "column blocks of %d do not leave statistics", 16 * p.wn * p.nt);
@@ -326,6 +418,10 @@ gs_status launch_block(int mode, const WidePlan& p, const bf16_t* x, const bf16_
     case kGateUp: return launch_mode<kGateUp>(p, x, w, out, M, N, K, stats, stream);
     default: return launch_mode<kStats>(p, x, w, out, M, N, K, stats, stream);
   }
+}
+
+gs_status launch_block_qkv(const WidePlan& p, const bf16_t* x, const bf16_t* w, const QkvOut& out, int M, int N, int K, hipStream_t stream) {
+  return launch_mode<kQkvHeads>(p, x, w, nullptr, M, N, K, nullptr, stream, out);
 }
 
 }  // namespace gs

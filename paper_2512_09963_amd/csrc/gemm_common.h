@@ -141,8 +141,9 @@ __device__ __forceinline__ int row_swizzle(int row) { return ((row >> 1) & 7) ^ 
 
 // What a projection kernel stores.  kPlain: the fp32 sums [split][M][N]; kGateUp (one split): act[M][F] = silu(gate) * up as bf16, of a
 // [2F][K] matrix (N = 2F); kGateUpNorm: the same of rows that still need their factor (RowNorm), act in fragment order; kStats (one
-// split): the sums and (max, sum exp) of every row over the workgroup's columns.
-enum { kPlain = 0, kGateUp = 1, kStats = 2, kGateUpNorm = 3 };
+// split): the sums and (max, sum exp) of every row over the workgroup's columns; kQkvHeads (one split): Q, K and V of the fused QKV
+// projection, rotated and in their places (store_qkv_pair).
+enum { kPlain = 0, kGateUp = 1, kStats = 2, kGateUpNorm = 3, kQkvHeads = 4 };
 
 // Launch of gemm_bf16_wide_kernel or (block) gemm_bf16_block_kernel: wm x wn waves of mt x nt tiles, kg groups of them, n_blocks
 // column blocks.
@@ -152,11 +153,14 @@ struct WidePlan {
   float us;      // modelled time, for more than 64 rows
 };
 // kForWholeSums: the projection must not be split over workgroups (its epilogue needs the whole sums); kForStats: it leaves statistics
-// where it needs no split.
-enum PlanFor { kForSums, kForWholeSums, kForStats };
+// where it needs no split.  kForHeads: whole sums, both halves of a rotation pair in one wave (gemm_block.hip).
+enum PlanFor { kForSums, kForWholeSums, kForStats, kForHeads };
 WidePlan wide_plan(int M, int N, int K, PlanFor use);
 // Whether gate/up (N = 2 F, a multiple of 128) is better unsplit with the SwiGLU in its epilogue than in the K splits of its plan.
 bool wide_gate_up_fused(int M, int N, int K);
+// Whether the QKV projection is better unsplit with the rotation and the KV append in its epilogue than its plan and their launch.
+bool block_qkv_fused(int M, int N, int K);
+gs_status launch_block_qkv(const WidePlan& p, const bf16_t* x, const bf16_t* w, const QkvOut& out, int M, int N, int K, hipStream_t stream);
 gs_status launch_wide(const WidePlan& p, const bf16_t* x, const bf16_t* w, float* out, int M, int N, int K,
                       hipStream_t stream);
 gs_status launch_wide_gate_up(const WidePlan& p, const bf16_t* x, const bf16_t* w, bf16_t* act, int M, int N, int K,

@@ -332,10 +332,12 @@ constexpr float kPartialUs = 0.39f * 64e-6f;      // of the 16 x 4 bytes that a 
 // The shape of kWideShapes and the K splits with the least time for more than 4 row tiles (N a multiple of 128).
 static WidePlan fastest_shape(int tiles, int N, int K, PlanFor use) {
   constexpr long kCus = 256;
+  const bool whole = use == kForWholeSums || use == kForHeads;
   WidePlan best{};
   for (const WideShape& w : kWideShapes) {
     const int cols = 16 * w.nt * w.wn;
     if (N % cols != 0 || (use == kForStats && cols % 128 != 0)) continue;
+    if (use == kForHeads && (!w.block || w.nt % 2 != 0 || w.mt > 8)) continue;      // (more row tiles beside that epilogue spill)
     WidePlan p{w.wm, w.wn, w.kg, w.mt, w.nt, ceil_div(tiles, w.wm * w.mt), N / cols, 1, 0, w.block, 0.f};
     if (!w.block) {
       // where one workgroup has all rows, K groups are better than the same tile without; they are not for weights that several
@@ -351,8 +353,8 @@ static WidePlan fastest_shape(int tiles, int N, int K, PlanFor use) {
     const float stream = 2e-6f / 7.83f * (float)N * (float)K * (1.f + 0.267f * (float)(p.m_chunks - 1));
     const long blocks = (long)p.n_blocks * p.m_chunks;
     // K splits: as many as give every compute unit one workgroup (two where it holds two), at least 8 steps each
-    for (long target = kCus; target <= (w.block && pairs && use != kForWholeSums && K >= 1024 ? 2 * kCus : kCus); target += kCus) {
-      cut_k(p, K, use == kForWholeSums ? 1 : std::max(1, std::min((int)(target / blocks), K / 512)));
+    for (long target = kCus; target <= (w.block && pairs && !whole && K >= 1024 ? 2 * kCus : kCus); target += kCus) {
+      cut_k(p, K, whole ? 1 : std::max(1, std::min((int)(target / blocks), K / 512)));
       const long wgs = blocks * p.splits, per_cu = (wgs + kCus - 1) / kCus, last = wgs % (2 * kCus);
       const float steps_us = !pairs ? (float)per_cu * w.single_us
                                     : (float)(wgs / (2 * kCus)) * w.pair_us + (last == 0 ? 0.f : last <= kCus ? w.single_us : w.pair_us);
@@ -401,6 +403,16 @@ bool wide_gate_up_fused(int M, int N, int K) {
   const WidePlan whole = wide_plan(M, N, K, kForWholeSums), split = wide_plan(M, N, K, kForSums);
   // fused: no fp32 sums and one launch less (3 us)
   return split.splits == 1 || whole.us - kPartialUs * (float)ceil_div(M, 16) * (float)N <= split.us + 3.f;
+}
+
+bool block_qkv_fused(int M, int N, int K) {
+  if (M <= 64 || N % 128 != 0) return false;
+  const WidePlan whole = wide_plan(M, N, K, kForHeads), split = wide_plan(M, N, K, kForSums);
+  // Its epilogue takes a little longer than storing fp32 sums (1024 rows of the 8B shape 51 -> 58 us per launch), in return for the launch that
+  // would read them again (15), so only where the shape that serves it is modelled no slower than the plan, which is from the same shape
+  // for the most part.  8B shape, 4 layers, us per pass at 800 / 1280 / 1800 rows 2294 -> 2240, 3235 -> 3216, 4668 -> 4637; beyond the line
+  // 512 rows 1453 and 1450, 640 1857 both, 1500 3778 and 3849; 324 rows, 8 layers, 2627 and 2697.
+  return whole.splits == 1 && whole.us <= split.us;
 }
 
 template <int MODE>

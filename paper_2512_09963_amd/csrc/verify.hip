@@ -3,7 +3,8 @@
 // First one launch for the embedding, the first norm, the per-row tables and the attention work list; then
 // per layer: add+RMSNorm -> QKV projection -> rotary + KV append -> attention -> O projection
 //            -> add+RMSNorm -> gate/up projection -> SwiGLU -> down projection
-// where the attention may be two launches (merge of KV splits) and the gate/up projection apply the SwiGLU itself;
+// where the attention may be two launches (merge of KV splits), the gate/up projection apply the SwiGLU itself and the QKV projection of many
+// rows the rotation and the KV append;
 // in blocks of a few rows (rows_fused):
 //            QKV projection (with the norm, rotary and KV append) -> attention -> O projection (with the residual sum)
 //            -> gate/up projection (with the norm and the SwiGLU) -> down projection (with the residual sum).
@@ -25,6 +26,8 @@ gs_status launch_pack_weight_w4(const void* q, const void* scales, const void* z
 gs_status launch_gemm(int dtype, const void* X, const void* W, float* P, int M, int N, int K, hipStream_t stream);
 bool gate_up_fused(int dtype, int M, int F, int K);
 gs_status launch_gemm_gate_up(int dtype, const void* X, const void* W, void* act, int M, int F, int K, hipStream_t stream);
+bool qkv_fused(int dtype, const void* X, const void* W, const QkvOut& out, int M, int K);
+gs_status launch_gemm_qkv(const void* X, const void* W, const QkvOut& out, int M, int K, hipStream_t stream);
 bool rows_fused(int dtype, int M, int d, int hq, int qkv, int F);
 gs_status launch_rows_qkv(int dtype, const void* h, const void* w, const RowNorm& norm, const QkvOut& out, int M, int K,
                           hipStream_t stream);
@@ -469,6 +472,8 @@ extern "C" gs_status gs_verify_batch(gs_ctx* ctx, const gs_kv_cache* kv, const g
                          m.n_heads, m.n_kv_heads, m.head_dim};
     if (fused) {
       GS_STAGE(GS_STAGE_GEMM, gs::launch_rows_qkv(m.dtype, p.h, ctx->wqkv[l], norm, out, rows, d, stream));
+    } else if (gs::qkv_fused(m.dtype, p.h, ctx->wqkv[l], out, rows, d)) {
+      GS_STAGE(GS_STAGE_GEMM, gs::launch_gemm_qkv(p.h, ctx->wqkv[l], out, rows, d, stream));
     } else {
       GS_STAGE(GS_STAGE_GEMM, gs::launch_gemm(m.dtype, p.h, ctx->wqkv[l], p.partial, rows, qkv, d, stream));
       GS_STAGE(GS_STAGE_GLUE, gs::launch_rope_append(act, p.partial, gs::gemm_splits(m.dtype, rows, qkv, d), rows, out, stream));

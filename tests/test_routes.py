@@ -124,3 +124,21 @@ def test_layers_of_five_launches_refuse_more_rows(dtype, most):
 ])
 def test_attention_key_groups_of_prompts(gamma, ctx, groups):
     assert attention_key_groups(8, 4, gamma, ctx)[0] == groups
+
+
+class _QkvOut(C.Structure):
+    _fields_ = [(n, C.c_void_p) for n in ("row_slot", "rope", "q", "k_pages", "v_pages")] + [(n, C.c_int) for n in ("page_size", "n_heads", "n_kv", "hd")]
+
+
+@pytest.mark.parametrize("M,fused", [(17, False), (64, False), (128, False), (324, False), (512, False), (640, False), (800, True), (1024, True),
+                                     (1280, True), (1500, False), (1800, True), (2047, True)])
+def test_qkv_projections_of_many_rows_store_heads(M, fused):
+    """Where whole sums are modelled no slower, and operands and places are aligned; bf16 alone."""
+    rule = _rule("_ZN2gs9qkv_fusedEiPKvS1_RKNS_6QkvOutEii", C.c_bool, C.c_int, C.c_void_p, C.c_void_p, C.POINTER(_QkvOut), C.c_int, C.c_int)
+
+    def ask(dtype=1, x=4096, w=4096, q=4096, k=4096, v=4096):
+        return rule(dtype, x, w, C.byref(_QkvOut(4096, 4096, q, k, v, 16, 32, 8, 128)), M, 4096)
+
+    assert ask() == fused and ask(k=4100, v=4104) == fused
+    assert not ask(dtype=0) and not ask(dtype=2)
+    assert not ask(x=4104) and not ask(w=4104) and not ask(k=4098) and not ask(v=4100)
