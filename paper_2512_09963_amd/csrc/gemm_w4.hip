@@ -428,7 +428,13 @@ gs_status launch_pack_weight_w4(const void* q, const void* scales, const void* z
 //   33 to 96 rows: 4 waves x 2 K groups, or 2 x 4 (narrow matrices, below); two column tiles per wave (a fragment read from LDS feeds two MFMAs) for matrices of
 //     192 blocks of 256 columns and more, and where every wave still gets 16 steps; otherwise one
 //     (92 rows, isolated: 8192 x 28672 49 us with two, 54 with one; 8192 x 8192 22.0 and 20.8; 10240 x 8192 26.5 and 25.8)
-//   more rows: chunks of 128; 8 waves side by side with one tile (two do not fit the registers)
+//   more rows: chunks of 128; 4 waves x 2 K groups with two column tiles where that gives three compute units in four a workgroup of at least
+//     eight steps per group, else 8 waves side by side with one tile and shorter K splits.  With one tile the fragments read from LDS
+//     are at its limit of 128 bytes per cycle; two tiles fit the registers with one step of weights and activations ahead.  Isolated,
+//     us, one tile -> two: 28672 x 4096 at 128 / 256 / 1024 / 2047 rows 37.3 -> 35.2, 63.6 -> 57.8, 247 -> 233, 461 -> 435; 1024 rows of 4096 x 14336
+//     111 -> 103, of 6144 x 4096 55.4 -> 51.2; 312 rows of 57344 x 8192 340 -> 313, of 8192 x 28672 180 -> 163; at the line 4096 x 4096 at 300 rows
+//     19.3 -> 19.1, 6144 x 4096 at 160 18.7 -> 18.5; before it 4096 x 4096 at 250 rows 16.0 -> 18.8, 2560 x 2560 at 1024 21.0 -> 22.9.  (512 columns
+//     per workgroup, 8 x 1 waves: 217 for the first at 1024 rows, but 1026 for 128256 x 4096, 964 this way; one wave per SIMD 250.)
 // Inside a verification step, us per launch (predecessor, with two LDS buffers and one burst of loads per step, in
 // brackets): 92 rows, 70B shape: gate/up 101 (123, and 8.5 for the separate SwiGLU), 8192 x 28672 52, 8192 x 8192 22.9 (67
 // on average), QKV 27.3 (33.5), LM head 205 (250); 53 rows, 8B shape: gate/up 26.3 (32, and 6), 4096 x 14336 and 4096 x 4096 13.2 on
@@ -443,10 +449,15 @@ static W4Plan w4_plan(int M, int N, int K) {
   p.m_chunks = ceil_div(M, 32 * p.mt);
   int target = 256;      // workgroups: one per compute unit
   p.nt = 1;
-  if (p.mt == 1 || p.mt == 4) {
+  if (p.mt == 1) {
     p.waves = N % 256 == 0 ? 8 : 4;
     p.kg = p.waves == 8 ? 1 : 2;
     if (M <= 16) target = 512;
+  } else if (p.mt == 4) {
+    const bool fills = (long)(N / 256) * p.m_chunks * (K / 1024) >= 192;
+    p.nt = N % 256 == 0 && fills ? 2 : 1;
+    p.waves = N % 256 == 0 && !fills ? 8 : 4;
+    p.kg = p.waves == 8 ? 1 : 2;
   } else {
     p.waves = 4;
     p.kg = 2;
@@ -486,8 +497,11 @@ static int w4_gate_up_blocks(int M, int F) {
 }
 bool w4_gate_up_fused(int M, int F) { return w4_gate_up_blocks(M, F) > 128; }
 
+// Steps in registers: four of weights, of activations one up to 64 rows (registers: isolated 53 x 4096 x 14336 17.2 -> 16.7 us with one
+// instead of two, LM head at 53 / 12 rows 92.6 -> 90.9 / 68.9 -> 66.6) and two for 96 (LM head of the 70B shape 217.5 -> 215.7);
+// 128 rows with two tiles: two and one.  Whole step of the 8B shape, 8 servers: 908 -> 892 us.
 #define GS_W4(WN, KG, MT, NT, WPE, MODE)                                                                            \
-  gemm_w4_kernel<WN, KG, MT, NT, 4, 2, WPE, MODE><<<grid, 64 * WN * KG, 0, stream>>>(x, codes, meta, P, M, N, K, k_per, chunks)
+  gemm_w4_kernel<WN, KG, MT, NT, (MT) == 4 && (NT) == 2 ? 2 : 4, (MT) == 3 || ((MT) == 4 && (NT) == 1) ? 2 : 1, WPE, MODE><<<grid, 64 * WN * KG, 0, stream>>>(x, codes, meta, P, M, N, K, k_per, chunks)
 
 // act [M][F] (bf16) = silu(X Wg^T) * (X Wu^T); only where w4_gate_up_fused.
 gs_status launch_gemm_w4_gate_up(const void* X, const void* Wpacked, void* act, int M, int F, int K, hipStream_t stream) {
@@ -530,7 +544,8 @@ gs_status launch_gemm_w4(const void* X, const void* Wpacked, float* P, int M, in
       else GS_W4(2, 4, 3, 1, 2, kPlain);
       break;
     default:
-      if (p.waves == 8) GS_W4(8, 1, 4, 1, 2, kPlain);
+      if (p.nt == 2) GS_W4(4, 2, 4, 2, 2, kPlain);
+      else if (p.waves == 8) GS_W4(8, 1, 4, 1, 2, kPlain);
       else if (p.waves == 4) GS_W4(4, 2, 4, 1, 2, kPlain);
       else GS_W4(2, 2, 4, 1, 1, kPlain);
   }
