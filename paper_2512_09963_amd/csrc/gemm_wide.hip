@@ -44,7 +44,10 @@ typedef unsigned int uintx4_t __attribute__((ext_vector_type(4)));
 // MODE: kPlain stores the fp32 sums [split][M][N] at P; kGateUp (one split): the wave's tiles are NT / 2 feature tiles of
 // the gate half and the same ones of the up half of a [2F][K] matrix (N = 2F), and act[M][F] = silu(gate) * up is
 // stored as bf16 at P; kGateUpNorm: the same of rows that still need their factor (RowNorm), act in fragment order; kStats (one split): also (max, sum exp) of every row over the workgroup's columns.
-// DB, DA: steps of weights and of activations held in registers.  POL: cache policy of the weight loads (2: do not
+// DB, DA: steps of weights and of activations held in registers: three and one (a step in use, two of weights on their way).  More loads in
+// flight queue up in the memory system and delay each other: whole steps, us, with 5 / 4 / 3 / 2 of weights: 8 servers of the 8B shape 4104 / 4066 /
+// 4022 / 4011, 16 of the 70B shape 1852 / 1840 / 1827 / 1831, one server 888 / 884 / 881; two steps of activations instead of one: 4089 and 4058.
+// POL: cache policy of the weight loads (2: do not
 // displace other lines; for weights that one workgroup reads once).
 // 1-D grid: K splits x column blocks x row chunks.  Workgroups are handed to the 8 XCDs round robin by their index; an XCD takes a
 // contiguous range of (split, column block, row chunk), so the row chunks of a column block run on one XCD, and all but the first find
@@ -434,45 +437,45 @@ static gs_status launch_mode(const WidePlan& plan, const bf16_t* x, const bf16_t
       <<<grid, 64 * WM * WN * KG, 0, stream>>>(x, w, out, M, N, K, p.k_per, p.m_chunks, stats, p.n_blocks, norm)
   if constexpr (MODE == kGateUpNorm) {
     static_assert(kMaxRows <= 32, "two row tiles in one row chunk");
-    if (p.wn == 8) GS_WIDE(1, 8, 1, 2, 2, 4, 2, 2, 2);
-    else GS_WIDE(1, 4, 2, 2, 2, 4, 2, 2, 2);
+    if (p.wn == 8) GS_WIDE(1, 8, 1, 2, 2, 3, 1, 2, 2);
+    else GS_WIDE(1, 4, 2, 2, 2, 3, 1, 2, 2);
     GS_LAUNCH_CHECK("gemm_bf16_wide");
     return GS_OK;
   }
   if constexpr (MODE != kGateUpNorm) {
   if (p.wn == 8) {
     switch (p.mt) {
-      case 2: GS_WIDE(1, 8, 1, 2, 2, 4, 2, 2, 2); break;
-      case 4: GS_WIDE(1, 8, 1, 4, 2, 4, 2, 2, 2); break;
-      case 6: GS_WIDE(1, 8, 1, 6, 2, 4, 2, 2, 2); break;
-      case 8: GS_WIDE(1, 8, 1, 8, 2, 4, 2, 2, 2); break;
-      case 10: GS_WIDE(1, 8, 1, 10, 2, 4, 2, 2, 2); break;
-      default: GS_WIDE(1, 8, 1, 12, 2, 4, 2, 2, 2);
+      case 2: GS_WIDE(1, 8, 1, 2, 2, 3, 1, 2, 2); break;
+      case 4: GS_WIDE(1, 8, 1, 4, 2, 3, 1, 2, 2); break;
+      case 6: GS_WIDE(1, 8, 1, 6, 2, 3, 1, 2, 2); break;
+      case 8: GS_WIDE(1, 8, 1, 8, 2, 3, 1, 2, 2); break;
+      case 10: GS_WIDE(1, 8, 1, 10, 2, 3, 1, 2, 2); break;
+      default: GS_WIDE(1, 8, 1, 12, 2, 3, 1, 2, 2);
     }
   } else if (MODE == kPlain && p.kg == 4) {
     if constexpr (MODE == kPlain) {
-      if (p.mt == 2) GS_WIDE(1, 2, 4, 2, 2, 4, 2, 2, 2);
-      else GS_WIDE(1, 2, 4, 4, 2, 4, 2, 2, 2);
+      if (p.mt == 2) GS_WIDE(1, 2, 4, 2, 2, 3, 1, 2, 2);
+      else GS_WIDE(1, 2, 4, 4, 2, 3, 1, 2, 2);
     }
   } else if (MODE == kStats && p.m_chunks == 1 && p.mt == 12) {
-    if constexpr (MODE == kStats) GS_WIDE(1, 4, 1, 12, 2, 4, 2, 2, 1);      // (spills where two workgroups share the registers)
+    if constexpr (MODE == kStats) GS_WIDE(1, 4, 1, 12, 2, 3, 1, 2, 1);      // (spills where two workgroups share the registers)
   } else if (p.m_chunks == 1 && (MODE == kStats || p.kg == 2)) {
     // (the statistics take whole sums: one K group there, and two workgroups per compute unit)
     constexpr int KG = MODE == kStats ? 1 : 2;
     switch (p.mt) {
-      case 2: GS_WIDE(1, 4, KG, 2, 2, 4, 2, 2, 2); break;
-      case 4: GS_WIDE(1, 4, KG, 4, 2, 4, 2, 2, 2); break;
-      case 6: GS_WIDE(1, 4, KG, 6, 2, 4, 2, 2, 2); break;
-      case 8: GS_WIDE(1, 4, KG, 8, 2, 4, 2, 2, 2); break;
-      default: GS_WIDE(1, 4, KG, 10, 2, 4, 2, 2, 2);
+      case 2: GS_WIDE(1, 4, KG, 2, 2, 3, 1, 2, 2); break;
+      case 4: GS_WIDE(1, 4, KG, 4, 2, 3, 1, 2, 2); break;
+      case 6: GS_WIDE(1, 4, KG, 6, 2, 3, 1, 2, 2); break;
+      case 8: GS_WIDE(1, 4, KG, 8, 2, 3, 1, 2, 2); break;
+      default: GS_WIDE(1, 4, KG, 10, 2, 3, 1, 2, 2);
     }
   } else {
     switch (p.mt) {
-      case 4: GS_WIDE(1, 4, 1, 4, 2, 4, 2, 0, 2); break;
-      case 6: GS_WIDE(1, 4, 1, 6, 2, 4, 2, 0, 2); break;
-      case 8: GS_WIDE(1, 4, 1, 8, 2, 4, 2, 0, 2); break;
-      case 10: GS_WIDE(1, 4, 1, 10, 2, 4, 2, 0, 2); break;
-      default: GS_WIDE(1, 4, 1, 12, 2, 4, 2, 0, 2);
+      case 4: GS_WIDE(1, 4, 1, 4, 2, 3, 1, 0, 2); break;
+      case 6: GS_WIDE(1, 4, 1, 6, 2, 3, 1, 0, 2); break;
+      case 8: GS_WIDE(1, 4, 1, 8, 2, 3, 1, 0, 2); break;
+      case 10: GS_WIDE(1, 4, 1, 10, 2, 3, 1, 0, 2); break;
+      default: GS_WIDE(1, 4, 1, 12, 2, 3, 1, 0, 2);
     }
   }
   }
